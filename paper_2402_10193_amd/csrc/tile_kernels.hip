@@ -20,28 +20,52 @@ __global__ __launch_bounds__(256) void tile_base_kernel(const uint16_t* __restri
     }
 }
 
-// One thread per lane slot of the tiled signs: slot (rb KT + kt) 64 + l holds 8 bytes, byte v =
-// bits 8 g .. 8 g + 7 of packed word 8 kt + v of row 16 rb + l % 16   (g = l / 16).
+// Tiled signs: lane slot l = (r, g) of tile (rb, kt) holds 8 bytes, byte v = bits 8 g .. 8 g + 7 of packed word 8 kt + v of
+// row 16 rb + r.  Bound by HBM (1/4 byte per element moved in all).  One thread takes one row of one tile: its 8 words in
+// two 128-bit loads, a byte transpose in registers, and the 8 bytes of each of the four lane groups out; a wavefront is 16
+// rows x 4 neighbouring tiles, so that it reads whole 128-byte lines and writes 128 contiguous bytes per tile and group.
+// (One thread per lane slot, four threads each loading the same 8 words one by one, took 17.2 us for 11008 x 4096 where
+// this takes 4.6.)  VEC: rows start at 16-byte boundaries (in % 128 == 0); otherwise word by word.
+template <bool VEC>
 __global__ __launch_bounds__(256) void tile_signs_kernel(const uint32_t* __restrict__ packed, u32x2* __restrict__ st,
-                                                          const int64_t out, const int64_t in, const int64_t KT,
-                                                          const int64_t n_slots) {
-    const int64_t words_per_row = in >> 5;
-    for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < n_slots; u += (int64_t)gridDim.x * blockDim.x) {
-        const int l = (int)(u & 63);
-        const int64_t tile = u >> 6, kt = tile % KT, rb = tile / KT;
-        const int64_t row = rb * kTileRows + (l & 15);
-        const int sh = 8 * (l >> 4);
-        u32x2 val = {0u, 0u};
-        if (row < out) {
+                                                          const int64_t out, const int words_per_row, const uint32_t KT,
+                                                          const uint32_t n_rows_of_tiles) {
+    const uint32_t t = blockIdx.x * 256u + threadIdx.x;   // tiles * 16 < 2^23 (a tiled base is below 4 GiB)
+    if (t >= n_rows_of_tiles) return;
+    const uint32_t tile = t >> 4, rb = tile / KT, kt = tile - rb * KT;
+    const int r = (int)(t & 15);
+    const int64_t row = (int64_t)rb * kTileRows + r;
+    const int w0 = (int)kt * 8;                           // first word of the row
+    uint32_t w[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
+    if (row < out) {
+        const uint32_t* src = packed + row * words_per_row + w0;
+        if constexpr (VEC) {                              // groups of 4 words lie inside the row or beyond it
 #pragma unroll
-            for (int v = 0; v < 8; ++v) {
-                const int64_t wi = kt * 8 + v;
-                const uint32_t byte = wi < words_per_row ? ((packed[row * words_per_row + wi] >> sh) & 0xFFu) : 0u;
-                val[v >> 2] |= byte << (8 * (v & 3));
-            }
+            for (int h = 0; h < 2; ++h)
+                if (w0 + 4 * h < words_per_row) {
+                    const u32x4 q = *(const u32x4*)(src + 4 * h);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) w[4 * h + i] = q[i];
+                }
+        } else {
+#pragma unroll
+            for (int v = 0; v < 8; ++v)
+                if (w0 + v < words_per_row) w[v] = src[v];
         }
-        st[u] = val;
     }
+    u32x2 val[4];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {                         // 4 x 4 byte transpose of words 4 h .. 4 h + 3
+        const uint32_t* q = w + 4 * h;
+        const uint32_t a = __builtin_amdgcn_perm(q[1], q[0], 0x05010400u), b = __builtin_amdgcn_perm(q[3], q[2], 0x05010400u);
+        const uint32_t c = __builtin_amdgcn_perm(q[1], q[0], 0x07030602u), d = __builtin_amdgcn_perm(q[3], q[2], 0x07030602u);
+        val[0][h] = __builtin_amdgcn_perm(b, a, 0x05040100u);
+        val[1][h] = __builtin_amdgcn_perm(b, a, 0x07060302u);
+        val[2][h] = __builtin_amdgcn_perm(d, c, 0x05040100u);
+        val[3][h] = __builtin_amdgcn_perm(d, c, 0x07060302u);
+    }
+#pragma unroll
+    for (int g = 0; g < 4; ++g) st[(int64_t)tile * 64 + g * 16 + r] = val[g];
 }
 
 // One 16-byte unit of the 8-bit base layout per thread: unit u = ((tile * 4 + i) * 64 + l), bytes [h][e] =
@@ -93,9 +117,15 @@ hipError_t launch_tile_base(const uint16_t* w, int64_t out, int64_t in, uint16_t
 }
 
 hipError_t launch_tile_signs(const uint32_t* packed, int64_t out, int64_t in, uint32_t* st_out, hipStream_t st) {
-    const int64_t KT = tiled_k_tiles(in), n_slots = tiled_row_blocks(out) * KT * 64;
-    hipLaunchKernelGGL(tile_signs_kernel, dim3(grid_for(n_slots, 256)), dim3(256), 0, st, packed, (u32x2*)st_out, out, in, KT,
-                       n_slots);
+    const int64_t KT = tiled_k_tiles(in), n = tiled_row_blocks(out) * KT * kTileRows;
+    if (n > (int64_t)1 << 30) return hipErrorInvalidValue;
+    if (n == 0) return hipSuccess;
+    const dim3 grid((unsigned)((n + 255) / 256)), block(256);
+    const int wpr = (int)(in >> 5);
+    if (wpr % 4 == 0)
+        hipLaunchKernelGGL(tile_signs_kernel<true>, grid, block, 0, st, packed, (u32x2*)st_out, out, wpr, (uint32_t)KT, (uint32_t)n);
+    else
+        hipLaunchKernelGGL(tile_signs_kernel<false>, grid, block, 0, st, packed, (u32x2*)st_out, out, wpr, (uint32_t)KT, (uint32_t)n);
     return hipGetLastError();
 }
 
