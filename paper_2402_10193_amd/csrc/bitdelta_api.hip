@@ -197,8 +197,8 @@ hipError_t run_prefill(const uint16_t* x, const void* w, const uint32_t* const* 
         return bd::launch_linear_prefill_merged(x, (const uint16_t*)w, packed_by_tenant, alpha_by_tenant, dst,
                                                 dst + row_token.size(), n_mtiles, y, T, out, in, halve_last_round, tiled, st);
     if (big_waves)
-        return bd::launch_linear_prefill_big(x, (const uint16_t*)w, packed_by_tenant, alpha_by_tenant, dst,
-                                             dst + row_token.size(), n_mtiles, y, T, out, in, big_waves, halve_last_round, tiled, st);
+        return bd::launch_linear_prefill_big(x, w, packed_by_tenant, alpha_by_tenant, wscale, dst, dst + row_token.size(), n_mtiles, y, T,
+                                             out, in, big_waves, halve_last_round, tiled, st);
     if (tiled) return hipErrorInvalidValue;   // the 128 x 128 tiles read the row-major tensors only
     return bd::launch_linear_prefill(x, w, packed_by_tenant, alpha_by_tenant, wscale, dst, dst + row_token.size(), n_mtiles, y,
                                      out, in, k_planes, st);
@@ -790,8 +790,11 @@ static bd_status gemm_entry(const uint16_t* x_f16, const void* w, size_t w_bytes
     if (in == 0) return BD_ERR_UNSUPPORTED;   // the empty reduction (y = 0) is bd_linear_multitenant's
     const size_t need = prefill_table_bytes(T, n_tenants);
     if (!workspace || workspace_bytes < need || misaligned(workspace, 256)) return BD_ERR_WORKSPACE;
+    // The 8-bit base: 128 x 256 tiles where whole 64-wide steps and a full tile's width of output rows are there, as for fp16.
+    // (k planes stay on the 128 x 128 tiles: their sums are formed in fp16 in LDS, which the large tile has no room for.)
+    const bool big = wscale && k_planes == 0 && out >= 256 && bd::prefill_big_fits(T, out, in);
     return run_prefill(x_f16, w, packed_by_tenant, alpha_by_tenant, tenant_of_token, y_f16, T, out, in, workspace,
-                       (hipStream_t)stream, 0, false, k_planes, wscale) == hipSuccess
+                       (hipStream_t)stream, big ? 4 : 0, big, k_planes, wscale) == hipSuccess
                ? BD_OK
                : BD_ERR_DEVICE;
 }

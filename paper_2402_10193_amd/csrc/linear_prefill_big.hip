@@ -23,6 +23,8 @@
 // The same tile body also runs the left-hand side of Eq. 6, X (W + alpha S) with the bracket rounded to
 // fp16, as ONE product on tiles of 256 tokens x 256 features (linear_prefill_merged_kernel; the caller
 // asks for it by name): see MERGED at prefill_big_tile.
+#include <type_traits>
+
 #include "bd_device.h"
 #include "bd_launch.h"
 
@@ -114,11 +116,19 @@ __device__ __forceinline__ void mfma_in_place(float16v& acc, const half8 a, cons
 // TILED: W and the signs are read from the serving layout of the decode kernel (tiles of 16 rows x 256 k in
 // matrix-core operand order, bd_tile_base / bd_tile_signs): a 16-byte chunk of a row is a 16-byte chunk there too,
 // 2 KiB per row block and step in one piece, and a row's sign bytes of a step are four 2-byte pieces 128 bytes apart.
-template <int WM, int TM, bool MERGED, bool TILED>
+// Q8: W is the row-major int8 q of the 8-bit base.  A byte u = q + 128 next to the constant 0x64 is the fp16 number 1024 + u,
+// minus 1152 it is q exactly: four byte shuffles and four packed additions per 16-byte chunk on its way into LDS (80 vector
+// instructions per step and thread next to 128 MFMAs), the base accumulator holds sum_k x q, and the row's scale multiplies
+// the finished sum.  Against the 128 x 128 tiles (up projection of Llama-2-7B): 8 x 512 tokens 816 -> 611 us, 1024 tokens of
+// 5 tenants 277 -> 199 us, 100 tokens of 4 tenants 136 -> 72 us.
+enum BgSource { kSrcRowMajor, kSrcTiled, kSrcQ8 };
+template <int WM, int TM, bool MERGED, BgSource SRC>
 __device__ __forceinline__ void prefill_big_tile(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ w, const uint32_t* const* __restrict__ packed_by_tenant,
     const float* __restrict__ alpha_by_tenant, const int32_t* __restrict__ tile_tokens, const int32_t* __restrict__ tile_tenant,
-    uint16_t* __restrict__ y, const int64_t out, const int64_t in, const int mt, const int nt, const int r0) {
+    uint16_t* __restrict__ y, const int64_t out, const int64_t in, const int mt, const int nt, const int r0,
+    const float* __restrict__ wscale = nullptr) {
+    constexpr bool TILED = SRC == kSrcTiled, Q8 = SRC == kSrcQ8;
     extern __shared__ __align__(16) unsigned char lds[];   // [2 buffers: x, W, sign words][table][tokens]
     using Lds = BgLds<TM>;
     constexpr int kBgBufBytes = Lds::kBuf, kBgLutBytes = Lds::kLut;
@@ -143,6 +153,8 @@ __device__ __forceinline__ void prefill_big_tile(
     constexpr int kSets = (WM == 1 && TM <= kBgM) ? 2 : 1;   // (256 rows: the registers hold one set)
     static_assert(!MERGED || WM == 1, "the merged form runs one wavefront per SIMD");
     static_assert(!TILED || WM == 1, "the tiled sources are written for one row of signs per thread");
+    static_assert(!Q8 || (WM == 1 && !MERGED), "the 8-bit base runs the two-product form, one wavefront per SIMD");
+    using WChunk = std::conditional_t<Q8, u32x2, u32x4>;   // 8 weights of a row
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 2, wn = wave & 3;
     const int64_t n0 = (int64_t)nt * kBgN;
@@ -156,12 +168,14 @@ __device__ __forceinline__ void prefill_big_tile(
     // overlap: W (kernel arguments only), then the tile's tenant and tokens; behind those x, the sign pointer, the signs.
     const unsigned char* const xbase = (const unsigned char*)x;
     const int64_t k_tiles = (in + 255) >> 8;                       // of the serving layout
-    constexpr int kWStep = TILED ? 2048 : kBgRowBytes;              // bytes a thread's W address advances per step
-    const unsigned char* const wbase = TILED ? (const unsigned char*)w + (n0 >> 4) * k_tiles * 8192 : (const unsigned char*)(w + n0 * in);
+    constexpr int kWStep = TILED ? 2048 : (Q8 ? kBgK : kBgRowBytes);   // bytes a thread's W address advances per step
+    const unsigned char* const wbase = TILED ? (const unsigned char*)w + (n0 >> 4) * k_tiles * 8192
+                                             : (const unsigned char*)w + n0 * in * (Q8 ? 1 : 2);
     uint32_t xsrc[kBgXPer], wsrc[kBgWPer];
     lds_bytes xdst[kBgXPer], wdst[kBgWPer];   // in buffer 0
     struct Staged {
-        u32x4 xg[kBgXPer], wg[kBgWPer];
+        u32x4 xg[kBgXPer];
+        WChunk wg[kBgWPer];
         uint32_t s0, s1;      // row-major signs: the row's two words of the step
         uint32_t su[4];       // tiled signs: the 2 bytes (slices 2 (step % 4), + 1) of the row's lanes g = 0..3
     };
@@ -173,10 +187,10 @@ __device__ __forceinline__ void prefill_big_tile(
         const int64_t wrow = n0 + row < out ? row : out - 1 - n0;
         // tiled: row block wrow / 16, slice c8 / 4 of the step's two, lane (wrow % 16, c8 % 4)
         wsrc[i] = TILED ? (uint32_t)((wrow >> 4) * k_tiles * 8192) + (c8 >> 2) * 1024 + (c8 & 3) * 256 + (uint32_t)(wrow & 15) * 16
-                        : (uint32_t)(wrow * in * 2) + c8 * 16;
+                        : (uint32_t)(wrow * in * (Q8 ? 1 : 2)) + c8 * (Q8 ? 8 : 16);
         wdst[i] = lds_at(Lds::kWBase + bg_off(row, c8));
         asm volatile("" : "+v"(wdst[i]));   // a register of its own: derived from xdst[i], it would cost an addition per use
-        set0.wg[i] = *(const u32x4*)(wbase + wsrc[i]);
+        set0.wg[i] = *(const WChunk*)(wbase + wsrc[i]);
     }
     const int tenant = tile_tenant[mt];
     int tokv[kBgXPer];
@@ -184,7 +198,7 @@ __device__ __forceinline__ void prefill_big_tile(
     for (int i = 0; i < kBgXPer; ++i) tokv[i] = tile_tokens[r0 + ((tid + kThreads * i) >> 3)];
     if (kSets == 2) {
 #pragma unroll
-        for (int i = 0; i < kBgWPer; ++i) set1.wg[i] = *(const u32x4*)(wbase + (int64_t)step_b * kWStep + wsrc[i]);
+        for (int i = 0; i < kBgWPer; ++i) set1.wg[i] = *(const WChunk*)(wbase + (int64_t)step_b * kWStep + wsrc[i]);
     }
     __builtin_amdgcn_sched_barrier(0);
 
@@ -250,14 +264,31 @@ __device__ __forceinline__ void prefill_big_tile(
             st.xg[item] = *(const u32x4*)(xbase + (int64_t)step * kBgRowBytes + xsrc[item]);
         } else if (item < kBgXPer + kBgWPer) {
             asm volatile("" : "+v"(wsrc[item - kBgXPer]));
-            st.wg[item - kBgXPer] = *(const u32x4*)(wbase + (int64_t)step * kWStep + wsrc[item - kBgXPer]);
+            st.wg[item - kBgXPer] = *(const WChunk*)(wbase + (int64_t)step * kWStep + wsrc[item - kBgXPer]);
         } else {
             fetch_signs(st, step);
         }
     };
+    // Q8: 4 bytes q (two's complement) -> 4 fp16 numbers q in words 2 h, 2 h + 1 of a chunk
+    auto q8_half = [](u32x4& c, const int h, const uint32_t b4) __attribute__((always_inline)) {
+        const uint32_t u = b4 ^ 0x80808080u;
+        const half2v off = half2v{(_Float16)1152.f, (_Float16)1152.f};
+        c[2 * h] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2v, __builtin_amdgcn_perm(0x64646464u, u, 0x04010400u)) - off);
+        c[2 * h + 1] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2v, __builtin_amdgcn_perm(0x64646464u, u, 0x04030402u)) - off);
+    };
+    u32x4 q8_chunk;   // the chunk that is being converted, half of it per pair of MFMAs
     auto stage_item = [&](const Staged& st, const int buf, const int item) {
         if (item < kBgXPer) lds_put<u32x4>(xdst[item] + buf * Lds::kXStride, st.xg[item]);
-        else if (item < kBgXPer + kBgWPer) lds_put<u32x4>(wdst[item - kBgXPer] + buf * Lds::kWStride, st.wg[item - kBgXPer]);
+        else if (item < kBgXPer + kBgWPer) {
+            const int i = item - kBgXPer;
+            if constexpr (Q8) {
+                q8_half(q8_chunk, 0, st.wg[i][0]);
+                q8_half(q8_chunk, 1, st.wg[i][1]);
+                lds_put<u32x4>(wdst[i] + buf * Lds::kWStride, q8_chunk);
+            } else {
+                lds_put<u32x4>(wdst[i] + buf * Lds::kWStride, st.wg[i]);
+            }
+        }
         else if (TILED) {
             // su[g] = (byte of slice v, byte of slice v + 1) of lane g: the row's words are (v: g = 0..3), (v + 1: g = 0..3)
             const uint32_t lo = st.su[0] | (st.su[1] << 16), hi = st.su[2] | (st.su[3] << 16);
@@ -390,8 +421,24 @@ __device__ __forceinline__ void prefill_big_tile(
                     mfma_in_place(accd[i][j], a[cur][i], bs[cur][j]);
                     // pair p of the step: item p leaves for LDS after pair p, and is fetched again after pair p + kLag
                     const int p = sl * MI * 2 + q;
-                    if (p < kItems) stage_item(next, buf ^ 1, p);
-                    if (p >= kLag && p - kLag < kItems) fetch_item(next, step3, p - kLag);
+                    if constexpr (Q8 && MI == 4) {
+                        // a W chunk takes two pairs, half of its conversion behind each; it is fetched again behind the
+                        // pair after them.  Then the x chunks and the signs.
+                        static_assert(MI != 4 || 2 * kBgWPer + kBgXPer + 1 <= 3 * MI * 2, "all items are staged before the barrier slice");
+                        constexpr int kX0 = 2 * kBgWPer;
+                        if (p < kX0) {
+                            q8_half(q8_chunk, p & 1, next.wg[p / 2][p & 1]);
+                            if (p & 1) lds_put<u32x4>(wdst[p / 2] + (buf ^ 1) * Lds::kWStride, q8_chunk);
+                        }
+                        if (p >= 2 && p <= kX0 && (p & 1) == 0) fetch_item(next, step3, kBgXPer + p / 2 - 1);
+                        if (p >= kX0 && p < kX0 + kBgXPer) stage_item(next, buf ^ 1, p - kX0);
+                        if (p == kX0 + kBgXPer) stage_item(next, buf ^ 1, kItems - 1);
+                        if (p > kX0 + kBgXPer && p <= kX0 + 2 * kBgXPer) fetch_item(next, step3, p - kX0 - kBgXPer - 1);
+                        if (p == kX0 + 2 * kBgXPer + 1) fetch_item(next, step3, kItems - 1);
+                    } else {
+                        if (p < kItems) stage_item(next, buf ^ 1, p);
+                        if (p >= kLag && p - kLag < kItems) fetch_item(next, step3, p - kLag);
+                    }
                     __builtin_amdgcn_sched_barrier(0);
                 }
             __builtin_amdgcn_sched_barrier(0);
@@ -475,6 +522,14 @@ __device__ __forceinline__ void prefill_big_tile(
     // 32 j + l % 32 of the wavefront's 64.  The rows go to LDS as fp16 and leave as whole 16-byte pieces: written
     // from the accumulator layout y would take 256 two-byte stores per lane.
     const lds_bytes orow = lds_at(wave * (kWaveM * kBgOutRowBytes));
+    float ws[2] = {1.f, 1.f};   // Q8: the scales of this lane's two output rows (rows beyond `out` are never stored)
+    if constexpr (Q8) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int64_t n = n0 + wn * 64 + 32 * j + r32;
+            ws[j] = wscale[n < out ? n : out - 1];
+        }
+    }
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -483,7 +538,7 @@ __device__ __forceinline__ void prefill_big_tile(
             for (int e = 0; e < 16; ++e) {
                 const int row = 32 * i + 8 * (e >> 2) + 4 * hi + (e & 3);
                 lds_put<uint16_t>(orow + row * kBgOutRowBytes + (32 * j + r32) * 2,
-                                  f2h_rne(MERGED ? accb[i][j][e] : accb[i][j][e] + alpha * accd[i][j][e]));
+                                  f2h_rne(MERGED ? accb[i][j][e] : (Q8 ? ws[j] * accb[i][j][e] : accb[i][j][e]) + alpha * accd[i][j][e]));
             }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -527,22 +582,26 @@ __device__ __forceinline__ bool bg_tile_of_block(const int n_mtiles, const int n
     return true;
 }
 
-template <int WM, bool TILED>
+template <int WM, BgSource SRC>
 __global__ __launch_bounds__(256 * WM, 1) void linear_prefill_big_kernel(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ w, const uint32_t* const* __restrict__ packed_by_tenant,
     const float* __restrict__ alpha_by_tenant, const int32_t* __restrict__ row_token, const int32_t* __restrict__ tile_tenant,
-    uint16_t* __restrict__ y, const int64_t out, const int64_t in, const int n_mtiles, const int n_ntiles, const int n_full) {
+    uint16_t* __restrict__ y, const int64_t out, const int64_t in, const int n_mtiles, const int n_ntiles, const int n_full,
+    const float* __restrict__ wscale) {
     int mt, nt, half;
     if (!bg_tile_of_block(n_mtiles, n_ntiles, n_full, &mt, &nt, &half)) return;
     const int32_t* const tile_tokens = row_token + mt * kBgM;
     if constexpr (WM == 1) {
-        if (half >= 0) {
-            prefill_big_tile<1, kBgM / 2, false, TILED>(x, w, packed_by_tenant, alpha_by_tenant, tile_tokens, tile_tenant, y, out, in, mt, nt,
-                                                 half * (kBgM / 2));
+        // half a tile: of a last round that is cut in two, or where the tile's upper half is empty (rows are filled from the top)
+        if (half >= 0 || tile_tokens[kBgM / 2] < 0) {
+            const int r0 = half > 0 ? kBgM / 2 : 0;
+            if (tile_tokens[r0] < 0) return;   // nothing in this half
+            prefill_big_tile<1, kBgM / 2, false, SRC>(x, w, packed_by_tenant, alpha_by_tenant, tile_tokens, tile_tenant, y, out, in, mt, nt,
+                                                      r0, wscale);
             return;
         }
     }
-    prefill_big_tile<WM, kBgM, false, TILED>(x, w, packed_by_tenant, alpha_by_tenant, tile_tokens, tile_tenant, y, out, in, mt, nt, 0);
+    prefill_big_tile<WM, kBgM, false, SRC>(x, w, packed_by_tenant, alpha_by_tenant, tile_tokens, tile_tenant, y, out, in, mt, nt, 0, wscale);
 }
 
 // The merged form on token tiles of 256 rows (row_token holds 256 entries per tile): a wavefront multiplies 256
@@ -561,10 +620,10 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_merged_kernel(
     if (half >= 0 || tile_tokens[kBgM] < 0) {
         const int r0 = half > 0 ? kBgM : 0;
         if (tile_tokens[r0] < 0) return;   // nothing in this half
-        prefill_big_tile<1, kBgM, true, TILED>(x, w, packed_by_tenant, alpha_by_tenant, tile_tokens, tile_tenant, y, out, in, mt, nt, r0);
+        prefill_big_tile<1, kBgM, true, TILED ? kSrcTiled : kSrcRowMajor>(x, w, packed_by_tenant, alpha_by_tenant, tile_tokens, tile_tenant, y, out, in, mt, nt, r0);
         return;
     }
-    prefill_big_tile<1, kMergedTile, true, TILED>(x, w, packed_by_tenant, alpha_by_tenant, tile_tokens, tile_tenant, y, out, in, mt, nt, 0);
+    prefill_big_tile<1, kMergedTile, true, TILED ? kSrcTiled : kSrcRowMajor>(x, w, packed_by_tenant, alpha_by_tenant, tile_tokens, tile_tenant, y, out, in, mt, nt, 0);
 }
 
 // T: rows of x (its byte offsets and those inside one 256-row band of W must fit 32 bits)
@@ -588,11 +647,11 @@ hipError_t whole_tiles(int64_t tiles, bool halve_last_round, int64_t* n_full) {
     return hipSuccess;
 }
 
-template <typename Kernel>
+template <typename Kernel, typename... More>
 hipError_t launch_tiles(Kernel kernel, PerDeviceOnce& lds_limit, int lds_bytes, int threads, const uint16_t* x, const uint16_t* w,
                         const uint32_t* const* packed_by_tenant, const float* alpha_by_tenant, const int32_t* row_token,
                         const int32_t* tile_tenant, int n_mtiles, int n_ntiles, uint16_t* y, int64_t out, int64_t in,
-                        bool halve_last_round, hipStream_t st) {
+                        bool halve_last_round, hipStream_t st, More... more) {
     const hipError_t ea = lds_limit.run([&] {
         hipFuncAttributes fa;
         const hipError_t e = hipFuncGetAttributes(&fa, (const void*)kernel);
@@ -608,31 +667,33 @@ hipError_t launch_tiles(Kernel kernel, PerDeviceOnce& lds_limit, int lds_bytes, 
     const int64_t n_virtual = n_full + 2 * (tiles - n_full);
     const unsigned grid = (unsigned)((n_virtual + round - 1) / round * round);   // surplus workgroups return at once
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), lds_bytes, st, x, w, packed_by_tenant, alpha_by_tenant, row_token,
-                       tile_tenant, y, out, in, n_mtiles, n_ntiles, (int)n_full);
+                       tile_tenant, y, out, in, n_mtiles, n_ntiles, (int)n_full, more...);
     return hipGetLastError();
 }
 
 }  // namespace
 
 // waves: 4 (one wavefront per SIMD) or 8 (two); row_token: 128 entries per token tile; tiled (4 wavefronts only): w and
-// the tenants' signs in the serving layout
-hipError_t launch_linear_prefill_big(const uint16_t* x, const uint16_t* w, const uint32_t* const* packed_by_tenant,
-                                     const float* alpha_by_tenant, const int32_t* row_token, const int32_t* tile_tenant,
-                                     int n_mtiles, uint16_t* y, int64_t T, int64_t out, int64_t in, int waves, bool halve_last_round,
-                                     bool tiled, hipStream_t st) {
-    if (!prefill_big_fits(T, out, in) || (waves != 4 && waves != 8) || (tiled && waves != 4)) return hipErrorInvalidValue;
+// the tenants' signs in the serving layout; wscale != nullptr (4 wavefronts, row-major): w is the int8 base, wscale its scales
+hipError_t launch_linear_prefill_big(const uint16_t* x, const void* w_any, const uint32_t* const* packed_by_tenant,
+                                     const float* alpha_by_tenant, const float* wscale, const int32_t* row_token,
+                                     const int32_t* tile_tenant, int n_mtiles, uint16_t* y, int64_t T, int64_t out, int64_t in,
+                                     int waves, bool halve_last_round, bool tiled, hipStream_t st) {
+    if (!prefill_big_fits(T, out, in) || (waves != 4 && waves != 8) || ((tiled || wscale) && waves != 4) || (tiled && wscale))
+        return hipErrorInvalidValue;
     const int n_ntiles = (int)((out + kBgN - 1) / kBgN);
     const int64_t tiles = (int64_t)n_mtiles * n_ntiles;
     if (tiles < 1 || tiles > (int64_t)1 << 30) return hipErrorInvalidValue;
-    static PerDeviceOnce once4, once8, once4t;
-    if (tiled)
-        return launch_tiles(linear_prefill_big_kernel<1, true>, once4t, kBgLdsBytes, 256, x, w, packed_by_tenant, alpha_by_tenant,
-                            row_token, tile_tenant, n_mtiles, n_ntiles, y, out, in, halve_last_round, st);
-    if (waves == 4)
-        return launch_tiles(linear_prefill_big_kernel<1, false>, once4, kBgLdsBytes, 256, x, w, packed_by_tenant, alpha_by_tenant,
-                            row_token, tile_tenant, n_mtiles, n_ntiles, y, out, in, halve_last_round, st);
-    return launch_tiles(linear_prefill_big_kernel<2, false>, once8, kBgLdsBytes, 512, x, w, packed_by_tenant, alpha_by_tenant, row_token,
-                        tile_tenant, n_mtiles, n_ntiles, y, out, in, false, st);
+    static PerDeviceOnce once[4];
+    const uint16_t* w = (const uint16_t*)w_any;
+    auto go = [&](auto kernel, PerDeviceOnce& o, int threads, bool halve) {
+        return launch_tiles(kernel, o, kBgLdsBytes, threads, x, w, packed_by_tenant, alpha_by_tenant, row_token, tile_tenant, n_mtiles,
+                            n_ntiles, y, out, in, halve, st, wscale);
+    };
+    if (tiled) return go(linear_prefill_big_kernel<1, kSrcTiled>, once[0], 256, halve_last_round);
+    if (wscale) return go(linear_prefill_big_kernel<1, kSrcQ8>, once[1], 256, halve_last_round);
+    if (waves == 4) return go(linear_prefill_big_kernel<1, kSrcRowMajor>, once[2], 256, halve_last_round);
+    return go(linear_prefill_big_kernel<2, kSrcRowMajor>, once[3], 512, false);
 }
 
 // One product on W + alpha S (formed in fp16 on the way to the matrix cores); row_token: kPrefillMergedTile = 256
