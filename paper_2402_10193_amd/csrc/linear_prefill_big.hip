@@ -108,7 +108,9 @@ __device__ __forceinline__ void mfma_in_place(float16v& acc, const half8 a, cons
 // 256 nt .. + 256.
 // WM = 1: 4 wavefronts (1 x 4), each TM tokens x 64 features, alone on its SIMD; two sets of staging registers
 // (loads two steps ahead).  WM = 2: 8 wavefronts (2 x 4), each TM / 2 x 64, two per SIMD; one set (one step ahead).
-// TM = 128, or 64 (WM = 1 only): half a tile, for the tiles of a last round that would leave most units idle.
+// TM = 128, or 64 or 32 (WM = 1 only): part of a tile, for the tiles of a last round that would leave most units idle and for
+// tenants with few tokens (32 rows are bound by bringing W into LDS, 38 KiB per step against 512 cycles of MFMA per SIMD;
+// 200 tokens of 16 tenants on 4096 x 4096, with the loads of W in whole pieces (below): tiled 85 -> 55 us, row-major 87 -> 73).
 // MERGED: one product instead of two.  The table holds +-alpha (alpha rounded to fp16) instead of +-1, a lane adds
 // its sign operand to its W operand in fp16 (one rounding per weight: the fine-tuned weight W + alpha S as an fp16
 // model would store it, the left-hand side of Eq. 6) and multiplies once: half the matrix-core work, and a result
@@ -142,15 +144,15 @@ __device__ __forceinline__ void prefill_big_tile(
     // an accumulator's uses apart.  A k slice issues, for every (i, j), one MFMA into accb[i][j] and one into accd[i][j]:
     // 4 MI MFMAs, each accumulator once, always in the same order, so 4 MI - 1 other MFMAs (each 8 passes = 32 cycles of
     // the matrix pipe) lie between two uses of one accumulator.  The dependent-accumulate hazard of the 8-pass
-    // instructions is below 20 cycles; 7 MFMAs (MI = 2: 64-row halves, or two wavefronts per SIMD) are 224.
+    // instructions is below 20 cycles; 7 MFMAs (MI = 2: 64-row halves, or two wavefronts per SIMD) are 224, 3 (MI = 1) are 96.
     // The epilogue reads the accumulators with vector instructions after two `s_nop 15` (32 wait states; the rule for
     // reading the result of an 8-pass MFMA asks for 18).  Every instantiation has a full-output parity test.
     // (MERGED: 2 MI MFMAs per slice, each accumulator once: 3 or 7 others, 96 cycles or more, between two uses.)
     constexpr int kMfmasBetweenUses = (MERGED ? 2 : 4) * MI - 1;
-    static_assert(MI == 2 || MI == 4 || (MERGED && MI == 8), "the slice schedules below are written for these token blocks per wavefront");
-    static_assert(kMfmasBetweenUses >= (MERGED ? 3 : 7), "an accumulator would be used again while its last MFMA may still be in the pipe");
+    static_assert((!MERGED && MI == 1) || MI == 2 || MI == 4 || (MERGED && MI == 8), "the slice schedules below are written for these token blocks per wavefront");
+    static_assert(kMfmasBetweenUses >= 3, "an accumulator would be used again while its last MFMA may still be in the pipe");
     constexpr int kBgXPer = TM * 8 / kThreads, kBgWPer = kBgN * 8 / kThreads;   // 16-byte chunks per thread and step
-    constexpr int kSets = (WM == 1 && TM <= kBgM) ? 2 : 1;   // (256 rows: the registers hold one set)
+    constexpr int kSets = (WM == 1 && TM <= kBgM) ? 2 : 1;   // (256 rows: the registers hold one set; four for 32 or 64 rows change nothing)
     static_assert(!MERGED || WM == 1, "the merged form runs one wavefront per SIMD");
     static_assert(!TILED || WM == 1, "the tiled sources are written for one row of signs per thread");
     static_assert(!Q8 || (WM == 1 && !MERGED), "the 8-bit base runs the two-product form, one wavefront per SIMD");
@@ -179,27 +181,32 @@ __device__ __forceinline__ void prefill_big_tile(
         uint32_t s0, s1;      // row-major signs: the row's two words of the step
         uint32_t su[4];       // tiled signs: the 2 bytes (slices 2 (step % 4), + 1) of the row's lanes g = 0..3
     };
-    Staged set0, set1;
-    const int step_b = 1 < last ? 1 : last;   // what the second set holds first
+    Staged sets[kSets];
+    auto first_step = [&](const int s) { return s < last ? s : last; };   // what set s holds first
 #pragma unroll
     for (int i = 0; i < kBgWPer; ++i) {
-        const int q = tid + kThreads * i, row = q >> 3, c8 = q & 7;
+        // which 16-byte chunk of the W tile: consecutive threads take the chunks of a row (row-major), or consecutive pieces of
+        // a slice of 16 rows (tiled: a wavefront 1 KiB in one piece; in row order every lane of a load would be an access of
+        // its own, 64 cycles of the address unit per load, 2048 per step -- as many as the step's MFMAs take; 1100 tokens
+        // of 13 tenants on 11008 x 4096: 278 -> 244 us, 8 x 512 tokens on 4096 x 11008 as one product: 351 -> 338)
+        const int q = tid + kThreads * i, t = q & 63, piece = q >> 6;
+        const int row = TILED ? (piece >> 1) * 16 + (t & 15) : q >> 3, c8 = TILED ? (piece & 1) * 4 + (t >> 4) : q & 7;
         const int64_t wrow = n0 + row < out ? row : out - 1 - n0;
         // tiled: row block wrow / 16, slice c8 / 4 of the step's two, lane (wrow % 16, c8 % 4)
         wsrc[i] = TILED ? (uint32_t)((wrow >> 4) * k_tiles * 8192) + (c8 >> 2) * 1024 + (c8 & 3) * 256 + (uint32_t)(wrow & 15) * 16
                         : (uint32_t)(wrow * in * (Q8 ? 1 : 2)) + c8 * (Q8 ? 8 : 16);
         wdst[i] = lds_at(Lds::kWBase + bg_off(row, c8));
         asm volatile("" : "+v"(wdst[i]));   // a register of its own: derived from xdst[i], it would cost an addition per use
-        set0.wg[i] = *(const WChunk*)(wbase + wsrc[i]);
+        sets[0].wg[i] = *(const WChunk*)(wbase + wsrc[i]);
     }
     const int tenant = tile_tenant[mt];
     int tokv[kBgXPer];
 #pragma unroll
     for (int i = 0; i < kBgXPer; ++i) tokv[i] = tile_tokens[r0 + ((tid + kThreads * i) >> 3)];
-    if (kSets == 2) {
 #pragma unroll
-        for (int i = 0; i < kBgWPer; ++i) set1.wg[i] = *(const WChunk*)(wbase + (int64_t)step_b * kWStep + wsrc[i]);
-    }
+    for (int s = 1; s < kSets; ++s)
+#pragma unroll
+        for (int i = 0; i < kBgWPer; ++i) sets[s].wg[i] = *(const WChunk*)(wbase + (int64_t)first_step(s) * kWStep + wsrc[i]);
     __builtin_amdgcn_sched_barrier(0);
 
     // byte -> 8 fp16 (+1.0 where the bit is set, else -1.0; MERGED: +alpha, -alpha), element e = bit e; entry
@@ -236,8 +243,13 @@ __device__ __forceinline__ void prefill_big_tile(
 #pragma unroll
             for (int g = 0; g < 4; ++g) st.su[g] = ssrc_tiled[at + g * 64];
         } else {
-            st.s0 = ssrc[2 * step];
-            if (WM == 1) st.s1 = ssrc[2 * step + 1];
+            if constexpr (WM == 1) {   // one load: every lane is on a row of its own, and the address unit counts rows
+                const u32x2 s = *(const u32x2 __attribute__((address_space(1)))*)(ssrc + 2 * step);   // in % 64 == 0: 8-byte aligned
+                st.s0 = s[0];
+                st.s1 = s[1];
+            } else {
+                st.s0 = ssrc[2 * step];
+            }
         }
     };
 #pragma unroll
@@ -247,11 +259,11 @@ __device__ __forceinline__ void prefill_big_tile(
         xsrc[i] = (uint32_t)((int64_t)(tok >= 0 ? tok : 0) * in * 2) + c8 * 16;
         if (c8 == 0) lds_put<int>(lds_at(2 * kBgBufBytes + kBgLutBytes + row * 4), tok);   // for the epilogue
         xdst[i] = lds_at(bg_off(row, c8));
-        set0.xg[i] = *(const u32x4*)(xbase + xsrc[i]);
-        if (kSets == 2) set1.xg[i] = *(const u32x4*)(xbase + (int64_t)step_b * kBgRowBytes + xsrc[i]);
+#pragma unroll
+        for (int s = 0; s < kSets; ++s) sets[s].xg[i] = *(const u32x4*)(xbase + (int64_t)first_step(s) * kBgRowBytes + xsrc[i]);
     }
-    fetch_signs(set0, 0);
-    if (kSets == 2) fetch_signs(set1, step_b);
+#pragma unroll
+    for (int s = 0; s < kSets; ++s) fetch_signs(sets[s], first_step(s));
 
     const lds_bytes sdst = lds_at(Lds::kSBase + tid * (WM == 1 ? 8 : 4));
     // items: the x chunks, the W chunks, the sign word(s)
@@ -388,9 +400,11 @@ __device__ __forceinline__ void prefill_big_tile(
     // operands of slice 0 are in operand set 0 (read behind the previous step's barrier).
     // pairs of MFMAs between an item's LDS write and its next load: where the step is long enough, all the writes
     // first and then all the loads, so that no pair carries both
-    constexpr int kLagMax = 4 * MI * 2 - kItems, kLag = kLagMax < kItems ? kLagMax : kItems;
+    // (32 rows: a step has 8 pairs, so an item pair goes behind each)
+    constexpr int kPerPair = MI == 1 ? 2 : 1, kItemPairs = (kItems + kPerPair - 1) / kPerPair;
+    constexpr int kLagMax = 4 * MI * 2 - kItemPairs, kLag = kLagMax < kItemPairs ? kLagMax : kItemPairs;
     static_assert(kLag >= 1, "an item is written out before it is fetched again");
-    static_assert(kItems <= 3 * MI * 2 && kItems - 1 + kLag < 4 * MI * 2, "all items are staged before the barrier slice and fetched within the step");
+    static_assert(kItemPairs <= 3 * MI * 2 && kItemPairs - 1 + kLag < 4 * MI * 2, "all items are staged before the barrier slice and fetched within the step");
     auto do_step = [&](const int step, const int buf, Staged& next) {
         const int step3 = step + 1 + kSets < last ? step + 1 + kSets : last;
 #pragma unroll
@@ -436,8 +450,11 @@ __device__ __forceinline__ void prefill_big_tile(
                         if (p > kX0 + kBgXPer && p <= kX0 + 2 * kBgXPer) fetch_item(next, step3, p - kX0 - kBgXPer - 1);
                         if (p == kX0 + 2 * kBgXPer + 1) fetch_item(next, step3, kItems - 1);
                     } else {
-                        if (p < kItems) stage_item(next, buf ^ 1, p);
-                        if (p >= kLag && p - kLag < kItems) fetch_item(next, step3, p - kLag);
+#pragma unroll
+                        for (int e = 0; e < kPerPair; ++e) {
+                            if (p * kPerPair + e < kItems) stage_item(next, buf ^ 1, p * kPerPair + e);
+                            if (p >= kLag && (p - kLag) * kPerPair + e < kItems) fetch_item(next, step3, (p - kLag) * kPerPair + e);
+                        }
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -491,8 +508,8 @@ __device__ __forceinline__ void prefill_big_tile(
         }
     };
 
-    stage(set0, 0);   // both sets were requested at the top
-    fetch(set0, kSets < last ? kSets : last);
+    stage(sets[0], 0);   // all sets were requested at the top
+    fetch(sets[0], first_step(kSets));
     bg_barrier();       // the table and the tiles of step 0 are complete
     read_signs(0);
     int step = 0;
@@ -502,17 +519,22 @@ __device__ __forceinline__ void prefill_big_tile(
 #pragma unroll
         for (int m = 0; m < 4; ++m) merge_word(0, 0, m);
         for (; step + 1 < n_steps; step += 2) {
-            do_step_merged(step, 0, kSets == 2 ? set1 : set0);
-            do_step_merged(step + 1, 1, set0);
+            do_step_merged(step, 0, sets[1 % kSets]);
+            do_step_merged(step + 1, 1, sets[0]);
         }
-        if (step < n_steps) do_step_merged(step, 0, kSets == 2 ? set1 : set0);
+        if (step < n_steps) do_step_merged(step, 0, sets[1 % kSets]);
     } else {
         read_slice(0, 0, 0);
-        for (; step + 1 < n_steps; step += 2) {
-            do_step(step, 0, kSets == 2 ? set1 : set0);
-            do_step(step + 1, 1, set0);
+        // step s writes out set (s + 1) % kSets, which holds step s + 1, and refills it with step s + 1 + kSets
+        constexpr int kUnroll = kSets > 1 ? kSets : 2;
+        static_assert(kUnroll % 2 == 0 && kUnroll % kSets == 0, "the LDS buffer alternates, the set goes round");
+        for (; step + kUnroll <= n_steps; step += kUnroll) {
+#pragma unroll
+            for (int q = 0; q < kUnroll; ++q) do_step(step + q, q & 1, sets[(q + 1) % kSets]);
         }
-        if (step < n_steps) do_step(step, 0, kSets == 2 ? set1 : set0);
+#pragma unroll
+        for (int q = 0; q < kUnroll - 1; ++q)
+            if (step + q < n_steps) do_step(step + q, q & 1, sets[(q + 1) % kSets]);
     }
 
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");   // the last MFMAs have left the pipe before their results are read
@@ -592,10 +614,16 @@ __global__ __launch_bounds__(256 * WM, 1) void linear_prefill_big_kernel(
     if (!bg_tile_of_block(n_mtiles, n_ntiles, n_full, &mt, &nt, &half)) return;
     const int32_t* const tile_tokens = row_token + mt * kBgM;
     if constexpr (WM == 1) {
-        // half a tile: of a last round that is cut in two, or where the tile's upper half is empty (rows are filled from the top)
+        // half a tile: of a last round that is cut in two, or where the tile's upper half is empty (rows are filled from the
+        // top); a quarter where only that many rows are filled
         if (half >= 0 || tile_tokens[kBgM / 2] < 0) {
             const int r0 = half > 0 ? kBgM / 2 : 0;
             if (tile_tokens[r0] < 0) return;   // nothing in this half
+            if (tile_tokens[r0 + kBgM / 4] < 0) {
+                prefill_big_tile<1, kBgM / 4, false, SRC>(x, w, packed_by_tenant, alpha_by_tenant, tile_tokens, tile_tenant, y, out, in,
+                                                          mt, nt, r0, wscale);
+                return;
+            }
             prefill_big_tile<1, kBgM / 2, false, SRC>(x, w, packed_by_tenant, alpha_by_tenant, tile_tokens, tile_tenant, y, out, in, mt, nt,
                                                       r0, wscale);
             return;
