@@ -133,10 +133,10 @@ bd_status bd_compress_batch(int32_t n, const uint16_t* const* w_base_f16, const 
  * Up to 32 tokens run as one decode launch and need no workspace.  More tokens (the prefill regime
  * of Sec. 4.3: many tokens per tenant) can run as ONE matrix-core GEMM launch over all tokens if
  * `workspace` holds bd_workspace_bytes(BD_OP_LINEAR_MULTITENANT, T, out, in, n_tenants) bytes
- * (256-byte aligned; it receives the token permutation).  With a NULL or smaller workspace the same
- * result is produced by ceil(T / 32) decode launches, each re-reading the base; with a workspace the
- * library takes whichever of the two a cost estimate on the host says is quicker (GEMM tiles hold one
- * tenant's tokens only, so a batch with a few tokens per tenant is cheaper as decode launches).
+ * (256-byte aligned; it receives the token permutation).  Without one the same result (up to the order of
+ * additions) is produced by ceil(T / 32) decode launches, each re-reading the base, or, for in % 128 == 0, by a
+ * kernel for tens to a few hundred tokens with a few per tenant, which reads the base once per 128 columns (a
+ * tenant's tokens padded to 16); the library takes whichever a cost estimate on the host says is quickest.
  * Speed: this call reads the tensors in the canonical row-major layout, which costs a decode launch four times the
  * cache accesses per byte of the serving layout; a decode step through it runs at about two thirds of the rate of
  * bd_linear_multitenant_tiled on the same matrices (and the grouped tiled call saves three launches per layer on top).
@@ -206,7 +206,8 @@ bd_status bd_tile_signs(const uint32_t* packed, int64_t out, int64_t in, uint32_
  * Tokens are grouped by tenant inside the call, over the whole batch; up to 32 tokens are one launch
  * (two 16-column tiles that share the base registers), more run as several launches of 32 consecutive
  * tokens of the grouped order (the base is then streamed once per launch, a delta once per launch that
- * holds one of its tenant's tokens).  Needs no workspace. */
+ * holds one of its tenant's tokens) or, where an estimate says it is quicker, through the kernel for tens to a few
+ * hundred tokens (see bd_linear_multitenant; in % 128 == 0).  Needs no workspace. */
 bd_status bd_linear_multitenant_tiled(const uint16_t* x_f16, const uint16_t* w_tiled,
                                       const uint32_t* const* tiled_by_tenant,
                                       const float* alpha_by_tenant,
@@ -242,7 +243,8 @@ bd_status bd_linear_multitenant_tiled_gemm(const uint16_t* x_f16, const uint16_t
  *   tiled_by_mat_tenant HOST [n_mats * n_tenants], entry m * n_tenants + e = tenant e's delta of matrix m
  *   alpha_by_mat        HOST [n_mats] of device arrays [n_tenants]
  *   y_f16               HOST [n_mats] of device pointers, y_m is [T, out[m]]
- *   out                 HOST [n_mats]; `in`, x, T and tenant_of_token are shared. */
+ *   out                 HOST [n_mats]; `in`, x, T and tenant_of_token are shared.
+ * Up to 32 tokens give the bits of n_mats separate calls; with more, the kernel is chosen for the group as a whole. */
 bd_status bd_linear_multitenant_tiled_group(int32_t n_mats, const uint16_t* x_f16,
                                             const uint16_t* const* w_tiled,
                                             const uint32_t* const* tiled_by_mat_tenant,

@@ -5,6 +5,7 @@
 
 #include <atomic>
 #include <stdint.h>
+#include <type_traits>
 
 #include "bd_device.h"
 
@@ -70,6 +71,24 @@ hipError_t launch_linear_prefill_merged(const uint16_t* x, const uint16_t* w, co
                                         const float* alpha_by_tenant, const int32_t* row_token, const int32_t* tile_tenant,
                                         int n_mtiles, uint16_t* y, int64_t T, int64_t out, int64_t in, bool halve_last_round,
                                         bool tiled, hipStream_t st);
+
+// Batches of tens to a few hundred tokens (linear_wide.hip): tokens sorted by tenant, every tenant padded to tiles of 16
+// columns.  Everything travels in the kernel arguments.
+constexpr int kWideMaxTiles = 64;          // column tiles of one launch
+constexpr int kWideMaxChunk = 8;           // column tiles of one workgroup
+constexpr uint32_t kWideNoToken = 0xFFFFu; // an empty column (token ids are below 65535)
+struct WideArgs {
+    const uint16_t* x;                          // [T, in]
+    const uint16_t* w;                          // [out, in] row-major, or the tiled base
+    uint16_t* y;                                // [T, out]
+    const uint32_t* const* packed_by_tenant;    // row-major: the caller's device table
+    const float* alpha_by_tenant;               // device
+    int32_t out, in, KT, units, row_blocks, n_tiles, tiles_per_chunk;
+    const uint32_t* signs[kWideMaxTiles];       // tiled: the tile's tenant's delta
+    int32_t tenant[kWideMaxTiles];
+    uint16_t col_token[kWideMaxTiles][16];
+};
+hipError_t launch_linear_wide(const WideArgs& args, int row_blocks_per_group, bool rowmajor, hipStream_t st);
 
 // 8-bit round-to-nearest base: q [out, in] int8 and one binary32 scale per row; the compressor against scale * q
 hipError_t launch_quantize_rtn8(const uint16_t* w, int64_t out, int64_t in, int8_t* q, float* scale, hipStream_t st);

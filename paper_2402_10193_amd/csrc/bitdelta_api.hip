@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <utility>
 #include <vector>
 
 #include "bd_launch.h"
@@ -204,47 +205,170 @@ hipError_t run_prefill(const uint16_t* x, const void* w, const uint32_t* const* 
                                      out, in, k_planes, st);
 }
 
-// Which way is quicker for T > 32 tokens when both are possible: one GEMM launch, whose tiles of 128 token rows
-// never mix tenants (a tenant with 3 tokens still costs a whole tile), or decode launches of 32 tokens each, which
-// re-read the base per launch but spend nothing on empty rows.  Rough model from measured rates (MI355X, graph
-// replay): a 128 x 256 tile takes 1.45 us per 64-wide k step plus 10 us around the loop, one tile per compute unit at
-// a time; a decode launch of the matrix-core kernel on the row-major tensors takes 7 us plus its base bytes at
-// 6.2 TB/s plus the sign bytes of its job slots (4, 8 or 16: at least 4 are multiplied) at 3.1 TB/s (7B shapes,
-// 1 to 16 tenants: 20 to 35 us per launch); the vector-ALU kernel streams everything at 1.3 TB/s plus 8 us.  A wrong guess costs time, never correctness.
-bool prefill_gemm_pays(const int32_t* tenant_of_token, int64_t T, int64_t out, int64_t in, int32_t n_tenants, bool big,
-                       bool decode_on_matrix_cores) {
-    std::vector<int32_t> count((size_t)n_tenants, 0);
-    for (int64_t i = 0; i < T; ++i) ++count[(size_t)tenant_of_token[i]];
-    int64_t n_mtiles = 0;
-    for (int32_t t = 0; t < n_tenants; ++t) n_mtiles += (count[(size_t)t] + bd::kPrefillTile - 1) / bd::kPrefillTile;
+// ---- batches between a decode launch and a GEMM: linear_wide.hip ----
+
+int cus_or_256() {
     int cus = 256;
     if (bd::device_cu_count(&cus) != hipSuccess || cus < 1) cus = 256;
-    const double steps = (double)in / 64.0;
-    double gemm_us;
-    if (big) {
-        const int64_t tiles = n_mtiles * ((out + 255) / 256);
-        gemm_us = (double)((tiles + cus - 1) / cus) * (steps * 1.45 + 10.0);
-    } else {   // 128 x 128 tiles, two workgroups per compute unit
-        const int64_t tiles = n_mtiles * ((out + 127) / 128);
-        gemm_us = (double)((tiles + 2 * cus - 1) / (2 * cus)) * (steps * 1.9 + 10.0);
+    return cus;
+}
+
+// Column tiles of one call: tokens sorted by tenant (stable), each tenant cut into tiles of 16 columns.
+struct WideTiles {
+    std::vector<int32_t> tenant;               // per tile
+    std::vector<uint16_t> token;               // 16 per tile, kWideNoToken where empty
+};
+WideTiles wide_tiles(const int32_t* tenant_of_token, int64_t T) {
+    std::vector<int32_t> order((size_t)T);
+    for (int64_t i = 0; i < T; ++i) order[(size_t)i] = (int32_t)i;
+    std::stable_sort(order.begin(), order.end(),
+                     [&](int32_t a, int32_t b) { return tenant_of_token[a] < tenant_of_token[b]; });
+    WideTiles t;
+    int in_tile = 16;
+    for (int64_t i = 0; i < T; ++i) {
+        const int32_t tenant = tenant_of_token[order[(size_t)i]];
+        if (in_tile == 16 || tenant != t.tenant.back()) {
+            t.tenant.push_back(tenant);
+            t.token.insert(t.token.end(), 16, (uint16_t)bd::kWideNoToken);
+            in_tile = 0;
+        }
+        t.token[(t.tenant.size() - 1) * 16 + (size_t)in_tile++] = (uint16_t)order[(size_t)i];
     }
-    double decode_us = 0.0;
-    std::vector<int32_t> seen((size_t)n_tenants, -1);
-    for (int64_t t0 = 0, chunk = 0; t0 < T; t0 += kMaxDecodeTokens, ++chunk) {
-        const int64_t n = std::min<int64_t>(kMaxDecodeTokens, T - t0);
-        int distinct = 0;
-        for (int64_t i = t0; i < t0 + n; ++i) {
-            int32_t& s = seen[(size_t)tenant_of_token[i]];
-            if (s != (int32_t)chunk) {
-                s = (int32_t)chunk;
-                ++distinct;
+    return t;
+}
+
+// How a launch of n column tiles is cut: row blocks per workgroup (1 or 2), column tiles per workgroup, and its estimated
+// time.  Fitted to 1024 x 1024, 4096 x 4096 and 4096 x 11008 with 4 to 24 tiles: 5 us around a workgroup's loop, in it
+// 0.45 us (one row block) or 0.70 us (two) per column tile and 1024 of `in`; one workgroup per compute unit at a time.
+struct WidePlan {
+    int R, per_chunk;
+    double us;
+};
+WidePlan wide_plan(int n, int64_t out, int64_t in, int cus) {
+    WidePlan best{0, 0, 1e30};
+    const int64_t rb = bd::tiled_row_blocks(out);
+    const double per_wave = (double)((in / 128 + 7) / 8);
+    for (int R = 1; R <= 2; ++R) {
+        const int64_t groups = (rb + R - 1) / R;
+        const int min_chunks = (n + bd::kWideMaxChunk - 1) / bd::kWideMaxChunk;
+        for (int chunks = min_chunks; chunks <= min_chunks + 3 && chunks <= n; ++chunks) {
+            const int per = (n + chunks - 1) / chunks, run = (per + 1) / 2 * 2;   // instantiated for 2, 4, 6, 8
+            const int64_t wgs = groups * ((n + per - 1) / per);
+            const double us = (double)((wgs + cus - 1) / cus) * (5.0 + per_wave * run * (R == 1 ? 0.45 : 0.70));
+            if (us < best.us) best = WidePlan{R, per, us};
+        }
+    }
+    return best;
+}
+double wide_us(int n_all, int active, int64_t out, int64_t in, int cus) {
+    double us = 2.0;
+    const int launches = (n_all + bd::kWideMaxTiles - 1) / bd::kWideMaxTiles;
+    for (int l = 0; l < launches; ++l)
+        us += wide_plan((int)((int64_t)n_all * (l + 1) / launches - (int64_t)n_all * l / launches), out, in, cus).us;
+    const double elems = (double)out * (double)in;   // the stream: the base once, every active tenant's signs once
+    return std::max(us, 6.0 + elems * (2.0 + (double)active / 8.0) / 4.5e6);
+}
+
+bool wide_fits(int64_t T, int64_t out, int64_t in) {
+    return in >= 128 && in % 128 == 0 && out >= 1 && T < 65535 && (uint64_t)T * (uint64_t)in * 2 < ((uint64_t)1 << 32) &&
+           (uint64_t)(bd::tiled_row_blocks(out) * bd::tiled_k_tiles(in)) * bd::kTileBaseBytes < ((uint64_t)1 << 32);
+}
+
+// packed_dev: the row-major tensors (device pointer table); otherwise w is the tiled base and tiled_host the tenants' tiled deltas
+hipError_t run_wide(const WideTiles& t, const uint16_t* x, const uint16_t* w, const uint32_t* const* packed_dev,
+                    const uint32_t* const* tiled_host, const float* alpha, uint16_t* y, int64_t out, int64_t in, hipStream_t st) {
+    const int cus = cus_or_256(), n_all = (int)t.tenant.size(), launches = (n_all + bd::kWideMaxTiles - 1) / bd::kWideMaxTiles;
+    for (int l = 0; l < launches; ++l) {
+        const int first = (int)((int64_t)n_all * l / launches), n = (int)((int64_t)n_all * (l + 1) / launches) - first;
+        bd::WideArgs a;
+        std::memset(&a, 0, sizeof(a));
+        a.x = x;
+        a.w = w;
+        a.y = y;
+        a.packed_by_tenant = packed_dev;
+        a.alpha_by_tenant = alpha;
+        a.out = (int32_t)out;
+        a.in = (int32_t)in;
+        a.KT = (int32_t)bd::tiled_k_tiles(in);
+        a.units = (int32_t)(in / 128);
+        a.row_blocks = (int32_t)bd::tiled_row_blocks(out);
+        a.n_tiles = n;
+        const WidePlan p = wide_plan(n, out, in, cus);
+        a.tiles_per_chunk = p.per_chunk;
+        for (int i = 0; i < n; ++i) {
+            a.tenant[i] = t.tenant[(size_t)(first + i)];
+            if (tiled_host) a.signs[i] = tiled_host[a.tenant[i]];
+            std::memcpy(a.col_token[i], &t.token[(size_t)(first + i) * 16], 32);
+        }
+        const hipError_t e = bd::launch_linear_wide(a, p.R, packed_dev != nullptr, st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+// What a batch of T > 32 tokens looks like to the three ways of running it: decode launches of 32 tokens of the sorted
+// order, which re-read the base per launch but spend nothing on empty rows; the wide kernel, 16-column tiles of one tenant;
+// the GEMM, tiles of 32, 64 or 128 rows of one tenant.  A wrong guess costs time, never correctness.
+struct BatchShape {
+    int active = 0, tiles16 = 0;
+    int64_t tiles32 = 0, tiles64 = 0, tiles128 = 0;      // GEMM tiles by the rows they run
+    std::vector<std::pair<int, int>> launches;           // of 32 tokens: (tokens, distinct tenants)
+};
+BatchShape batch_shape(const int32_t* tenant_of_token, int64_t T) {
+    std::vector<int32_t> sorted(tenant_of_token, tenant_of_token + T);
+    if (!std::is_sorted(sorted.begin(), sorted.end())) std::sort(sorted.begin(), sorted.end());
+    BatchShape s;
+    int in_launch = 0, distinct = 0;
+    for (int64_t i = 0; i < T;) {
+        int64_t e = i;
+        while (e < T && sorted[(size_t)e] == sorted[(size_t)i]) ++e;
+        int64_t n = e - i;
+        i = e;
+        ++s.active;
+        s.tiles16 += (int)((n + 15) / 16);
+        s.tiles128 += n / bd::kPrefillTile;
+        const int64_t rest = n % bd::kPrefillTile;
+        if (rest > 64) ++s.tiles128;
+        else if (rest > 32) ++s.tiles64;
+        else if (rest > 0) ++s.tiles32;
+        while (n > 0) {
+            const int take = (int)std::min<int64_t>(n, kMaxDecodeTokens - in_launch);
+            ++distinct;
+            in_launch += take;
+            n -= take;
+            if (in_launch == kMaxDecodeTokens) {
+                s.launches.emplace_back(in_launch, distinct);
+                in_launch = distinct = 0;
             }
         }
-        const double elems = (double)out * (double)in;
-        decode_us += decode_on_matrix_cores ? 7.0 + 2.0 * elems / 6.2e6 + (double)std::max(distinct, 4) * elems / 8.0 / 3.1e6
-                                            : 8.0 + elems * (2.0 + (double)distinct / 8.0) / 1.3e6;
     }
-    return gemm_us < decode_us;
+    if (in_launch > 0) s.launches.emplace_back(in_launch, distinct);
+    return s;
+}
+// The row-major GEMM.  Measured (4096 and 11008 x 4096, graph replay): a 128 x 256 tile takes 1.42 us per 64-wide k step, 1.25
+// with 64 rows and 0.85 with 32, plus 8 us around the loop, one tile per compute unit at a time, and 5 us for the tables.
+double gemm_us(const BatchShape& s, int64_t out, int64_t in, bool big, int cus) {
+    const double steps = (double)in / 64.0;
+    if (!big) {   // 128 x 128 tiles, two workgroups per compute unit, whatever rows are filled
+        const int64_t tiles = (s.tiles32 + s.tiles64 + s.tiles128) * ((out + 127) / 128);
+        return 5.0 + (double)((tiles + 2 * cus - 1) / (2 * cus)) * (steps * 1.9 + 10.0);
+    }
+    const int64_t nt = (out + 255) / 256, tiles = (s.tiles32 + s.tiles64 + s.tiles128) * nt;
+    const double all = (double)nt * (steps * (s.tiles32 * 0.85 + s.tiles64 * 1.25 + s.tiles128 * 1.42)) + 8.0 * (double)tiles;
+    return 5.0 + all / (double)tiles * (double)((tiles + cus - 1) / cus);
+}
+// Decode launches.  Row-major tensors: 7 us plus the base at 6.2 TB/s plus the sign bytes of the launch's job slots (4, 8 or 16
+// per column tile) at 3.1 TB/s, half as much again with two column tiles (20 to 36 us on 4096 x 4096); the vector-ALU
+// kernel streams everything at 1.3 TB/s plus 8 us.  Serving layout: 8 us plus all bytes at 4.6 TB/s (14 to 37 us for the
+// linears of Llama-2-7B), one launch for the matrices of a group (`elems` is their sum).
+double decode_us(const BatchShape& s, double elems, bool tiled, bool on_matrix_cores) {
+    double us = 0.0;
+    for (const auto& [tokens, distinct] : s.launches) {
+        if (tiled) us += 8.0 + elems * (2.0 + (double)distinct / 8.0) / 4.6e6;
+        else if (!on_matrix_cores) us += 8.0 + elems * (2.0 + (double)distinct / 8.0) / 1.3e6;
+        else us += (7.0 + 2.0 * elems / 6.2e6 + (double)std::max(distinct, 4) * elems / 8.0 / 3.1e6) * (tokens > 16 ? 1.5 : 1.0);
+    }
+    return us;
 }
 
 }  // namespace
@@ -431,8 +555,20 @@ bd_status bd_linear_multitenant_variant(const uint16_t* x_f16, const uint16_t* w
     if (prefill_variant && !can_prefill) return need > 0 && in > 0 ? BD_ERR_WORKSPACE : BD_ERR_UNSUPPORTED;
     if (big_variant && !bd::prefill_big_fits(T, out, in)) return BD_ERR_UNSUPPORTED;
     const bool big_default = out >= 256 && bd::prefill_big_fits(T, out, in);
-    if (can_prefill &&
-        (prefill_variant || (variant == 0 && prefill_gemm_pays(tenant_of_token, T, out, in, n_tenants, big_default, mfma_ok)))) {
+    bool gemm_pays = prefill_variant;
+    if (variant == 0 && T > kMaxDecodeTokens && in > 0) {   // the library's choice, by estimated time
+        const BatchShape shape = batch_shape(tenant_of_token, T);
+        const int cus = cus_or_256();
+        const double by_decode = decode_us(shape, (double)out * (double)in, false, mfma_ok);
+        const double by_gemm = can_prefill ? gemm_us(shape, out, in, big_default, cus) : 1e30;
+        if (mfma_ok && wide_fits(T, out, in) && wide_us(shape.tiles16, shape.active, out, in, cus) < std::min(by_decode, by_gemm))
+            return run_wide(wide_tiles(tenant_of_token, T), x_f16, w_base_f16, packed_by_tenant, nullptr, alpha_by_tenant, y_f16, out, in,
+                            hs) == hipSuccess
+                       ? BD_OK
+                       : BD_ERR_DEVICE;
+        gemm_pays = by_gemm < by_decode;
+    }
+    if (can_prefill && gemm_pays) {
         // the large tile (one workgroup per CU, 256 output features wide) pays off when there are at least that many
         int big_waves = 0;
         if (variant == kVariantPrefillBig8) big_waves = 8;
@@ -570,6 +706,29 @@ bd_status tiled_linear_impl(int32_t n_mats, const uint16_t* x_f16, const uint16_
     // A token takes k columns (one per plane) of a 16-column tile; a launch covers two tiles.  More tokens than one
     // launch takes: all of them are sorted by tenant first (stable), so that a tenant's tokens share launches and
     // its delta is streamed as few times as possible; the kernel finds the rows of x and y through the token ids.
+    // Serving layout, one plane, more tokens than a launch takes: the wide kernel, a launch per matrix, where its estimate is
+    // below that of the decode launches, which take the matrices of a group together.
+    if (!rm && !q8 && k == 1 && T > bd::kMaxDecodeTokens) {
+        const BatchShape shape = batch_shape(tenant_of_token, T);
+        const int cus = cus_or_256();
+        bool fits = true;
+        double wide = 0.0, elems = 0.0;
+        for (int m = 0; m < n_mats; ++m) {
+            if (out[m] == 0) continue;
+            fits = fits && wide_fits(T, out[m], in);
+            if (!fits) break;
+            wide += wide_us(shape.tiles16, shape.active, out[m], in, cus);
+            elems += (double)out[m] * (double)in;
+        }
+        if (fits && wide < decode_us(shape, elems, true, true)) {
+            const WideTiles tiles = wide_tiles(tenant_of_token, T);
+            for (int m = 0; m < n_mats; ++m)
+                if (out[m] > 0 && run_wide(tiles, x_f16, w_tiled[m], nullptr, tiled_by_mat_tenant + (size_t)m * n_tenants, alpha_by_mat[m],
+                                           y_f16[m], out[m], in, (hipStream_t)stream) != hipSuccess)
+                    return BD_ERR_DEVICE;
+            return BD_OK;
+        }
+    }
     const int per_tile = bd::kTiledMaxTokens / k;
     const int per_launch = per_tile * bd::kTiledMaxCt;
     std::vector<int32_t> order((size_t)T);

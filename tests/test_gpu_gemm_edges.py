@@ -67,3 +67,74 @@ def test_gemm_q8_tiles(out, inn, counts):
     y = torch.full((len(t.tok), out), float("nan"), dtype=torch.float16, device=DEV)
     bd.linear_multitenant_gemm_q8(t.x, q, scale, bd.TenantTable(t.packed, t.alpha), t.tok, y=y)
     t.check(y, q.double() * scale.double()[:, None], f"q8 {out}x{inn} {counts}")
+
+
+# More than 32 tokens with a few per tenant: tiles of 16 columns (row-major and tiled), against float64 and the decode launches.
+# Rows of `out` around one and two row blocks, one unit of `in` and counts that are no multiple of the eight wavefronts,
+# columns of 1, 15, 16, 17 and 33 tokens, one and several chunks of column tiles, more than one launch's worth of tiles.
+WIDE = [
+    (1, 128, [33]),
+    (16, 256, [16, 17]),
+    (17, 384, [1, 15, 16, 17, 33, 0, 2]),
+    (33, 1152, [40]),
+    (47, 1024, [3] * 12),
+    (300, 2176, [7, 9, 20, 1, 30, 12, 5, 8]),
+    (4112, 512, [12] * 9),
+    (64, 640, [9] * 40 + [16] * 30),         # 70 column tiles: two launches
+    (2064, 1024, [15] * 3),                  # 129 row blocks: one per workgroup; 4 tiles per chunk
+    (4096, 256, [16] * 5),                   # two per workgroup, 6 tiles per chunk
+]
+
+
+@pytest.mark.parametrize("order", ["grouped", "shuffled"])
+@pytest.mark.parametrize("case", range(len(WIDE)))
+def test_wide_batches(case, order):
+    out, inn, counts = WIDE[case]
+    t = Tensors(out, inn, tokens_of(counts, order), len(counts), seed=case)
+    what = f"wide {out}x{inn} {counts} {order}"
+    nan = lambda: torch.full((len(t.tok), out), float("nan"), dtype=torch.float16, device=DEV)
+    table = bd.TenantTable(t.packed, t.alpha)
+    for ws in ("auto", None):
+        y = bd.linear_multitenant(t.x, t.w, table, t.tok, y=nan(), workspace=ws)
+        t.check(y, what=what + f" row-major, workspace {ws}")
+        assert torch.equal(bd.linear_multitenant(t.x, t.w, table, t.tok, workspace=ws), y)      # bitwise reproducible
+    t.check(bd.linear_multitenant(t.x, t.w, table, t.tok, variant=2), what=what + " decode launches")
+    tiled = bd.TiledTenantTable([bd.tile_signs(p, out, inn) if n else None for p, n in zip(t.packed, counts)], t.alpha)
+    wt = bd.tile_base(t.w)
+    y = bd.linear_multitenant_tiled(t.x, wt, out, tiled, t.tok, y=nan())
+    t.check(y, what=what + " tiled")
+    group = bd.TiledGroup([wt, wt], [out, out], [tiled, tiled])
+    ya, yb = bd.linear_multitenant_tiled_group(t.x, group, t.tok, ys=[nan(), nan()])
+    t.check(ya, what=what + " group")
+    assert torch.equal(ya, yb), what + " group"
+
+
+def test_wide_non_finite_values():
+    """Infinities and NaN in x, W and the scales stay in their token, their output row, their tenant; an infinite scale gives
+    the sign of the +-1 sum, or NaN where that sum is zero, also where x is zero over whole parts of the row."""
+    out, inn, counts = 40, 1024, [20, 9, 131]
+    t = Tensors(out, inn, tokens_of(counts), 3, seed=99)
+    clean_x, clean_w = t.x.clone(), t.w.clone()
+    t.x[3, 5] = float("inf")
+    t.x[7, 900] = float("nan")
+    t.w[11, 130] = float("nan")
+    t.x[20:29, 128:] = 0                       # tenant 1: seven of eight units are zero
+    t.x[21] = 0
+    alpha = t.alpha.clone()
+    alpha[1] = float("inf")
+    table = bd.TenantTable(t.packed, alpha)
+    s1 = t.x[20:29].double() @ expand(t.packed[1], inn).t()
+    tiled = [bd.tile_signs(p, out, inn) for p in t.packed]
+    for y, clean in ((bd.linear_multitenant(t.x, t.w, table, t.tok),
+                      bd.linear_multitenant(clean_x, clean_w, bd.TenantTable(t.packed, t.alpha), t.tok)),
+                     (bd.linear_multitenant_tiled(t.x, bd.tile_base(t.w), out, bd.TiledTenantTable(tiled, alpha), t.tok),
+                      bd.linear_multitenant_tiled(clean_x, bd.tile_base(clean_w), out, bd.TiledTenantTable(tiled, t.alpha), t.tok))):
+        keep_rows = [i for i in range(len(t.tok)) if i not in (3, 7) and not 20 <= i < 29]
+        keep_cols = [n for n in range(out) if n != 11]
+        assert torch.equal(y[keep_rows][:, keep_cols], clean[keep_rows][:, keep_cols])
+        assert torch.isnan(y[7]).all() and torch.isnan(y[:, 11]).all()
+        assert not torch.isfinite(y[3]).any()
+        got = y[20:29][:, keep_cols]
+        want = s1[:, keep_cols]
+        assert torch.equal(torch.isnan(got), want == 0)
+        assert torch.equal(got[want != 0], torch.where(want[want != 0] > 0, float("inf"), float("-inf")).half())
