@@ -728,16 +728,24 @@ static hipError_t launch_tiled_t(const TiledArgs& args, int n_jobs, hipStream_t 
     const unsigned grid = (unsigned)((rb_total + rounds - 1) / rounds);
     int n_waves = kMaxWavesTiled;
     while (n_waves > 1 && n_waves > args.KT) n_waves >>= 1;
-    if (args.n_ct == 2) {   // 17..32 tokens: two column tiles, streamed x
-        if (n_jobs <= 4) return launch_inst<Q8, RM, 4, 0, 2>(args, n_waves, grid, st);
-        if (n_jobs <= 8) return launch_inst<Q8, RM, 8, 0, 2>(args, n_waves, grid, st);
-        return launch_inst<Q8, RM, 16, 0, 2>(args, n_waves, grid, st);
-    }
     int xsteps = 0;
     if (args.KT > 0 && args.KT % n_waves == 0 && args.KT / n_waves <= 2) xsteps = args.KT / n_waves;
-    if (n_jobs <= 4) return launch_nj<Q8, RM, 4>(args, n_waves, xsteps, grid, st);
-    if (n_jobs <= 8) return launch_nj<Q8, RM, 8>(args, n_waves, xsteps, grid, st);
-    return launch_nj<Q8, RM, 16>(args, n_waves, xsteps, grid, st);
+    auto go = [&](auto nj) {
+        constexpr int NJ = decltype(nj)::value;
+        if (args.n_ct == 2) return launch_inst<Q8, RM, NJ, 0, 2>(args, n_waves, grid, st);   // 17..32 tokens: two column tiles, streamed x
+        return launch_nj<Q8, RM, NJ>(args, n_waves, xsteps, grid, st);
+    };
+    // A slot without a job costs as much as one with: its signs are requested (slot 0's again) and looked up.  With slots for 4, 8
+    // or 16 only, a 7B layer took 142 us with 9 tenants and 149 with 12 (134 and 139 over the 8-bit base); in steps of two it
+    // takes 125 and 137 (103 and 117).
+    if (n_jobs <= 2) return go(std::integral_constant<int, 2>{});
+    if (n_jobs <= 4) return go(std::integral_constant<int, 4>{});
+    if (n_jobs <= 6) return go(std::integral_constant<int, 6>{});
+    if (n_jobs <= 8) return go(std::integral_constant<int, 8>{});
+    if (n_jobs <= 10) return go(std::integral_constant<int, 10>{});
+    if (n_jobs <= 12) return go(std::integral_constant<int, 12>{});
+    if (n_jobs <= 14) return go(std::integral_constant<int, 14>{});
+    return go(std::integral_constant<int, 16>{});
 }
 
 }  // namespace bd

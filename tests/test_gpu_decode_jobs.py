@@ -1,0 +1,33 @@
+"""Decode launches with every number of job slots (distinct tenants per column tile) and every way a launch of 17 to 32 tokens is
+cut into its two column tiles, against float64 products of the same tensors (bound: see test_gpu_gemm_edges)."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+from paper_2402_10193_amd import binding as bd   # noqa: E402
+from test_gpu_gemm_edges import Tensors, tokens_of   # noqa: E402
+
+DEV = "cuda"
+
+MIXES = [[1] * n for n in range(1, 33)] + [
+    [16, 1], [1, 16], [17], [32], [8, 8, 8], [15, 2, 15], [1, 30, 1], [5, 6, 7, 8], [2] * 16, [3] * 10, [13] + [1] * 15, [1] * 15 + [13],
+]
+
+
+@pytest.mark.parametrize("mix", range(len(MIXES)))
+def test_decode_launches(mix):
+    counts = MIXES[mix]
+    out, inn = [(40, 2048), (33, 640), (272, 2176)][mix % 3]     # x resident (one k tile per wavefront); streamed; streamed, ragged
+    t = Tensors(out, inn, tokens_of(counts, "shuffled"), len(counts), seed=mix)
+    what = f"{out}x{inn} {counts}"
+    tiled = bd.TiledTenantTable([bd.tile_signs(p, out, inn) for p in t.packed], t.alpha)
+    table = bd.TenantTable(t.packed, t.alpha)
+    q, scale = bd.quantize_base_q8(t.w)
+    w8 = q.double() * scale.double()[:, None]
+    t.check(bd.linear_multitenant_tiled(t.x, bd.tile_base(t.w), out, tiled, t.tok), what=what + " tiled")
+    t.check(bd.linear_multitenant(t.x, t.w, table, t.tok), what=what + " row-major")
+    # the 8-bit base: the sum runs over x (1152 + q) and 1152 sum x is taken off again, 2 * 1152 / 127 of the magnitude more per term
+    for y in (bd.linear_multitenant_tiled_q8(t.x, bd.tile_base_q8(q, scale), out, tiled, t.tok),
+              bd.linear_multitenant_q8(t.x, q, scale, table, t.tok)):
+        t.check(y, w8, what + " 8-bit base", extra=(2304.0 * scale.double())[None, :] * t.x.double().abs().sum(dim=1, keepdim=True))
