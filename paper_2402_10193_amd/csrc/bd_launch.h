@@ -55,21 +55,22 @@ hipError_t launch_linear_prefill(const uint16_t* x, const void* w, const uint32_
                                  const float* alpha_by_tenant, const float* wscale, const int32_t* row_token,
                                  const int32_t* tile_tenant, int n_mtiles, uint16_t* y, int64_t out, int64_t in,
                                  int k_planes, hipStream_t st);
-// the 128 x 256 tile GEMM of linear_prefill_big.hip; T = rows of x; halve_last_round (4 wavefronts only): the tiles of a
+// the 128 x 256 tile GEMM of linear_prefill_big.hip; T = rows of x; the first n_large token tiles are the ones with more than
+// half a tile of rows (they run first); halve_last_round (4 wavefronts only): the tiles of a
 // last round that would occupy at most half of the compute units run as two workgroups of 64 token rows each;
 // tiled (4 wavefronts only): w and the tenants' sign tensors are in the serving layout (bd_tile_base / bd_tile_signs);
 // wscale != nullptr (4 wavefronts, row-major): w is the int8 base [out, in], wscale its per-row scales
 bool prefill_big_fits(int64_t T, int64_t out, int64_t in);
 hipError_t launch_linear_prefill_big(const uint16_t* x, const void* w, const uint32_t* const* packed_by_tenant,
                                      const float* alpha_by_tenant, const float* wscale, const int32_t* row_token,
-                                     const int32_t* tile_tenant, int n_mtiles, uint16_t* y, int64_t T, int64_t out, int64_t in,
+                                     const int32_t* tile_tenant, int n_mtiles, int n_large, uint16_t* y, int64_t T, int64_t out, int64_t in,
                                      int waves, bool halve_last_round, bool tiled, hipStream_t st);
 // the same product as one GEMM on W + alpha S, the sum formed in fp16 on the way to the matrix cores; its token tiles
 // (row_token, tile_tenant) have kPrefillMergedTile rows; halve_last_round: as above, with halves of 128 rows
 constexpr int kPrefillMergedTile = 256;
 hipError_t launch_linear_prefill_merged(const uint16_t* x, const uint16_t* w, const uint32_t* const* packed_by_tenant,
                                         const float* alpha_by_tenant, const int32_t* row_token, const int32_t* tile_tenant,
-                                        int n_mtiles, uint16_t* y, int64_t T, int64_t out, int64_t in, bool halve_last_round,
+                                        int n_mtiles, int n_large, uint16_t* y, int64_t T, int64_t out, int64_t in, bool halve_last_round,
                                         bool tiled, hipStream_t st);
 
 // Batches of tens to a few hundred tokens (linear_wide.hip): tokens sorted by tenant, every tenant padded to tiles of 16

@@ -23,6 +23,7 @@
 // The same tile body also runs the left-hand side of Eq. 6, X (W + alpha S) with the bracket rounded to
 // fp16, as ONE product on tiles of 256 tokens x 256 features (linear_prefill_merged_kernel; the caller
 // asks for it by name): see MERGED at prefill_big_tile.
+#include <algorithm>
 #include <type_traits>
 
 #include "bd_device.h"
@@ -61,7 +62,7 @@ constexpr int kBgLdsBytes = BgLds<kBgM>::kTotal;
 // Epilogue: a wavefront's rows of y as fp16, 64 features + 16 B of padding each (rows 4 apart, which one LDS
 // instruction writes together, then fall into different banks), in the tile buffers, which are free by then.
 constexpr int kBgOutRowBytes = 64 * 2 + 16;
-constexpr int kBgPanel = 4, kBgChunk = 32, kBgXcds = 8;  // launch order: 8 x 4 tiles (1024 tokens x 1024 features) per XCD at a time
+constexpr int kBgPanel = 4, kBgXcds = 8;   // launch order: an XCD runs 8 x 4 tiles (1024 tokens x 1024 features) at a time
 
 __device__ __forceinline__ int bg_off(const int row, const int chunk) {
     return row * kBgRowBytes + ((chunk ^ ((row >> 1) & 7)) << 4);
@@ -584,21 +585,33 @@ __device__ __forceinline__ void prefill_big_tile(
     }
 }
 
-// Launch order -> tile.  Tiles are numbered in panels of 8 N tiles, row-major inside, and an XCD takes chunks of 32
-// consecutive numbers, so that the workgroups it runs together form a compact block of tiles.  The tiles from n_full
-// on are run as two workgroups of half a tile each (n_full = all of them: none).  Returns false for a surplus workgroup.
-__device__ __forceinline__ bool bg_tile_of_block(const int n_mtiles, const int n_ntiles, const int n_full, int* mt, int* nt,
+// Launch order -> tile.  Tiles are numbered in panels of kBgPanel N tiles, row-major inside.  The first n_large token tiles hold
+// more than half a tile of rows and take about twice as long as the others: they are numbered first, over all N tiles,
+// so that the launch ends with short tiles.  The tiles from n_full on are run as two workgroups of half a tile each (n_full
+// = all of them: none).  Workgroup ids go round-robin over the XCDs; of each of the three stretches (long, short, halves) an
+// XCD takes one contiguous eighth, so that the tiles it runs together form a compact block and no XCD is left with more
+// long tiles than another.  Returns false for a surplus workgroup.
+__device__ __forceinline__ bool bg_tile_of_block(const int n_mtiles, const int n_large, const int n_ntiles, const int n_full, int* mt, int* nt,
                                                  int* half) {
-    const int L = blockIdx.x, xcd = L % kBgXcds, slot = L / kBgXcds;
-    const int chunk = (slot / kBgChunk) * kBgXcds + xcd;
-    const int v = chunk * kBgChunk + slot % kBgChunk;
-    const int n_tiles = n_mtiles * n_ntiles;
-    if (v >= n_full + 2 * (n_tiles - n_full)) return false;
-    const int t = v < n_full ? v : n_full + ((v - n_full) >> 1);
-    const int per_panel = n_mtiles * kBgPanel;
+    const int xcd = (int)blockIdx.x % kBgXcds;
+    int slot = (int)blockIdx.x / kBgXcds, v = -1;
+    const int n_tiles = n_mtiles * n_ntiles, n_long = min(n_large * n_ntiles, n_full);
+    const int begin[4] = {0, n_long, n_full, n_full + 2 * (n_tiles - n_full)};
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+        const int64_t len = begin[s + 1] - begin[s];
+        const int lo = begin[s] + (int)(len * xcd / kBgXcds), hi = begin[s] + (int)(len * (xcd + 1) / kBgXcds);
+        if (v < 0 && slot < hi - lo) v = lo + slot;
+        slot -= hi - lo;
+    }
+    if (v < 0) return false;
+    int t = v < n_full ? v : n_full + ((v - n_full) >> 1);
+    const bool large = t < n_large * n_ntiles;
+    if (!large) t -= n_large * n_ntiles;
+    const int m0 = large ? 0 : n_large, per_panel = (large ? n_large : n_mtiles - n_large) * kBgPanel;
     const int panel = t / per_panel, tp = t - panel * per_panel;
     const int width = n_ntiles - panel * kBgPanel < kBgPanel ? n_ntiles - panel * kBgPanel : kBgPanel;
-    *mt = tp / width;
+    *mt = m0 + tp / width;
     *nt = panel * kBgPanel + tp % width;
     *half = v < n_full ? -1 : (v - n_full) & 1;
     return true;
@@ -608,10 +621,10 @@ template <int WM, BgSource SRC>
 __global__ __launch_bounds__(256 * WM, 1) void linear_prefill_big_kernel(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ w, const uint32_t* const* __restrict__ packed_by_tenant,
     const float* __restrict__ alpha_by_tenant, const int32_t* __restrict__ row_token, const int32_t* __restrict__ tile_tenant,
-    uint16_t* __restrict__ y, const int64_t out, const int64_t in, const int n_mtiles, const int n_ntiles, const int n_full,
+    uint16_t* __restrict__ y, const int64_t out, const int64_t in, const int n_mtiles, const int n_large, const int n_ntiles, const int n_full,
     const float* __restrict__ wscale) {
     int mt, nt, half;
-    if (!bg_tile_of_block(n_mtiles, n_ntiles, n_full, &mt, &nt, &half)) return;
+    if (!bg_tile_of_block(n_mtiles, n_large, n_ntiles, n_full, &mt, &nt, &half)) return;
     const int32_t* const tile_tokens = row_token + mt * kBgM;
     if constexpr (WM == 1) {
         // half a tile: of a last round that is cut in two, or where the tile's upper half is empty (rows are filled from the
@@ -635,19 +648,24 @@ __global__ __launch_bounds__(256 * WM, 1) void linear_prefill_big_kernel(
 // The merged form on token tiles of 256 rows (row_token holds 256 entries per tile): a wavefront multiplies 256
 // tokens x 64 features per operand of W that it reads, looks up and adds, which is what lets the matrix cores run
 // most of the time although every such operand costs eight instructions.  A tile whose upper 128 rows are empty (a
-// tenant's last tile; the rows of a tile are filled from the top) runs as 128 rows; the tiles from n_full on run as
-// two workgroups of 128 rows each.
+// tenant's last tile; the rows of a tile are filled from the top) runs as 128 rows, or 64 where that holds them; the tiles
+// from n_full on run as two workgroups of 128 rows each.
 template <bool TILED>
 __global__ __launch_bounds__(256, 1) void linear_prefill_merged_kernel(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ w, const uint32_t* const* __restrict__ packed_by_tenant,
     const float* __restrict__ alpha_by_tenant, const int32_t* __restrict__ row_token, const int32_t* __restrict__ tile_tenant,
-    uint16_t* __restrict__ y, const int64_t out, const int64_t in, const int n_mtiles, const int n_ntiles, const int n_full) {
+    uint16_t* __restrict__ y, const int64_t out, const int64_t in, const int n_mtiles, const int n_large, const int n_ntiles, const int n_full) {
     int mt, nt, half;
-    if (!bg_tile_of_block(n_mtiles, n_ntiles, n_full, &mt, &nt, &half)) return;
+    if (!bg_tile_of_block(n_mtiles, n_large, n_ntiles, n_full, &mt, &nt, &half)) return;
     const int32_t* const tile_tokens = row_token + mt * kMergedTile;
     if (half >= 0 || tile_tokens[kBgM] < 0) {
         const int r0 = half > 0 ? kBgM : 0;
         if (tile_tokens[r0] < 0) return;   // nothing in this half
+        if (tile_tokens[r0 + kBgM / 2] < 0) {   // at most 64 rows
+            prefill_big_tile<1, kBgM / 2, true, TILED ? kSrcTiled : kSrcRowMajor>(x, w, packed_by_tenant, alpha_by_tenant, tile_tokens,
+                                                                                  tile_tenant, y, out, in, mt, nt, r0);
+            return;
+        }
         prefill_big_tile<1, kBgM, true, TILED ? kSrcTiled : kSrcRowMajor>(x, w, packed_by_tenant, alpha_by_tenant, tile_tokens, tile_tenant, y, out, in, mt, nt, r0);
         return;
     }
@@ -678,7 +696,7 @@ hipError_t whole_tiles(int64_t tiles, bool halve_last_round, int64_t* n_full) {
 template <typename Kernel, typename... More>
 hipError_t launch_tiles(Kernel kernel, PerDeviceOnce& lds_limit, int lds_bytes, int threads, const uint16_t* x, const uint16_t* w,
                         const uint32_t* const* packed_by_tenant, const float* alpha_by_tenant, const int32_t* row_token,
-                        const int32_t* tile_tenant, int n_mtiles, int n_ntiles, uint16_t* y, int64_t out, int64_t in,
+                        const int32_t* tile_tenant, int n_mtiles, int n_large, int n_ntiles, uint16_t* y, int64_t out, int64_t in,
                         bool halve_last_round, hipStream_t st, More... more) {
     const hipError_t ea = lds_limit.run([&] {
         hipFuncAttributes fa;
@@ -688,14 +706,16 @@ hipError_t launch_tiles(Kernel kernel, PerDeviceOnce& lds_limit, int lds_bytes, 
         return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
     });
     if (ea != hipSuccess) return ea;
-    const int64_t tiles = (int64_t)n_mtiles * n_ntiles, round = (int64_t)kBgChunk * kBgXcds;
+    const int64_t tiles = (int64_t)n_mtiles * n_ntiles;
     int64_t n_full = tiles;
     const hipError_t ew = whole_tiles(tiles, halve_last_round, &n_full);
     if (ew != hipSuccess) return ew;
-    const int64_t n_virtual = n_full + 2 * (tiles - n_full);
-    const unsigned grid = (unsigned)((n_virtual + round - 1) / round * round);   // surplus workgroups return at once
+    const int64_t n_long = std::min<int64_t>((int64_t)n_large * n_ntiles, n_full);
+    int64_t per_xcd = 0;   // the most workgroups an XCD has of each stretch; surplus ones return at once
+    for (const int64_t len : {n_long, n_full - n_long, 2 * (tiles - n_full)}) per_xcd += (len + kBgXcds - 1) / kBgXcds;
+    const unsigned grid = (unsigned)(per_xcd * kBgXcds);
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), lds_bytes, st, x, w, packed_by_tenant, alpha_by_tenant, row_token,
-                       tile_tenant, y, out, in, n_mtiles, n_ntiles, (int)n_full, more...);
+                       tile_tenant, y, out, in, n_mtiles, n_large, n_ntiles, (int)n_full, more...);
     return hipGetLastError();
 }
 
@@ -705,7 +725,7 @@ hipError_t launch_tiles(Kernel kernel, PerDeviceOnce& lds_limit, int lds_bytes, 
 // the tenants' signs in the serving layout; wscale != nullptr (4 wavefronts, row-major): w is the int8 base, wscale its scales
 hipError_t launch_linear_prefill_big(const uint16_t* x, const void* w_any, const uint32_t* const* packed_by_tenant,
                                      const float* alpha_by_tenant, const float* wscale, const int32_t* row_token,
-                                     const int32_t* tile_tenant, int n_mtiles, uint16_t* y, int64_t T, int64_t out, int64_t in,
+                                     const int32_t* tile_tenant, int n_mtiles, int n_large, uint16_t* y, int64_t T, int64_t out, int64_t in,
                                      int waves, bool halve_last_round, bool tiled, hipStream_t st) {
     if (!prefill_big_fits(T, out, in) || (waves != 4 && waves != 8) || ((tiled || wscale) && waves != 4) || (tiled && wscale))
         return hipErrorInvalidValue;
@@ -716,7 +736,7 @@ hipError_t launch_linear_prefill_big(const uint16_t* x, const void* w_any, const
     const uint16_t* w = (const uint16_t*)w_any;
     auto go = [&](auto kernel, PerDeviceOnce& o, int threads, bool halve) {
         return launch_tiles(kernel, o, kBgLdsBytes, threads, x, w, packed_by_tenant, alpha_by_tenant, row_token, tile_tenant, n_mtiles,
-                            n_ntiles, y, out, in, halve, st, wscale);
+                            n_large, n_ntiles, y, out, in, halve, st, wscale);
     };
     if (tiled) return go(linear_prefill_big_kernel<1, kSrcTiled>, once[0], 256, halve_last_round);
     if (wscale) return go(linear_prefill_big_kernel<1, kSrcQ8>, once[1], 256, halve_last_round);
@@ -728,7 +748,7 @@ hipError_t launch_linear_prefill_big(const uint16_t* x, const void* w_any, const
 // entries per token tile.
 hipError_t launch_linear_prefill_merged(const uint16_t* x, const uint16_t* w, const uint32_t* const* packed_by_tenant,
                                         const float* alpha_by_tenant, const int32_t* row_token, const int32_t* tile_tenant,
-                                        int n_mtiles, uint16_t* y, int64_t T, int64_t out, int64_t in, bool halve_last_round,
+                                        int n_mtiles, int n_large, uint16_t* y, int64_t T, int64_t out, int64_t in, bool halve_last_round,
                                         bool tiled, hipStream_t st) {
     if (!prefill_big_fits(T, out, in)) return hipErrorInvalidValue;
     const int n_ntiles = (int)((out + kBgN - 1) / kBgN);
@@ -737,9 +757,9 @@ hipError_t launch_linear_prefill_merged(const uint16_t* x, const uint16_t* w, co
     static PerDeviceOnce once, once_t;
     if (tiled)
         return launch_tiles(linear_prefill_merged_kernel<true>, once_t, BgLds<kMergedTile>::kTotal, 256, x, w, packed_by_tenant,
-                            alpha_by_tenant, row_token, tile_tenant, n_mtiles, n_ntiles, y, out, in, halve_last_round, st);
+                            alpha_by_tenant, row_token, tile_tenant, n_mtiles, n_large, n_ntiles, y, out, in, halve_last_round, st);
     return launch_tiles(linear_prefill_merged_kernel<false>, once, BgLds<kMergedTile>::kTotal, 256, x, w, packed_by_tenant, alpha_by_tenant,
-                        row_token, tile_tenant, n_mtiles, n_ntiles, y, out, in, halve_last_round, st);
+                        row_token, tile_tenant, n_mtiles, n_large, n_ntiles, y, out, in, halve_last_round, st);
 }
 
 }  // namespace bd

@@ -139,3 +139,25 @@ def test_wide_non_finite_values():
         want = s1[:, keep_cols]
         assert torch.equal(torch.isnan(got), want == 0)
         assert torch.equal(got[want != 0], torch.where(want[want != 0] > 0, float("inf"), float("-inf")).half())
+
+
+def test_gemm_more_tiles_than_compute_units():
+    """Over 256 tiles of all heights (32, 64, 128 rows; 64, 128, 256 of the one-product form), long ones first, an eighth of either
+    kind per XCD: every output element is written, by its own tile."""
+    out, inn, counts = 8456, 64, [130, 5, 64, 65, 33, 0, 300, 1, 90, 260]
+    t = Tensors(out, inn, tokens_of(counts, "shuffled"), len(counts))
+    tiled = bd.TiledTenantTable([bd.tile_signs(p, out, inn) for p in t.packed], t.alpha)
+    wt = bd.tile_base(t.w)
+    nan = lambda: torch.full((len(t.tok), out), float("nan"), dtype=torch.float16, device=DEV)
+    t.check(bd.linear_multitenant_tiled_gemm(t.x, wt, out, tiled, t.tok, y=nan()), what="two products")
+    t.check(bd.linear_multitenant(t.x, t.w, bd.TenantTable(t.packed, t.alpha), t.tok, y=nan(), variant=5), what="row-major")
+    q, scale = bd.quantize_base_q8(t.w)
+    y = bd.linear_multitenant_gemm_q8(t.x, q, scale, bd.TenantTable(t.packed, t.alpha), t.tok, y=nan())
+    t.check(y, q.double() * scale.double()[:, None], "8-bit base")
+    y = bd.linear_multitenant_tiled_gemm(t.x, wt, out, tiled, t.tok, one_product=True, y=nan())
+    for e in set(t.tok):   # one product: the fine-tuned weight rounded to binary16
+        rows = torch.tensor([i for i, k in enumerate(t.tok) if k == e], device=DEV)
+        w = (t.w.double() + t.alpha[e].double() * expand(t.packed[e], inn)).half().double()
+        exact, mag = t.x[rows].double() @ w.t(), t.x[rows].double().abs() @ w.abs().t()
+        bound = 2.0**-11 * exact.abs() + 2.0**-25 + inn**0.5 * 2.0**-23 * mag
+        assert ((y[rows].double() - exact).abs() <= bound).all(), e
