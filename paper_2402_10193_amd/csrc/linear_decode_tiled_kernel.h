@@ -38,12 +38,11 @@
 //
 // Row-major tensors (RM; what bd_compress writes and bd_linear_multitenant takes).  The same kernel reads W
 // [out, in] fp16 and packed signs [out, in/32] as they are: slice v of a base tile is then 16 rows x 64 bytes
-// (lane (r, g) reads 16 bytes of row r), and a tenant's signs of a tile are 16 rows x 32 bytes, of which lane
-// (r, g) loads words 2 g and 2 g + 1.  Those hold sign BYTE i of slices 2 g and 2 g + 1 for every lane group i,
-// while the lane needs byte g of all eight slices: the four lanes of a row exchange them with two byte shuffles,
-// a swap between the wavefront's halves, two more shuffles and a swap between neighbouring rows of 16 lanes
-// (v_permlane32_swap / v_permlane16_swap), six vector instructions per job and task.  The tenants' pointers
-// come from the caller's device table (one scalar load each) instead of the kernel arguments.
+// (fetched with 16 lanes side by side in a row and turned into operand order through LDS rows of the wavefront's own), and a
+// tenant's signs of a tile are 16 rows x 32 bytes: lane (r, j) fetches those of row r for job slot 4 p + j, and the lanes of
+// a row exchange them so that lane (r, g) holds byte g of all eight words for all four slots (byte shuffles inside the lane,
+// v_permlane32_swap / v_permlane16_swap between them: six vector instructions per job and task).  The tenants' pointers
+// come from the caller's device table instead of the kernel arguments.  Long rows with many slots: see S4.
 //
 // This header is the kernel; linear_decode_tiled.hip, linear_decode_tiled_q8.hip and linear_decode_rowmajor.hip
 // instantiate it for the fp16 base, the 8-bit base and the row-major tensors (three translation units, so that
@@ -68,14 +67,23 @@ constexpr int kStageRowBytes = kTileK * 2 + 16;
 constexpr int kStageBytes = 16 * kStageRowBytes;
 // LDS after the table: one region per wavefront = slots for the partial tiles of finished row blocks.
 // Resident x is staged there before the first task (the slots overlay the staging rows).
-template <int XSTEPS> struct LdsPlan {
-    static constexpr int kRedSlots = 8;   // 16 x 16 tiles; a row block takes one per column tile
-    static constexpr int kRegion = (XSTEPS > 0 && kStageBytes > kRedSlots * kRedBytesPerWave) ? kStageBytes : kRedSlots * kRedBytesPerWave;
+// Row-major fp16 base: behind the slots a room of 16 rows x 256 bytes, in which half a base tile at a time goes from rows
+// to operand order.
+constexpr int kRoomBytes = 16 * 256;
+template <int XSTEPS, bool ROOM> struct LdsPlan {
+    static constexpr int kRedSlots = ROOM ? 4 : 8;   // 16 x 16 tiles; a row block takes one per column tile
+    static constexpr int kRoom = kRedSlots * kRedBytesPerWave;   // where the room starts in the region
+    static constexpr int kUsed = kRoom + (ROOM ? kRoomBytes : 0);
+    static constexpr int kRegion = (XSTEPS > 0 && kStageBytes > kUsed) ? kStageBytes : kUsed;
     // behind the regions: (span, token) of every column of both column tiles, for the threads that write y
     static constexpr int kMeta = kLutBytes + kMaxWavesTiled * kRegion;
-    static constexpr int kTotal = kMeta + kTiledMaxCt * kTiledMaxTokens * 8;
+    // row-major: the address of every job slot's signs
+    static constexpr int kPtr = kMeta + kTiledMaxCt * kTiledMaxTokens * 8;
+    static constexpr int kTotal = kPtr + kTiledMaxCt * kTiledMaxJobs * 8;
 };
-static_assert(LdsPlan<0>::kTotal <= 160 * 1024 && LdsPlan<2>::kTotal <= 160 * 1024, "LDS budget");
+static_assert(LdsPlan<0, false>::kTotal <= 160 * 1024 && LdsPlan<2, false>::kTotal <= 160 * 1024 && LdsPlan<0, true>::kTotal <= 160 * 1024 &&
+                  LdsPlan<2, true>::kTotal <= 160 * 1024,
+              "LDS budget");
 
 __device__ __forceinline__ void lds_wave_sync() {   // order this wavefront's LDS writes before its later reads
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -104,7 +112,29 @@ __device__ __forceinline__ u32x4 lut_read(const u32x2 s, const int v, const uint
     return *(lds_u32x4_ptr)(uintptr_t)addr;
 }
 
-// Row-major signs.  In: this lane's words 2 g and 2 g + 1 of its row (lane (r, g) = (lane % 16, lane / 16)); byte i of
+// Row-major signs, four job slots at a time.  In: lane (r, j) = (lane % 16, lane / 16) holds the 8 words that row r of job slot j
+// has for the tile; byte i of word w is the sign byte of slice w for lane group i.  Out: s[j] = byte g of words 0..3 and of
+// words 4..7 of job slot j, in lane (r, g): what the tiled layout holds there.  A byte transpose inside the lane, then a
+// transpose of (register, lane group) by two swaps each way: 24 instructions for 4 jobs.  All 64 lanes must be active.
+__device__ __forceinline__ void rm_turn_signs(const u32x4 lo, const u32x4 hi, u32x2 (&s)[4]) {
+    u32x4 in[2] = {lo, hi};
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const u32x4 w = in[h];
+        const uint32_t p0 = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u), p1 = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u);
+        const uint32_t q0 = __builtin_amdgcn_perm(w[1], w[0], 0x07030602u), q1 = __builtin_amdgcn_perm(w[3], w[2], 0x07030602u);
+        const uint32_t t0 = __builtin_amdgcn_perm(p1, p0, 0x05040100u), t1 = __builtin_amdgcn_perm(p1, p0, 0x07060302u);
+        const uint32_t t2 = __builtin_amdgcn_perm(q1, q0, 0x05040100u), t3 = __builtin_amdgcn_perm(q1, q0, 0x07060302u);
+        const auto a02 = __builtin_amdgcn_permlane32_swap(t0, t2, false, false), a13 = __builtin_amdgcn_permlane32_swap(t1, t3, false, false);
+        const auto b01 = __builtin_amdgcn_permlane16_swap(a02[0], a13[0], false, false);
+        const auto b23 = __builtin_amdgcn_permlane16_swap(a02[1], a13[1], false, false);
+        s[0][h] = b01[0];
+        s[1][h] = b01[1];
+        s[2][h] = b23[0];
+        s[3][h] = b23[1];
+    }
+}
+// Row-major signs, one job slot at a time (see S4).  In: this lane's words 2 g and 2 g + 1 of its row (lane (r, g) = (lane % 16, lane / 16)); byte i of
 // word w is the sign byte of slice w for lane group i.  Out: s[0] = byte g of words 0, 1, 4, 5 and s[1] = byte g of
 // words 2, 3, 6, 7 (in that order), i.e. everything lane (r, g) needs.  All 64 lanes must be active.
 __device__ __forceinline__ u32x2 rm_gather_sign_bytes(const u32x2 w) {
@@ -148,7 +178,14 @@ __device__ __forceinline__ u32x4 lut_read_rm(const u32x2 s, const int v, const u
 // then come in pairs that share the base registers, so the base is still read once.
 // RM: row-major W (fp16, or the int8 q of the 8-bit base with its `out` scales) and packed signs (one matrix,
 // in % 128 == 0) instead of the tiled tensors.
-template <int NJ, int XSTEPS, int NCT, bool Q8, bool RM = false>
+// (The row-major fp16 base passes through LDS rows unless x of two k tiles and the signs of more than 12 slots leave no
+// registers for it; streaming x instead costs more: 11008 x 4096 with 16 tenants 49 against 57 us.)
+constexpr bool rm_base_through_lds(int nj, int xsteps, bool q8, bool rm) { return rm && !q8 && !(xsteps == 2 && nj > 12); }
+// S4 (row-major): the signs are fetched for four job slots at a time, 16 bytes per lane, every lane a row of a slot (128 cycles of
+// the address unit for four slots), instead of 8 bytes per lane, four lanes a row, slot by slot (256 cycles).  But a row's 32
+// bytes then come in two requests, and where `in` is long and the slots are many the requests to L2 are what counts:
+// 4096 x 4096 with 32 tenants 32 against 37 us, 8192 x 8192 141 against 130, 11008 x 4096 with 28 tenants 93 against 90.
+template <int NJ, int XSTEPS, int NCT, bool Q8, bool RM = false, bool S4 = RM>
 __global__ __launch_bounds__(kMaxWavesTiled * kWave) void linear_decode_tiled_kernel(const TiledArgs a) {
     constexpr uint32_t kWTile = Q8 ? kTileBaseQ8Bytes : kTileBaseBytes;   // bytes of one base tile
     constexpr int kWLoads = Q8 ? 4 : 8;                                   // 1 KiB loads per base tile
@@ -158,7 +195,8 @@ __global__ __launch_bounds__(kMaxWavesTiled * kWave) void linear_decode_tiled_ke
     const int nw = blockDim.x >> 6;
     const int c = lane & 15;   // A row (output row) for loads, B/D column (token) for MFMA operands and results
     const int g = lane >> 4;
-    using Plan = LdsPlan<XSTEPS>;
+    constexpr bool ROOM = rm_base_through_lds(NJ, XSTEPS, Q8, RM);
+    using Plan = LdsPlan<XSTEPS, ROOM>;
     static_assert(NCT == 1 || XSTEPS == 0, "two column tiles only with streamed x");
     // Touch every 64-byte line of the kernel arguments at once: the first read of a line is a trip
     // to memory, and taken one after the other (pointer tables are indexed by values read before)
@@ -208,7 +246,14 @@ __global__ __launch_bounds__(kMaxWavesTiled * kWave) void linear_decode_tiled_ke
     for (int ct = 0; ct < NCT; ++ct)
 #pragma unroll
         for (int j = 0; j < NJ; ++j) sp[ct][j] = RM ? nullptr : (const unsigned char*)a.signs[ct][m_req][j];
-    // Row-major: the tenants' pointers come from the caller's table in device memory.  Sixteen pointers held as
+    // Row-major: the tenants' pointers come from the caller's table in device memory and wait in LDS; a lane takes the one of
+    // the job slot it fetches for.
+    if constexpr (S4) {
+        if (threadIdx.x < kTiledMaxCt * kTiledMaxJobs)
+            *(uint64_t*)(smem + Plan::kPtr + threadIdx.x * 8) =
+                (uint64_t)a.packed_by_tenant[a.job_tenant[threadIdx.x / kTiledMaxJobs][threadIdx.x % kTiledMaxJobs]];
+    }
+    // One slot at a time: sixteen pointers held as
     // scalars cannot be dropped and fetched again like kernel arguments, and would push the kernel's vector
     // registers into scratch; so lane j of one register pair holds the pointer of job slot j, and a sign load
     // takes its base address from there with two v_readlane.
@@ -216,7 +261,7 @@ __global__ __launch_bounds__(kMaxWavesTiled * kWave) void linear_decode_tiled_ke
 #pragma unroll
     for (int ct = 0; ct < NCT; ++ct) {
         ptr_lo[ct] = ptr_hi[ct] = 0u;
-        if constexpr (RM) {
+        if constexpr (RM && !S4) {
             int tenant_l = a.job_tenant[ct][0];
 #pragma unroll
             for (int i = 1; i < kTiledMaxJobs; ++i) tenant_l = (lane == i) ? a.job_tenant[ct][i] : tenant_l;
@@ -235,12 +280,22 @@ __global__ __launch_bounds__(kMaxWavesTiled * kWave) void linear_decode_tiled_ke
     };
     // Byte offsets of a task's loads = a uniform part (tile) + this lane's part.  Tiled: the lane's part is its place
     // inside a tile.  Row-major: the uniform part is the k tile only and the lane's part carries the row, so it
-    // changes with the row block (rows beyond `out` read the last row again; their results are never stored).
+    // changes with the row block (rows beyond `out` read the last row again; their results are never stored).  A row-major
+    // fp16 base is fetched with 16 lanes side by side in a row: load 4 h + j covers rows 4 j .. 4 j + 3 of half h of the tile,
+    // 16-byte chunk c ^ row in lane c of the row, and is turned into operand order in the wavefront's room of LDS.  (In
+    // operand order neighbouring lanes are on different rows, every lane an access of its own: 64 cycles of the address
+    // unit per load, 512 per task, and with the signs twice what the memory leaves time for.)
+    uint32_t wrow[4] = {0u, 0u, 0u, 0u};
     uint32_t lane16 = (uint32_t)lane * 16u, lane8 = (uint32_t)lane * 8u;
     auto rm_lane_offsets = [&](const int rb) {
         const int row = min(rb * kTileRows + c, a.out[0] - 1);
         lane16 = (uint32_t)row * ((uint32_t)a.in * (Q8 ? 1u : 2u)) + (uint32_t)g * 16u;
-        lane8 = (uint32_t)row * ((uint32_t)a.in >> 3) + (uint32_t)g * 8u;
+        lane8 = (uint32_t)row * ((uint32_t)a.in >> 3) + (S4 ? 0u : (uint32_t)g * 8u);
+        if constexpr (ROOM) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                wrow[j] = (uint32_t)min(rb * kTileRows + 4 * j + g, a.out[0] - 1) * ((uint32_t)a.in * 2u) + ((uint32_t)(c ^ (4 * j + g)) << 4);
+        }
     };
     if constexpr (RM) rm_lane_offsets(rb_req);
     auto w_off = [&](const int rb, const int kt) {   // uniform byte offset of tile (rb, kt) of the base
@@ -260,12 +315,40 @@ __global__ __launch_bounds__(kMaxWavesTiled * kWave) void linear_decode_tiled_ke
     };
     // Row-major, `in` = 128 mod 256: the last k tile of a row has 4 slices.  No load may reach beyond the row (the
     // last row ends the tensor), so slices 4..7 of such a tile read slices 0..3 again and are replaced by zeros when
-    // they are multiplied; lane groups 2, 3 read the row's first sign words instead of theirs (any valid words do:
-    // their x is zero).  All of it is uniform arithmetic per task, no branch around a load.
+    // they are multiplied; words 4..7 of its signs are words 0..3 again (any valid words do: their x is zero).  All of it is
+    // uniform arithmetic per task, no branch around a load.
     const int kt_short = (RM && (a.in % kTileK) != 0) ? KT - 1 : -1;
     auto w_base_hi = [&](const int kt) {   // the pointer slices 4..7 of tile kt are read through
         return (RM && kt == kt_short) ? wt - (kWLoads / 2) * kSliceStride : wt;
     };
+    // request number v of a base tile (woff: the tile's offset, the lane's part included unless ROOM)
+    auto ld_base = [&](const unsigned char* const hi, const uint32_t woff, const int v) __attribute__((always_inline)) {
+        const unsigned char* const p = v >= kWLoads / 2 ? hi : wt;
+        if constexpr (ROOM) {
+            uint32_t r = wrow[v & 3];
+            asm volatile("" : "+v"(r));
+            return ldg16(p, woff + r + (v >= 4 ? 256u : 0u));
+        } else {
+            return ld_w(p, woff + (uint32_t)v * kSliceStride);
+        }
+    };
+    // Row-major signs of four job slots 4 p .. 4 p + 3: lane (c, j) the 32 bytes that row c of slot 4 p + j has for the tile.
+    typedef const u32x4 __attribute__((address_space(1)))* global_u32x4;
+    auto ld_s4 = [&](u32x2 (&s4)[4], const int ct, const int p, const int kt) __attribute__((always_inline)) {
+        uint32_t l8 = lane8;
+        asm volatile("" : "+v"(l8));
+        const uint64_t ptr = *(const uint64_t*)(smem + Plan::kPtr + (ct * kTiledMaxJobs + 4 * p + g) * 8) + l8 + (uint32_t)kt * (uint32_t)(kTileK / 8);
+        const u32x4 lo = *(global_u32x4)ptr, hi = *(global_u32x4)(ptr + (kt == kt_short ? 0u : 16u));
+        s4[0] = u32x2{lo[0], lo[1]};
+        s4[1] = u32x2{lo[2], lo[3]};
+        s4[2] = u32x2{hi[0], hi[1]};
+        s4[3] = u32x2{hi[2], hi[3]};
+    };
+    auto turn_s4 = [&](u32x2 (&s4)[4]) __attribute__((always_inline)) {
+        rm_turn_signs(u32x4{s4[0][0], s4[0][1], s4[1][0], s4[1][1]}, u32x4{s4[2][0], s4[2][1], s4[3][0], s4[3][1]}, s4);
+    };
+
+    // one slot at a time: in a short last tile lane groups 2, 3 read the row's first sign words (any valid words do)
     auto s_lane_off = [&](const uint32_t off_u, const uint32_t l8, const int kt) {
         uint32_t off = off_u + l8;
         if constexpr (RM) off = (kt == kt_short && g >= 2) ? l8 - (uint32_t)g * 8u : off;
@@ -344,12 +427,13 @@ __global__ __launch_bounds__(kMaxWavesTiled * kWave) void linear_decode_tiled_ke
         if constexpr (XSTEPS == 2) x_fetch(xraw[1], kb + kstride);
     }
     u32x4 wr[kWLoads];   // fp16 base: slice v; 8-bit base: slices 2 i and 2 i + 1 (8 bytes each)
-    u32x2 sr[NJ];
+    constexpr int kSg = (NJ + 3) / 4;
+    u32x2 sr[kSg][4];    // job slot j: sr[j / 4][j % 4] (row-major: four slots' words as fetched until the first of them is due)
     if (have_work) {
-        const uint32_t woff0 = w_off(rb_req, kb) + lane16;
+        const uint32_t woff0 = w_off(rb_req, kb) + (ROOM ? 0u : lane16);
         const unsigned char* const wt_hi0 = w_base_hi(kb);
 #pragma unroll
-        for (int v = 0; v < kWLoads; ++v) wr[v] = ld_w(v >= kWLoads / 2 ? wt_hi0 : wt, woff0 + (uint32_t)v * kSliceStride);
+        for (int v = 0; v < kWLoads; ++v) wr[v] = ld_base(wt_hi0, woff0, v);
     }
 
     // ---- the table: entry b, copy cp at 256 b + 16 cp; element e = bit e of b ? +1.0 : -1.0.
@@ -386,10 +470,37 @@ __global__ __launch_bounds__(kMaxWavesTiled * kWave) void linear_decode_tiled_ke
         for (int v = 0; v < 8; ++v) xop[v] = *(const u32x4*)(region + c * kStageRowBytes + 64 * v + 16 * g);
     };
 
-    if (have_work) {
-        const uint32_t soff0 = s_lane_off(s_off(rb_req, kb), lane8, kb);
+    // a row-major base tile, as fetched -> operands, in place
+    auto w_turn = [&]() __attribute__((always_inline)) {
+        unsigned char* const room = region + Plan::kRoom;
+        const uint32_t get = (uint32_t)c * 256u + ((uint32_t)(c ^ g) << 4);   // chunk 4 v + g of row c is at get ^ 64 v
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) sr[j] = ld_s(sign_ptr(0, j), soff0);
+        for (int h = 0; h < 2; ++h) {
+            lds_wave_sync();
+#pragma unroll
+            for (int j = 0; j < 4; ++j) *(u32x4*)(room + j * 1024 + lane * 16) = wr[4 * h + j];
+            lds_wave_sync();
+#pragma unroll
+            for (int v = 0; v < 4; ++v) wr[4 * h + v] = *(const u32x4*)(room + (get ^ (64u * v)));
+        }
+    };
+
+    if (have_work) {
+        // (row-major: resident x, requested first, takes its registers before the signs are requested; all three at once do
+        // not fit)
+        if constexpr (ROOM) {
+#pragma unroll
+            for (int i = 0; i < (XSTEPS > 0 ? XR : 0); ++i) x_to_operands(xraw[i], xs[i]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (S4) {
+#pragma unroll
+            for (int p = 0; p < kSg; ++p) ld_s4(sr[p], 0, p, kb);
+        } else {
+            const uint32_t soff0 = s_lane_off(s_off(rb_req, kb), lane8, kb);
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) sr[j / 4][j % 4] = ld_s(sign_ptr(0, j), soff0);
+        }
     }
 
     // this lane's column: owning job, tenant (for the scale)
@@ -417,7 +528,8 @@ __global__ __launch_bounds__(kMaxWavesTiled * kWave) void linear_decode_tiled_ke
         __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
     }
 #pragma unroll
-    for (int i = 0; i < (XSTEPS > 0 ? XR : 0); ++i) x_to_operands(xraw[i], xs[i]);
+    for (int i = 0; i < (XSTEPS > 0 && !ROOM ? XR : 0); ++i) x_to_operands(xraw[i], xs[i]);
+    if constexpr (ROOM) w_turn();
     const uint32_t lanebits = (uint32_t)c << 4;
 
     float4v accb[NCT], dsel[NCT], accs[NCT];   // accs (8-bit base only): sum_k x of the column, in every row
@@ -450,7 +562,7 @@ __global__ __launch_bounds__(kMaxWavesTiled * kWave) void linear_decode_tiled_ke
         // "uniform base + lane offset" of every load out of the loop as a 64-bit register pair per load.
         uint32_t l16 = lane16, l8 = lane8;
         asm volatile("" : "+v"(l16), "+v"(l8));
-        const uint32_t woff = w_off(rb_next, kt_next) + l16, soff = s_lane_off(s_off(rb_next, kt_next), l8, kt_next);
+        const uint32_t woff = w_off(rb_next, kt_next) + (ROOM ? 0u : l16), soff = s_lane_off(s_off(rb_next, kt_next), l8, kt_next);
         const unsigned char* const wt_hi = w_base_hi(kt_next);
         const bool short_cur = RM && kt_cur == kt_short;
         // ---- base product; W[v] of the next task goes into the register group just read.  The wavefront runs at a higher
@@ -467,14 +579,14 @@ __global__ __launch_bounds__(kMaxWavesTiled * kWave) void linear_decode_tiled_ke
                                                                   __builtin_bit_cast(half8, xr[v]), accb[CT], 0, 0, 0);
                 accs[CT] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ones, __builtin_bit_cast(half8, xr[v]), accs[CT], 0, 0, 0);
                 if constexpr (MORE && NEW_BASE) {
-                    if (v & 1) wr[v >> 1] = ld_w((v >> 1) >= kWLoads / 2 ? wt_hi : wt, woff + (uint32_t)(v >> 1) * kSliceStride);
+                    if (v & 1) wr[v >> 1] = ld_base(wt_hi, woff, v >> 1);
                 }
             } else {
                 u32x4 wv = wr[v];
                 if (RM && v >= 4) wv = short_cur ? u32x4{0u, 0u, 0u, 0u} : wv;
                 accb[CT] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, wv),
                                                                   __builtin_bit_cast(half8, xr[v]), accb[CT], 0, 0, 0);
-                if constexpr (MORE && NEW_BASE) wr[v] = ld_w(v >= 4 ? wt_hi : wt, woff + (uint32_t)v * kSliceStride);
+                if constexpr (MORE && NEW_BASE) wr[v] = ld_base(wt_hi, woff, v);
             }
             __builtin_amdgcn_sched_barrier(0);   // keep each request behind the MFMA that frees its registers
         }
@@ -484,40 +596,59 @@ __global__ __launch_bounds__(kMaxWavesTiled * kWave) void linear_decode_tiled_ke
         // ---- delta jobs.  The 8 NJ (job, slice) pairs of the task form one sequence; the table
         // look-up of pair i + kLookAhead is issued before the MFMA of pair i, through a ring of
         // operand registers, and a job's sign words are re-requested as soon as its last address exists.
-        // (row-major with 16 jobs and resident x: a shorter ring, so that the two registers the row offsets take do not end up
-        // in scratch.  Measured with rings of 4 to 14 look-ups ahead: the depth does not change the time of a task.)
-        constexpr int kLookAhead = (RM && NJ == 16 && XSTEPS > 0) ? 4 : 6, kRing = kLookAhead + 2, kPairs = 8 * NJ;
+        // (row-major with many jobs and resident x: a shorter ring, so that nothing ends up in scratch.  Measured with rings of 4 to 14 look-ups ahead: the depth does not change the time of a task.)
+        constexpr int kLookAhead = RM && XSTEPS > 0 && (ROOM ? NJ >= 10 && XSTEPS == 2 : NJ == 16) ? 4 : 6, kRing = kLookAhead + 2, kPairs = 8 * NJ;
         u32x4 ring[kRing];
         float4v sel = {0.f, 0.f, 0.f, 0.f};   // the job owning this lane's column, this tile
         auto look_up = [&](const int i) __attribute__((always_inline)) {      // i = 8 * job + slice
             const int j = i >> 3, v = i & 7;
-            if constexpr (RM) {
-                if (v == 0) sr[j] = rm_gather_sign_bytes(sr[j]);
-                ring[i % kRing] = lut_read_rm(sr[j], v, lanebits);
-            } else {
-                ring[i % kRing] = lut_read(sr[j], v, lanebits);
+            if constexpr (S4) {
+                if (v == 0 && j % 4 == 0) turn_s4(sr[j / 4]);
+            } else if constexpr (RM) {
+                if (v == 0) sr[j / 4][j % 4] = rm_gather_sign_bytes(sr[j / 4][j % 4]);
             }
-            if constexpr (MORE) {
-                if (v == 7) sr[j] = ld_s(sign_ptr(CT_NEXT, j), soff);
+            ring[i % kRing] = RM && !S4 ? lut_read_rm(sr[j / 4][j % 4], v, lanebits) : lut_read(sr[j / 4][j % 4], v, lanebits);
+            if constexpr (MORE && S4) {
+                if (v == 7 && (j % 4 == 3 || j == NJ - 1)) ld_s4(sr[j / 4], CT_NEXT, j / 4, kt_next);
+            } else if constexpr (MORE) {
+                if (v == 7) sr[j / 4][j % 4] = ld_s(sign_ptr(CT_NEXT, j), soff);
             }
         };
 #pragma unroll
         for (int i = 0; i < kLookAhead; ++i) look_up(i);
         float4v acc = {0.f, 0.f, 0.f, 0.f};
+        auto finish_job = [&](const int j) __attribute__((always_inline)) {
+            const bool mine = (myjob[CT] == j);
 #pragma unroll
-        for (int i = 0; i < kPairs; ++i) {
+            for (int q = 0; q < 4; ++q) sel[q] = mine ? acc[q] : sel[q];
+            // pin the selection here: left alone, the compiler sinks all of them below the last job
+            // and keeps one live accumulator per job
+            asm volatile("" : "+v"(sel[0]), "+v"(sel[1]), "+v"(sel[2]), "+v"(sel[3]));
+            acc = float4v{0.f, 0.f, 0.f, 0.f};
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto pair = [&](const int i) __attribute__((always_inline)) {
             if (i + kLookAhead < kPairs) look_up(i + kLookAhead);
             acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, ring[i % kRing]),
                                                          __builtin_bit_cast(half8, xr[i & 7]), acc, 0, 0, 0);
-            if ((i & 7) == 7) {
-                const bool mine = (myjob[CT] == (i >> 3));
+        };
+        if constexpr (S4 || ROOM) {
+            // Two loops, unrolled from the inside: as one of 128 iterations it is too large for the compiler to unroll once the
+            // row-major exchanges are in it, and the operands then live in scratch.
 #pragma unroll
-                for (int q = 0; q < 4; ++q) sel[q] = mine ? acc[q] : sel[q];
-                // pin the selection here: left alone, the compiler sinks all of them below the last job
-                // and keeps one live accumulator per job
-                asm volatile("" : "+v"(sel[0]), "+v"(sel[1]), "+v"(sel[2]), "+v"(sel[3]));
-                acc = float4v{0.f, 0.f, 0.f, 0.f};
-                __builtin_amdgcn_sched_barrier(0);
+            for (int j = 0; j < NJ; ++j) {
+                if constexpr (MORE && NEW_BASE && ROOM) {   // the next base tile has arrived: the last job hides its trip through LDS
+                    if (j == NJ - 1) w_turn();
+                }
+#pragma unroll
+                for (int v = 0; v < 8; ++v) pair(8 * j + v);
+                finish_job(j);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < kPairs; ++i) {
+                pair(i);
+                if ((i & 7) == 7) finish_job(i >> 3);
             }
         }
         dsel[CT] += sel;
@@ -676,10 +807,10 @@ __global__ __launch_bounds__(kMaxWavesTiled * kWave) void linear_decode_tiled_ke
     }
 }
 
-template <bool Q8, bool RM, int NJ, int XSTEPS, int NCT = 1>
+template <bool Q8, bool RM, int NJ, int XSTEPS, int NCT = 1, bool S4 = RM>
 static hipError_t launch_inst(const TiledArgs& args, int n_waves, unsigned grid, hipStream_t st) {
-    auto kernel = linear_decode_tiled_kernel<NJ, XSTEPS, NCT, Q8, RM>;
-    const size_t lds = (size_t)LdsPlan<XSTEPS>::kTotal;
+    auto kernel = linear_decode_tiled_kernel<NJ, XSTEPS, NCT, Q8, RM, S4>;
+    const size_t lds = (size_t)LdsPlan<XSTEPS, rm_base_through_lds(NJ, XSTEPS, Q8, RM)>::kTotal;
     static PerDeviceOnce lds_limit;   // one per instantiation
     const hipError_t ea = lds_limit.run([&] {
         hipFuncAttributes fa;
@@ -695,8 +826,16 @@ static hipError_t launch_inst(const TiledArgs& args, int n_waves, unsigned grid,
 
 template <bool Q8, bool RM, int NJ>
 static hipError_t launch_nj(const TiledArgs& args, int n_waves, int xsteps, unsigned grid, hipStream_t st) {
+    // Row-major with more than 8 job slots and rows of more than 24 k tiles, or with more than 10 in both column tiles and several
+    // row blocks per workgroup: the signs slot by slot (see S4; below that, four slots at a time is the better one).
+    if constexpr (RM && NJ > 8) {
+        if (xsteps == 0 && (args.KT > 24 || (NJ > 10 && args.n_ct == 2 && args.rb_end[args.n_mats - 1] > (int)grid)))
+            return args.n_ct == 2 ? launch_inst<Q8, RM, NJ, 0, 2, false>(args, n_waves, grid, st)
+                                  : launch_inst<Q8, RM, NJ, 0, 1, false>(args, n_waves, grid, st);
+    }
+    if (args.n_ct == 2) return launch_inst<Q8, RM, NJ, 0, 2>(args, n_waves, grid, st);   // 17..32 tokens: two column tiles, streamed x
     if (xsteps == 1) return launch_inst<Q8, RM, NJ, 1>(args, n_waves, grid, st);
-    if (xsteps == 2) return launch_inst<Q8, RM, NJ, 2>(args, n_waves, grid, st);
+    if (xsteps == 2) return launch_inst<Q8, RM, NJ, 2, 1, RM && (Q8 || NJ <= 12)>(args, n_waves, grid, st);
     return launch_inst<Q8, RM, NJ, 0>(args, n_waves, grid, st);
 }
 
@@ -731,9 +870,7 @@ static hipError_t launch_tiled_t(const TiledArgs& args, int n_jobs, hipStream_t 
     int xsteps = 0;
     if (args.KT > 0 && args.KT % n_waves == 0 && args.KT / n_waves <= 2) xsteps = args.KT / n_waves;
     auto go = [&](auto nj) {
-        constexpr int NJ = decltype(nj)::value;
-        if (args.n_ct == 2) return launch_inst<Q8, RM, NJ, 0, 2>(args, n_waves, grid, st);   // 17..32 tokens: two column tiles, streamed x
-        return launch_nj<Q8, RM, NJ>(args, n_waves, xsteps, grid, st);
+        return launch_nj<Q8, RM, decltype(nj)::value>(args, n_waves, args.n_ct == 2 ? 0 : xsteps, grid, st);
     };
     // A slot without a job costs as much as one with: its signs are requested (slot 0's again) and looked up.  With slots for 4, 8
     // or 16 only, a 7B layer took 142 us with 9 tenants and 149 with 12 (134 and 139 over the 8-bit base); in steps of two it

@@ -31,3 +31,16 @@ def test_decode_launches(mix):
     for y in (bd.linear_multitenant_tiled_q8(t.x, bd.tile_base_q8(q, scale), out, tiled, t.tok),
               bd.linear_multitenant_q8(t.x, q, scale, table, t.tok)):
         t.check(y, w8, what + " 8-bit base", extra=(2304.0 * scale.double())[None, :] * t.x.double().abs().sum(dim=1, keepdim=True))
+
+
+@pytest.mark.parametrize("out,inn", [(24, 6528), (40, 4096), (4160, 384)])   # 25.5 k tiles a row; x of two tiles resident; several row blocks per workgroup
+@pytest.mark.parametrize("n", [3, 8, 9, 11, 13, 16, 18, 22, 27, 32])
+def test_row_major_rows_of_every_kind(out, inn, n):
+    """The ways the row-major kernel fetches base and signs, chosen by the number of job slots and k tiles (the last half tile
+    of a row ends the tensor)."""
+    t = Tensors(out, inn, tokens_of([1] * n, "shuffled"), n, seed=n)
+    table = bd.TenantTable(t.packed, t.alpha)
+    q, scale = bd.quantize_base_q8(t.w)
+    t.check(bd.linear_multitenant(t.x, t.w, table, t.tok), what=f"{out}x{inn} {n}")
+    t.check(bd.linear_multitenant_q8(t.x, q, scale, table, t.tok), q.double() * scale.double()[:, None], f"{out}x{inn} {n} 8-bit base",
+            extra=(2304.0 * scale.double())[None, :] * t.x.double().abs().sum(dim=1, keepdim=True))
