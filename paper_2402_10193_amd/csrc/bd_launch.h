@@ -53,7 +53,7 @@ hipError_t launch_prefill_meta_runs(const PrefillMetaChunk& chunk, int32_t* dst,
 // plane.  wscale != nullptr: w is the row-major int8 base ([out, in] bytes) and wscale its per-row scales.
 hipError_t launch_linear_prefill(const uint16_t* x, const void* w, const uint32_t* const* packed_by_tenant,
                                  const float* alpha_by_tenant, const float* wscale, const int32_t* row_token,
-                                 const int32_t* tile_tenant, int n_mtiles, uint16_t* y, int64_t out, int64_t in,
+                                 const int32_t* tile_tenant, int n_mtiles, int n_large, uint16_t* y, int64_t out, int64_t in,
                                  int k_planes, hipStream_t st);
 // the 128 x 256 tile GEMM of linear_prefill_big.hip; T = rows of x; the first n_large token tiles are the ones with more than
 // half a tile of rows (they run first); halve_last_round (4 wavefronts only): the tiles of a

@@ -225,7 +225,7 @@ hipError_t run_prefill(const uint16_t* x, const void* w, const uint32_t* const* 
         return bd::launch_linear_prefill_big(x, w, packed_by_tenant, alpha_by_tenant, wscale, dst, dst + row_token.size(), n_mtiles, n_large, y, T,
                                              out, in, big_waves, halve_last_round, tiled, st);
     if (tiled) return hipErrorInvalidValue;   // the 128 x 128 tiles read the row-major tensors only
-    return bd::launch_linear_prefill(x, w, packed_by_tenant, alpha_by_tenant, wscale, dst, dst + row_token.size(), n_mtiles, y,
+    return bd::launch_linear_prefill(x, w, packed_by_tenant, alpha_by_tenant, wscale, dst, dst + row_token.size(), n_mtiles, n_large, y,
                                      out, in, k_planes, st);
 }
 

@@ -45,7 +45,6 @@ constexpr int kPfChunks = kPrefillK / 8;                   // 16-byte chunks per
 constexpr int kPfPerThread = kPrefillTile * kPfChunks / 256;
 constexpr int kPfLutBytes = 16 * 32 * 8;                   // [nibble][copy] of 4 fp16
 constexpr int kPfPanel = 8;                                // N tiles per column panel of the launch order
-constexpr int kPfChunk = 64;                               // consecutive tiles one XCD works on together (32 CUs x 2 workgroups)
 constexpr int kPfXcds = 8;
 
 }  // namespace
@@ -75,7 +74,7 @@ __global__ __launch_bounds__(256, 2) void linear_prefill_kernel(
     const uint16_t* __restrict__ x, const void* __restrict__ w_any, const uint32_t* const* __restrict__ packed_by_tenant,
     const float* __restrict__ alpha_by_tenant, const float* __restrict__ wscale, const int32_t* __restrict__ row_token,
     const int32_t* __restrict__ tile_tenant, uint16_t* __restrict__ y, const int64_t out, const int64_t in,
-    const int n_mtiles, const int n_ntiles, const int k_planes) {
+    const int n_mtiles, const int n_large, const int n_ntiles, const int k_planes) {
     __shared__ __align__(16) unsigned char lds[3 * kPfTileBytes + kPfLutBytes];
     unsigned char* const xs = lds;
     unsigned char* const ws = lds + kPfTileBytes;
@@ -88,19 +87,32 @@ __global__ __launch_bounds__(256, 2) void linear_prefill_kernel(
     // Launch order -> tile.  Workgroup ids go round-robin over the 8 XCDs, each with an L2 of its own; the
     // workgroups an XCD runs together (ids L, L+8, ...) should form a compact block of tiles so that every x
     // and W slice it fetches serves 8 of them.  Tiles are numbered panel by panel (8 N tiles wide, row-major
-    // inside), cut into chunks of 64 = 8 x 8 tiles, and chunk c goes to XCD c % 8.
+    // inside), first those of the n_large token tiles with more than half their rows, then the others, and of either
+    // stretch an XCD takes one contiguous eighth.
     int mt, nt;
     {
-        const int L = blockIdx.x, xcd = L % kPfXcds, slot = L / kPfXcds;
-        const int chunk = (slot / kPfChunk) * kPfXcds + xcd;
-        const int t = chunk * kPfChunk + slot % kPfChunk;
-        if (t >= n_mtiles * n_ntiles) return;   // the grid is padded to whole rounds of chunks
-        const int per_panel = n_mtiles * kPfPanel;
+        const int L = blockIdx.x, xcd = L % kPfXcds;
+        int slot = L / kPfXcds, t = -1, nm = n_large, m0 = 0;
+        const int64_t len0 = (int64_t)n_large * n_ntiles, len1 = (int64_t)(n_mtiles - n_large) * n_ntiles;
+        const int lo0 = (int)(len0 * xcd / kPfXcds), hi0 = (int)(len0 * (xcd + 1) / kPfXcds);
+        const int lo1 = (int)(len1 * xcd / kPfXcds), hi1 = (int)(len1 * (xcd + 1) / kPfXcds);
+        if (slot < hi0 - lo0) {
+            t = lo0 + slot;
+        } else {
+            slot -= hi0 - lo0;
+            if (slot >= hi1 - lo1) return;   // the grid is padded to the largest share
+            t = lo1 + slot;
+            m0 = n_large;
+            nm = n_mtiles - n_large;
+        }
+        const int per_panel = nm * kPfPanel;
         const int panel = t / per_panel, tp = t - panel * per_panel;
         const int width = n_ntiles - panel * kPfPanel < kPfPanel ? n_ntiles - panel * kPfPanel : kPfPanel;
-        mt = tp / width;
+        mt = m0 + tp / width;
         nt = panel * kPfPanel + tp % width;
     }
+    // the wavefronts of an empty upper half (rows are filled from the top) stage with the others and multiply nothing
+    const bool multiply = wm == 0 || row_token[mt * kPrefillTile + 64] >= 0;
     const int64_t n0 = (int64_t)nt * kPrefillTile;
     const int tenant = tile_tenant[mt];
     constexpr int NP = PLANES ? kPfMaxPlanes : 1;
@@ -254,6 +266,7 @@ __global__ __launch_bounds__(256, 2) void linear_prefill_kernel(
         if (k0 + kPrefillK < in) fetch(k0 + kPrefillK);
 #pragma unroll
         for (int h = 0; h < kPrefillK / 32; ++h) {
+            if (!multiply) break;
             half8 a[4], bw[4], bs[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -305,16 +318,17 @@ hipError_t launch_prefill_meta_runs(const PrefillMetaChunk& chunk, int32_t* dst,
 // wscale != nullptr: w is the row-major int8 base and wscale its per-row scales.
 hipError_t launch_linear_prefill(const uint16_t* x, const void* w, const uint32_t* const* packed_by_tenant,
                                  const float* alpha_by_tenant, const float* wscale, const int32_t* row_token,
-                                 const int32_t* tile_tenant, int n_mtiles, uint16_t* y, int64_t out, int64_t in,
+                                 const int32_t* tile_tenant, int n_mtiles, int n_large, uint16_t* y, int64_t out, int64_t in,
                                  int k_planes, hipStream_t st) {
     const int n_ntiles = (int)((out + kPrefillTile - 1) / kPrefillTile);
     const int64_t tiles = (int64_t)n_mtiles * n_ntiles;
     if (tiles < 1 || tiles > (int64_t)1 << 30 || k_planes < 0 || k_planes > kPfMaxPlanes) return hipErrorInvalidValue;
-    const int64_t round = (int64_t)kPfChunk * kPfXcds;                      // one chunk for every XCD
-    const unsigned grid = (unsigned)((tiles + round - 1) / round * round);   // surplus workgroups return at once
+    // an eighth of either stretch for every XCD; surplus workgroups return at once
+    const int64_t len0 = (int64_t)n_large * n_ntiles, len1 = tiles - len0;
+    const unsigned grid = (unsigned)(((len0 + kPfXcds - 1) / kPfXcds + (len1 + kPfXcds - 1) / kPfXcds) * kPfXcds);
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, st, x, w, packed_by_tenant, alpha_by_tenant, wscale, row_token,
-                           tile_tenant, y, out, in, n_mtiles, n_ntiles, k_planes);
+                           tile_tenant, y, out, in, n_mtiles, n_large, n_ntiles, k_planes);
         return hipGetLastError();
     };
     if (k_planes > 0) return wscale ? go(linear_prefill_kernel<true, true>) : go(linear_prefill_kernel<true, false>);
