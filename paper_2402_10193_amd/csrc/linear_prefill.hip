@@ -69,7 +69,8 @@ __global__ __launch_bounds__(256) void prefill_meta_runs_kernel(const PrefillMet
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 constexpr int kPfMaxPlanes = 8;
 
-template <bool PLANES, bool Q8>
+// NP: 0 = one plane per tenant; 2, 4 or 8 = the most planes this instantiation takes.
+template <int NP_MAX, bool Q8>
 __global__ __launch_bounds__(256, 2) void linear_prefill_kernel(
     const uint16_t* __restrict__ x, const void* __restrict__ w_any, const uint32_t* const* __restrict__ packed_by_tenant,
     const float* __restrict__ alpha_by_tenant, const float* __restrict__ wscale, const int32_t* __restrict__ row_token,
@@ -115,7 +116,12 @@ __global__ __launch_bounds__(256, 2) void linear_prefill_kernel(
     const bool multiply = wm == 0 || row_token[mt * kPrefillTile + 64] >= 0;
     const int64_t n0 = (int64_t)nt * kPrefillTile;
     const int tenant = tile_tenant[mt];
-    constexpr int NP = PLANES ? kPfMaxPlanes : 1;
+    constexpr bool PLANES = NP_MAX > 0;
+    constexpr int NP = PLANES ? NP_MAX : 1;
+    // Up to four planes: their words of the next step are in registers like the other operands.  Fetched when they are staged
+    // (eight planes: no registers for more) a step waits for the trip: 60 tokens of 3 tenants with two planes on 4096 x 4096
+    // 191 us, 129 prefetched; 2000 of 9 on 4096 x 11008 1078 and 698.
+    constexpr bool kPrefetchPlanes = NP_MAX > 0 && NP_MAX <= 4;
     const int np = PLANES ? k_planes : 1;
     const float alpha = PLANES ? 1.f : alpha_by_tenant[tenant];
     const int64_t words_per_row = in >> 5;
@@ -163,6 +169,12 @@ __global__ __launch_bounds__(256, 2) void linear_prefill_kernel(
     }
 
     u32x4 xg[kPfPerThread], wg[kPfPerThread];   // Q8: a chunk of W is 8 bytes, in wg[i][0..1]
+    uint32_t pw[NP];               // planes: this thread's word of every plane (row tid % 128, word tid / 128 of the step)
+    auto fetch_planes = [&](const int64_t k0) {
+        const int64_t wi = (k0 >> 5) + (tid >> 7);
+#pragma unroll
+        for (int j = 0; j < NP; ++j) pw[j] = (j < np && wi < words_per_row) ? ssrc[j][srow_off + wi] : 0u;
+    };
     uint32_t sw[kPrefillK / 32];   // one plane: the row's words of the next step; several planes are fetched when they are staged
     // elements beyond `in` (second half of the last step when in % 64 == 32) are fetched as zeros
     auto fetch = [&](const int64_t k0) {
@@ -181,6 +193,7 @@ __global__ __launch_bounds__(256, 2) void linear_prefill_kernel(
                 }
             }
         }
+        if constexpr (kPrefetchPlanes) fetch_planes(k0);
         if constexpr (!PLANES) {
             if (tid < 128) {
 #pragma unroll
@@ -213,12 +226,7 @@ __global__ __launch_bounds__(256, 2) void linear_prefill_kernel(
             auto signed_alpha = [](const uint32_t entry, const uint32_t a) {
                 return __builtin_bit_cast(half2v, (a & 0x7FFF7FFFu) | (entry & 0x80008000u));
             };
-            // every thread one word per plane (row tid % 128, word tid / 128 of the step), fetched here: the registers
-            // of a prefetch for eight planes are not there
-            const int64_t wi = (k0 >> 5) + h;
-            uint32_t pw[NP];
-#pragma unroll
-            for (int j = 0; j < NP; ++j) pw[j] = (j < np && wi < words_per_row) ? ssrc[j][srow_off + wi] : 0u;
+            if constexpr (!kPrefetchPlanes) fetch_planes(k0);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 half2v d[4];
@@ -331,8 +339,11 @@ hipError_t launch_linear_prefill(const uint16_t* x, const void* w, const uint32_
                            tile_tenant, y, out, in, n_mtiles, n_large, n_ntiles, k_planes);
         return hipGetLastError();
     };
-    if (k_planes > 0) return wscale ? go(linear_prefill_kernel<true, true>) : go(linear_prefill_kernel<true, false>);
-    return wscale ? go(linear_prefill_kernel<false, true>) : go(linear_prefill_kernel<false, false>);
+    if (k_planes > 0 && wscale) return hipErrorInvalidValue;   // k planes together with the 8-bit base: no entry point
+    if (k_planes > 4) return go(linear_prefill_kernel<8, false>);
+    if (k_planes > 2) return go(linear_prefill_kernel<4, false>);
+    if (k_planes > 0) return go(linear_prefill_kernel<2, false>);
+    return wscale ? go(linear_prefill_kernel<0, true>) : go(linear_prefill_kernel<0, false>);
 }
 
 }  // namespace bd
