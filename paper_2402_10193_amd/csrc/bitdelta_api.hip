@@ -15,7 +15,7 @@ namespace {
 using bd::DecodeMeta;
 using bd::kMaxDecodeTokens;
 
-constexpr int kVersion = 220;   // 0.2.20
+constexpr int kVersion = 221;   // 0.2.21
 constexpr int kVariantRowWave = 1;
 constexpr int kVariantRowMajorMfma = 2;   // the matrix-core decode kernel on the row-major tensors (in % 128 == 0)
 constexpr int kVariantPrefillSmall = 4;   // T > 32 with a workspace: the 128 x 128 tile GEMM
@@ -278,6 +278,7 @@ WidePlan wide_plan(int n, int64_t out, int64_t in, int cus) {
     }
     return best;
 }
+constexpr double kWideMargin = 1.1;   // the estimates are right to about a tenth: the wide kernel is taken where it wins by more
 double wide_us(int n_all, int active, int64_t out, int64_t in, int cus) {
     double us = 2.0;
     const int launches = (n_all + bd::kWideMaxTiles - 1) / bd::kWideMaxTiles;
@@ -579,7 +580,7 @@ bd_status bd_linear_multitenant_variant(const uint16_t* x_f16, const uint16_t* w
         const int cus = cus_or_256();
         const double by_decode = decode_us(shape, (double)out * (double)in, false, mfma_ok);
         const double by_gemm = can_prefill ? gemm_us(shape, out, in, big_default, cus) : 1e30;
-        if (mfma_ok && wide_fits(T, out, in) && wide_us(shape.tiles16, shape.active, out, in, cus) < std::min(by_decode, by_gemm))
+        if (mfma_ok && wide_fits(T, out, in) && kWideMargin * wide_us(shape.tiles16, shape.active, out, in, cus) < std::min(by_decode, by_gemm))
             return run_wide(wide_tiles(tenant_of_token, T), x_f16, w_base_f16, packed_by_tenant, nullptr, alpha_by_tenant, y_f16, out, in,
                             hs) == hipSuccess
                        ? BD_OK
@@ -759,7 +760,7 @@ bd_status tiled_linear_impl(int32_t n_mats, const uint16_t* x_f16, const uint16_
             wide += wide_us(shape.tiles16, shape.active, out[m], in, cus);
             elems += (double)out[m] * (double)in;
         }
-        if (fits && wide < decode_us(shape, elems, true, true)) {
+        if (fits && kWideMargin * wide < decode_us(shape, elems, true, true)) {
             const WideTiles tiles = wide_tiles(tenant_of_token, T);
             for (int m = 0; m < n_mats; ++m)
                 if (out[m] > 0 && run_wide(tiles, x_f16, w_tiled[m], nullptr, tiled_by_mat_tenant + (size_t)m * n_tenants, alpha_by_mat[m],

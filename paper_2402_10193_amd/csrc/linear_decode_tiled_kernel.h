@@ -826,12 +826,15 @@ static hipError_t launch_inst(const TiledArgs& args, int n_waves, unsigned grid,
 
 template <bool Q8, bool RM, int NJ>
 static hipError_t launch_nj(const TiledArgs& args, int n_waves, int xsteps, unsigned grid, hipStream_t st) {
-    // Row-major with more than 8 job slots and rows of more than 24 k tiles, or with more than 10 in both column tiles and several
-    // row blocks per workgroup: the signs slot by slot (see S4; below that, four slots at a time is the better one).
+    // Row-major, rows of more than 24 k tiles and more than 8 job slots (4 with two column tiles), or more than 6 in both column
+    // tiles and several row blocks per workgroup: the signs slot by slot (see S4; below that, four slots at a time is the
+    // better one.  4271 x 9088, 31 tokens of 15 tenants: four at a time 97 us, slot by slot 86).
+    if constexpr (RM && NJ > 4) {
+        if (xsteps == 0 && args.n_ct == 2 && (args.KT > 24 || (NJ > 6 && args.rb_end[args.n_mats - 1] > (int)grid)))
+            return launch_inst<Q8, RM, NJ, 0, 2, false>(args, n_waves, grid, st);
+    }
     if constexpr (RM && NJ > 8) {
-        if (xsteps == 0 && (args.KT > 24 || (NJ > 10 && args.n_ct == 2 && args.rb_end[args.n_mats - 1] > (int)grid)))
-            return args.n_ct == 2 ? launch_inst<Q8, RM, NJ, 0, 2, false>(args, n_waves, grid, st)
-                                  : launch_inst<Q8, RM, NJ, 0, 1, false>(args, n_waves, grid, st);
+        if (xsteps == 0 && args.n_ct == 1 && args.KT > 24) return launch_inst<Q8, RM, NJ, 0, 1, false>(args, n_waves, grid, st);
     }
     if (args.n_ct == 2) return launch_inst<Q8, RM, NJ, 0, 2>(args, n_waves, grid, st);   // 17..32 tokens: two column tiles, streamed x
     if (xsteps == 1) return launch_inst<Q8, RM, NJ, 1>(args, n_waves, grid, st);
