@@ -376,8 +376,8 @@ double gemm_us(const BatchShape& s, int64_t out, int64_t in, bool big, int cus) 
     const double all = (double)nt * (steps * (s.tiles32 * 0.85 + s.tiles64 * 1.25 + s.tiles128 * 1.42)) + 8.0 * (double)tiles;
     return 5.0 + all / (double)tiles * (double)((tiles + cus - 1) / cus);
 }
-// Decode launches.  Row-major tensors: 7 us plus the base at 6.2 TB/s plus the sign bytes of the launch's job slots (4, 8 or 16
-// per column tile) at 3.1 TB/s, half as much again with two column tiles (20 to 36 us on 4096 x 4096); the vector-ALU
+// Decode launches.  Row-major tensors: 7 us plus the base at 6.2 TB/s plus the sign bytes of the launch's tenants (at
+// least four) at 3.1 TB/s, half as much again with two column tiles (20 to 36 us on 4096 x 4096); the vector-ALU
 // kernel streams everything at 1.3 TB/s plus 8 us.  Serving layout: 8 us plus all bytes at 4.6 TB/s (14 to 37 us for the
 // linears of Llama-2-7B), one launch for the matrices of a group (`elems` is their sum).
 double decode_us(const BatchShape& s, double elems, bool tiled, bool on_matrix_cores) {
