@@ -165,7 +165,10 @@ bd_status bd_linear_multitenant(const uint16_t* x_f16, const uint16_t* w_base_f1
  *              once to binary16, as a per-tenant fp16 model would store it) and multiplies once, 256 x 256
  *              tiles.  Half the matrix-core work of variants 4 to 7; the result differs from theirs by that
  *              rounding of the weights (about 2e-4 of the largest output at in = 4096) and equals, up to
- *              summation order, bd_linear_naive on bd_materialize'd weights.  Same conditions as 5. */
+ *              summation order, bd_linear_naive on bd_materialize'd weights.  Same conditions as 5.
+ *   variant 10 the kernel for tens to a few hundred tokens with a few per tenant, for any T (in % 128 == 0, x and base
+ *              below 4 GiB, else BD_ERR_UNSUPPORTED; no workspace); 16 R + n: with R = 1 or 2 row blocks and up to n column
+ *              tiles per workgroup (n = 1 .. 8) instead of the library's split */
 bd_status bd_linear_multitenant_variant(const uint16_t* x_f16, const uint16_t* w_base_f16,
                                         const uint32_t* const* packed_by_tenant,
                                         const float* alpha_by_tenant,
@@ -215,6 +218,16 @@ bd_status bd_linear_multitenant_tiled(const uint16_t* x_f16, const uint16_t* w_t
                                       uint16_t* y_f16,
                                       int64_t T, int64_t out, int64_t in, int32_t n_tenants,
                                       void* stream);
+
+/* bd_linear_multitenant_tiled with the kernel chosen by the caller: 0 = the library's choice, 2 = decode launches,
+ * 10 or 16 R + n = the kernel for tens to a few hundred tokens (see bd_linear_multitenant_variant). */
+bd_status bd_linear_multitenant_tiled_variant(const uint16_t* x_f16, const uint16_t* w_tiled,
+                                              const uint32_t* const* tiled_by_tenant,
+                                              const float* alpha_by_tenant,
+                                              const int32_t* tenant_of_token,
+                                              uint16_t* y_f16,
+                                              int64_t T, int64_t out, int64_t in, int32_t n_tenants,
+                                              void* stream, int32_t variant);
 
 /* The prefill regime of Sec. 4.3 (many tokens per tenant) on the SAME serving layout, so that one copy of the base and
  * of every delta serves both decode and prefill: all T tokens (1 <= T <= 65535) in ONE matrix-core GEMM launch, tokens

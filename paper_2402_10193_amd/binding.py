@@ -26,7 +26,7 @@ EXPORTS = ["bd_status_string", "bd_version", "bd_workspace_bytes", "bd_pack_sign
            "bd_group_tokens",
            "bd_linear_multitenant", "bd_linear_multitenant_variant", "bd_materialize", "bd_linear_naive",
            "bd_probe_read", "bd_probe_copy", "bd_tiled_base_bytes", "bd_tiled_signs_bytes", "bd_tile_base",
-           "bd_tile_signs", "bd_linear_multitenant_tiled", "bd_linear_multitenant_tiled_gemm", "bd_linear_multitenant_tiled_group",
+           "bd_tile_signs", "bd_linear_multitenant_tiled", "bd_linear_multitenant_tiled_variant", "bd_linear_multitenant_tiled_gemm", "bd_linear_multitenant_tiled_group",
            "bd_compress_iterated",
            "bd_linear_multitenant_tiled_kbit", "bd_linear_multitenant_tiled_group_kbit", "bd_delta_image_bytes",
            "bd_delta_image_build", "bd_delta_image_check", "bd_delta_image_entry", "bd_delta_file_write",
@@ -81,6 +81,8 @@ def lib() -> ctypes.CDLL:
         L.bd_tile_signs.argtypes = [vp, i64, i64, vp, vp]
         pvp, pi64 = ctypes.POINTER(vp), ctypes.POINTER(i64)
         L.bd_linear_multitenant_tiled.argtypes = [vp, vp, pvp, vp, pi, vp, i64, i64, i64, i32, vp]
+        L.bd_linear_multitenant_tiled_variant.argtypes = [vp, vp, pvp, vp, pi, vp, i64, i64, i64, i32, vp, i32]
+        L.bd_linear_multitenant_tiled_variant.restype = ctypes.c_int
         L.bd_linear_multitenant_tiled_group.argtypes = [i32, vp, pvp, pvp, pvp, pi, pvp, i64, pi64, i64, i32, vp]
         L.bd_linear_multitenant_tiled_gemm.argtypes = [vp, vp, pvp, vp, pi, vp, i64, i64, i64, i32, i32, vp, sz, vp]
         L.bd_linear_multitenant_tiled_gemm.restype = ctypes.c_int
@@ -440,8 +442,8 @@ class TiledTenantTable:
 
 def linear_multitenant_tiled(x: torch.Tensor, w_tiled: torch.Tensor, out: int, tenants: TiledTenantTable,
                              tenant_of_token: Sequence[int], y: Optional[torch.Tensor] = None, stream=None,
-                             tok_array=None) -> torch.Tensor:
-    """bd_linear_multitenant_tiled: y fp16 [T, out]."""
+                             tok_array=None, variant: int = 0) -> torch.Tensor:
+    """bd_linear_multitenant_tiled (variant 0) or bd_linear_multitenant_tiled_variant: y fp16 [T, out]."""
     _dev(x, torch.float16, "x")
     _dev(w_tiled, torch.float16, "w_tiled")
     T, inn = x.shape
@@ -449,8 +451,8 @@ def linear_multitenant_tiled(x: torch.Tensor, w_tiled: torch.Tensor, out: int, t
         y = torch.empty((T, out), dtype=torch.float16, device=x.device)
     _dev(y, torch.float16, "y")
     tok = tok_array if tok_array is not None else _tok_array(tenant_of_token)
-    _check(lib().bd_linear_multitenant_tiled(_ptr(x), _ptr(w_tiled), tenants.host_ptrs, _ptr(tenants.alpha), tok,
-                                             _ptr(y), T, out, inn, tenants.n_tenants, _stream(stream)),
+    args = (_ptr(x), _ptr(w_tiled), tenants.host_ptrs, _ptr(tenants.alpha), tok, _ptr(y), T, out, inn, tenants.n_tenants, _stream(stream))
+    _check(lib().bd_linear_multitenant_tiled(*args) if variant == 0 else lib().bd_linear_multitenant_tiled_variant(*args, int(variant)),
            "bd_linear_multitenant_tiled")
     return y
 

@@ -23,6 +23,7 @@ constexpr int kVariantPrefillBig = 5;     // ... the 128 x 256 tile GEMM (in % 6
 constexpr int kVariantPrefillBig8 = 6;    // ... the same tile with two wavefronts per SIMD
 constexpr int kVariantPrefillBigWhole = 7;   // ... as 5, but never cutting the tiles of the last round in two
 constexpr int kVariantPrefillMerged = 8;     // ... one product on W + alpha S, formed in fp16 on the way to the matrix cores (256 x 256 tiles)
+constexpr int kVariantWide = 10;             // the kernel for tens to a few hundred tokens; 16 R + n: R row blocks and up to n column tiles per workgroup
 
 inline bool misaligned(const void* p, size_t a) { return ((uintptr_t)p & (a - 1)) != 0; }
 
@@ -288,6 +289,13 @@ double wide_us(int n_all, int active, int64_t out, int64_t in, int cus) {
     return std::max(us, 6.0 + elems * (2.0 + (double)active / 8.0) / 4.5e6);
 }
 
+// The split that a variant number asks for: 0 = the plan's, -1 = none of the kernel's.
+int wide_split_of_variant(int32_t variant) {
+    if (variant == kVariantWide) return 0;
+    const int R = variant >> 4, n = variant & 15;
+    return (R == 1 || R == 2) && n >= 1 && n <= bd::kWideMaxChunk ? variant : -1;
+}
+
 bool wide_fits(int64_t T, int64_t out, int64_t in) {
     return in >= 128 && in % 128 == 0 && out >= 1 && T < 65535 && (uint64_t)T * (uint64_t)in * 2 < ((uint64_t)1 << 32) &&
            (uint64_t)(bd::tiled_row_blocks(out) * bd::tiled_k_tiles(in)) * bd::kTileBaseBytes < ((uint64_t)1 << 32);
@@ -295,7 +303,8 @@ bool wide_fits(int64_t T, int64_t out, int64_t in) {
 
 // packed_dev: the row-major tensors (device pointer table); otherwise w is the tiled base and tiled_host the tenants' tiled deltas
 hipError_t run_wide(const WideTiles& t, const uint16_t* x, const uint16_t* w, const uint32_t* const* packed_dev,
-                    const uint32_t* const* tiled_host, const float* alpha, uint16_t* y, int64_t out, int64_t in, hipStream_t st) {
+                    const uint32_t* const* tiled_host, const float* alpha, uint16_t* y, int64_t out, int64_t in, hipStream_t st,
+                    int split = 0) {
     const int cus = cus_or_256(), n_all = (int)t.tenant.size(), launches = (n_all + bd::kWideMaxTiles - 1) / bd::kWideMaxTiles;
     for (int l = 0; l < launches; ++l) {
         const int first = (int)((int64_t)n_all * l / launches), n = (int)((int64_t)n_all * (l + 1) / launches) - first;
@@ -312,7 +321,7 @@ hipError_t run_wide(const WideTiles& t, const uint16_t* x, const uint16_t* w, co
         a.units = (int32_t)(in / 128);
         a.row_blocks = (int32_t)bd::tiled_row_blocks(out);
         a.n_tiles = n;
-        const WidePlan p = wide_plan(n, out, in, cus);
+        const WidePlan p = split ? WidePlan{split >> 4, std::min(split & 15, n), 0.0} : wide_plan(n, out, in, cus);
         a.tiles_per_chunk = p.per_chunk;
         for (int i = 0; i < n; ++i) {
             a.tenant[i] = t.tenant[(size_t)(first + i)];
@@ -541,7 +550,7 @@ bd_status tiled_linear_impl(int32_t n_mats, const uint16_t* x_f16, const uint16_
                             const uint32_t* const* tiled_by_mat_tenant, const float* const* alpha_by_mat,
                             const int32_t* tenant_of_token, uint16_t* const* y_f16, int64_t T, const int64_t* out,
                             int64_t in, int32_t n_tenants, int32_t k, void* stream, bool q8,
-                            const uint32_t* const* packed_rowmajor_dev, const float* wscale_rowmajor = nullptr);
+                            const uint32_t* const* packed_rowmajor_dev, const float* wscale_rowmajor = nullptr, int32_t variant = 0);
 }
 
 bd_status bd_linear_multitenant_variant(const uint16_t* x_f16, const uint16_t* w_base_f16,
@@ -556,9 +565,17 @@ bd_status bd_linear_multitenant_variant(const uint16_t* x_f16, const uint16_t* w
     const bool big_variant = variant == kVariantPrefillBig || variant == kVariantPrefillBig8 || variant == kVariantPrefillBigWhole ||
                              merged_variant;
     const bool prefill_variant = variant == kVariantPrefillSmall || big_variant;
-    if (variant != 0 && variant != kVariantRowWave && variant != kVariantRowMajorMfma && !prefill_variant)
+    const int wide_split = wide_split_of_variant(variant);
+    if (variant != 0 && variant != kVariantRowWave && variant != kVariantRowMajorMfma && !prefill_variant && wide_split < 0)
         return BD_ERR_UNSUPPORTED;
     if (T == 0 || out == 0) return BD_OK;
+    auto wide = [&](const int split) {
+        return run_wide(wide_tiles(tenant_of_token, T), x_f16, w_base_f16, packed_by_tenant, nullptr, alpha_by_tenant, y_f16, out, in,
+                        (hipStream_t)stream, split) == hipSuccess
+                   ? BD_OK
+                   : BD_ERR_DEVICE;
+    };
+    if (wide_split >= 0) return wide_fits(T, out, in) ? wide(wide_split) : BD_ERR_UNSUPPORTED;
     // 128-bit sign loads need whole, aligned 4-word groups; 32-bit lane offsets need tensors below 4 GiB
     const bool mfma_ok = (in % 128 == 0) && in > 0 && (uint64_t)out * (uint64_t)in * 2 < ((uint64_t)1 << 32) &&
                          (uint64_t)T * (uint64_t)in * 2 < ((uint64_t)1 << 32);
@@ -581,10 +598,7 @@ bd_status bd_linear_multitenant_variant(const uint16_t* x_f16, const uint16_t* w
         const double by_decode = decode_us(shape, (double)out * (double)in, false, mfma_ok);
         const double by_gemm = can_prefill ? gemm_us(shape, out, in, big_default, cus) : 1e30;
         if (mfma_ok && wide_fits(T, out, in) && kWideMargin * wide_us(shape.tiles16, shape.active, out, in, cus) < std::min(by_decode, by_gemm))
-            return run_wide(wide_tiles(tenant_of_token, T), x_f16, w_base_f16, packed_by_tenant, nullptr, alpha_by_tenant, y_f16, out, in,
-                            hs) == hipSuccess
-                       ? BD_OK
-                       : BD_ERR_DEVICE;
+            return wide(0);
         gemm_pays = by_gemm < by_decode;
     }
     if (can_prefill && gemm_pays) {
@@ -701,7 +715,7 @@ bd_status tiled_linear_impl(int32_t n_mats, const uint16_t* x_f16, const uint16_
                             const uint32_t* const* tiled_by_mat_tenant, const float* const* alpha_by_mat,
                             const int32_t* tenant_of_token, uint16_t* const* y_f16, int64_t T, const int64_t* out,
                             int64_t in, int32_t n_tenants, int32_t k, void* stream, bool q8,
-                            const uint32_t* const* packed_rowmajor_dev, const float* wscale_rowmajor) {
+                            const uint32_t* const* packed_rowmajor_dev, const float* wscale_rowmajor, int32_t variant) {
     const bool rm = packed_rowmajor_dev != nullptr;
     if (rm && (n_mats != 1 || in % 128 != 0 || (q8 && (!wscale_rowmajor || k != 1)))) return BD_ERR_UNSUPPORTED;
     if (n_mats < 1 || n_mats > bd::kTiledMaxMats) return BD_ERR_SHAPE;
@@ -743,12 +757,14 @@ bd_status tiled_linear_impl(int32_t n_mats, const uint16_t* x_f16, const uint16_
                 if (misaligned(p, 16)) return BD_ERR_ALIGN;
             }
     }
-    // A token takes k columns (one per plane) of a 16-column tile; a launch covers two tiles.  More tokens than one
-    // launch takes: all of them are sorted by tenant first (stable), so that a tenant's tokens share launches and
-    // its delta is streamed as few times as possible; the kernel finds the rows of x and y through the token ids.
     // Serving layout, one plane, more tokens than a launch takes: the wide kernel, a launch per matrix, where its estimate is
     // below that of the decode launches, which take the matrices of a group together.
-    if (!rm && !q8 && k == 1 && T > bd::kMaxDecodeTokens) {
+    const int wide_split = wide_split_of_variant(variant);
+    if (wide_split >= 0) {
+        for (int m = 0; m < n_mats; ++m)
+            if (out[m] > 0 && !wide_fits(T, out[m], in)) return BD_ERR_UNSUPPORTED;
+    }
+    if (wide_split >= 0 || (!rm && !q8 && k == 1 && variant == 0 && T > bd::kMaxDecodeTokens)) {
         const BatchShape shape = batch_shape(tenant_of_token, T);
         const int cus = cus_or_256();
         bool fits = true;
@@ -760,15 +776,18 @@ bd_status tiled_linear_impl(int32_t n_mats, const uint16_t* x_f16, const uint16_
             wide += wide_us(shape.tiles16, shape.active, out[m], in, cus);
             elems += (double)out[m] * (double)in;
         }
-        if (fits && kWideMargin * wide < decode_us(shape, elems, true, true)) {
+        if (wide_split >= 0 || (fits && kWideMargin * wide < decode_us(shape, elems, true, true))) {
             const WideTiles tiles = wide_tiles(tenant_of_token, T);
             for (int m = 0; m < n_mats; ++m)
                 if (out[m] > 0 && run_wide(tiles, x_f16, w_tiled[m], nullptr, tiled_by_mat_tenant + (size_t)m * n_tenants, alpha_by_mat[m],
-                                           y_f16[m], out[m], in, (hipStream_t)stream) != hipSuccess)
+                                           y_f16[m], out[m], in, (hipStream_t)stream, std::max(wide_split, 0)) != hipSuccess)
                     return BD_ERR_DEVICE;
             return BD_OK;
         }
     }
+    // A token takes k columns (one per plane) of a 16-column tile; a launch covers two tiles.  More tokens than one
+    // launch takes: all of them are sorted by tenant first (stable), so that a tenant's tokens share launches and
+    // its delta is streamed as few times as possible; the kernel finds the rows of x and y through the token ids.
     const int per_tile = bd::kTiledMaxTokens / k;
     const int per_launch = per_tile * bd::kTiledMaxCt;
     std::vector<int32_t> order((size_t)T);
@@ -926,6 +945,15 @@ bd_status bd_linear_multitenant_tiled(const uint16_t* x_f16, const uint16_t* w_t
                                       int32_t n_tenants, void* stream) {
     return tiled_linear_impl(1, x_f16, &w_tiled, tiled_by_tenant, &alpha_by_tenant, tenant_of_token, &y_f16, T, &out, in,
                              n_tenants, 1, stream, false, nullptr);
+}
+
+bd_status bd_linear_multitenant_tiled_variant(const uint16_t* x_f16, const uint16_t* w_tiled,
+                                              const uint32_t* const* tiled_by_tenant, const float* alpha_by_tenant,
+                                              const int32_t* tenant_of_token, uint16_t* y_f16, int64_t T, int64_t out, int64_t in,
+                                              int32_t n_tenants, void* stream, int32_t variant) {
+    if (variant != 0 && variant != kVariantRowMajorMfma && wide_split_of_variant(variant) < 0) return BD_ERR_UNSUPPORTED;
+    return tiled_linear_impl(1, x_f16, &w_tiled, tiled_by_tenant, &alpha_by_tenant, tenant_of_token, &y_f16, T, &out, in,
+                             n_tenants, 1, stream, false, nullptr, nullptr, variant);
 }
 
 bd_status bd_linear_multitenant_tiled_gemm(const uint16_t* x_f16, const uint16_t* w_tiled, const uint32_t* const* tiled_by_tenant,

@@ -70,7 +70,8 @@ def test_gemm_q8_tiles(out, inn, counts):
     t.check(y, q.double() * scale.double()[:, None], f"q8 {out}x{inn} {counts}")
 
 
-# More than 32 tokens with a few per tenant: tiles of 16 columns (row-major and tiled), against float64 and the decode launches.
+# More than 32 tokens with a few per tenant, as the library chooses to run them (which kernel that is, an estimate says),
+# against float64; the kernel of 16-column tiles by its number: test_wide_every_split.
 # Rows of `out` around one and two row blocks, one unit of `in` and counts that are no multiple of the eight wavefronts,
 # columns of 1, 15, 16, 17 and 33 tokens, one and several chunks of column tiles, more than one launch's worth of tiles.
 WIDE = [
@@ -82,8 +83,8 @@ WIDE = [
     (300, 2176, [7, 9, 20, 1, 30, 12, 5, 8]),
     (4112, 512, [12] * 9),
     (64, 640, [9] * 40 + [16] * 30),         # 70 column tiles: two launches
-    (2064, 1024, [15] * 3),                  # 129 row blocks: one per workgroup; 4 tiles per chunk
-    (4096, 256, [16] * 5),                   # two per workgroup, 6 tiles per chunk
+    (2064, 1024, [15] * 3),                  # 129 row blocks
+    (4096, 256, [16] * 5),
 ]
 
 
@@ -108,6 +109,30 @@ def test_wide_batches(case, order):
     ya, yb = bd.linear_multitenant_tiled_group(t.x, group, t.tok, ys=[nan(), nan()])
     t.check(ya, what=what + " group")
     assert torch.equal(ya, yb), what + " group"
+
+
+# The kernel of 16-column tiles, asked for by number, in every split it has: one and two row blocks per workgroup, every number
+# of column tiles, the last chunk partly filled; `out` that ends inside a row block and inside a pair of them; units of `in`
+# fewer than the eight wavefronts, as many, and an odd number of them.
+WIDE_SPLITS = [16 * r + n for r in (1, 2) for n in range(1, 9)]
+
+
+@pytest.mark.parametrize("variant", [10] + WIDE_SPLITS)
+@pytest.mark.parametrize("out,inn,counts", [
+    (41, 1152, [20, 1, 33, 16, 0, 15, 40]),      # 11 column tiles; 3 row blocks; 9 units
+    (16, 128, [17]),                             # 1 row block, 1 unit, 2 column tiles
+    (373, 2176, [9, 31, 2, 5]),                  # 24 row blocks, 17 units
+    (64, 640, [9] * 40 + [16] * 30),             # 70 column tiles: two launches
+])
+def test_wide_every_split(out, inn, counts, variant):
+    t = Tensors(out, inn, tokens_of(counts, "shuffled"), len(counts), seed=variant)
+    what = f"wide {out}x{inn} {counts} variant {variant}"
+    nan = lambda: torch.full((len(t.tok), out), float("nan"), dtype=torch.float16, device=DEV)
+    y = bd.linear_multitenant(t.x, t.w, bd.TenantTable(t.packed, t.alpha), t.tok, y=nan(), variant=variant)
+    t.check(y, what=what + " row-major")
+    tiled = bd.TiledTenantTable([bd.tile_signs(p, out, inn) if n else None for p, n in zip(t.packed, counts)], t.alpha)
+    y = bd.linear_multitenant_tiled(t.x, bd.tile_base(t.w), out, tiled, t.tok, y=nan(), variant=variant)
+    t.check(y, what=what + " tiled")
 
 
 def test_wide_non_finite_values():

@@ -120,6 +120,39 @@ def test_prefill_gemms_replayed_from_a_graph(ref):
             check_close(got[0], y32, "prefill graph replay against the oracle")
 
 
+def test_wide_batches_replayed_from_a_graph(ref):
+    """The kernel for tens to a few hundred tokens on both layouts, its tables in the kernel arguments; 70 column tiles: two
+    launches per call."""
+    out, inn, nt = 72, 640, 70
+    tok = [e for e in range(nt) for _ in range(1 + e % 16)]
+    T, tok_arr = len(tok), bd._tok_array(tok)
+    prob = TiledProblem(ref, out, inn, nt, tag=("graph", "wide"))
+    x = torch.empty((T, inn), dtype=torch.float16, device=DEV)
+    y, yt = (torch.empty((T, out), dtype=torch.float16, device=DEV) for _ in range(2))
+
+    def run():
+        bd.linear_multitenant(x, prob.w_base, prob.table, tok, y=y, tok_array=tok_arr, variant=10, workspace=None)
+        bd.linear_multitenant_tiled(x, prob.w_tiled, out, prob.ttable, tok, y=yt, tok_array=tok_arr, variant=10)
+    x.copy_(prob.x(T, tag="warm"))
+    graph = _capture(run)
+    for rep in range(3):
+        _p(f"wide graph, replay {rep}")
+        x.copy_(prob.x(T, tag=("rep", rep)))
+        y.fill_(float("nan"))
+        yt.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        got = [y.clone(), yt.clone()]
+        want = [bd.linear_multitenant(x, prob.w_base, prob.table, tok, variant=10, workspace=None),
+                bd.linear_multitenant_tiled(x, prob.w_tiled, out, prob.ttable, tok, variant=10)]
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), f"replay {rep}"
+        if rep == 0:
+            _, y32 = ref.linear_multitenant(to_np(x), prob.w_base_np, prob.packed_np, prob.alpha_np, tok)
+            check_close(got[0], y32, "wide graph replay against the oracle")
+            check_close(got[1], y32, "wide graph replay against the oracle")
+
+
 def test_compressor_without_allocation_replayed_from_a_graph(ref):
     out, inn = 272, 1024
     base = synth.base_weight(out, inn, device=DEV, tag=("graph", "cb"))

@@ -92,6 +92,21 @@ def test_linear_argument_errors_are_caught_on_the_host(bd):
     assert fv(A, 2 * A, 3 * A, 4 * A, many, 5 * A, 64, 16, 128, 1, 6 * A, 1 << 20, 0, 9) == 7
 
 
+def test_wide_variant_argument_errors(bd):
+    """The kernel of 16-column tiles by number: unknown splits, and shapes it cannot run, on both layouts."""
+    L = bd.lib()
+    ptrs = (ctypes.c_void_p * 1)(3 * A)
+    rm = lambda v, inn=128, out=16, T=1, tok=_tok(0): L.bd_linear_multitenant_variant(A, 2 * A, 3 * A, 4 * A, tok, 5 * A, T, out, inn, 1, 0, 0, 0, v)
+    ti = lambda v, inn=128, out=16, T=1, tok=_tok(0): L.bd_linear_multitenant_tiled_variant(A, 2 * A, ptrs, 4 * A, tok, 5 * A, T, out, inn, 1, 0, v)
+    for f in (rm, ti):
+        for v in (3, 11, 16, 16 + 15, 32, 32 + 15, 48 + 1, 64 + 1, -1, 99):
+            assert f(v) == 7, v
+        for v in (10, 16 + 1, 32 + 1):
+            assert f(v, inn=96) == 7, v
+            assert f(v, tok=_tok(1)) == 4 and f(v, T=0) == 0 and f(v, out=0) == 0
+    assert ti(4) == 7 and ti(1) == 7 and rm(10, inn=0) == 7
+
+
 def test_tiled_gemm_argument_errors(bd):
     """bd_linear_multitenant_tiled_gemm: every error is found on the host before anything is launched."""
     L = bd.lib()
