@@ -128,7 +128,8 @@ bd_status bd_compress_batch(int32_t n, const uint16_t* const* w_base_f16, const 
  *                    nothing.
  *   y_f16            [T, out]  fp16 result; must not overlap x or w_base (BD_ERR_ALIAS)
  * Both products accumulate in binary32, alpha multiplies the finished +-1 sum in binary32 and
- * the result is rounded once to fp16 (nearest even).
+ * the result is rounded once to fp16 (nearest even).  (In decode launches the sum of each wavefront's share of `in`, at most
+ * eight of them, which are then added: an infinite alpha gives NaN where one of those is zero.)
  * T == 0 or out == 0 is a no-op returning BD_OK.  T up to 65535.
  * Up to 32 tokens run as one decode launch and need no workspace.  More tokens (the prefill regime
  * of Sec. 4.3: many tokens per tenant) can run as ONE matrix-core GEMM launch over all tokens if
@@ -168,7 +169,7 @@ bd_status bd_linear_multitenant(const uint16_t* x_f16, const uint16_t* w_base_f1
  *              summation order, bd_linear_naive on bd_materialize'd weights.  Same conditions as 5.
  *   variant 10 the kernel for tens to a few hundred tokens with a few per tenant, for any T (in % 128 == 0, x and base
  *              below 4 GiB, else BD_ERR_UNSUPPORTED; no workspace); 16 R + n: with R = 1 or 2 row blocks and up to n column
- *              tiles per workgroup (n = 1 .. 8) instead of the library's split */
+ *              tiles per workgroup instead of the library's split (n = 1 .. 10 with R = 1, 1 .. 6 with R = 2) */
 bd_status bd_linear_multitenant_variant(const uint16_t* x_f16, const uint16_t* w_base_f16,
                                         const uint32_t* const* packed_by_tenant,
                                         const float* alpha_by_tenant,
@@ -198,8 +199,9 @@ bd_status bd_tile_base(const uint16_t* w_f16, int64_t out, int64_t in, uint16_t*
  * (bd_tiled_signs_bytes(out, in) bytes). */
 bd_status bd_tile_signs(const uint32_t* packed, int64_t out, int64_t in, uint32_t* signs_tiled, void* stream);
 
-/* The multi-tenant linear of Eq. 6 over the serving layout; same arithmetic and rounding as
- * bd_linear_multitenant.
+/* The multi-tenant linear of Eq. 6 over the serving layout; the arithmetic and rounding of
+ * bd_linear_multitenant's decode launches.  A token's result does not depend on the other tokens of the call, however many
+ * there are (finite scales; an infinite one multiplies the whole row's +-1 sum in the kernel for tens to a few hundred tokens).
  *   w_tiled          tiled base (bd_tile_base)
  *   tiled_by_tenant  HOST array of n_tenants DEVICE pointers to tiled deltas (bd_tile_signs); the
  *                    pointers travel in the kernel arguments, so no device-side pointer table is read.
@@ -220,7 +222,8 @@ bd_status bd_linear_multitenant_tiled(const uint16_t* x_f16, const uint16_t* w_t
                                       void* stream);
 
 /* bd_linear_multitenant_tiled with the kernel chosen by the caller: 0 = the library's choice, 2 = decode launches,
- * 10 or 16 R + n = the kernel for tens to a few hundred tokens (see bd_linear_multitenant_variant). */
+ * 10 or 16 R + n = the kernel for tens to a few hundred tokens (see bd_linear_multitenant_variant; R = 2 with n = 5 or 6
+ * only where `in` makes 1, 2, 4 or 8 k tiles of 256).  All of them give the same bits for finite scales. */
 bd_status bd_linear_multitenant_tiled_variant(const uint16_t* x_f16, const uint16_t* w_tiled,
                                               const uint32_t* const* tiled_by_tenant,
                                               const float* alpha_by_tenant,
@@ -257,7 +260,7 @@ bd_status bd_linear_multitenant_tiled_gemm(const uint16_t* x_f16, const uint16_t
  *   alpha_by_mat        HOST [n_mats] of device arrays [n_tenants]
  *   y_f16               HOST [n_mats] of device pointers, y_m is [T, out[m]]
  *   out                 HOST [n_mats]; `in`, x, T and tenant_of_token are shared.
- * Up to 32 tokens give the bits of n_mats separate calls; with more, the kernel is chosen for the group as a whole. */
+ * The bits of n_mats separate calls. */
 bd_status bd_linear_multitenant_tiled_group(int32_t n_mats, const uint16_t* x_f16,
                                             const uint16_t* const* w_tiled,
                                             const uint32_t* const* tiled_by_mat_tenant,

@@ -13,15 +13,21 @@
 // features x 32 k, B = 32 k x 16 tokens) and fetches 4 KiB of x.  In operand order neighbouring lanes are different tokens,
 // every lane an access of its own, and the address unit takes 64 cycles per KiB; so x is fetched with 16 lanes side by side
 // in a row (16 cycles) and turned round through LDS rows that belong to the wavefront (16-byte chunk q of row r at place
-// q ^ r: neither the writes nor the reads share a bank).  Row-major bases take the same way.  With direct loads 200 tokens of
-// 16 tenants on 4096 x 4096 took 89 us (row-major) and 59 us (tiled), now 50 and 46; the GEMM of 32-row tiles 73 us.  What is
-// left: 12 us around the loop of a workgroup, and in it 97 instructions per column tile and unit (16 of them MFMAs) of two
-// wavefronts per SIMD, matrix cores 36 % and LDS 53 % of the cycles busy.
+// q ^ r: neither the writes nor the reads share a bank).  Row-major bases take the same way.  200 tokens of 16 tenants on
+// 4096 x 4096, weights from HBM: 54 us on either layout; decode launches 137 (row-major) and 123 (tiled), the GEMM of 32-row
+// tiles 76.  What is left: some 4 us around the loop of a workgroup, and in it the issue of two wavefronts per SIMD.
 // R = 2 halves the fetches of x per product; R = 1 where two row blocks per workgroup would leave compute units idle.
-// Registers (two wavefronts per SIMD, 256 each): accumulators 4 R MT, the base of two units 32 R, x 32, four table operands
-// 16, the signs of a unit R MT.  So the +-1 sum of a column tile lives for one unit only: it is scaled by alpha and added to
-// the base product in binary32 when the next tile has begun (another order of additions than the GEMM's, the same
-// precision).
+//
+// The sums.  Base product and +-1 sum have accumulators of their own, and a scale never multiplies an unfinished sum inside
+// the loop.  (With one set of accumulators, the +-1 sum of each unit scaled and added to the base product, eight column tiles and two
+// row blocks fit the registers and 400 tokens of 32 tenants took 100 us where it is 105 now; but where the +-1 sums of units
+// cancel, the result then carried the rounding of alpha times the parts, and an infinite scale made an infinity of a sum of zero.)
+//   Row-major: the wavefronts' sums are added, base and +-1 apart, and alpha multiplies the finished one, as in the GEMM.
+//   Tiled: the arithmetic of the decode kernel, addition for addition (its k tiles per wavefront, the +-1 sum of a k tile from
+//   zero and then added to those before it, the wavefronts' scaled parts in order), so that a token's result does not depend on
+//   which of the two the batch was given to.
+// Registers (two wavefronts per SIMD, 256 each): accumulators 8 R MT, tiled 12 R MT where wavefronts have several k tiles; the base
+// of two units 32 R, x 32, two table operands 8, the signs of a unit R MT.  That sets the most column tiles (wide_max_chunk).
 // Signs become operands through the byte table of the decode kernel (256 entries x 16 copies x 16 B in LDS, one
 // v_perm_b32 and one ds_read_b128 per 8 signs and lane).
 #include "bd_device.h"
@@ -32,7 +38,6 @@ namespace bd {
 
 namespace {
 
-constexpr int kWideWaves = 8;
 constexpr int kWideUnit = 128;                        // reduction elements per unit: 4 MFMA slices
 constexpr int kWideLutBytes = 256 * 16 * 16;
 typedef const u32x4 __attribute__((address_space(3)))* wide_lds_u32x4;
@@ -44,12 +49,12 @@ __device__ __forceinline__ void wide_wave_sync() {   // a wavefront's LDS access
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// LDS: the table, two 4 KiB rooms per wavefront in which 16 rows x 128 k change their order; the partial tiles of four
-// wavefronts overlay both after the loop.  Behind them what is looked up per column tile.
+// LDS: the table, two 4 KiB rooms per wavefront in which 16 rows x 128 k change their order; the partial tiles of eight
+// wavefronts and one more set overlay both after the loop.  Behind them what is looked up per column tile.
 template <int R, int MT>
 struct WideLds {
     static constexpr int kRooms = kWideLutBytes;
-    static constexpr int kRed = 4 * R * MT * 1024;
+    static constexpr int kRed = 9 * R * MT * 1024;
     static constexpr int kOff = kWideLutBytes + kWideWaves * 8192;   // [ct][lane group][i]: byte offset of x row 4 i + group
     static constexpr int kTok = kOff + MT * 64;                      // [ct][column]: token or -1
     static constexpr int kGroups = (R * MT + 3) / 4;                 // row-major signs are fetched four (ct, row block) at a time
@@ -61,7 +66,8 @@ struct WideLds {
 
 }  // namespace
 
-template <int R, int MT, bool RM>
+// TILE_SUMS: the +-1 sum of every pair of units (a k tile) apart
+template <int R, int MT, bool RM, bool TILE_SUMS>
 __global__ __launch_bounds__(kWideWaves * kWave) void linear_wide_kernel(const WideArgs a) {
     using Lds = WideLds<R, MT>;
     constexpr int kGroups = Lds::kGroups;
@@ -96,26 +102,28 @@ __global__ __launch_bounds__(kWideWaves * kWave) void linear_wide_kernel(const W
             *(uint64_t*)(smem + Lds::kSp + q * 8) = (uint64_t)(p + (int64_t)row * (a.in >> 3));
         }
     }
-    float alpha[MT];
     const unsigned char* sp[MT];
 #pragma unroll
     for (int ct = 0; ct < MT; ++ct) {
         const int tile = tile0 + min(ct, n_tiles - 1);
         const float al = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, a.alpha_by_tenant[a.tenant[tile]])));
         if (threadIdx.x == 0) *(float*)(smem + Lds::kAlpha + ct * 4) = al;
-        // An infinite scale (a fine-tune with an infinity in it) times the +-1 sum of one unit would be NaN wherever that part
-        // alone is zero: it is carried as +-1e26, which any sum but zero (6e-8 at least) takes beyond 1e18 and every base product
-        // (4.3e9 `in` at most) stays below, and told apart again when y is written.
-        alpha[ct] = __builtin_isinf(al) ? __builtin_copysignf(1e26f, al) : al;
         sp[ct] = RM ? nullptr : (const unsigned char*)a.signs[tile];
     }
     const unsigned char* const xg = (const unsigned char*)a.x;
     const unsigned char* const wg = (const unsigned char*)a.w;
     // This wavefront's units.  Row-major: every 8th, so that the 16-byte pieces of a 128-byte line of signs are asked for by
-    // the 8 wavefronts at about the same time; tiled: a contiguous range.
-    const int u_begin = RM ? wave : wave * a.units / kWideWaves;
-    const int u_step = RM ? kWideWaves : 1;
-    const int u_count = RM ? (a.units - wave + kWideWaves - 1) / kWideWaves : (wave + 1) * a.units / kWideWaves - u_begin;
+    // the 8 wavefronts at about the same time.  Tiled: the units of a contiguous range of k tiles (256 elements), the range
+    // that the decode kernel deals to this wavefront; with fewer k tiles than wavefronts some have none.
+    int nw = kWideWaves;                               // wavefronts that have units
+    int u_begin = wave, u_half = kWideWaves, u_step = 2 * kWideWaves, u_count = (a.units - wave + kWideWaves - 1) / kWideWaves;
+    if constexpr (!RM) {
+        while (nw > 1 && nw > a.KT) nw >>= 1;
+        u_begin = 2 * (wave * a.KT / nw);
+        u_half = 1;
+        u_step = 2;
+        u_count = wave < nw ? min(2 * ((wave + 1) * a.KT / nw), a.units) - u_begin : 0;
+    }
 
     // the table: entry b, copy cp at 256 b + 16 cp; element e = bit e of b ? +1.0 : -1.0
     for (int q = threadIdx.x; q < 256 * 16; q += kWideWaves * kWave) {
@@ -195,11 +203,12 @@ __global__ __launch_bounds__(kWideWaves * kWave) void linear_wide_kernel(const W
         w = u32x4{b01[0], b01[1], b23[0], b23[1]};
     };
 
-    float4v acc[R][MT];
+    float4v acc[R][MT], dsum[R][MT];                   // base product, +-1 sum
+    float4v dtile[TILE_SUMS ? R : 1][TILE_SUMS ? MT : 1];   // +-1 sum of the k tile that is being multiplied
 #pragma unroll
     for (int r = 0; r < R; ++r)
 #pragma unroll
-        for (int ct = 0; ct < MT; ++ct) acc[r][ct] = float4v{0.f, 0.f, 0.f, 0.f};
+        for (int ct = 0; ct < MT; ++ct) acc[r][ct] = dsum[r][ct] = float4v{0.f, 0.f, 0.f, 0.f};
 
     u32x4 wr[2][R][4];                                 // the base of this unit and of the next one
     u32x4 xs[4], xo[4];                                // x of the next column tile as fetched; this one's operands
@@ -229,7 +238,7 @@ __global__ __launch_bounds__(kWideWaves * kWave) void linear_wide_kernel(const W
     }
     u32x4 off_next = ld_off(2 % MT);                   // rows of the tile that is requested next
     constexpr int kPer = 4 * R;                        // (slice, row block) pairs of a column tile
-    constexpr int kAhead = 4;                          // table operands in flight (6 and 8 are not faster)
+        constexpr int kAhead = 2;                          // table operands in flight (3, 4, 6 and 8 are not faster)
     static_assert(kAhead <= MT * kPer, "the first operands belong to one unit");
     u32x4 ring[kAhead];
     auto look_up = [&](const uint32_t s, const int v) __attribute__((always_inline)) {
@@ -239,7 +248,6 @@ __global__ __launch_bounds__(kWideWaves * kWave) void linear_wide_kernel(const W
 
     // One unit: all column tiles against this unit's R x 4 slices of the base (register set B).  u_next: the unit whose
     // operands are requested as registers fall free (the last unit requests itself again).
-    float4v dprev[R];
     // table operand of pair n (= 4 R ct + R v + r) of the unit
     auto look_up_pair = [&](const int n, const int u_next) __attribute__((always_inline)) {
         const int ct = n / kPer, v = n % kPer / R, r = n % R, f = ct * R + r;
@@ -259,7 +267,6 @@ __global__ __launch_bounds__(kWideWaves * kWave) void linear_wide_kernel(const W
         for (int n = 0; n < kAhead; ++n) look_up_pair(n, u_next);
 #pragma unroll
         for (int ct = 0; ct < MT; ++ct) {
-            float4v d[R];
             // the next tile's x into the other room, and the one after it requested
             unsigned char* const to = room + ((B * MT + ct + 1) & 1) * 4096;
             wide_wave_sync();
@@ -274,7 +281,9 @@ __global__ __launch_bounds__(kWideWaves * kWave) void linear_wide_kernel(const W
                 const half8 xv = __builtin_bit_cast(half8, xo[v]);
                 acc[r][ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, wr[B][r][v]), xv, acc[r][ct], 0, 0, 0);
                 const float4v zero = {0.f, 0.f, 0.f, 0.f};
-                d[r] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, ring[(ct * kPer + i) % kAhead]), xv, v == 0 ? zero : d[r], 0, 0, 0);
+                float4v& d = TILE_SUMS ? dtile[TILE_SUMS ? r : 0][TILE_SUMS ? ct : 0] : dsum[r][ct];
+                d = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, ring[(ct * kPer + i) % kAhead]), xv,
+                                                           TILE_SUMS && B == 0 && v == 0 ? zero : d, 0, 0, 0);
                 if (ct * kPer + i + kAhead < MT * kPer) look_up_pair(ct * kPer + i + kAhead, u_next);
                 if (r == R - 1) xo[v] = *(const u32x4*)(to + room_get(v));   // slice v has met its last row block
                 // the next unit's base, dealt over this unit's pairs
@@ -285,20 +294,17 @@ __global__ __launch_bounds__(kWideWaves * kWave) void linear_wide_kernel(const W
                     for (int q = (slot * kAll + kSlots - 1) / kSlots; q < ((slot + 1) * kAll + kSlots - 1) / kSlots; ++q)
                         wr[B ^ 1][q % R][q / R] = ld_w(u_next, q % R, q / R);
                 }
-                // the previous tile's +-1 sums have left the matrix cores: scale and add them
-                if (ct > 0 && i >= kPer - R) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[r][ct - 1][e] = __builtin_fmaf(alpha[ct - 1], dprev[r][e], acc[r][ct - 1][e]);
+                // the previous tile's +-1 sums have left the matrix cores: add them up
+                if constexpr (TILE_SUMS) {
+                    if (B == 1 && ct > 0 && i >= kPer - R) dsum[r][ct - 1] += dtile[r][ct - 1];
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
-#pragma unroll
-            for (int r = 0; r < R; ++r) dprev[r] = d[r];
         }
+        if constexpr (TILE_SUMS && B == 1) {
 #pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[r][MT - 1][e] = __builtin_fmaf(alpha[MT - 1], dprev[r][e], acc[r][MT - 1][e]);
+            for (int r = 0; r < R; ++r) dsum[r][MT - 1] += dtile[r][MT - 1];
+        }
         // a row-major base: fetched rows -> operands, through the room that the next tile is not in
         if constexpr (RM) {
             unsigned char* const to = room + ((B * MT + MT + 1) & 1) * 4096;
@@ -307,54 +313,108 @@ __global__ __launch_bounds__(kWideWaves * kWave) void linear_wide_kernel(const W
         }
     };
     {
-        int k = 0;
-        for (; k + 1 < u_count; k += 2) {
-            const int u = u_begin + k * u_step, u2 = u + u_step, u3 = k + 2 < u_count ? u2 + u_step : u2;
-            unit(std::integral_constant<int, 0>{}, u, u2);
-            unit(std::integral_constant<int, 1>{}, u2, u3);
+        int k = 0, u = u_begin;
+        for (; k + 1 < u_count; k += 2, u += u_step) {
+            unit(std::integral_constant<int, 0>{}, u, u + u_half);
+            unit(std::integral_constant<int, 1>{}, u + u_half, k + 2 < u_count ? u + u_step : u + u_half);
         }
-        if (k < u_count) unit(std::integral_constant<int, 0>{}, u_begin + k * u_step, u_begin + k * u_step);
+        if (k < u_count) {                             // the half k tile that ends a row
+            unit(std::integral_constant<int, 0>{}, u, u);
+            if constexpr (TILE_SUMS) {
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int ct = 0; ct < MT; ++ct) dsum[r][ct] += dtile[r][ct];
+            }
+        }
     }
 
-    // ---- the wavefronts' partial tiles: 4 .. 7 hand theirs to 0 .. 3, whose sums are added in order and written
+    // ---- the wavefronts' partial tiles are added and written: [r][ct][column][row], a set of them is kSet bytes
+    constexpr int kSet = R * MT * 1024;
+    const int lane_at = (c * 16 + 4 * g) * 4;
+    auto put = [&](const int at, auto value) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int ct = 0; ct < MT; ++ct) *(float4v*)(smem + at + lane_at + (r * MT + ct) * 1024) = value(r, ct);
+    };
+    auto scale_of = [&](const int ct) { return *(const float*)(smem + Lds::kAlpha + ct * 4); };
     __syncthreads();                                   // the table is no longer read
-    unsigned char* const mine = smem + (wave & 3) * (R * MT * 1024) + (c * 16 + 4 * g) * 4;   // [r][ct][column][row]
-    if (wave >= 4) {
+    bool any_inf = false;
+    if constexpr (RM) {
+        // base and +-1 sum apart: 4 .. 7 hand theirs to 0 .. 3, whose sums are added in order; the scale multiplies the finished one
+        const int mine = (wave & 3) * 2 * kSet;
+        if (wave >= 4) {
+            put(mine, [&](int r, int ct) { return acc[r][ct]; });
+            put(mine + kSet, [&](int r, int ct) { return dsum[r][ct]; });
+        }
+        __syncthreads();
+        if (wave < 4) {
+            put(mine, [&](int r, int ct) { return acc[r][ct] + *(const float4v*)(smem + mine + lane_at + (r * MT + ct) * 1024); });
+            put(mine + kSet, [&](int r, int ct) { return dsum[r][ct] + *(const float4v*)(smem + mine + kSet + lane_at + (r * MT + ct) * 1024); });
+        }
+    } else {
+        // as the decode kernel: every wavefront scales its own part, and the parts are added in order.  An infinite scale would
+        // make NaN of a part that is zero; it multiplies the finished sum instead (behind the parts, kSet bytes).
 #pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-            for (int ct = 0; ct < MT; ++ct) *(float4v*)(mine + (r * MT + ct) * 1024) = acc[r][ct];
-    }
-    __syncthreads();
-    if (wave < 4) {
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-            for (int ct = 0; ct < MT; ++ct) {
-                float4v* const p = (float4v*)(mine + (r * MT + ct) * 1024);
-                *p = acc[r][ct] + *p;
+        for (int ct = 0; ct < MT; ++ct) any_inf = any_inf || __builtin_isinf(scale_of(ct));
+        if (any_inf) {
+            put(wave * kSet, [&](int r, int ct) { return dsum[r][ct]; });
+            __syncthreads();
+            for (int idx = threadIdx.x; idx < R * MT * 256; idx += kWideWaves * kWave) {
+                float t = 0.f;
+                for (int w = 0; w < nw; ++w) t += *(const float*)(smem + w * kSet + idx * 4);
+                *(float*)(smem + 8 * kSet + idx * 4) = t;
             }
+            __syncthreads();
+        }
+        put(wave * kSet, [&](int r, int ct) {
+            const float al = scale_of(ct);
+            float4v p = acc[r][ct];
+            if (!__builtin_isinf(al)) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) p[e] = acc[r][ct][e] + al * dsum[r][ct][e];
+            }
+            return p;
+        });
     }
     __syncthreads();
-    const int n_el = n_tiles * 16 * (R * 16);
-    for (int idx = threadIdx.x; idx < n_el; idx += kWideWaves * kWave) {
-        const int row = idx % (R * 16), col = idx / (R * 16);   // consecutive threads: consecutive features of a token
+    const bool whole = (a.out & 3) == 0 && ((uintptr_t)a.y & 7) == 0;
+    for (int idx = threadIdx.x; idx < n_tiles * 16 * (R * 4); idx += kWideWaves * kWave) {   // four features of a token each
+        const int row = idx % (R * 4) * 4, col = idx / (R * 4);   // consecutive threads: consecutive features
         const int tok = *(const int*)(smem + Lds::kTok + col * 4);
         const int n = rb0 * kTileRows + row;
         if (tok < 0 || n >= a.out) continue;
-        const unsigned char* p = smem + ((row >> 4) * MT + (col >> 4)) * 1024 + ((col & 15) * 16 + (row & 15)) * 4;
-        float s = 0.f;
+        const unsigned char* const p = smem + ((row >> 4) * MT + (col >> 4)) * 1024 + ((col & 15) * 16 + (row & 15)) * 4;
+        const float al = scale_of(col >> 4);
+        float4v s = {0.f, 0.f, 0.f, 0.f}, t = {0.f, 0.f, 0.f, 0.f};
+        if constexpr (RM) {
 #pragma unroll
-        for (int w = 0; w < 4; ++w) s += *(const float*)(p + w * (R * MT * 1024));
-        const float al = *(const float*)(smem + Lds::kAlpha + (col >> 4) * 4);
-        if (__builtin_isinf(al) && __builtin_fabsf(s) < 1e15f) s = al * 0.f;   // infinity times a sum of zero
-        a.y[(int64_t)tok * a.out + n] = f2h_rne(s);
+            for (int w = 0; w < 4; ++w) {
+                s += *(const float4v*)(p + 2 * w * kSet);
+                t += *(const float4v*)(p + (2 * w + 1) * kSet);
+            }
+        } else {
+            for (int w = 0; w < nw; ++w) s += *(const float4v*)(p + w * kSet);
+            if (any_inf) t = *(const float4v*)(p + 8 * kSet);
+        }
+        uint16_t h[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) h[e] = f2h_rne(RM || (any_inf && __builtin_isinf(al)) ? s[e] + al * t[e] : s[e]);
+        uint16_t* const y = a.y + (int64_t)tok * a.out + n;
+        if (whole) {
+            *(u32x2*)y = u32x2{(uint32_t)h[0] | (uint32_t)h[1] << 16, (uint32_t)h[2] | (uint32_t)h[3] << 16};
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (n + e < a.out) y[e] = h[e];
+        }
     }
 }
 
-template <int R, int MT, bool RM>
+template <int R, int MT, bool RM, bool TILE_SUMS>
 static hipError_t launch_wide_inst(const WideArgs& args, hipStream_t st) {
-    auto kernel = linear_wide_kernel<R, MT, RM>;
+    auto kernel = linear_wide_kernel<R, MT, RM, TILE_SUMS>;
     constexpr int lds = WideLds<R, MT>::kTotal;
     static_assert(lds <= 160 * 1024, "LDS budget");
     static PerDeviceOnce once;
@@ -374,22 +434,30 @@ static hipError_t launch_wide_inst(const WideArgs& args, hipStream_t st) {
 
 // args.n_tiles column tiles (1 .. kWideMaxTiles) in chunks of args.tiles_per_chunk (1 .. kWideMaxChunk), R row blocks per workgroup
 hipError_t launch_linear_wide(const WideArgs& args, int R, bool rowmajor, hipStream_t st) {
-    if (args.n_tiles < 1 || args.n_tiles > kWideMaxTiles || args.tiles_per_chunk < 1 || args.tiles_per_chunk > kWideMaxChunk || args.in < 128 ||
+    if (args.n_tiles < 1 || args.n_tiles > kWideMaxTiles || args.tiles_per_chunk < 1 || args.in < 128 ||
         args.in % kWideUnit != 0 || args.units != args.in / kWideUnit || args.out < 1 || (R != 1 && R != 2) ||
         (rowmajor && !args.packed_by_tenant))
         return hipErrorInvalidValue;
-    auto go = [&](auto r_tag, auto rm_tag) {
-        constexpr int RR = decltype(r_tag)::value;
-        constexpr bool M = decltype(rm_tag)::value;
-        if (args.tiles_per_chunk <= 2) return launch_wide_inst<RR, 2, M>(args, st);
-        if (args.tiles_per_chunk <= 4) return launch_wide_inst<RR, 4, M>(args, st);
-        if (args.tiles_per_chunk <= 6) return launch_wide_inst<RR, 6, M>(args, st);
-        return launch_wide_inst<RR, 8, M>(args, st);
+    const int n = args.tiles_per_chunk;
+    if (n < 1 || n > wide_max_chunk(R, args.KT, rowmajor)) return hipErrorInvalidValue;
+    // tiled: the +-1 sums of k tiles are added up apart, unless no wavefront has more than one
+    auto go = [&](auto r_tag, auto mt_tag) {
+        constexpr int RR = decltype(r_tag)::value, M = decltype(mt_tag)::value;
+        if (rowmajor) return launch_wide_inst<RR, M, true, false>(args, st);
+        if constexpr (RR == 2 && M == 6) return launch_wide_inst<RR, M, false, false>(args, st);
+        else return launch_wide_inst<RR, M, false, true>(args, st);
     };
-    using One = std::integral_constant<int, 1>;
-    using Two = std::integral_constant<int, 2>;
-    if (rowmajor) return R == 1 ? go(One{}, std::true_type{}) : go(Two{}, std::true_type{});
-    return R == 1 ? go(One{}, std::false_type{}) : go(Two{}, std::false_type{});
+    auto go_r = [&](auto r_tag) {
+        if (n <= 2) return go(r_tag, std::integral_constant<int, 2>{});
+        if (n <= 4) return go(r_tag, std::integral_constant<int, 4>{});
+        if (n <= 6) return go(r_tag, std::integral_constant<int, 6>{});
+        if constexpr (decltype(r_tag)::value == 1) {
+            if (n <= 8) return go(r_tag, std::integral_constant<int, 8>{});
+            return go(r_tag, std::integral_constant<int, 10>{});
+        }
+        return hipErrorInvalidValue;
+    };
+    return R == 1 ? go_r(std::integral_constant<int, 1>{}) : go_r(std::integral_constant<int, 2>{});
 }
 
 }  // namespace bd

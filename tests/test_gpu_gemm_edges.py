@@ -113,8 +113,8 @@ def test_wide_batches(case, order):
 
 # The kernel of 16-column tiles, asked for by number, in every split it has: one and two row blocks per workgroup, every number
 # of column tiles, the last chunk partly filled; `out` that ends inside a row block and inside a pair of them; units of `in`
-# fewer than the eight wavefronts, as many, and an odd number of them.
-WIDE_SPLITS = [16 * r + n for r in (1, 2) for n in range(1, 9)]
+# fewer than the eight wavefronts, as many, and an odd number of them; k tiles likewise.
+WIDE_SPLITS = [16 + n for n in range(1, 11)] + [32 + n for n in range(1, 7)]
 
 
 @pytest.mark.parametrize("variant", [10] + WIDE_SPLITS)
@@ -123,6 +123,8 @@ WIDE_SPLITS = [16 * r + n for r in (1, 2) for n in range(1, 9)]
     (16, 128, [17]),                             # 1 row block, 1 unit, 2 column tiles
     (373, 2176, [9, 31, 2, 5]),                  # 24 row blocks, 17 units
     (64, 640, [9] * 40 + [16] * 30),             # 70 column tiles: two launches
+    (24, 2048, [40, 7]),                         # eight k tiles: one per wavefront
+    (35, 4480, [12, 18, 30]),                    # 17.5 k tiles
 ])
 def test_wide_every_split(out, inn, counts, variant):
     t = Tensors(out, inn, tokens_of(counts, "shuffled"), len(counts), seed=variant)
@@ -131,8 +133,68 @@ def test_wide_every_split(out, inn, counts, variant):
     y = bd.linear_multitenant(t.x, t.w, bd.TenantTable(t.packed, t.alpha), t.tok, y=nan(), variant=variant)
     t.check(y, what=what + " row-major")
     tiled = bd.TiledTenantTable([bd.tile_signs(p, out, inn) if n else None for p, n in zip(t.packed, counts)], t.alpha)
-    y = bd.linear_multitenant_tiled(t.x, bd.tile_base(t.w), out, tiled, t.tok, y=nan(), variant=variant)
+    wt = bd.tile_base(t.w)
+    if variant >= 37 and (inn + 255) // 256 not in (1, 2, 4, 8):   # no room for the sums of three kinds
+        with pytest.raises(bd.BitDeltaError):
+            bd.linear_multitenant_tiled(t.x, wt, out, tiled, t.tok, variant=variant)
+        return
+    y = bd.linear_multitenant_tiled(t.x, wt, out, tiled, t.tok, y=nan(), variant=variant)
     t.check(y, what=what + " tiled")
+    # on the serving layout: the decode launches' bits, at scales of a fine-tune and where alpha times a part of the row's +-1 sum
+    # is much larger than the result
+    assert torch.equal(y, bd.linear_multitenant_tiled(t.x, wt, out, tiled, t.tok, variant=2)), what
+    large = bd.TiledTenantTable(tiled.tiled, t.alpha * 2e4)
+    assert torch.equal(*(bd.linear_multitenant_tiled(t.x, wt, out, large, t.tok, variant=v) for v in (variant, 2))), what
+
+
+def test_a_token_on_the_serving_layout_does_not_depend_on_its_batch():
+    """Batches of 1, 2, 31, 90 and 200 tokens and a group of two matrices: the same bits for the same token."""
+    out, inn, counts = 528, 1536, [3, 40, 9, 1, 17, 0, 60, 20, 50]
+    t = Tensors(out, inn, tokens_of(counts, "shuffled"), len(counts), seed=5)
+    tiled = bd.TiledTenantTable([bd.tile_signs(p, out, inn) for p in t.packed], t.alpha)
+    wt = bd.tile_base(t.w)
+    y = bd.linear_multitenant_tiled(t.x, wt, out, tiled, t.tok)
+    for first, n in ((0, 1), (7, 2), (100, 31), (60, 90)):
+        part = bd.linear_multitenant_tiled(t.x[first:first + n].contiguous(), wt, out, tiled, t.tok[first:first + n])
+        assert torch.equal(part, y[first:first + n]), (first, n)
+    group = bd.TiledGroup([wt, wt], [out, out], [tiled, tiled])
+    for part in bd.linear_multitenant_tiled_group(t.x, group, t.tok):
+        assert torch.equal(part, y), "group"
+
+
+@pytest.mark.parametrize("variant", [10, 18, 24, 26, 34, 38])
+def test_wide_sums_that_cancel(variant):
+    """Whole numbers in x, so that +-1 sums are exact, and about one in fifty of them zero although no part of the row is.  A large
+    scale must not leave the rounding of its products with the parts (bound of `check`: rounding of the base product and
+    one of alpha times the finished sum); an infinite one gives the sign of the sum, and NaN where it is zero or the base
+    product is the opposite infinity."""
+    out, inn, counts = 200, 2048, [9, 20, 33]
+    t = Tensors(out, inn, tokens_of(counts), 3, seed=41)
+    t.x = torch.randint(-1, 2, t.x.shape, device=DEV, generator=torch.Generator(device=DEV).manual_seed(3)).half()
+    t.alpha = torch.tensor([65504.0, 0.25, 60000.0], device=DEV)
+    s = torch.empty((len(t.tok), out), dtype=torch.float64, device=DEV)
+    for e in set(t.tok):
+        rows = torch.tensor([i for i, k in enumerate(t.tok) if k == e], device=DEV)
+        s[rows] = t.x[rows].double() @ expand(t.packed[e], inn).t()
+    assert (s == 0).sum() > 100
+    base, a = t.x.double() @ t.w.double().t(), t.alpha[torch.tensor(t.tok, device=DEV)].double()[:, None]
+    y = bd.linear_multitenant(t.x, t.w, bd.TenantTable(t.packed, t.alpha), t.tok, variant=variant)
+    exact = base + a * s
+    bound = 2.0**-11 * exact.abs() + 2.0**-25 + inn**0.5 * 2.0**-23 * (t.x.double().abs() @ t.w.double().abs().t()) + 2.0**-23 * (a * s).abs()
+    small = exact.abs() < 65000                                  # beyond: fp16 infinity
+    assert ((y.double() - exact).abs() <= bound)[small].all()
+
+    alpha = torch.tensor([float("inf"), 0.002, float("-inf")], device=DEV)
+    t.w[7, 30], t.w[9, 1500] = float("inf"), float("-inf")
+    base = t.x.double() @ t.w.double().t()
+    want = base + alpha[torch.tensor(t.tok, device=DEV)].double()[:, None] * s
+    rows = torch.tensor([i for i, k in enumerate(t.tok) if k != 1], device=DEV)
+    tiled = bd.TiledTenantTable([bd.tile_signs(p, out, inn) for p in t.packed], alpha)
+    for y in (bd.linear_multitenant(t.x, t.w, bd.TenantTable(t.packed, alpha), t.tok, variant=variant),
+              bd.linear_multitenant_tiled(t.x, bd.tile_base(t.w), out, tiled, t.tok, variant=variant)):
+        got, exp = y[rows].double(), want[rows]
+        assert torch.equal(torch.isnan(got), torch.isnan(exp))
+        assert torch.equal(torch.nan_to_num(got, nan=0.0), torch.nan_to_num(exp, nan=0.0))
 
 
 def test_wide_non_finite_values():

@@ -99,7 +99,7 @@ def test_wide_variant_argument_errors(bd):
     rm = lambda v, inn=128, out=16, T=1, tok=_tok(0): L.bd_linear_multitenant_variant(A, 2 * A, 3 * A, 4 * A, tok, 5 * A, T, out, inn, 1, 0, 0, 0, v)
     ti = lambda v, inn=128, out=16, T=1, tok=_tok(0): L.bd_linear_multitenant_tiled_variant(A, 2 * A, ptrs, 4 * A, tok, 5 * A, T, out, inn, 1, 0, v)
     for f in (rm, ti):
-        for v in (3, 11, 16, 16 + 15, 32, 32 + 15, 48 + 1, 64 + 1, -1, 99):
+        for v in (3, 11, 16, 16 + 11, 16 + 15, 32, 32 + 7, 48 + 1, 64 + 1, -1, 99):
             assert f(v) == 7, v
         for v in (10, 16 + 1, 32 + 1):
             assert f(v, inn=96) == 7, v
