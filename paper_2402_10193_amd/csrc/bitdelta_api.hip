@@ -123,26 +123,39 @@ size_t tiled_gemm_workspace_bytes(int64_t T, int32_t n_tenants) {
     return tables + (((size_t)n_tenants * 8 + 8 + 255) & ~(size_t)255);
 }
 
+// Token ids by tenant, tokens of one tenant in their order.  (Tenant ids have been checked.)
+std::vector<int32_t> order_by_tenant(const int32_t* tenant_of_token, int64_t T, int32_t n_tenants) {
+    std::vector<int32_t> order((size_t)T);
+    if (std::is_sorted(tenant_of_token, tenant_of_token + T)) {
+        for (int64_t i = 0; i < T; ++i) order[(size_t)i] = (int32_t)i;
+    } else if (n_tenants <= 8 * T) {
+        std::vector<int32_t> next((size_t)n_tenants + 1, 0);
+        for (int64_t i = 0; i < T; ++i) ++next[(size_t)tenant_of_token[i] + 1];
+        for (int32_t t = 0; t < n_tenants; ++t) next[(size_t)t + 1] += next[(size_t)t];
+        for (int64_t i = 0; i < T; ++i) order[(size_t)next[(size_t)tenant_of_token[i]]++] = (int32_t)i;
+    } else {   // a table of counts would be larger than the batch
+        for (int64_t i = 0; i < T; ++i) order[(size_t)i] = (int32_t)i;
+        std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return tenant_of_token[a] < tenant_of_token[b]; });
+    }
+    return order;
+}
+
 int cus_or_256() {
     int cus = 256;
     if (bd::device_cu_count(&cus) != hipSuccess || cus < 1) cus = 256;
     return cus;
 }
 
-// Sorts the tokens by tenant (stable), cuts them into tiles of 128 rows (merged: 256) that never mix tenants, writes
+// Cuts the tokens (`order`: sorted by tenant) into tiles of 128 rows (merged: 256) that never mix tenants, writes
 // the two tables into the workspace (through kernel arguments: no host-to-device copy call) and runs the GEMM.
 // k_planes = 0: one plane per tenant; 1..8: tables indexed by tenant * k_planes + plane.  wscale: the 8-bit base's row
-// scales (w is then the int8 tensor).  Both go through the 128 x 128 tiles (big_waves = 0).
+// scales (w is then the int8 tensor).  big_waves = 0: the 128 x 128 tiles.
 hipError_t run_prefill(const uint16_t* x, const void* w, const uint32_t* const* packed_by_tenant,
-                       const float* alpha_by_tenant, const int32_t* tenant_of_token, uint16_t* y, int64_t T, int64_t out,
+                       const float* alpha_by_tenant, const int32_t* tenant_of_token, const std::vector<int32_t>& order, uint16_t* y, int64_t T, int64_t out,
                        int64_t in, void* workspace, hipStream_t st, int big_waves, bool halve_last_round,
                        int k_planes = 0, const float* wscale = nullptr, bool merged = false,
                        const uint32_t* const* tiled_by_tenant_host = nullptr, int32_t n_tenants = 0) {
     const int64_t tile_rows = merged ? bd::kPrefillMergedTile : bd::kPrefillTile;
-    std::vector<int32_t> order((size_t)T);
-    for (int64_t i = 0; i < T; ++i) order[(size_t)i] = (int32_t)i;
-    std::stable_sort(order.begin(), order.end(),
-                     [&](int32_t a, int32_t b) { return tenant_of_token[a] < tenant_of_token[b]; });
     // The tiles: (first token of the sorted order, rows).  Where they fill the compute units more than once, those with more than
     // half a tile of rows run first and the launch ends with short ones (with an eighth of either kind for every XCD: 1100 tokens of
     // 13 tenants on 11008 x 4096 264 -> 232 us, as one product 269 -> 229; 3000 of 12 on 4096 x 4096 189 -> 162).  Tiles that all run
@@ -232,26 +245,22 @@ hipError_t run_prefill(const uint16_t* x, const void* w, const uint32_t* const* 
 
 // ---- batches between a decode launch and a GEMM: linear_wide.hip ----
 
-// Column tiles of one call: tokens sorted by tenant (stable), each tenant cut into tiles of 16 columns.
+// Column tiles of one call: each tenant's tokens cut into tiles of 16 columns.
 struct WideTiles {
     std::vector<int32_t> tenant;               // per tile
     std::vector<uint16_t> token;               // 16 per tile, kWideNoToken where empty
 };
-WideTiles wide_tiles(const int32_t* tenant_of_token, int64_t T) {
-    std::vector<int32_t> order((size_t)T);
-    for (int64_t i = 0; i < T; ++i) order[(size_t)i] = (int32_t)i;
-    std::stable_sort(order.begin(), order.end(),
-                     [&](int32_t a, int32_t b) { return tenant_of_token[a] < tenant_of_token[b]; });
+WideTiles wide_tiles(const int32_t* tenant_of_token, const std::vector<int32_t>& order) {
     WideTiles t;
     int in_tile = 16;
-    for (int64_t i = 0; i < T; ++i) {
-        const int32_t tenant = tenant_of_token[order[(size_t)i]];
+    for (size_t i = 0; i < order.size(); ++i) {
+        const int32_t tenant = tenant_of_token[order[i]];
         if (in_tile == 16 || tenant != t.tenant.back()) {
             t.tenant.push_back(tenant);
             t.token.insert(t.token.end(), 16, (uint16_t)bd::kWideNoToken);
             in_tile = 0;
         }
-        t.token[(t.tenant.size() - 1) * 16 + (size_t)in_tile++] = (uint16_t)order[(size_t)i];
+        t.token[(t.tenant.size() - 1) * 16 + (size_t)in_tile++] = (uint16_t)order[i];
     }
     return t;
 }
@@ -358,14 +367,13 @@ struct BatchShape {
     int64_t tiles32 = 0, tiles64 = 0, tiles128 = 0;      // GEMM tiles by the rows they run
     std::vector<std::pair<int, int>> launches;           // of 32 tokens: (tokens, distinct tenants)
 };
-BatchShape batch_shape(const int32_t* tenant_of_token, int64_t T) {
-    std::vector<int32_t> sorted(tenant_of_token, tenant_of_token + T);
-    if (!std::is_sorted(sorted.begin(), sorted.end())) std::sort(sorted.begin(), sorted.end());
+BatchShape batch_shape(const int32_t* tenant_of_token, const std::vector<int32_t>& order) {
+    const int64_t T = (int64_t)order.size();
     BatchShape s;
     int in_launch = 0, distinct = 0;
     for (int64_t i = 0; i < T;) {
         int64_t e = i;
-        while (e < T && sorted[(size_t)e] == sorted[(size_t)i]) ++e;
+        while (e < T && tenant_of_token[order[(size_t)e]] == tenant_of_token[order[(size_t)i]]) ++e;
         int64_t n = e - i;
         i = e;
         ++s.active;
@@ -585,13 +593,16 @@ bd_status bd_linear_multitenant_variant(const uint16_t* x_f16, const uint16_t* w
     if (variant != 0 && variant != kVariantRowWave && variant != kVariantRowMajorMfma && !prefill_variant && wide_split < 0)
         return BD_ERR_UNSUPPORTED;
     if (T == 0 || out == 0) return BD_OK;
+    std::vector<int32_t> order;
     auto wide = [&](const int split) {
-        return run_wide(wide_tiles(tenant_of_token, T), x_f16, w_base_f16, packed_by_tenant, nullptr, alpha_by_tenant, y_f16, out, in,
+        return run_wide(wide_tiles(tenant_of_token, order), x_f16, w_base_f16, packed_by_tenant, nullptr, alpha_by_tenant, y_f16, out, in,
                         (hipStream_t)stream, split) == hipSuccess
                    ? BD_OK
                    : BD_ERR_DEVICE;
     };
-    if (wide_split >= 0) return wide_fits(T, out, in) ? wide(wide_split) : BD_ERR_UNSUPPORTED;
+    if (wide_split >= 0 && !wide_fits(T, out, in)) return BD_ERR_UNSUPPORTED;
+    if (T > kMaxDecodeTokens || wide_split >= 0) order = order_by_tenant(tenant_of_token, T, n_tenants);
+    if (wide_split >= 0) return wide(wide_split);
     // 128-bit sign loads need whole, aligned 4-word groups; 32-bit lane offsets need tensors below 4 GiB
     const bool mfma_ok = (in % 128 == 0) && in > 0 && (uint64_t)out * (uint64_t)in * 2 < ((uint64_t)1 << 32) &&
                          (uint64_t)T * (uint64_t)in * 2 < ((uint64_t)1 << 32);
@@ -609,7 +620,7 @@ bd_status bd_linear_multitenant_variant(const uint16_t* x_f16, const uint16_t* w
     const bool big_default = out >= 256 && bd::prefill_big_fits(T, out, in);
     bool gemm_pays = prefill_variant;
     if (variant == 0 && T > kMaxDecodeTokens && in > 0) {   // the library's choice, by estimated time
-        const BatchShape shape = batch_shape(tenant_of_token, T);
+        const BatchShape shape = batch_shape(tenant_of_token, order);
         const int cus = cus_or_256();
         const double by_decode = decode_us(shape, (double)out * (double)in, false, mfma_ok);
         const double by_gemm = can_prefill ? gemm_us(shape, out, in, big_default, cus) : 1e30;
@@ -624,7 +635,7 @@ bd_status bd_linear_multitenant_variant(const uint16_t* x_f16, const uint16_t* w
         if (variant == kVariantPrefillBig || variant == kVariantPrefillBigWhole || variant == kVariantPrefillMerged ||
             (variant == 0 && big_default))
             big_waves = 4;
-        return run_prefill(x_f16, w_base_f16, packed_by_tenant, alpha_by_tenant, tenant_of_token, y_f16, T, out, in,
+        return run_prefill(x_f16, w_base_f16, packed_by_tenant, alpha_by_tenant, tenant_of_token, order, y_f16, T, out, in,
                            workspace, hs, big_waves, variant != kVariantPrefillBigWhole, 0, nullptr, merged_variant) == hipSuccess
                    ? BD_OK
                    : BD_ERR_DEVICE;
@@ -775,13 +786,14 @@ bd_status tiled_linear_impl(int32_t n_mats, const uint16_t* x_f16, const uint16_
     }
     // Serving layout, one plane, more tokens than a launch takes: the wide kernel, a launch per matrix, where its estimate is
     // below that of the decode launches, which take the matrices of a group together.
+    const std::vector<int32_t> order = order_by_tenant(tenant_of_token, T, n_tenants);
     const int wide_split = wide_split_of_variant(variant, in, false);
     if (wide_split >= 0) {
         for (int m = 0; m < n_mats; ++m)
             if (out[m] > 0 && !wide_fits(T, out[m], in)) return BD_ERR_UNSUPPORTED;
     }
     if (wide_split >= 0 || (!rm && !q8 && k == 1 && variant == 0 && T > bd::kMaxDecodeTokens)) {
-        const BatchShape shape = batch_shape(tenant_of_token, T);
+        const BatchShape shape = batch_shape(tenant_of_token, order);
         const int cus = cus_or_256();
         bool fits = true;
         double wide = 0.0, elems = 0.0;
@@ -793,7 +805,7 @@ bd_status tiled_linear_impl(int32_t n_mats, const uint16_t* x_f16, const uint16_
             elems += (double)out[m] * (double)in;
         }
         if (wide_split >= 0 || (fits && kWideMargin * wide < decode_us(shape, elems, true, true))) {
-            const WideTiles tiles = wide_tiles(tenant_of_token, T);
+            const WideTiles tiles = wide_tiles(tenant_of_token, order);
             for (int m = 0; m < n_mats; ++m)
                 if (out[m] > 0 && run_wide(tiles, x_f16, w_tiled[m], nullptr, tiled_by_mat_tenant + (size_t)m * n_tenants, alpha_by_mat[m],
                                            y_f16[m], out[m], in, (hipStream_t)stream, std::max(wide_split, 0)) != hipSuccess)
@@ -806,9 +818,6 @@ bd_status tiled_linear_impl(int32_t n_mats, const uint16_t* x_f16, const uint16_
     // its delta is streamed as few times as possible; the kernel finds the rows of x and y through the token ids.
     const int per_tile = bd::kTiledMaxTokens / k;
     const int per_launch = per_tile * bd::kTiledMaxCt;
-    std::vector<int32_t> order((size_t)T);
-    for (int64_t i = 0; i < T; ++i) order[(size_t)i] = (int32_t)i;
-    std::stable_sort(order.begin(), order.end(), [&](int32_t p, int32_t q) { return tenant_of_token[p] < tenant_of_token[q]; });
     for (int64_t t0 = 0; t0 < T; t0 += per_launch) {
         const int n = (int)std::min<int64_t>(per_launch, T - t0);
         bd::TiledArgs a;
@@ -993,7 +1002,7 @@ bd_status bd_linear_multitenant_tiled_gemm(const uint16_t* x_f16, const uint16_t
     if (in == 0 || !bd::prefill_big_fits(T, out, in)) return BD_ERR_UNSUPPORTED;   // whole k steps of 64
     const size_t need = tiled_gemm_workspace_bytes(T, n_tenants);
     if (!workspace || workspace_bytes < need || misaligned(workspace, 256)) return BD_ERR_WORKSPACE;
-    return run_prefill(x_f16, w_tiled, nullptr, alpha_by_tenant, tenant_of_token, y_f16, T, out, in, workspace, (hipStream_t)stream, 4,
+    return run_prefill(x_f16, w_tiled, nullptr, alpha_by_tenant, tenant_of_token, order_by_tenant(tenant_of_token, T, n_tenants), y_f16, T, out, in, workspace, (hipStream_t)stream, 4,
                        true, 0, nullptr, one_product != 0, tiled_by_tenant, n_tenants) == hipSuccess
                ? BD_OK
                : BD_ERR_DEVICE;
@@ -1037,7 +1046,7 @@ static bd_status gemm_entry(const uint16_t* x_f16, const void* w, size_t w_bytes
     // The 8-bit base: 128 x 256 tiles where whole 64-wide steps and a full tile's width of output rows are there, as for fp16.
     // (k planes stay on the 128 x 128 tiles: their sums are formed in fp16 in LDS, which the large tile has no room for.)
     const bool big = wscale && k_planes == 0 && out >= 256 && bd::prefill_big_fits(T, out, in);
-    return run_prefill(x_f16, w, packed_by_tenant, alpha_by_tenant, tenant_of_token, y_f16, T, out, in, workspace,
+    return run_prefill(x_f16, w, packed_by_tenant, alpha_by_tenant, tenant_of_token, order_by_tenant(tenant_of_token, T, n_tenants), y_f16, T, out, in, workspace,
                        (hipStream_t)stream, big ? 4 : 0, big, k_planes, wscale) == hipSuccess
                ? BD_OK
                : BD_ERR_DEVICE;

@@ -228,6 +228,29 @@ def test_wide_non_finite_values():
         assert torch.equal(got[want != 0], torch.where(want[want != 0] > 0, float("inf"), float("-inf")).half())
 
 
+@pytest.mark.parametrize("n_tenants", [7, 8 * 40, 8 * 40 + 1, 3000])
+def test_tokens_grouped_whatever_the_tenant_ids(n_tenants):
+    """Ids close together and far apart (grouped through a table of counts, or by sorting where that would be larger than the
+    batch): the bits of the same batch with the ids 0..6."""
+    out, inn, ids = 48, 640, sorted({0, 1, 2, n_tenants // 2, n_tenants - 3, n_tenants - 2, n_tenants - 1})
+    close = tokens_of([9, 3, 11, 1, 5, 8, 3][:len(ids)], "shuffled")
+    t = Tensors(out, inn, close, len(ids))
+    packed = [t.packed[0]] * n_tenants
+    alpha = torch.zeros(n_tenants, device=DEV)
+    for i, e in enumerate(ids):
+        packed[e], alpha[e] = t.packed[i], t.alpha[i]
+    far = [ids[e] for e in close]
+    a, b = bd.TenantTable(t.packed, t.alpha), bd.TenantTable(packed, alpha)
+    for variant in (0, 2, 4, 5, 10):
+        assert torch.equal(*(bd.linear_multitenant(t.x, t.w, table, tok, variant=variant) for table, tok in ((a, close), (b, far)))), variant
+    st = [bd.tile_signs(p, out, inn) for p in t.packed]
+    a = bd.TiledTenantTable(st, t.alpha)
+    b = bd.TiledTenantTable([st[ids.index(e)] if e in ids else None for e in range(n_tenants)], alpha)
+    wt = bd.tile_base(t.w)
+    assert torch.equal(*(bd.linear_multitenant_tiled(t.x, wt, out, table, tok) for table, tok in ((a, close), (b, far))))
+    assert torch.equal(*(bd.linear_multitenant_tiled_gemm(t.x, wt, out, table, tok) for table, tok in ((a, close), (b, far))))
+
+
 def test_gemm_more_tiles_than_compute_units():
     """Over 256 tiles of all heights (32, 64, 128 rows; 64, 128, 256 of the one-product form), long ones first, an eighth of either
     kind per XCD: every output element is written, by its own tile."""
