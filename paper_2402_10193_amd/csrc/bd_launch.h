@@ -77,9 +77,11 @@ hipError_t launch_linear_prefill_merged(const uint16_t* x, const uint16_t* w, co
 // columns.  Everything travels in the kernel arguments.
 constexpr int kWideWaves = 8;              // wavefronts of a workgroup, which split `in`
 constexpr int kWideMaxTiles = 64;          // column tiles of one launch
+// wavefronts that the KT k tiles of 256 of a row are dealt to on the serving layout, as in the decode kernel
+constexpr int wide_k_waves(int KT) { return KT >= 8 ? 8 : KT >= 4 ? 4 : KT >= 2 ? 2 : 1; }
 // column tiles of a workgroup of R = 1 or 2 row blocks at most: what its accumulators leave registers for (two sets of them; three on the
 // serving layout where a wavefront has more than one of the KT k tiles of 256: unless KT is 1, 2, 4 or 8)
-constexpr int wide_max_chunk(int R, int KT, bool rowmajor) { return R == 1 ? 10 : rowmajor || (KT <= kWideWaves && (KT & (KT - 1)) == 0) ? 6 : 4; }
+constexpr int wide_max_chunk(int R, int KT, bool rowmajor) { return R == 1 ? 10 : rowmajor || KT == wide_k_waves(KT) ? 6 : 4; }
 constexpr uint32_t kWideNoToken = 0xFFFFu; // an empty column (token ids are below 65535)
 struct WideArgs {
     const uint16_t* x;                          // [T, in]

@@ -265,19 +265,23 @@ WideTiles wide_tiles(const int32_t* tenant_of_token, const std::vector<int32_t>&
     return t;
 }
 
-// Units (128 of `in`) that the time of a workgroup goes by: its 8 wavefronts sit two to a SIMD and issue in turn, so it lies
-// between the longest wavefront and half the longest pair (a third and two thirds, fitted).
-double wide_units(int64_t in, bool rowmajor) {
-    const int units = (int)(in / 128), KT = (int)bd::tiled_k_tiles(in);
-    int nw = bd::kWideWaves, longest = 0, pair = 0, u[bd::kWideWaves] = {};
-    while (!rowmajor && nw > 1 && nw > KT) nw >>= 1;
-    for (int w = 0; w < nw; ++w)
-        u[w] = rowmajor ? (units - w + bd::kWideWaves - 1) / bd::kWideWaves : std::min(2 * ((w + 1) * KT / nw), units) - 2 * (w * KT / nw);
+// What the time of eight wavefronts goes by that have u[w] steps each, two to a SIMD, issuing in turn: between the longest
+// wavefront and half the longest pair (a third and two thirds, fitted).
+double steps_of_waves(const int (&u)[8]) {
+    int longest = 0, pair = 0;
     for (int w = 0; w < 4; ++w) {
         longest = std::max({longest, u[w], u[w + 4]});
         pair = std::max(pair, u[w] + u[w + 4]);
     }
     return (longest + pair) / 3.0;
+}
+// Units (128 of `in`) of the wavefronts of a workgroup of the wide kernel
+double wide_units(int64_t in, bool rowmajor) {
+    const int units = (int)(in / 128), KT = (int)bd::tiled_k_tiles(in), nw = bd::wide_k_waves(KT), subs = 8 / nw;
+    int u[8];
+    for (int w = 0; w < 8; ++w)
+        u[w] = rowmajor ? (units - w + 7) / 8 : std::min(2 * ((w / subs + 1) * KT / nw), units) - 2 * (w / subs * KT / nw);
+    return steps_of_waves(u);
 }
 
 // How a launch of n column tiles is cut: row blocks per workgroup (1 or 2), column tiles per workgroup, and its estimated
@@ -293,7 +297,7 @@ WidePlan wide_plan(int n, int64_t out, int64_t in, int cus, bool rowmajor) {
     const int64_t rb = bd::tiled_row_blocks(out), per_xcd = std::max(1, cus / 8);
     const double units = wide_units(in, rowmajor);
     for (int R = 1; R <= 2; ++R) {
-        const int64_t groups = (rb + R - 1) / R;
+        const int64_t per_group = R * (rowmajor ? 1 : 8 / bd::wide_k_waves((int)bd::tiled_k_tiles(in))), groups = (rb + per_group - 1) / per_group;
         for (int run = 2; run <= bd::wide_max_chunk(R, (int)bd::tiled_k_tiles(in), rowmajor); run += 2) {   // instantiated for even numbers
             const int chunks = (n + run - 1) / run;   // all but the last one full
             const int64_t rounds = ((groups + 7) / 8 * chunks + per_xcd - 1) / per_xcd;

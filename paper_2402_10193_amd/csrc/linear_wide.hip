@@ -25,7 +25,8 @@
 //   Row-major: the wavefronts' sums are added, base and +-1 apart, and alpha multiplies the finished one, as in the GEMM.
 //   Tiled: the arithmetic of the decode kernel, addition for addition (its k tiles per wavefront, the +-1 sum of a k tile from
 //   zero and then added to those before it, the wavefronts' scaled parts in order), so that a token's result does not depend on
-//   which of the two the batch was given to.
+//   which of the two the batch was given to.  Fewer k tiles than wavefronts: the workgroup takes 2, 4 or 8 times the row blocks
+//   (237 tokens of 13 tenants on 1676 x 768, where the decode kernel deals three k tiles to two wavefronts: 11 us, 21 with six idle).
 // Registers (two wavefronts per SIMD, 256 each): accumulators 8 R MT, tiled 12 R MT where wavefronts have several k tiles; the base
 // of two units 32 R, x 32, two table operands 8, the signs of a unit R MT.  That sets the most column tiles (wide_max_chunk).
 // Signs become operands through the byte table of the decode kernel (256 entries x 16 copies x 16 B in LDS, one
@@ -79,9 +80,14 @@ __global__ __launch_bounds__(kWideWaves * kWave) void linear_wide_kernel(const W
     // follow each other on one XCD, so that its L2 serves the base to all of them.
     const int n_chunks = (a.n_tiles + a.tiles_per_chunk - 1) / a.tiles_per_chunk;
     const int per_xcd = (int)blockIdx.x >> 3;
-    const int rb0 = ((per_xcd / n_chunks) * 8 + ((int)blockIdx.x & 7)) * R;
+    // Tiled: the k tiles are dealt to nw wavefronts (wide_k_waves); where that is fewer than eight, the workgroup takes `subs` times as
+    // many row blocks and the wavefronts of a SIMD are on different parts of `in`.
+    const int nw = RM ? kWideWaves : wide_k_waves(a.KT), subs = RM ? 1 : kWideWaves / nw;
+    const int k_part = wave / subs, sub = wave % subs;
+    const int rb_first = ((per_xcd / n_chunks) * 8 + ((int)blockIdx.x & 7)) * (R * subs);
+    const int rb0 = rb_first + sub * R;
     const int tile0 = (per_xcd % n_chunks) * a.tiles_per_chunk;
-    if (rb0 >= a.row_blocks) return;                  // the grid is padded to whole groups of 8
+    if (rb_first >= a.row_blocks) return;             // the grid is padded to whole groups of 8
     const int n_tiles = min(a.tiles_per_chunk, a.n_tiles - tile0);   // 1 .. MT; the surplus repeats the last one, unstored
     const uint32_t row_bytes = (uint32_t)a.in * 2u;
 
@@ -113,16 +119,14 @@ __global__ __launch_bounds__(kWideWaves * kWave) void linear_wide_kernel(const W
     const unsigned char* const xg = (const unsigned char*)a.x;
     const unsigned char* const wg = (const unsigned char*)a.w;
     // This wavefront's units.  Row-major: every 8th, so that the 16-byte pieces of a 128-byte line of signs are asked for by
-    // the 8 wavefronts at about the same time.  Tiled: the units of a contiguous range of k tiles (256 elements), the range
-    // that the decode kernel deals to this wavefront; with fewer k tiles than wavefronts some have none.
-    int nw = kWideWaves;                               // wavefronts that have units
+    // the 8 wavefronts at about the same time.  Tiled: those of a contiguous range of k tiles (256 elements), the range that the decode
+    // kernel deals to a wavefront.
     int u_begin = wave, u_half = kWideWaves, u_step = 2 * kWideWaves, u_count = (a.units - wave + kWideWaves - 1) / kWideWaves;
     if constexpr (!RM) {
-        while (nw > 1 && nw > a.KT) nw >>= 1;
-        u_begin = 2 * (wave * a.KT / nw);
+        u_begin = 2 * (k_part * a.KT / nw);
         u_half = 1;
         u_step = 2;
-        u_count = wave < nw ? min(2 * ((wave + 1) * a.KT / nw), a.units) - u_begin : 0;
+        u_count = min(2 * ((k_part + 1) * a.KT / nw), a.units) - u_begin;
     }
 
     // the table: entry b, copy cp at 256 b + 16 cp; element e = bit e of b ? +1.0 : -1.0
@@ -339,8 +343,43 @@ __global__ __launch_bounds__(kWideWaves * kWave) void linear_wide_kernel(const W
             for (int ct = 0; ct < MT; ++ct) *(float4v*)(smem + at + lane_at + (r * MT + ct) * 1024) = value(r, ct);
     };
     auto scale_of = [&](const int ct) { return *(const float*)(smem + Lds::kAlpha + ct * 4); };
+    // y of the row blocks of subs [s0, s0 + n_s), whose parts are in LDS; finished: infinite scales multiply the sum at 8 kSet
+    const bool whole = (a.out & 3) == 0 && ((uintptr_t)a.y & 7) == 0;
+    auto write_y = [&](const int s0, const int n_s, const bool finished) __attribute__((always_inline)) {
+        const int per = n_tiles * 16 * (R * 4);
+        for (int idx = threadIdx.x; idx < n_s * per; idx += kWideWaves * kWave) {   // four features of a token each
+            const int s = RM ? 0 : s0 + idx / per, i = RM ? idx : idx % per;
+            const int row = i % (R * 4) * 4, col = i / (R * 4);   // consecutive threads: consecutive features
+            const int tok = *(const int*)(smem + Lds::kTok + col * 4);
+            const int n = (rb_first + s * R) * kTileRows + row;
+            if (tok < 0 || n >= a.out) continue;
+            const unsigned char* const p = smem + ((row >> 4) * MT + (col >> 4)) * 1024 + ((col & 15) * 16 + (row & 15)) * 4;
+            const float al = scale_of(col >> 4);
+            float4v sum = {0.f, 0.f, 0.f, 0.f}, t = {0.f, 0.f, 0.f, 0.f};
+            if constexpr (RM) {
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    sum += *(const float4v*)(p + 2 * w * kSet);
+                    t += *(const float4v*)(p + (2 * w + 1) * kSet);
+                }
+            } else {
+                for (int w = 0; w < nw; ++w) sum += *(const float4v*)(p + (w * subs + s) * kSet);
+                if (finished) t = *(const float4v*)(p + 8 * kSet);
+            }
+            uint16_t h[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) h[e] = f2h_rne(RM || (finished && __builtin_isinf(al)) ? sum[e] + al * t[e] : sum[e]);
+            uint16_t* const y = a.y + (int64_t)tok * a.out + n;
+            if (whole) {
+                *(u32x2*)y = u32x2{(uint32_t)h[0] | (uint32_t)h[1] << 16, (uint32_t)h[2] | (uint32_t)h[3] << 16};
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (n + e < a.out) y[e] = h[e];
+            }
+        }
+    };
     __syncthreads();                                   // the table is no longer read
-    bool any_inf = false;
     if constexpr (RM) {
         // base and +-1 sum apart: 4 .. 7 hand theirs to 0 .. 3, whose sums are added in order; the scale multiplies the finished one
         const int mine = (wave & 3) * 2 * kSet;
@@ -353,22 +392,11 @@ __global__ __launch_bounds__(kWideWaves * kWave) void linear_wide_kernel(const W
             put(mine, [&](int r, int ct) { return acc[r][ct] + *(const float4v*)(smem + mine + lane_at + (r * MT + ct) * 1024); });
             put(mine + kSet, [&](int r, int ct) { return dsum[r][ct] + *(const float4v*)(smem + mine + kSet + lane_at + (r * MT + ct) * 1024); });
         }
+        __syncthreads();
+        write_y(0, 1, true);
     } else {
-        // as the decode kernel: every wavefront scales its own part, and the parts are added in order.  An infinite scale would
-        // make NaN of a part that is zero; it multiplies the finished sum instead (behind the parts, kSet bytes).
-#pragma unroll
-        for (int ct = 0; ct < MT; ++ct) any_inf = any_inf || __builtin_isinf(scale_of(ct));
-        if (any_inf) {
-            put(wave * kSet, [&](int r, int ct) { return dsum[r][ct]; });
-            __syncthreads();
-            for (int idx = threadIdx.x; idx < R * MT * 256; idx += kWideWaves * kWave) {
-                float t = 0.f;
-                for (int w = 0; w < nw; ++w) t += *(const float*)(smem + w * kSet + idx * 4);
-                *(float*)(smem + 8 * kSet + idx * 4) = t;
-            }
-            __syncthreads();
-        }
-        put(wave * kSet, [&](int r, int ct) {
+        // as the decode kernel: every wavefront scales its own part, and the parts are added in order
+        auto scaled = [&](int r, int ct) {
             const float al = scale_of(ct);
             float4v p = acc[r][ct];
             if (!__builtin_isinf(al)) {
@@ -376,38 +404,30 @@ __global__ __launch_bounds__(kWideWaves * kWave) void linear_wide_kernel(const W
                 for (int e = 0; e < 4; ++e) p[e] = acc[r][ct][e] + al * dsum[r][ct][e];
             }
             return p;
-        });
-    }
-    __syncthreads();
-    const bool whole = (a.out & 3) == 0 && ((uintptr_t)a.y & 7) == 0;
-    for (int idx = threadIdx.x; idx < n_tiles * 16 * (R * 4); idx += kWideWaves * kWave) {   // four features of a token each
-        const int row = idx % (R * 4) * 4, col = idx / (R * 4);   // consecutive threads: consecutive features
-        const int tok = *(const int*)(smem + Lds::kTok + col * 4);
-        const int n = rb0 * kTileRows + row;
-        if (tok < 0 || n >= a.out) continue;
-        const unsigned char* const p = smem + ((row >> 4) * MT + (col >> 4)) * 1024 + ((col & 15) * 16 + (row & 15)) * 4;
-        const float al = scale_of(col >> 4);
-        float4v s = {0.f, 0.f, 0.f, 0.f}, t = {0.f, 0.f, 0.f, 0.f};
-        if constexpr (RM) {
+        };
+        bool any_inf = false;
 #pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                s += *(const float4v*)(p + 2 * w * kSet);
-                t += *(const float4v*)(p + (2 * w + 1) * kSet);
-            }
-        } else {
-            for (int w = 0; w < nw; ++w) s += *(const float4v*)(p + w * kSet);
-            if (any_inf) t = *(const float4v*)(p + 8 * kSet);
+        for (int ct = 0; ct < MT; ++ct) any_inf = any_inf || __builtin_isinf(scale_of(ct));
+        if (!any_inf) {
+            put(wave * kSet, scaled);
+            __syncthreads();
+            write_y(0, subs, false);
+            return;
         }
-        uint16_t h[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) h[e] = f2h_rne(RM || (any_inf && __builtin_isinf(al)) ? s[e] + al * t[e] : s[e]);
-        uint16_t* const y = a.y + (int64_t)tok * a.out + n;
-        if (whole) {
-            *(u32x2*)y = u32x2{(uint32_t)h[0] | (uint32_t)h[1] << 16, (uint32_t)h[2] | (uint32_t)h[3] << 16};
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (n + e < a.out) y[e] = h[e];
+        // An infinite scale would make NaN of a part that is zero: it multiplies the finished sum, which goes behind the parts.
+        for (int s = 0; s < subs; ++s) {
+            if (sub == s) put(wave * kSet, [&](int r, int ct) { return dsum[r][ct]; });
+            __syncthreads();
+            for (int idx = threadIdx.x; idx < R * MT * 256; idx += kWideWaves * kWave) {
+                float t = 0.f;
+                for (int w = 0; w < nw; ++w) t += *(const float*)(smem + (w * subs + s) * kSet + idx * 4);
+                *(float*)(smem + 8 * kSet + idx * 4) = t;
+            }
+            __syncthreads();
+            if (sub == s) put(wave * kSet, scaled);
+            __syncthreads();
+            write_y(s, 1, true);
+            __syncthreads();
         }
     }
 }
@@ -426,7 +446,8 @@ static hipError_t launch_wide_inst(const WideArgs& args, hipStream_t st) {
         return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     });
     if (ea != hipSuccess) return ea;
-    const unsigned groups = (unsigned)((args.row_blocks + R - 1) / R);
+    const int per_group = R * (RM ? 1 : kWideWaves / wide_k_waves(args.KT));
+    const unsigned groups = (unsigned)((args.row_blocks + per_group - 1) / per_group);
     const unsigned chunks = (unsigned)((args.n_tiles + args.tiles_per_chunk - 1) / args.tiles_per_chunk);
     hipLaunchKernelGGL(kernel, dim3((groups + 7) / 8 * 8 * chunks), dim3(kWideWaves * kWave), lds, st, args);
     return hipGetLastError();
