@@ -285,9 +285,9 @@ double wide_units(int64_t in, bool rowmajor) {
 }
 
 // How a launch of n column tiles is cut: row blocks per workgroup (1 or 2), column tiles per workgroup, and its estimated
-// time.  Workgroups take turns on the compute units of their XCD (LDS allows one at a time); the row blocks are dealt to the
-// XCDs.  Fitted to 3480 times (450 batches of 33 to 600 tokens of 1 to 64 tenants, 300 .. 12000 x 512 .. 11520, every split, from
-// graphs): 10 % at the 10 % and 90 % quantiles, and the split it picks is the quickest or within 4 % of it in 95 % of the batches.
+// time: workgroups take turns on the compute units of their XCD (LDS allows one at a time, the row blocks are dealt to the XCDs), some 4 us
+// around the loop of each, and every chunk fetches the base again.  Fitted to 3480 times: the batches described at BatchShape, every
+// split.  10 % at the 10 % and 90 % quantiles; the split it picks is the quickest or within 7 % of it in 95 % of the batches.
 struct WidePlan {
     int R, per_chunk;
     double us;
@@ -301,16 +301,15 @@ WidePlan wide_plan(int n, int64_t out, int64_t in, int cus, bool rowmajor) {
         for (int run = 2; run <= bd::wide_max_chunk(R, (int)bd::tiled_k_tiles(in), rowmajor); run += 2) {   // instantiated for even numbers
             const int chunks = (n + run - 1) / run;   // all but the last one full
             const int64_t rounds = ((groups + 7) / 8 * chunks + per_xcd - 1) / per_xcd;
-            const double us = (double)rounds * (rowmajor ? 3.9 + units * (R == 1 ? 0.51 * run : 0.2 + 0.765 * run)
-                                                         : 3.4 + units * (R == 1 ? 0.50 * run : 0.72 * run));
+            const double loop = units * (run - 1) * (rowmajor ? (R == 1 ? 0.52 : 0.79) : (R == 1 ? 0.48 : 0.69));
+            const double us = (double)rounds * ((rowmajor ? 3.9 : 4.1) + loop) + (double)chunks * (double)out * (double)in * (rowmajor ? 0.15e-6 : 0.11e-6);
             if (us < best.us) best = WidePlan{R, std::min(run, n), us};
         }
     }
     return best;
 }
-constexpr double kWideMargin = 1.1;   // the estimates are right to about a tenth: the wide kernel is taken where it wins by more
 double wide_us(int n_all, int active, int64_t out, int64_t in, int cus, bool rowmajor) {
-    double us = 2.0;
+    double us = 3.0;
     const int launches = (n_all + bd::kWideMaxTiles - 1) / bd::kWideMaxTiles;
     for (int l = 0; l < launches; ++l)
         us += wide_plan((int)((int64_t)n_all * (l + 1) / launches - (int64_t)n_all * l / launches), out, in, cus, rowmajor).us;
@@ -363,66 +362,105 @@ hipError_t run_wide(const WideTiles& t, const uint16_t* x, const uint16_t* w, co
     return hipSuccess;
 }
 
+// Where a launch of n tokens (sorted by tenant) is cut into its two column tiles.  Both tiles run as many job slots as the
+// one with more jobs needs, so the cut that balances the jobs is taken; of those, one between two tenants (a tenant on both
+// sides has its delta streamed twice), then the one nearest the middle.  (18 tokens of 18 tenants as 16 + 2 took nearly as long as 32:
+// 274 us for a 7B layer; as 9 + 9 they take 221.)  A column's result does not depend on its tile.
+int split_of_launch(const int32_t* tenant_of_token, const int32_t* order, int n, int per_tile, int* jobs = nullptr) {
+    int runs_before[2 * bd::kTiledMaxTokens + 1];   // runs_before[i]: tenants among the first i tokens
+    runs_before[0] = 0;
+    auto new_run = [&](int i) { return i == 0 || tenant_of_token[order[i]] != tenant_of_token[order[i - 1]]; };
+    for (int i = 0; i < n; ++i) runs_before[i + 1] = runs_before[i] + (new_run(i) ? 1 : 0);
+    int best = per_tile, best_cost = 1 << 30;
+    for (int s = n - per_tile; s <= per_tile; ++s) {   // 1 <= n - per_tile <= s: both tiles hold a token
+        const int left = runs_before[s], cut = new_run(s) ? 0 : 1, right = runs_before[n] - left + cut;
+        const int cost = std::max(left, right) * 1024 + cut * 512 + std::abs(2 * s - n);
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = s;
+            if (jobs) *jobs = std::max(left, right);
+        }
+    }
+    return best;
+}
+
 // What a batch of T > 32 tokens looks like to the three ways of running it: decode launches of 32 tokens of the sorted
 // order, which re-read the base per launch but spend nothing on empty rows; the wide kernel, 16-column tiles of one tenant;
 // the GEMM, tiles of 32, 64 or 128 rows of one tenant.  A wrong guess costs time, never correctness.
+// The estimates were fitted to batches of 33 to 600 tokens of 1 to 64 tenants on 300 .. 12000 x 512 .. 11520, weights from HBM, replayed from
+// graphs (250 row-major, 200 on the serving layout): each is within 10 % at its 10 % and 90 % quantiles (the GEMM's 15 %).  Of 150 other
+// batches each, up to 4096 (row-major) or 1500 tokens, 5 % ran more than 8 % (5 %) longer than the quickest of the three ways, 1 % more than 17 % (8 %).
 struct BatchShape {
+    struct Launch {
+        int tokens, tenants, jobs;                       // jobs of its fuller column tile
+    };
     int active = 0, tiles16 = 0;
     int64_t tiles32 = 0, tiles64 = 0, tiles128 = 0;      // GEMM tiles by the rows they run
-    std::vector<std::pair<int, int>> launches;           // of 32 tokens: (tokens, distinct tenants)
+    int64_t runs = 0;                                    // stretches of consecutive tokens of one tenant
+    std::vector<Launch> launches;
 };
 BatchShape batch_shape(const int32_t* tenant_of_token, const std::vector<int32_t>& order) {
     const int64_t T = (int64_t)order.size();
     BatchShape s;
-    int in_launch = 0, distinct = 0;
     for (int64_t i = 0; i < T;) {
         int64_t e = i;
-        while (e < T && tenant_of_token[order[(size_t)e]] == tenant_of_token[order[(size_t)i]]) ++e;
-        int64_t n = e - i;
+        for (; e < T && tenant_of_token[order[(size_t)e]] == tenant_of_token[order[(size_t)i]]; ++e)
+            if (e == i || order[(size_t)e] != order[(size_t)e - 1] + 1) ++s.runs;
+        const int64_t n = e - i, rest = n % bd::kPrefillTile;
         i = e;
         ++s.active;
         s.tiles16 += (int)((n + 15) / 16);
         s.tiles128 += n / bd::kPrefillTile;
-        const int64_t rest = n % bd::kPrefillTile;
         if (rest > 64) ++s.tiles128;
         else if (rest > 32) ++s.tiles64;
         else if (rest > 0) ++s.tiles32;
-        while (n > 0) {
-            const int take = (int)std::min<int64_t>(n, kMaxDecodeTokens - in_launch);
-            ++distinct;
-            in_launch += take;
-            n -= take;
-            if (in_launch == kMaxDecodeTokens) {
-                s.launches.emplace_back(in_launch, distinct);
-                in_launch = distinct = 0;
-            }
-        }
     }
-    if (in_launch > 0) s.launches.emplace_back(in_launch, distinct);
+    for (int64_t t0 = 0; t0 < T; t0 += kMaxDecodeTokens) {
+        const int n = (int)std::min<int64_t>(kMaxDecodeTokens, T - t0);
+        const int32_t* const o = order.data() + t0;
+        int tenants = 1;
+        for (int i = 1; i < n; ++i) tenants += tenant_of_token[o[i]] != tenant_of_token[o[i - 1]] ? 1 : 0;
+        int jobs = tenants;
+        if (n > bd::kTiledMaxTokens) split_of_launch(tenant_of_token, o, n, bd::kTiledMaxTokens, &jobs);
+        s.launches.push_back({n, tenants, jobs});
+    }
     return s;
 }
-// The row-major GEMM.  Measured (4096 and 11008 x 4096, graph replay): a 128 x 256 tile takes 1.42 us per 64-wide k step, 1.25
-// with 64 rows and 0.85 with 32, plus 8 us around the loop, one tile per compute unit at a time, and 5 us for the tables.
+// The row-major GEMM.  Per 64-wide k step a tile of 128, 64 or 32 rows takes 1.77, 1.3 or 0.75 us where the compute units are full, plus 2.7 us;
+// a last round of at most half of them (whose tiles of 128 rows run as halves) 0.68 us per step.  One tile per compute unit at a time.  The
+// token tables come first: from runs (320 to a launch, 0.1 us each) or as they are (960 ints and 2.2 us a launch).
 double gemm_us(const BatchShape& s, int64_t out, int64_t in, bool big, int cus) {
     const double steps = (double)in / 64.0;
+    const int64_t mtiles = s.tiles32 + s.tiles64 + s.tiles128, runs = s.runs + 3 * mtiles;
+    const int64_t by_value = (mtiles * (bd::kPrefillTile + 1) + 959) / 960, by_run = (runs + 319) / 320;
+    const double tables = 2.0 + (by_run < by_value ? 0.1 * (double)runs : 2.2 * (double)by_value);
     if (!big) {   // 128 x 128 tiles, two workgroups per compute unit, whatever rows are filled
-        const int64_t tiles = (s.tiles32 + s.tiles64 + s.tiles128) * ((out + 127) / 128);
-        return 5.0 + (double)((tiles + 2 * cus - 1) / (2 * cus)) * (steps * 1.9 + 10.0);
+        const int64_t tiles = mtiles * ((out + 127) / 128);
+        return tables + (double)((tiles + 2 * cus - 1) / (2 * cus)) * (steps * 1.9 + 10.0);
     }
-    const int64_t nt = (out + 255) / 256, tiles = (s.tiles32 + s.tiles64 + s.tiles128) * nt;
-    const double all = (double)nt * (steps * (s.tiles32 * 0.85 + s.tiles64 * 1.25 + s.tiles128 * 1.42)) + 8.0 * (double)tiles;
-    return 5.0 + all / (double)tiles * (double)((tiles + cus - 1) / cus);
+    const int64_t tiles = mtiles * ((out + 255) / 256), last = tiles % cus;
+    const double full = 2.7 + steps * (s.tiles32 * 0.75 + s.tiles64 * 1.3 + s.tiles128 * 1.77) / (double)mtiles;
+    const double rounds = (double)(tiles / cus) * full + (last == 0 ? 0.0 : 2 * last <= cus ? 2.7 + 0.68 * steps : full);
+    return tables + std::max(rounds, (double)out * (double)in * (2.0 + (double)s.active / 8.0) / 2.9e6);
 }
-// Decode launches.  Row-major tensors: 7 us plus the base at 6.2 TB/s plus the sign bytes of the launch's tenants (at
-// least four) at 3.1 TB/s, half as much again with two column tiles (20 to 36 us on 4096 x 4096); the vector-ALU
-// kernel streams everything at 1.3 TB/s plus 8 us.  Serving layout: 8 us plus all bytes at 4.6 TB/s (14 to 37 us for the
-// linears of Llama-2-7B), one launch for the matrices of a group (`elems` is their sum).
-double decode_us(const BatchShape& s, double elems, bool tiled, bool on_matrix_cores) {
+// k tiles of the wavefronts of a decode launch
+double decode_k_tiles(int64_t in, bool rowmajor) {
+    const int KT = (int)bd::tiled_k_tiles(in), nw = bd::wide_k_waves(KT);
+    int u[8] = {};
+    for (int w = 0; w < nw; ++w) u[w] = rowmajor ? (KT - w + nw - 1) / nw : (w + 1) * KT / nw - w * KT / nw;
+    return steps_of_waves(u);
+}
+// Decode launches over `row_blocks` (those of a group together, `elems` their weights): about 6 us each, and the longer of the
+// tasks (per row block, k tile and column tile 1.7 us and 0.2 (row-major) or 0.13 per job slot, slots in twos) and the
+// bytes at 2.9 or 3.3 TB/s (32 tokens of 8 tenants on 4096 x 4096: 19 us).  The vector-ALU kernel streams everything at 1.3 TB/s plus 8 us.
+double decode_us(const BatchShape& s, int64_t row_blocks, double elems, int64_t in, int cus, bool tiled, bool on_matrix_cores) {
     double us = 0.0;
-    for (const auto& [tokens, distinct] : s.launches) {
-        if (tiled) us += 8.0 + elems * (2.0 + (double)distinct / 8.0) / 4.6e6;
-        else if (!on_matrix_cores) us += 8.0 + elems * (2.0 + (double)distinct / 8.0) / 1.3e6;
-        else us += (7.0 + 2.0 * elems / 6.2e6 + (double)std::max(distinct, 4) * elems / 8.0 / 3.1e6) * (tokens > 16 ? 1.5 : 1.0);
+    const double tasks = (double)((row_blocks + cus - 1) / cus) * decode_k_tiles(in, !tiled);
+    for (const auto& l : s.launches) {
+        const double bytes = elems * (2.0 + (double)l.tenants / 8.0), slots = (double)((l.jobs + 1) / 2 * 2), ct = l.tokens > 16 ? 2.0 : 1.0;
+        if (!on_matrix_cores) us += 8.0 + bytes / 1.3e6;
+        else if (tiled) us += 6.2 + std::max(tasks * ct * (1.8 + 0.135 * slots), bytes / 3.3e6);
+        else us += 6.1 + std::max(tasks * ct * (1.65 + 0.21 * slots), bytes / 2.9e6);
     }
     return us;
 }
@@ -626,9 +664,9 @@ bd_status bd_linear_multitenant_variant(const uint16_t* x_f16, const uint16_t* w
     if (variant == 0 && T > kMaxDecodeTokens && in > 0) {   // the library's choice, by estimated time
         const BatchShape shape = batch_shape(tenant_of_token, order);
         const int cus = cus_or_256();
-        const double by_decode = decode_us(shape, (double)out * (double)in, false, mfma_ok);
+        const double by_decode = decode_us(shape, bd::tiled_row_blocks(out), (double)out * (double)in, in, cus, false, mfma_ok);
         const double by_gemm = can_prefill ? gemm_us(shape, out, in, big_default, cus) : 1e30;
-        if (mfma_ok && wide_fits(T, out, in) && kWideMargin * wide_us(shape.tiles16, shape.active, out, in, cus, true) < std::min(by_decode, by_gemm))
+        if (mfma_ok && wide_fits(T, out, in) && wide_us(shape.tiles16, shape.active, out, in, cus, true) < std::min(by_decode, by_gemm))
             return wide(0);
         gemm_pays = by_gemm < by_decode;
     }
@@ -716,27 +754,6 @@ bd_status bd_tile_signs(const uint32_t* packed, int64_t out, int64_t in, uint32_
 
 namespace {
 
-// Where a launch of n tokens (sorted by tenant) is cut into its two column tiles.  Both tiles run as many job slots as the
-// one with more jobs needs, so the cut that balances the jobs is taken; of those, one between two tenants (a tenant on both
-// sides has its delta streamed twice), then the one nearest the middle.  (18 tokens of 18 tenants as 16 + 2 took nearly as long as 32:
-// 274 us for a 7B layer; as 9 + 9 they take 221.)  A column's result does not depend on its tile.
-int split_of_launch(const int32_t* tenant_of_token, const int32_t* order, int n, int per_tile) {
-    int runs_before[2 * bd::kTiledMaxTokens + 1];   // runs_before[i]: tenants among the first i tokens
-    runs_before[0] = 0;
-    auto new_run = [&](int i) { return i == 0 || tenant_of_token[order[i]] != tenant_of_token[order[i - 1]]; };
-    for (int i = 0; i < n; ++i) runs_before[i + 1] = runs_before[i] + (new_run(i) ? 1 : 0);
-    int best = per_tile, best_cost = 1 << 30;
-    for (int s = n - per_tile; s <= per_tile; ++s) {   // 1 <= n - per_tile <= s: both tiles hold a token
-        const int left = runs_before[s], cut = new_run(s) ? 0 : 1, right = runs_before[n] - left + cut;
-        const int cost = std::max(left, right) * 1024 + cut * 512 + std::abs(2 * s - n);
-        if (cost < best_cost) {
-            best_cost = cost;
-            best = s;
-        }
-    }
-    return best;
-}
-
 // The tiled linear over n_mats matrices that share x, with k sign planes per tenant (k = 1: plain 1-bit
 // deltas).  Pointer table index: (m * n_tenants + tenant) * k + plane; scale index: tenant * k + plane.
 // q8: w_tiled point at 8-bit base tiles followed by their per-row scales (bd_tile_base_q8).
@@ -788,27 +805,27 @@ bd_status tiled_linear_impl(int32_t n_mats, const uint16_t* x_f16, const uint16_
                 if (misaligned(p, 16)) return BD_ERR_ALIGN;
             }
     }
+    const std::vector<int32_t> order = order_by_tenant(tenant_of_token, T, n_tenants);
     // Serving layout, one plane, more tokens than a launch takes: the wide kernel, a launch per matrix, where its estimate is
     // below that of the decode launches, which take the matrices of a group together.
-    const std::vector<int32_t> order = order_by_tenant(tenant_of_token, T, n_tenants);
     const int wide_split = wide_split_of_variant(variant, in, false);
-    if (wide_split >= 0) {
-        for (int m = 0; m < n_mats; ++m)
-            if (out[m] > 0 && !wide_fits(T, out[m], in)) return BD_ERR_UNSUPPORTED;
-    }
     if (wide_split >= 0 || (!rm && !q8 && k == 1 && variant == 0 && T > bd::kMaxDecodeTokens)) {
-        const BatchShape shape = batch_shape(tenant_of_token, order);
-        const int cus = cus_or_256();
         bool fits = true;
-        double wide = 0.0, elems = 0.0;
-        for (int m = 0; m < n_mats; ++m) {
-            if (out[m] == 0) continue;
-            fits = fits && wide_fits(T, out[m], in);
-            if (!fits) break;
-            wide += wide_us(shape.tiles16, shape.active, out[m], in, cus, false);
-            elems += (double)out[m] * (double)in;
+        for (int m = 0; m < n_mats; ++m) fits = fits && (out[m] == 0 || wide_fits(T, out[m], in));
+        if (wide_split >= 0 && !fits) return BD_ERR_UNSUPPORTED;
+        bool wide = wide_split >= 0;
+        if (!wide && fits) {
+            const BatchShape shape = batch_shape(tenant_of_token, order);
+            const int cus = cus_or_256();
+            double us = 0.0, elems = 0.0;
+            for (int m = 0; m < n_mats; ++m) {
+                if (out[m] == 0) continue;
+                us += wide_us(shape.tiles16, shape.active, out[m], in, cus, false);
+                elems += (double)out[m] * (double)in;
+            }
+            wide = us < decode_us(shape, row_blocks, elems, in, cus, true, true);
         }
-        if (wide_split >= 0 || (fits && kWideMargin * wide < decode_us(shape, elems, true, true))) {
+        if (wide) {
             const WideTiles tiles = wide_tiles(tenant_of_token, order);
             for (int m = 0; m < n_mats; ++m)
                 if (out[m] > 0 && run_wide(tiles, x_f16, w_tiled[m], nullptr, tiled_by_mat_tenant + (size_t)m * n_tenants, alpha_by_mat[m],
