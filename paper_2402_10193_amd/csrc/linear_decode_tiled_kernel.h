@@ -183,8 +183,7 @@ __device__ __forceinline__ u32x4 lut_read_rm(const u32x2 s, const int v, const u
 constexpr bool rm_base_through_lds(int nj, int xsteps, bool q8, bool rm) { return rm && !q8 && !(xsteps == 2 && nj > 12); }
 // S4 (row-major): the signs are fetched for four job slots at a time, 16 bytes per lane, every lane a row of a slot (128 cycles of
 // the address unit for four slots), instead of 8 bytes per lane, four lanes a row, slot by slot (256 cycles).  But a row's 32
-// bytes then come in two requests, and where `in` is long and the slots are many the requests to L2 are what counts:
-// 4096 x 4096 with 32 tenants 32 against 37 us, 8192 x 8192 141 against 130, 11008 x 4096 with 28 tenants 93 against 90.
+// bytes then come in two requests: launch_nj has the line between the two.
 template <int NJ, int XSTEPS, int NCT, bool Q8, bool RM = false, bool S4 = RM>
 __global__ __launch_bounds__(kMaxWavesTiled * kWave) void linear_decode_tiled_kernel(const TiledArgs a) {
     constexpr uint32_t kWTile = Q8 ? kTileBaseQ8Bytes : kTileBaseBytes;   // bytes of one base tile
@@ -826,15 +825,23 @@ static hipError_t launch_inst(const TiledArgs& args, int n_waves, unsigned grid,
 
 template <bool Q8, bool RM, int NJ>
 static hipError_t launch_nj(const TiledArgs& args, int n_waves, int xsteps, unsigned grid, hipStream_t st) {
-    // Row-major, rows of more than 24 k tiles and more than 8 job slots (4 with two column tiles), or more than 6 in both column
-    // tiles and several row blocks per workgroup: the signs slot by slot (see S4; below that, four slots at a time is the
-    // better one.  4271 x 9088, 31 tokens of 15 tenants: four at a time 97 us, slot by slot 86).
-    if constexpr (RM && NJ > 4) {
-        if (xsteps == 0 && args.n_ct == 2 && (args.KT > 24 || (NJ > 6 && args.rb_end[args.n_mats - 1] > (int)grid)))
-            return launch_inst<Q8, RM, NJ, 0, 2, false>(args, n_waves, grid, st);
-    }
-    if constexpr (RM && NJ > 8) {
-        if (xsteps == 0 && args.n_ct == 1 && args.KT > 24) return launch_inst<Q8, RM, NJ, 0, 1, false>(args, n_waves, grid, st);
+    // Row-major: the signs slot by slot (see S4) where that is the better one, both measured with the tensors coming from HBM (180
+    // + 260 + 290 launches of 2 to 32 tenants).  Four slots at a time issue half the loads, but ask L2 twice for a row's 32 bytes, and the second
+    // time the line may be gone: with long rows, with several row blocks per workgroup, and where rows of signs do not start on 128-byte
+    // lines (in % 1024 != 0), so that neighbouring k tiles share lines.  4 at a time / slot by slot, us:
+    //   one column tile, 11008 x 11008, 8 slots 109 / 93; 11008 x 5120, 16 slots 84 / 73; 4096 x 5760, 8 slots 24.2 / 23.0; 2500 x 5120,
+    //     12 slots 22.0 / 22.7; 8192 x 2304, 12 slots 24.0 / 25.2; 8-bit base, 11008 x 11520, 4 slots 69 / 64
+    //   two, 32 tenants: 11008 x 3328 94 / 85; 8192 x 2048 40 / 44; 4096 x 4096 40 / 42; 6000 x 5120 88 / 84; 2500 x 5760 (8-bit base) 52 / 47
+    if constexpr (RM && (NJ > 4 || (Q8 && NJ == 4))) {
+        const bool several = args.rb_end[args.n_mats - 1] > (int)grid, split_lines = args.in % 1024 != 0;
+        const int KT = args.KT;
+        if (xsteps == 0 && args.n_ct == 1 &&
+            (NJ > 4 ? KT > 24 || (KT > 16 && split_lines) || (KT > 12 && several) : (KT > 16 && split_lines) || (KT > 32 && several)))
+            return launch_inst<Q8, RM, NJ, 0, 1, false>(args, n_waves, grid, st);
+        if constexpr (NJ > 4) {
+            if (args.n_ct == 2 && (KT > 24 || (KT > 16 && (split_lines || (several && NJ > 6))) || (KT > 12 && split_lines && NJ > (several ? 6 : 8))))
+                return launch_inst<Q8, RM, NJ, 0, 2, false>(args, n_waves, grid, st);
+        }
     }
     if (args.n_ct == 2) return launch_inst<Q8, RM, NJ, 0, 2>(args, n_waves, grid, st);   // 17..32 tokens: two column tiles, streamed x
     if (xsteps == 1) return launch_inst<Q8, RM, NJ, 1>(args, n_waves, grid, st);

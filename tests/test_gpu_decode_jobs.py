@@ -33,7 +33,8 @@ def test_decode_launches(mix):
         t.check(y, w8, what + " 8-bit base", extra=(2304.0 * scale.double())[None, :] * t.x.double().abs().sum(dim=1, keepdim=True))
 
 
-@pytest.mark.parametrize("out,inn", [(24, 6528), (40, 4096), (4160, 384)])   # 25.5 k tiles a row; x of two tiles resident; several row blocks per workgroup
+# 25.5 k tiles a row; x of two tiles resident; several row blocks per workgroup; the same with 13.5 and with 20 k tiles; 20.5 k tiles
+@pytest.mark.parametrize("out,inn", [(24, 6528), (40, 4096), (4160, 384), (4120, 3456), (4104, 5120), (40, 5248)])
 @pytest.mark.parametrize("n", [3, 8, 9, 11, 13, 16, 18, 22, 27, 32])
 def test_row_major_rows_of_every_kind(out, inn, n):
     """The ways the row-major kernel fetches base and signs, chosen by the number of job slots and k tiles (the last half tile
