@@ -59,4 +59,22 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
+// 4 x 4 byte transpose: byte i of word j of the result = byte j of word i
+__device__ __forceinline__ u32x4 transpose_bytes(const u32x4 w) {
+    const uint32_t p0 = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u), p1 = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u);
+    const uint32_t q0 = __builtin_amdgcn_perm(w[1], w[0], 0x07030602u), q1 = __builtin_amdgcn_perm(w[3], w[2], 0x07030602u);
+    return u32x4{__builtin_amdgcn_perm(p1, p0, 0x05040100u), __builtin_amdgcn_perm(p1, p0, 0x07060302u),
+                 __builtin_amdgcn_perm(q1, q0, 0x05040100u), __builtin_amdgcn_perm(q1, q0, 0x07060302u)};
+}
+
+// Row-major signs.  In: lane (r, j) = (lane % 16, lane / 16) holds four words of row r of sign tensor j; byte i of a word belongs to lane
+// group i.  Out: word j of lane (r, g) = byte g of the four words of tensor j.  The byte transpose inside the lane, then a
+// transpose of (register, lane group) by two swaps each way: 12 instructions.  All 64 lanes must be active.
+__device__ __forceinline__ u32x4 turn_sign_words(const u32x4 w) {
+    const u32x4 t = transpose_bytes(w);
+    const auto a02 = __builtin_amdgcn_permlane32_swap(t[0], t[2], false, false), a13 = __builtin_amdgcn_permlane32_swap(t[1], t[3], false, false);
+    const auto b01 = __builtin_amdgcn_permlane16_swap(a02[0], a13[0], false, false), b23 = __builtin_amdgcn_permlane16_swap(a02[1], a13[1], false, false);
+    return u32x4{b01[0], b01[1], b23[0], b23[1]};
+}
+
 }  // namespace bd

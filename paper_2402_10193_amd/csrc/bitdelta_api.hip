@@ -1052,7 +1052,7 @@ bd_status bd_linear_multitenant_kbit(const uint16_t* x_f16, const uint16_t* w_ba
                              stream, false, planes_by_tenant);
 }
 
-// The GEMM form for any T >= 1 with k planes per tenant or the 8-bit base (128 x 128 tiles).
+// The GEMM form for any T >= 1 with k planes per tenant (128 x 128 tiles) or the 8-bit base (128 x 256 where the shape allows).
 static bd_status gemm_entry(const uint16_t* x_f16, const void* w, size_t w_bytes_per_el, const uint32_t* const* packed_by_tenant,
                             const float* alpha_by_tenant, const float* wscale, const int32_t* tenant_of_token, uint16_t* y_f16,
                             int64_t T, int64_t out, int64_t in, int32_t n_tenants, int k_planes, void* workspace,

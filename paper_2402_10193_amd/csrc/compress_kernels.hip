@@ -122,8 +122,8 @@ __global__ __launch_bounds__(kCompressThreads) void quantize_rtn8_kernel(const u
 // once, 8 elements per load, and stays in registers (up to CHUNKS per thread: in <= 2048 CHUNKS) between the maximum and
 // the division.  The quotient w / s takes a dozen instructions per weight, more than the memory leaves time for; t = w * (1 / s)
 // differs from it by less than 2^-22 |t| < 4e-5, so wherever t is farther than 1e-4 from the middle between two whole
-// numbers rint(t) is the answer, and only a wavefront that holds another t (about one chunk in forty), an infinity
-// or a NaN divides.  (11008 x 4096: 55.7 us with element loads, two passes and a division each; this takes 27.0 = 5.0 TB/s.)
+// numbers rint(t) is the answer, and a wavefront divides only its chunks (512 weights) that hold another t (about one in
+// eight of normal rows of 4096), an infinity or a NaN.  (11008 x 4096: 55.7 us with element loads, two passes and a division each; this takes 27.0 = 5.0 TB/s.)
 template <int CHUNKS>
 __global__ __launch_bounds__(kCompressThreads) void quantize_rtn8_vec_kernel(const uint16_t* __restrict__ w, int8_t* __restrict__ q,
                                                                               float* __restrict__ scale, const int n_vec) {

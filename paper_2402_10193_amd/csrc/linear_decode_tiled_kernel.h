@@ -114,25 +114,11 @@ __device__ __forceinline__ u32x4 lut_read(const u32x2 s, const int v, const uint
 
 // Row-major signs, four job slots at a time.  In: lane (r, j) = (lane % 16, lane / 16) holds the 8 words that row r of job slot j
 // has for the tile; byte i of word w is the sign byte of slice w for lane group i.  Out: s[j] = byte g of words 0..3 and of
-// words 4..7 of job slot j, in lane (r, g): what the tiled layout holds there.  A byte transpose inside the lane, then a
-// transpose of (register, lane group) by two swaps each way: 24 instructions for 4 jobs.  All 64 lanes must be active.
+// words 4..7 of job slot j, in lane (r, g): what the tiled layout holds there.
 __device__ __forceinline__ void rm_turn_signs(const u32x4 lo, const u32x4 hi, u32x2 (&s)[4]) {
-    u32x4 in[2] = {lo, hi};
+    const u32x4 a = turn_sign_words(lo), b = turn_sign_words(hi);
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const u32x4 w = in[h];
-        const uint32_t p0 = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u), p1 = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u);
-        const uint32_t q0 = __builtin_amdgcn_perm(w[1], w[0], 0x07030602u), q1 = __builtin_amdgcn_perm(w[3], w[2], 0x07030602u);
-        const uint32_t t0 = __builtin_amdgcn_perm(p1, p0, 0x05040100u), t1 = __builtin_amdgcn_perm(p1, p0, 0x07060302u);
-        const uint32_t t2 = __builtin_amdgcn_perm(q1, q0, 0x05040100u), t3 = __builtin_amdgcn_perm(q1, q0, 0x07060302u);
-        const auto a02 = __builtin_amdgcn_permlane32_swap(t0, t2, false, false), a13 = __builtin_amdgcn_permlane32_swap(t1, t3, false, false);
-        const auto b01 = __builtin_amdgcn_permlane16_swap(a02[0], a13[0], false, false);
-        const auto b23 = __builtin_amdgcn_permlane16_swap(a02[1], a13[1], false, false);
-        s[0][h] = b01[0];
-        s[1][h] = b01[1];
-        s[2][h] = b23[0];
-        s[3][h] = b23[1];
-    }
+    for (int j = 0; j < 4; ++j) s[j] = u32x2{a[j], b[j]};
 }
 // Row-major signs, one job slot at a time (see S4).  In: this lane's words 2 g and 2 g + 1 of its row (lane (r, g) = (lane % 16, lane / 16)); byte i of
 // word w is the sign byte of slice w for lane group i.  Out: s[0] = byte g of words 0, 1, 4, 5 and s[1] = byte g of

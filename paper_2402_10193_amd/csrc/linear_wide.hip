@@ -194,19 +194,6 @@ __global__ __launch_bounds__(kWideWaves * kWave) void linear_wide_kernel(const W
         const uint64_t ptr = *(const uint64_t*)(smem + Lds::kSp + p * 512 + lane * 8);
         return *(const wide_global_u32x4)(ptr + (uint32_t)u * 16u);   // (a generic pointer would make it a flat load, which LDS reads wait for)
     };
-    // ... and what lane (c, i) needs of pair j is byte i of the four words that lane (c, j) has: a byte transpose inside the
-    // lane, then a transpose of (register, lane group) by two swaps each way.
-    auto turn_s4 = [&](u32x4& w) __attribute__((always_inline)) {
-        const uint32_t p0 = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u), p1 = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u);
-        const uint32_t q0 = __builtin_amdgcn_perm(w[1], w[0], 0x07030602u), q1 = __builtin_amdgcn_perm(w[3], w[2], 0x07030602u);
-        const uint32_t t0 = __builtin_amdgcn_perm(p1, p0, 0x05040100u), t1 = __builtin_amdgcn_perm(p1, p0, 0x07060302u);
-        const uint32_t t2 = __builtin_amdgcn_perm(q1, q0, 0x05040100u), t3 = __builtin_amdgcn_perm(q1, q0, 0x07060302u);
-        // register i, lane group j -> register j, lane group i
-        const auto a02 = __builtin_amdgcn_permlane32_swap(t0, t2, false, false), a13 = __builtin_amdgcn_permlane32_swap(t1, t3, false, false);
-        const auto b01 = __builtin_amdgcn_permlane16_swap(a02[0], a13[0], false, false), b23 = __builtin_amdgcn_permlane16_swap(a02[1], a13[1], false, false);
-        w = u32x4{b01[0], b01[1], b23[0], b23[1]};
-    };
-
     float4v acc[R][MT], dsum[R][MT];                   // base product, +-1 sum
     float4v dtile[TILE_SUMS ? R : 1][TILE_SUMS ? MT : 1];   // +-1 sum of the k tile that is being multiplied
 #pragma unroll
@@ -255,7 +242,7 @@ __global__ __launch_bounds__(kWideWaves * kWave) void linear_wide_kernel(const W
     // table operand of pair n (= 4 R ct + R v + r) of the unit
     auto look_up_pair = [&](const int n, const int u_next) __attribute__((always_inline)) {
         const int ct = n / kPer, v = n % kPer / R, r = n % R, f = ct * R + r;
-        if (RM && f % 4 == 0 && v == 0) turn_s4(sg[f / 4]);
+        if (RM && f % 4 == 0 && v == 0) sg[f / 4] = turn_sign_words(sg[f / 4]);
         ring[n % kAhead] = look_up(sg[f / 4][f % 4], v);
         if (v == 3) {                                  // its last look-up has been issued: the next unit's
             if constexpr (RM) {

@@ -55,14 +55,10 @@ __global__ __launch_bounds__(256) void tile_signs_kernel(const uint32_t* __restr
     }
     u32x2 val[4];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {                         // 4 x 4 byte transpose of words 4 h .. 4 h + 3
-        const uint32_t* q = w + 4 * h;
-        const uint32_t a = __builtin_amdgcn_perm(q[1], q[0], 0x05010400u), b = __builtin_amdgcn_perm(q[3], q[2], 0x05010400u);
-        const uint32_t c = __builtin_amdgcn_perm(q[1], q[0], 0x07030602u), d = __builtin_amdgcn_perm(q[3], q[2], 0x07030602u);
-        val[0][h] = __builtin_amdgcn_perm(b, a, 0x05040100u);
-        val[1][h] = __builtin_amdgcn_perm(b, a, 0x07060302u);
-        val[2][h] = __builtin_amdgcn_perm(d, c, 0x05040100u);
-        val[3][h] = __builtin_amdgcn_perm(d, c, 0x07060302u);
+    for (int h = 0; h < 2; ++h) {
+        const u32x4 t = transpose_bytes(u32x4{w[4 * h], w[4 * h + 1], w[4 * h + 2], w[4 * h + 3]});
+#pragma unroll
+        for (int g = 0; g < 4; ++g) val[g][h] = t[g];
     }
 #pragma unroll
     for (int g = 0; g < 4; ++g) st[(int64_t)tile * 64 + g * 16 + r] = val[g];
