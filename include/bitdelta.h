@@ -136,8 +136,9 @@ bd_status bd_compress_batch(int32_t n, const uint16_t* const* w_base_f16, const 
  * `workspace` holds bd_workspace_bytes(BD_OP_LINEAR_MULTITENANT, T, out, in, n_tenants) bytes
  * (256-byte aligned; it receives the token permutation).  Without one the same result (up to the order of
  * additions) is produced by ceil(T / 32) decode launches, each re-reading the base, or, for in % 128 == 0, by a
- * kernel for tens to a few hundred tokens with a few per tenant, which reads the base once per 128 columns (a
- * tenant's tokens padded to 16); the library takes whichever a cost estimate on the host says is quickest.
+ * kernel for tens to a few hundred tokens with a few per tenant, which reads the base once per up to 160 columns (a
+ * tenant's tokens padded to 16); the library takes whichever a cost estimate on the host says is quickest for the
+ * whole batch, so the order of additions of a token may change with the other tokens of its call.
  * Speed: this call reads the tensors in the canonical row-major layout, which costs a decode launch four times the
  * cache accesses per byte of the serving layout; a decode step through it runs at about two thirds of the rate of
  * bd_linear_multitenant_tiled on the same matrices (and the grouped tiled call saves three launches per layer on top).
