@@ -229,7 +229,7 @@ __global__ __launch_bounds__(kWideWaves * kWave) void linear_wide_kernel(const W
     }
     u32x4 off_next = ld_off(2 % MT);                   // rows of the tile that is requested next
     constexpr int kPer = 4 * R;                        // (slice, row block) pairs of a column tile
-        constexpr int kAhead = 2;                          // table operands in flight (3, 4, 6 and 8 are not faster)
+    constexpr int kAhead = 2;                          // table operands in flight (3, 4, 6 and 8 are not faster)
     static_assert(kAhead <= MT * kPer, "the first operands belong to one unit");
     u32x4 ring[kAhead];
     auto look_up = [&](const uint32_t s, const int v) __attribute__((always_inline)) {
@@ -237,8 +237,6 @@ __global__ __launch_bounds__(kWideWaves * kWave) void linear_wide_kernel(const W
         return *(wide_lds_u32x4)(uintptr_t)addr;
     };
 
-    // One unit: all column tiles against this unit's R x 4 slices of the base (register set B).  u_next: the unit whose
-    // operands are requested as registers fall free (the last unit requests itself again).
     // table operand of pair n (= 4 R ct + R v + r) of the unit
     auto look_up_pair = [&](const int n, const int u_next) __attribute__((always_inline)) {
         const int ct = n / kPer, v = n % kPer / R, r = n % R, f = ct * R + r;
@@ -252,6 +250,8 @@ __global__ __launch_bounds__(kWideWaves * kWave) void linear_wide_kernel(const W
             }
         }
     };
+    // One unit: all column tiles against this unit's R x 4 slices of the base (register set B).  u_next: the unit whose
+    // operands are requested as registers fall free (the last unit requests itself again).
     auto unit = [&](auto b_tag, const int u, const int u_next) __attribute__((always_inline)) {
         constexpr int B = decltype(b_tag)::value;
 #pragma unroll
