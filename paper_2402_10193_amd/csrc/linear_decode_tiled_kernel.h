@@ -91,6 +91,9 @@ __device__ __forceinline__ void lds_wave_sync() {   // order this wavefront's LD
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Streamed x through a buffer resource: this offset is its end, where a load gives zeros without a memory access.  (x has fewer than
+// 2^32 bytes, rows of whole 64 bytes: the host checks it, so that no slice of a row begins this far.)
+constexpr uint32_t kXNowhere = 0xFFFFFFF0u;
 typedef const void __attribute__((address_space(1)))* gptr_t;
 typedef const u32x4 __attribute__((address_space(3)))* lds_u32x4_ptr;
 
@@ -167,10 +170,15 @@ __device__ __forceinline__ u32x4 lut_read_rm(const u32x2 s, const int v, const u
 // (The row-major fp16 base passes through LDS rows unless x of two k tiles and the signs of more than 12 slots leave no
 // registers for it; streaming x instead costs more: 11008 x 4096 with 16 tenants 49 against 57 us.)
 constexpr bool rm_base_through_lds(int nj, int xsteps, bool q8, bool rm) { return rm && !q8 && !(xsteps == 2 && nj > 12); }
+// RG = 2 (streamed x): a wavefront works on two row blocks of a matrix at the same time (k tile by k tile, one after the other), so that x of a
+// k tile is fetched once for both: it comes from L2, but its lines take their places among the pending requests of the L1, which are what
+// limits the stream (32 tokens: 16 KiB of x next to 8 KiB of base and 16 of signs per task).  The sums of the row block that is not being
+// multiplied change places with the other's: 16 moves per column tile and task.  Without any fetch of x a 70B layer with 32 tokens
+// took 877 us where it took 1064.  launch_nj has the line between one row block and two.
 // S4 (row-major): the signs are fetched for four job slots at a time, 16 bytes per lane, every lane a row of a slot (128 cycles of
 // the address unit for four slots), instead of 8 bytes per lane, four lanes a row, slot by slot (256 cycles).  But a row's 32
 // bytes then come in two requests: launch_nj has the line between the two.
-template <int NJ, int XSTEPS, int NCT, bool Q8, bool RM = false, bool S4 = RM>
+template <int NJ, int XSTEPS, int NCT, bool Q8, bool RM = false, bool S4 = RM, int RG = 1>
 __global__ __launch_bounds__(kMaxWavesTiled * kWave) void linear_decode_tiled_kernel(const TiledArgs a) {
     constexpr uint32_t kWTile = Q8 ? kTileBaseQ8Bytes : kTileBaseBytes;   // bytes of one base tile
     constexpr int kWLoads = Q8 ? 4 : 8;                                   // 1 KiB loads per base tile
@@ -182,7 +190,8 @@ __global__ __launch_bounds__(kMaxWavesTiled * kWave) void linear_decode_tiled_ke
     const int g = lane >> 4;
     constexpr bool ROOM = rm_base_through_lds(NJ, XSTEPS, Q8, RM);
     using Plan = LdsPlan<XSTEPS, ROOM>;
-    static_assert(NCT == 1 || XSTEPS == 0, "two column tiles only with streamed x");
+    static_assert((NCT == 1 && RG == 1) || XSTEPS == 0, "two column tiles and two row blocks only with streamed x");
+    static_assert(RG == 1 || RG == 2, "the other row block's sums change places with this one's");
     // Touch every 64-byte line of the kernel arguments at once: the first read of a line is a trip
     // to memory, and taken one after the other (pointer tables are indexed by values read before)
     // those trips would delay the first weight request by microseconds.
@@ -374,41 +383,31 @@ __global__ __launch_bounds__(kMaxWavesTiled * kWave) void linear_decode_tiled_ke
         for (int i = 0; i < kTiledMaxTokens; ++i) tok_c = (c == i && i < a.T[ct]) ? a.col_token[ct][i] : tok_c;
         xlane[ct] = (uint32_t)tok_c * row_bytes + (uint32_t)g * 16u;
     }
-    // A slice that lies beyond `in` (ragged tile only) reads the lane's last slice inside the row again (or the row's first
-    // bytes if it has none), valid memory, and x_zero_beyond replaces it by zeros once it has arrived: both paths issue the
-    // same eight loads, so the count of loads in flight at any later point is known at compile time and nothing has to
-    // wait for more than it needs.  The common path keeps its constant offsets (no address arithmetic per slice).
+    // A slice that lies beyond `in` (ragged tile only) is asked for at the end of the buffer resource and arrives as zeros: every path
+    // issues the same eight loads, so that the count of loads in flight at any later point is known at compile time and nothing
+    // has to wait for more than it needs, and no register is written again behind the load.
+    const auto xrsrc = __builtin_amdgcn_make_buffer_rsrc((void*)a.x, 0, kXNowhere, 0x00020000);
     auto x_fetch_operands = [&](u32x4 (&xop)[8], const int kt, const int ct) __attribute__((always_inline)) {
         uint32_t xl = ct == 0 ? xlane[0] : xlane[NCT - 1];
         asm volatile("" : "+v"(xl));
         const uint32_t off = xl + (uint32_t)kt * (uint32_t)(kTileK * 2);
-        if (kt != k_ragged) {
+        const int n_in = (a.in - kt * kTileK - 8 * g + 31) >> 5;   // this lane's slices inside the row (may be negative)
 #pragma unroll
-            for (int v = 0; v < 8; ++v) xop[v] = ldg16(xg, off + v * 64);
-        } else {
-            const int n_in = (a.in - kt * kTileK - 8 * g + 31) >> 5;   // this lane's slices inside the row (may be <= 0)
-            const uint32_t last = n_in > 0 ? off + (uint32_t)(n_in - 1) * 64u : xl;
-#pragma unroll
-            for (int v = 0; v < 8; ++v) xop[v] = ldg16(xg, min(off + (uint32_t)v * 64u, last));
-        }
-    };
-    auto x_zero_beyond = [&](u32x4 (&xop)[8], const int kt) __attribute__((always_inline)) {
-        if (kt == k_ragged) {
-#pragma unroll
-            for (int v = 0; v < 8; ++v)
-                if (kt * kTileK + 32 * v + 8 * g >= a.in) xop[v] = u32x4{0u, 0u, 0u, 0u};
-        }
+        for (int v = 0; v < 8; ++v) xop[v] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, v < n_in ? off + v * 64 : kXNowhere, 0, 0);
     };
     // ---- requests of the first task: x first, then the base, (the table,) then the signs.  x is small and every
     // workgroup asks for the same lines; asked for behind the first base tiles of all compute units (16 MB) it arrives
     // microseconds after them and the first base product waits for it.  (Measured: 1.3 % on launches of one matrix, nothing
     // on the grouped launches, whose end is set by the stream.)
-    constexpr int XR = XSTEPS > 0 ? XSTEPS : 1;   // x register sets in operand order
+    constexpr int XR = XSTEPS > 0 ? XSTEPS : NCT;   // x register sets in operand order
     u32x4 xs[XR][8];
-    u32x4 xraw[XR][8];                            // resident x as fetched; streamed x: the next task's operands
+    u32x4 xraw[XR][8];                            // resident x as fetched; streamed x, one column tile: the next k tile's operands
     if (have_work) {
         if constexpr (XSTEPS > 0) x_fetch(xraw[0], kb);
-        else x_fetch_operands(xs[0], kb, 0);
+        else {
+#pragma unroll
+            for (int ct = 0; ct < NCT; ++ct) x_fetch_operands(xs[XSTEPS > 0 ? 0 : ct], kb, ct);
+        }
         if constexpr (XSTEPS == 2) x_fetch(xraw[1], kb + kstride);
     }
     u32x4 wr[kWLoads];   // fp16 base: slice v; 8-bit base: slices 2 i and 2 i + 1 (8 bytes each)
@@ -506,7 +505,6 @@ __global__ __launch_bounds__(kMaxWavesTiled * kWave) void linear_decode_tiled_ke
 
     if (!have_work) return;   // uniform per workgroup (n_rb) / never true for steps (host: waves <= k tiles)
     if constexpr (XSTEPS == 0) {
-        x_zero_beyond(xs[0], kb);
         // Everything requested so far (the first task's tiles, the scales) has to be there before the first delta job
         // anyway.  Waiting for it here, once, keeps the compiler from putting a wait for a register of the prologue at
         // the top of the task loop, where it would drain the loads in flight at every task.
@@ -517,9 +515,14 @@ __global__ __launch_bounds__(kMaxWavesTiled * kWave) void linear_decode_tiled_ke
     if constexpr (ROOM) w_turn();
     const uint32_t lanebits = (uint32_t)c << 4;
 
-    float4v accb[NCT], dsel[NCT], accs[NCT];   // accs (8-bit base only): sum_k x of the column, in every row
+    // sums of the row blocks in work; accs (8-bit base only): sum_k x of the column, in every row
+    float4v accb[RG][NCT], dsel[RG][NCT], accs[NCT];
 #pragma unroll
-    for (int ct = 0; ct < NCT; ++ct) accb[ct] = dsel[ct] = accs[ct] = float4v{0.f, 0.f, 0.f, 0.f};
+    for (int ct = 0; ct < NCT; ++ct) {
+        accs[ct] = float4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int r = 0; r < RG; ++r) accb[r][ct] = dsel[r][ct] = float4v{0.f, 0.f, 0.f, 0.f};
+    }
     const half8 ones = __builtin_bit_cast(half8, u32x4{0x3C003C00u, 0x3C003C00u, 0x3C003C00u, 0x3C003C00u});
     // 8 bytes u -> 8 fp16 (1024 + u): byte next to 0x64
     auto q8_operand = [](const u32x4 w2, const int h) {
@@ -530,18 +533,20 @@ __global__ __launch_bounds__(kMaxWavesTiled * kWave) void linear_decode_tiled_ke
                                                __builtin_amdgcn_perm(0x64646464u, hi, 0x04030402u)});
     };
 
-    // One task = (row block, k tile, column tile CT).  MORE: there is a next task; its tile index is
+    // One task = (row block, k tile, column tile CT).  Its sums are accb[0], dsel[0].  MORE: there is a next task; its tile index is
     // tile_next and its pointers are current (wt, sp).  The base registers are re-requested by the
-    // last column tile of a (row block, k tile) only.  xr: this task's x in operand order; with
-    // streamed x the next task's (kt_next, next column tile) is fetched into xnext during the task
-    // and replaces xr at its end.
+    // last column tile of a (row block, k tile) only.  xr: this task's x in operand order.  Streamed x, last column tile, new_x (no other
+    // row block needs x of this k tile): x of k tile kt_next is fetched, the first column tile's into xnext while this task is
+    // multiplied (one column tile: it replaces xr at the end; two: xnext is that tile's own set), the second one's into xr when it is spent.
+    // first_rb: the first row block that meets this x (8-bit base: it adds up sum_k x for both).
     // (always_inline on the lambdas: left to its own judgement the compiler may keep one a function, and everything it
     // captures by reference -- every register array of the kernel -- then lives in scratch)
     auto task = [&](auto more_tag, auto ct_tag, u32x4 (&xr)[8], const int kt_cur, const int rb_next, const int kt_next,
-                    u32x4 (&xnext)[8]) __attribute__((always_inline)) {
+                    const bool first_rb, const bool new_x, u32x4 (&xnext)[8]) __attribute__((always_inline)) {
         constexpr bool MORE = decltype(more_tag)::value;
         constexpr int CT = decltype(ct_tag)::value;
         constexpr int CT_NEXT = (CT + 1) % NCT;
+        constexpr bool NEW_X = MORE && XSTEPS == 0 && CT == NCT - 1;   // streamed x: if new_x, this task is the last one that needs x of this k tile
         constexpr bool NEW_BASE = CT == NCT - 1;   // the next task is on another tile of W
         // The lane offsets pass through an empty asm in every task: otherwise the compiler hoists
         // "uniform base + lane offset" of every load out of the loop as a 64-bit register pair per load.
@@ -560,22 +565,30 @@ __global__ __launch_bounds__(kMaxWavesTiled * kWave) void linear_decode_tiled_ke
                 if constexpr (RM && CT == 0) {   // the first column tile finds the registers as loaded; the second, gathered
                     if ((v & 1) == 0) wr[v >> 1] = rm_gather_q8(wr[v >> 1]);
                 }
-                accb[CT] = __builtin_amdgcn_mfma_f32_16x16x32_f16(q8_operand(wr[v >> 1], v & 1),
-                                                                  __builtin_bit_cast(half8, xr[v]), accb[CT], 0, 0, 0);
-                accs[CT] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ones, __builtin_bit_cast(half8, xr[v]), accs[CT], 0, 0, 0);
+                accb[0][CT] = __builtin_amdgcn_mfma_f32_16x16x32_f16(q8_operand(wr[v >> 1], v & 1),
+                                                                  __builtin_bit_cast(half8, xr[v]), accb[0][CT], 0, 0, 0);
+                if constexpr (RG == 1) accs[CT] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ones, __builtin_bit_cast(half8, xr[v]), accs[CT], 0, 0, 0);
                 if constexpr (MORE && NEW_BASE) {
                     if (v & 1) wr[v >> 1] = ld_base(wt_hi, woff, v >> 1);
                 }
             } else {
                 u32x4 wv = wr[v];
                 if (RM && v >= 4) wv = short_cur ? u32x4{0u, 0u, 0u, 0u} : wv;
-                accb[CT] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, wv),
-                                                                  __builtin_bit_cast(half8, xr[v]), accb[CT], 0, 0, 0);
+                accb[0][CT] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, wv),
+                                                                  __builtin_bit_cast(half8, xr[v]), accb[0][CT], 0, 0, 0);
                 if constexpr (MORE && NEW_BASE) wr[v] = ld_base(wt_hi, woff, v);
             }
             __builtin_amdgcn_sched_barrier(0);   // keep each request behind the MFMA that frees its registers
         }
-        if constexpr (MORE && XSTEPS == 0) x_fetch_operands(xnext, kt_next, CT_NEXT);
+        if constexpr (Q8 && RG > 1) {
+            if (first_rb) {
+#pragma unroll
+                for (int v = 0; v < 8; ++v) accs[CT] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ones, __builtin_bit_cast(half8, xr[v]), accs[CT], 0, 0, 0);
+            }
+        }
+        if constexpr (NEW_X) {
+            if (RG == 1 || new_x) x_fetch_operands(xnext, kt_next, 0);
+        }
         __builtin_amdgcn_s_setprio(0);
         __builtin_amdgcn_sched_barrier(0);
         // ---- delta jobs.  The 8 NJ (job, slice) pairs of the task form one sequence; the table
@@ -636,16 +649,28 @@ __global__ __launch_bounds__(kMaxWavesTiled * kWave) void linear_decode_tiled_ke
                 if ((i & 7) == 7) finish_job(i >> 3);
             }
         }
-        dsel[CT] += sel;
-        if constexpr (MORE && XSTEPS == 0) {   // this task's x is spent: move the next one in
-            x_zero_beyond(xnext, kt_next);
+        dsel[0][CT] += sel;
+        if constexpr (NEW_X) {
+            if (RG == 1 || new_x) {
+                if constexpr (NCT == 1) {   // this task's x is spent: move the next one in
 #pragma unroll
-            for (int v = 0; v < 8; ++v) xr[v] = xnext[v];
+                    for (int v = 0; v < 8; ++v) {
+                        // (moves that stay here: as plain copies they sink behind the join with the path on which a row block ends, where the
+                        // compiler waits for every load in flight.  Identity permutations are not moved across control flow.)
+                        u32x4 t;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) t[i] = (uint32_t)__builtin_amdgcn_mov_dpp((int)xnext[v][i], 0xE4, 0xF, 0xF, true);
+                        xr[v] = t;
+                    }
+                } else {
+                    x_fetch_operands(xr, kt_next, 1);
+                }
+            }
         }
     };
 
     // The partial tiles of `n` finished row blocks, first one rbg0: add the wavefronts in a fixed order, write y.
-    auto flush = [&](const int rbg0, const int n, const bool more_follow) {
+    auto flush = [&](const int rbg0, const int n, const bool more_follow) __attribute__((always_inline)) {
         __syncthreads();
         for (int idx = threadIdx.x; idx < n * 256; idx += blockDim.x) {   // n slots = n / NCT row blocks
             const int slot = idx >> 8, e = idx & 255, col = e >> 4, row = e & 15;
@@ -674,26 +699,30 @@ __global__ __launch_bounds__(kMaxWavesTiled * kWave) void linear_decode_tiled_ke
 
     int slot = 0, flush_base = r0;
     int m_cur = m_req;
-    int rbi = 0;            // the row block being multiplied: r0 + rbi
-    bool last_rb = false;
-    float4v sc = {1.f, 1.f, 1.f, 1.f};   // 8-bit base: the scales of this lane's 4 output rows, asked for a row block ahead of their use
-    int m_nx = m_req, rb_nx = 0;         // where the requests go after this row block's last task
+    int rbi = 0;            // the first row block being multiplied: r0 + rbi
+    int pair = 0;           // 1: the one after it as well
+    bool last_rb = false;   // they are the last ones
+    float4v sc[RG];         // 8-bit base: the scales of this lane's 4 output rows, asked for long before their use
+    int m_nx = m_req, rb_nx = 0;         // where the requests go after the last task of these row blocks
     auto begin_rb = [&]() __attribute__((always_inline)) {
-        last_rb = rbi + 1 == n_rb;
+        if constexpr (RG == 2) pair = r0 + rbi + 1 < min(r1, a.rb_end[m_cur]) ? 1 : 0;
+        last_rb = rbi + pair + 1 == n_rb;
         if constexpr (Q8) {
-            int m_c, rb_c;
-            mat_of(r0 + rbi, m_c, rb_c);
-            const float* ws = m_c == 0 ? a.wscale[0] : (m_c == 1 ? a.wscale[1] : a.wscale[2]);
-            if constexpr (RM) {   // the caller's array of `out` scales: rows beyond `out` read the last one (never stored)
+            const float* ws = m_cur == 0 ? a.wscale[0] : (m_cur == 1 ? a.wscale[1] : a.wscale[2]);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) sc[i] = ws[min(rb_c * kTileRows + 4 * g + i, a.out[0] - 1)];
-            } else {
-                sc = *(const float4v*)(ws + rb_c * kTileRows + 4 * g);   // the scale array is padded to whole row blocks
+            for (int r = 0; r < RG; ++r) {
+                const int rb = rb_req + (r ? pair : 0);
+                if constexpr (RM) {   // the caller's array of `out` scales: rows beyond `out` read the last one (never stored)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) sc[r][i] = ws[min(rb * kTileRows + 4 * g + i, a.out[0] - 1)];
+                } else {
+                    sc[r] = *(const float4v*)(ws + rb * kTileRows + 4 * g);   // the scale array is padded to whole row blocks
+                }
             }
         }
         m_nx = m_req;
         rb_nx = 0;
-        if (!last_rb) mat_of(r0 + rbi + 1, m_nx, rb_nx);
+        if (!last_rb) mat_of(r0 + rbi + pair + 1, m_nx, rb_nx);
     };
     auto cross = [&]() __attribute__((always_inline)) {   // requests move on to the next row block: switch the pointers if it is in another matrix
         if constexpr (RM) rm_lane_offsets(rb_nx);
@@ -705,33 +734,31 @@ __global__ __launch_bounds__(kMaxWavesTiled * kWave) void linear_decode_tiled_ke
                 for (int j = 0; j < NJ; ++j) sp[ct][j] = (const unsigned char*)a.signs[ct][m_nx][j];
         }
     };
-    // row block done: this wavefront's partial tiles -> slots; the slots are added up and written when they are full
-    // more_tag: std::true_type / std::false_type where the caller knows whether another row block follows, RbDynamic
-    // where last_rb tells
+    // a row block is done: this wavefront's partial tiles -> slots; the slots are added up and written when they are full
+    // more_tag: std::true_type / std::false_type where the caller knows whether another one follows these, RbDynamic where last_rb tells
     struct RbDynamic {};
-    auto end_rb = [&](auto more_tag) __attribute__((always_inline)) {
+    auto end_rb = [&](auto r_tag, auto more_tag) __attribute__((always_inline)) {
+        constexpr int r = decltype(r_tag)::value;
         bool last;
         if constexpr (std::is_same<decltype(more_tag), RbDynamic>::value) last = last_rb;
-        else last = !decltype(more_tag)::value;
+        else last = !decltype(more_tag)::value && (RG == 1 || r == pair);
 #pragma unroll
         for (int ct = 0; ct < NCT; ++ct) {
             const float al = m_cur == 0 ? alpha_m[ct][0] : (m_cur == 1 ? alpha_m[ct][1] : alpha_m[ct][2]);
+            float4v p = accb[r][ct];
+            if constexpr (Q8) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) p[i] = sc[r][i] * (accb[r][ct][i] - 1152.f * accs[ct][i]);
+            }
             if (a.planes > 1) {   // several planes per token: only a token's first column carries the base product
-                int cc = c;
-                asm volatile("" : "+v"(cc));   // derived here, once per row block, instead of living in a register
-                bool first = false;
-#pragma unroll
-                for (int i = 0; i < kTiledMaxTokens; ++i) first = (cc == i && a.col_span[ct][i] > 0) ? true : first;
-                if (!first) accb[ct] = accs[ct] = float4v{0.f, 0.f, 0.f, 0.f};
+                const int span = *(const int*)(smem + Plan::kMeta + (ct * kTiledMaxTokens + c) * 8);
+                if (span == 0) p = float4v{0.f, 0.f, 0.f, 0.f};
             }
-            float4v r;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float base = Q8 ? sc[i] * (accb[ct][i] - 1152.f * accs[ct][i]) : accb[ct][i];
-                r[i] = base + al * dsel[ct][i];
-            }
-            *(float4v*)(region + ((slot + ct) * 256 + c * 16 + 4 * g) * 4) = r;   // [column][row]
-            accb[ct] = dsel[ct] = accs[ct] = float4v{0.f, 0.f, 0.f, 0.f};
+            for (int i = 0; i < 4; ++i) p[i] += al * dsel[r][ct][i];
+            *(float4v*)(region + ((slot + ct) * 256 + c * 16 + 4 * g) * 4) = p;   // [column][row]
+            accb[r][ct] = dsel[r][ct] = float4v{0.f, 0.f, 0.f, 0.f};
+            if (XSTEPS > 0) accs[ct] = float4v{0.f, 0.f, 0.f, 0.f};
         }
         slot += NCT;
         if (slot == Plan::kRedSlots || last) {
@@ -739,12 +766,14 @@ __global__ __launch_bounds__(kMaxWavesTiled * kWave) void linear_decode_tiled_ke
             flush_base += slot / NCT;
             slot = 0;
         }
+    };
+    auto next_rb = [&]() __attribute__((always_inline)) {
         m_cur = m_nx;
         m_req = m_nx;
         rb_req = rb_nx;
-        ++rbi;
+        rbi += 1 + pair;
     };
-    using Ct0 = std::integral_constant<int, 0>;
+    using I0 = std::integral_constant<int, 0>;
     using CtL = std::integral_constant<int, NCT - 1>;
     if constexpr (XSTEPS > 0) {
         while (rbi < n_rb) {
@@ -752,49 +781,77 @@ __global__ __launch_bounds__(kMaxWavesTiled * kWave) void linear_decode_tiled_ke
 #pragma unroll
             for (int ki = 0; ki < XSTEPS; ++ki) {
                 if (ki + 1 < XSTEPS) {
-                    task(std::true_type{}, Ct0{}, xs[ki], kb + ki * kstride, rb_req, kb + (ki + 1) * kstride, xraw[0]);
+                    task(std::true_type{}, I0{}, xs[ki], kb + ki * kstride, rb_req, kb + (ki + 1) * kstride, true, false, xraw[0]);
                 } else if (!last_rb) {
                     cross();
-                    task(std::true_type{}, Ct0{}, xs[ki], kb + ki * kstride, rb_nx, kb, xraw[0]);
+                    task(std::true_type{}, I0{}, xs[ki], kb + ki * kstride, rb_nx, kb, true, false, xraw[0]);
                 } else {
-                    task(std::false_type{}, Ct0{}, xs[ki], kb + ki * kstride, 0, 0, xraw[0]);
+                    task(std::false_type{}, I0{}, xs[ki], kb + ki * kstride, 0, 0, true, false, xraw[0]);
                 }
             }
-            end_rb(RbDynamic{});
+            end_rb(I0{}, RbDynamic{});
+            next_rb();
         }
     } else {
-        // Streamed x: ONE loop over all (row block, k tile) pairs but the last, with a single copy of the task that requests
-        // its successor, and the last task after the loop.  (As a loop nest with the last task inside it, the compiler
+        // Streamed x: ONE loop over all (k tile, row block) pairs but the last, with a single copy of the task that requests its
+        // successor, and the last one after the loop.  (As a loop nest with the last task inside it, the compiler
         // kept two sets of registers for the requested tiles, copied one into the other at the end of every task and
         // waited there for every outstanding load: nothing was in flight across a task boundary.)
         begin_rb();
-        int ki = 0;
-        const int total = n_rb * steps;
-        for (int t = 0; t + 1 < total; ++t) {
-            const bool inner = ki + 1 < steps;
+        int ki = 0, r = 0;
+        auto first_column_tile = [&]() __attribute__((always_inline)) {   // all but the last column tile: the next task stays on this tile
+            if constexpr (NCT == 2) task(std::true_type{}, I0{}, xs[0], kb + ki * kstride, rb_req + r, kb + ki * kstride, r == 0, false, xraw[0]);
+        };
+        auto other_row_block = [&]() __attribute__((always_inline)) {     // accb[0], dsel[0] are the sums of row block r
+            if constexpr (RG == 2) {
+                if (pair) {
+#pragma unroll
+                    for (int ct = 0; ct < NCT; ++ct) {
+                        const float4v b0 = accb[0][ct], d0 = dsel[0][ct];
+                        accb[0][ct] = accb[RG - 1][ct];
+                        dsel[0][ct] = dsel[RG - 1][ct];
+                        accb[RG - 1][ct] = b0;
+                        dsel[RG - 1][ct] = d0;
+                    }
+                    r ^= 1;
+                }
+            }
+        };
+        auto end_all = [&](auto more_tag) __attribute__((always_inline)) {
+            end_rb(I0{}, more_tag);
+            if constexpr (RG == 2) {
+                if (pair) end_rb(std::integral_constant<int, 1>{}, more_tag);
+            }
+        };
+        for (int t = n_rb * steps; t > 1; --t) {
             const int kt = kb + ki * kstride;
-            // all but the last column tile: the next task stays on this tile (same k tile, next columns)
-            if constexpr (NCT == 2) task(std::true_type{}, Ct0{}, xs[0], kt, rb_req, kt, xraw[0]);
-            if (!inner) cross();
-            task(std::true_type{}, CtL{}, xs[0], kt, inner ? rb_req : rb_nx, inner ? kt + kstride : kb, xraw[0]);
-            if (inner) {
-                ++ki;
-            } else {
-                end_rb(std::true_type{});
+            const bool last_r = RG == 1 || r == pair, done = last_r && ki + 1 == steps;
+            first_column_tile();
+            if (done) cross();
+            else if constexpr (RM && RG == 2) rm_lane_offsets(rb_req + (last_r ? 0 : 1));
+            task(std::true_type{}, CtL{}, xs[NCT - 1], kt, done ? rb_nx : rb_req + (last_r ? 0 : 1), !last_r ? kt : done ? kb : kt + kstride,
+                 r == 0, last_r, NCT == 2 ? xs[0] : xraw[0]);
+            other_row_block();
+            ki += last_r ? 1 : 0;
+            if (done) {
+                end_all(std::true_type{});
+#pragma unroll
+                for (int ct = 0; ct < NCT; ++ct) accs[ct] = float4v{0.f, 0.f, 0.f, 0.f};
+                next_rb();
                 begin_rb();
                 ki = 0;
             }
         }
-        const int kt = kb + ki * kstride;
-        if constexpr (NCT == 2) task(std::true_type{}, Ct0{}, xs[0], kt, rb_req, kt, xraw[0]);
-        task(std::false_type{}, CtL{}, xs[0], kt, 0, 0, xraw[0]);
-        end_rb(std::false_type{});
+        first_column_tile();
+        task(std::false_type{}, CtL{}, xs[NCT - 1], kb + ki * kstride, 0, 0, r == 0, false, xraw[0]);
+        other_row_block();
+        end_all(std::false_type{});
     }
 }
 
-template <bool Q8, bool RM, int NJ, int XSTEPS, int NCT = 1, bool S4 = RM>
+template <bool Q8, bool RM, int NJ, int XSTEPS, int NCT = 1, bool S4 = RM, int RG = 1>
 static hipError_t launch_inst(const TiledArgs& args, int n_waves, unsigned grid, hipStream_t st) {
-    auto kernel = linear_decode_tiled_kernel<NJ, XSTEPS, NCT, Q8, RM, S4>;
+    auto kernel = linear_decode_tiled_kernel<NJ, XSTEPS, NCT, Q8, RM, S4, RG>;
     const size_t lds = (size_t)LdsPlan<XSTEPS, rm_base_through_lds(NJ, XSTEPS, Q8, RM)>::kTotal;
     static PerDeviceOnce lds_limit;   // one per instantiation
     const hipError_t ea = lds_limit.run([&] {
@@ -818,21 +875,39 @@ static hipError_t launch_nj(const TiledArgs& args, int n_waves, int xsteps, unsi
     //   one column tile, 11008 x 11008, 8 slots 109 / 93; 11008 x 5120, 16 slots 84 / 73; 4096 x 5760, 8 slots 24.2 / 23.0; 2500 x 5120,
     //     12 slots 22.0 / 22.7; 8192 x 2304, 12 slots 24.0 / 25.2; 8-bit base, 11008 x 11520, 4 slots 69 / 64
     //   two, 32 tenants: 11008 x 3328 94 / 85; 8192 x 2048 40 / 44; 4096 x 4096 40 / 42; 6000 x 5120 88 / 84; 2500 x 5760 (8-bit base) 52 / 47
+    const bool several = args.rb_end[args.n_mats - 1] > (int)grid;
+    const int KT = args.KT;
+    // Streamed x: two row blocks at a time (RG) where workgroups have several, rows are long and x is a large part of what a task asks for.  One
+    // at a time / two, us, 12000 rows where nothing else is said:
+    //   one column tile: 3008 12 slots 28.4 / 28.0, 7104 12 slots 55.6 / 54.3, row-major 4992 10 slots 50.6 / 49.7, a 70B layer with 16 slots 616 / 588, 4
+    //     slots 341 / 338, 8-bit base 12 tokens 394 / 371; but 2496 10 and 12 slots 1.00, 704 to 1728 0.97 to 0.99 x, 6 slots up to 7104 0.97 to 0.99 x
+    //   two: 5 tenants, 20 tokens: 3008 31.4 / 30.2, 7104 59.1 / 55.7, a 70B layer 527 / 463, but 2496 29.4 / 29.7, 1216 21.6 / 22.8;
+    //     30 tenants: 1216 41.9 / 40.7, 2496 57.7 / 56.6, 7104 118.5 / 115.4, a 70B layer of 32 1088 / 1029, 8-bit base 5056 86.6 / 84.2, but 640 row-major 42.8 / 43.8
+    const bool two = several && (args.n_ct == 2 ? KT >= (NJ >= 12 ? 5 : 12) : KT >= (NJ >= 8 ? 12 : 30));
+    auto streamed = [&](auto nct_tag, auto s4_tag) {
+        constexpr int NCT = decltype(nct_tag)::value;
+        constexpr bool S4 = decltype(s4_tag)::value;
+        if constexpr (NJ > 2 || NCT == 2) {
+            if (two) return launch_inst<Q8, RM, NJ, 0, NCT, S4, 2>(args, n_waves, grid, st);
+        }
+        return launch_inst<Q8, RM, NJ, 0, NCT, S4>(args, n_waves, grid, st);
+    };
+    using One = std::integral_constant<int, 1>;
+    using Two = std::integral_constant<int, 2>;
     if constexpr (RM && (NJ > 4 || (Q8 && NJ == 4))) {
-        const bool several = args.rb_end[args.n_mats - 1] > (int)grid, split_lines = args.in % 1024 != 0;
-        const int KT = args.KT;
+        const bool split_lines = args.in % 1024 != 0;
         if (xsteps == 0 && args.n_ct == 1 &&
             (NJ > 4 ? KT > 24 || (KT > 16 && split_lines) || (KT > 12 && several) : (KT > 16 && split_lines) || (KT > 32 && several)))
-            return launch_inst<Q8, RM, NJ, 0, 1, false>(args, n_waves, grid, st);
+            return streamed(One{}, std::false_type{});
         if constexpr (NJ > 4) {
             if (args.n_ct == 2 && (KT > 24 || (KT > 16 && (split_lines || (several && NJ > 6))) || (KT > 12 && split_lines && NJ > (several ? 6 : 8))))
-                return launch_inst<Q8, RM, NJ, 0, 2, false>(args, n_waves, grid, st);
+                return streamed(Two{}, std::false_type{});
         }
     }
-    if (args.n_ct == 2) return launch_inst<Q8, RM, NJ, 0, 2>(args, n_waves, grid, st);   // 17..32 tokens: two column tiles, streamed x
+    if (args.n_ct == 2) return streamed(Two{}, std::bool_constant<RM>{});   // 17..32 tokens: two column tiles, streamed x
     if (xsteps == 1) return launch_inst<Q8, RM, NJ, 1>(args, n_waves, grid, st);
     if (xsteps == 2) return launch_inst<Q8, RM, NJ, 2, 1, RM && (Q8 || NJ <= 12)>(args, n_waves, grid, st);
-    return launch_inst<Q8, RM, NJ, 0>(args, n_waves, grid, st);
+    return streamed(One{}, std::bool_constant<RM>{});
 }
 
 template <bool Q8, bool RM = false>

@@ -45,3 +45,32 @@ def test_row_major_rows_of_every_kind(out, inn, n):
     t.check(bd.linear_multitenant(t.x, t.w, table, t.tok), what=f"{out}x{inn} {n}")
     t.check(bd.linear_multitenant_q8(t.x, q, scale, table, t.tok), q.double() * scale.double()[:, None], f"{out}x{inn} {n} 8-bit base",
             extra=(2304.0 * scale.double())[None, :] * t.x.double().abs().sum(dim=1, keepdim=True))
+
+
+# Streamed x: a workgroup's row blocks are multiplied two at a time where two of one matrix are left.  More row blocks than compute
+# units, so that workgroups have 2, 3 and 4 of them, odd numbers at the end of a matrix and of the launch; `in` whole k tiles, half
+# and ragged ones, one and several per wavefront.
+@pytest.mark.parametrize("counts", [[1, 2], [1] * 11, [16], [3] * 10, [30, 2]])
+@pytest.mark.parametrize("out,inn", [(4160, 640), (8208, 2176), (12300, 2336), (16400, 2304)])
+def test_row_blocks_in_pairs(out, inn, counts):
+    t = Tensors(out, inn, tokens_of(counts, "shuffled"), len(counts), seed=len(counts))
+    what = f"{out}x{inn} {counts}"
+    nan = lambda n=out: torch.full((len(t.tok), n), float("nan"), dtype=torch.float16, device=DEV)
+    signs = [bd.tile_signs(p, out, inn) for p in t.packed]
+    tiled, wt = bd.TiledTenantTable(signs, t.alpha), bd.tile_base(t.w)
+    y = bd.linear_multitenant_tiled(t.x, wt, out, tiled, t.tok, y=nan())
+    t.check(y, what=what + " tiled")
+    # matrices that end inside a workgroup's row blocks: each gives the bits of its own call
+    group = bd.TiledGroup([wt, wt, wt], [out, 48, 2000], [tiled] * 3)
+    for part, n in zip(bd.linear_multitenant_tiled_group(t.x, group, t.tok, ys=[nan(), nan(48), nan(2000)]), (out, 48, 2000)):
+        assert torch.equal(part, y[:, :n]), what + f" group, {n} rows"
+    two = bd.TiledPlaneTable([[s, s] for s in signs], t.alpha.repeat_interleave(2) * 0.5)
+    t.check(bd.linear_multitenant_tiled_kbit(t.x, wt, out, two, t.tok, y=nan()), what=what + " two planes of half the scale")
+    q, scale = bd.quantize_base_q8(t.w)
+    w8 = q.double() * scale.double()[:, None]
+    extra = t.x.double().abs() @ torch.full_like(w8, 2 * 1152.0 / 127).mul_(w8.abs().amax(dim=1, keepdim=True)).t()
+    t.check(bd.linear_multitenant_tiled_q8(t.x, bd.tile_base_q8(q, scale), out, tiled, t.tok, y=nan()), w8, what + " 8-bit base", extra)
+    if inn % 128 == 0:
+        table = bd.TenantTable(t.packed, t.alpha)
+        t.check(bd.linear_multitenant(t.x, t.w, table, t.tok, y=nan()), what=what + " row-major")
+        t.check(bd.linear_multitenant_q8(t.x, q, scale, table, t.tok, y=nan()), w8, what + " row-major, 8-bit base", extra)
