@@ -13,7 +13,7 @@ OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libbitdelta.so")
 
 SOURCES = ["bitdelta_api.hip", "compress_kernels.hip", "linear_rowwave.hip", "linear_decode_rowmajor.hip", "linear_decode_rowmajor_q8.hip",
-           "linear_decode_tiled.hip", "linear_decode_tiled_q8.hip", "tile_kernels.hip", "linear_prefill.hip", "linear_prefill_big.hip", "linear_wide.hip", "baseline_kernels.hip", "delta_image.hip"]
+           "linear_decode_tiled.hip", "linear_decode_tiled_q8.hip", "tile_kernels.hip", "linear_prefill.hip", "linear_prefill_big.hip", "linear_wide.hip", "linear_panel.hip", "baseline_kernels.hip", "delta_image.hip"]
 
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-ffp-contract=off",

@@ -95,6 +95,9 @@ struct WideArgs {
     uint16_t col_token[kWideMaxTiles][16];
 };
 hipError_t launch_linear_wide(const WideArgs& args, int row_blocks_per_group, bool rowmajor, hipStream_t st);
+// the same products on the row-major tensors, panels of four row blocks (linear_panel.hip)
+constexpr int kPanelRowBlocks = 4, kPanelMaxChunk = 5;
+hipError_t launch_linear_panel(const WideArgs& args, hipStream_t st);
 
 // 8-bit round-to-nearest base: q [out, in] int8 and one binary32 scale per row; the compressor against scale * q
 hipError_t launch_quantize_rtn8(const uint16_t* w, int64_t out, int64_t in, int8_t* q, float* scale, hipStream_t st);

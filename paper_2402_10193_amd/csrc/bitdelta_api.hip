@@ -284,8 +284,8 @@ double wide_units(int64_t in, bool rowmajor) {
     return steps_of_waves(u);
 }
 
-// How a launch of n column tiles is cut: row blocks per workgroup (1 or 2), column tiles per workgroup, and its estimated
-// time: workgroups take turns on the compute units of their XCD (LDS allows one at a time, the row blocks are dealt to the XCDs), some 4 us
+// How a launch of n column tiles is cut: row blocks per workgroup (1 or 2; kPanelRowBlocks: the panel kernel), column tiles per workgroup, and its
+// estimated time: workgroups take turns on the compute units of their XCD (LDS allows one at a time, the row blocks are dealt to the XCDs), some 4 us
 // around the loop of each, and every chunk fetches the base again.  Fitted to 3480 times: the batches described at BatchShape, every
 // split.  10 % at the 10 % and 90 % quantiles; the split it picks is the quickest or within 7 % of it in 95 % of the batches.
 struct WidePlan {
@@ -304,6 +304,20 @@ WidePlan wide_plan(int n, int64_t out, int64_t in, int cus, bool rowmajor) {
             const double loop = units * (run - 1) * (rowmajor ? (R == 1 ? 0.52 : 0.79) : (R == 1 ? 0.48 : 0.69));
             const double us = (double)rounds * ((rowmajor ? 3.9 : 4.1) + loop) + (double)chunks * (double)out * (double)in * (rowmajor ? 0.15e-6 : 0.11e-6);
             if (us < best.us) best = WidePlan{R, std::min(run, n), us};
+        }
+    }
+    // The panel kernel (row-major): one workgroup per compute unit too, some 3 us around its loop, 0.31 us per iteration and column tile.
+    // Fitted to 90 batches of 33 to 700 tokens on 300 .. 12000 x 512 .. 11520 with every chunk size: 7.5 % at the 10 % and 90 % quantiles, its
+    // pick within 5 % of the quickest in all of them.  Where it lies against the others (us, the other ways' best / panel): 4096 x 4096 200 tokens of
+    // 16 tenants 55 / 34, 11008 x 4096 500 of 32 285 / 220, 1280 x 3278 604 of 64 90 / 54; with few rows or one token per tenant the others win:
+    // 996 x 7680 154 of 7 21 / 28, 330 x 2816 87 of 4 10 / 14, 6828 x 8320 58 of 51 241 / 324.
+    if (rowmajor) {
+        const int64_t groups = (rb + bd::kPanelRowBlocks - 1) / bd::kPanelRowBlocks, iterations = (in / 128 + 1) / 2;
+        for (int run = 2; run <= bd::kPanelMaxChunk; ++run) {
+            const int chunks = (n + run - 1) / run;
+            const int64_t rounds = ((groups + 7) / 8 * chunks + per_xcd - 1) / per_xcd;
+            const double us = (double)rounds * (3.4 + 0.306 * (double)(iterations * run)) + (double)chunks * (double)out * (double)in * 0.074e-6;
+            if (us < best.us) best = WidePlan{bd::kPanelRowBlocks, std::min(run, n), us};
         }
     }
     return best;
@@ -356,7 +370,7 @@ hipError_t run_wide(const WideTiles& t, const uint16_t* x, const uint16_t* w, co
             if (tiled_host) a.signs[i] = tiled_host[a.tenant[i]];
             std::memcpy(a.col_token[i], &t.token[(size_t)(first + i) * 16], 32);
         }
-        const hipError_t e = bd::launch_linear_wide(a, p.R, packed_dev != nullptr, st);
+        const hipError_t e = p.R == bd::kPanelRowBlocks ? bd::launch_linear_panel(a, st) : bd::launch_linear_wide(a, p.R, packed_dev != nullptr, st);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

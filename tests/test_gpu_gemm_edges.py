@@ -147,6 +147,32 @@ def test_wide_every_split(out, inn, counts, variant):
     assert torch.equal(*(bd.linear_multitenant_tiled(t.x, wt, out, large, t.tok, variant=v) for v in (variant, 2))), what
 
 
+# Panels of four row blocks (row-major, variant 10 where the plan prefers them): chunks of 2 to 5 column tiles, the last one partly
+# filled; one, two, an odd number and more than four units per half of `in`, the second half a unit shorter or empty; `out` that
+# ends inside a row block, a panel, and not at a multiple of four.
+@pytest.mark.parametrize("tiles", [8, 11, 16, 19, 20, 66])
+@pytest.mark.parametrize("out,inn", [(4096, 128), (4090, 256), (4033, 384), (4050, 1152), (4067, 1280), (2050, 2304)])
+def test_wide_panels(out, inn, tiles):
+    counts = [[16, 3, 1, 15, 9][i % 5] for i in range(tiles - 2)] + [17]
+    t = Tensors(out, inn, tokens_of(counts, "shuffled"), len(counts), seed=tiles)
+    table = bd.TenantTable(t.packed, t.alpha)
+    what = f"panels {out}x{inn} {tiles} tiles"
+    y = torch.full((len(t.tok), out), float("nan"), dtype=torch.float16, device=DEV)
+    t.check(bd.linear_multitenant(t.x, t.w, table, t.tok, y=y, variant=10), what=what)
+    assert torch.equal(bd.linear_multitenant(t.x, t.w, table, t.tok, variant=10), y), what       # bitwise reproducible
+    # infinities and NaN stay in their token and their row; an infinite scale gives the sign of the +-1 sum
+    t.x[5, inn - 1], t.x[9, 0], t.w[out - 1, 3] = float("inf"), float("nan"), float("nan")
+    alpha = t.alpha.clone()
+    alpha[t.tok[0]] = float("inf")
+    bad = bd.linear_multitenant(t.x, t.w, bd.TenantTable(t.packed, alpha), t.tok, variant=10)
+    keep = [i for i, e in enumerate(t.tok) if i not in (5, 9) and e != t.tok[0]]
+    assert torch.equal(bad[keep][:, :-1], y[keep][:, :-1]) and torch.isnan(bad[9]).all() and torch.isnan(bad[:, -1]).all()
+    assert not torch.isfinite(bad[5]).any()
+    s = t.x[0].double() @ expand(t.packed[t.tok[0]], inn).t()
+    sure = (s.abs() > 1e-3) & (torch.arange(out, device=DEV) < out - 1)
+    assert torch.equal(bad[0][sure], torch.where(s > 0, float("inf"), float("-inf")).half()[sure])
+
+
 def test_a_token_on_the_serving_layout_does_not_depend_on_its_batch():
     """Batches of 1, 2, 31, 90 and 200 tokens and a group of two matrices: the same bits for the same token."""
     out, inn, counts = 528, 1536, [3, 40, 9, 1, 17, 0, 60, 20, 50]
