@@ -133,9 +133,17 @@ def workspace_bytes(op: int, T: int, out: int, inn: int, n_tenants: int) -> int:
     return int(lib().bd_workspace_bytes(int(op), T, out, inn, n_tenants))
 
 
+# The handle of the current stream without the Stream object around it: torch.cuda.current_stream().cuda_stream takes 2.9 us, a third of
+# what the host spends on a small call (8.5 us, of which the launch itself 6), this 0.2.
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream) -> int:
     if stream is None:
-        return int(torch.cuda.current_stream().cuda_stream)
+        if _current_raw_stream is None or _current_device is None or not torch.cuda.is_initialized():
+            return int(torch.cuda.current_stream().cuda_stream)
+        return int(_current_raw_stream(_current_device()))
     if isinstance(stream, torch.cuda.Stream):
         return int(stream.cuda_stream)
     return int(stream)

@@ -162,3 +162,16 @@ def test_tiled_group_equals_separate_calls(ref):
         assert torch.equal(ys[i], y1), i
         _, y32 = ref.linear_multitenant(to_np(x), p.w_base_np, p.packed_np, p.alpha_np, tok)
         check_close(ys[i], y32, f"group matrix {i}")
+
+
+def test_calls_go_to_the_current_stream():
+    """The handle that a call without a stream takes is the current stream's: the default one, one made current, and the outer
+    one again behind it."""
+    assert bd._stream(None) == torch.cuda.current_stream().cuda_stream
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        assert bd._stream(None) == s.cuda_stream != 0
+        with torch.cuda.stream(torch.cuda.default_stream()):
+            assert bd._stream(None) == torch.cuda.default_stream().cuda_stream
+        assert bd._stream(None) == s.cuda_stream == bd._stream(s)
+    assert bd._stream(None) == torch.cuda.current_stream().cuda_stream
