@@ -317,12 +317,14 @@ bd_status bd_linear_multitenant_q8(const uint16_t* x_f16, const int8_t* q, const
 
 /* The GEMM form (the prefill regime of Sec. 4.3, many tokens per tenant) of the two extensions of Sec. 4.2, for any
  * T >= 1 (T <= 65535): tokens are sorted by tenant and cut into tiles of 128 rows that never mix tenants, every tile
- * is a matrix-core GEMM over `in` (tiles of 128 x 128 of y, 128 x 256 for the 8-bit base).  Tensors row-major as
+ * is a matrix-core GEMM over `in` (tiles of 128 x 128 of y, 128 x 256 for the 8-bit base); prompts of a few tokens, or few rows of y, run
+ * in panels of 64 rows by column tiles of 16 tokens where an estimate says that this is quicker (in % 64 == 0, k <= 4).  Tensors row-major as
  * bd_compress_iterated / bd_quantize_base_q8 + bd_compress_q8 write them; in % 32 == 0.
  *   workspace   bd_workspace_bytes(BD_OP_LINEAR_GEMM, T, out, in, n_tenants) bytes, 256-byte aligned, device memory;
  *               holds the token tables of this call until the launch has run (one call at a time per workspace)
  * _gemm_kbit (fidelity of Delta, k planes): y[t] = x[t] W_base^T + x[t] D_e^T with D_e = sum_j alpha[e*k+j] S_{e,j}
- *   added up in fp16 in ascending j (one rounding per plane; 2^-11 of the delta term against the exact sum);
+ *   added up in fp16 in ascending j (one rounding per plane; 2^-11 of the delta term against the exact sum), or, in panels, every
+ *   plane's +-1 sum on its own in binary32;
  *   planes_by_tenant, alpha_by_tenant as for bd_linear_multitenant_kbit; k outside 1..BD_MAX_PLANES: BD_ERR_SHAPE.
  * _gemm_q8 (quantized base models): y[t,n] = wscale[n] * sum_k x[t,k] q[n,k] + alpha[e] * (x[t] S_e^T)[n];
  *   q [out, in] int8, wscale [out] binary32 (device), packed_by_tenant / alpha_by_tenant as for bd_linear_multitenant.

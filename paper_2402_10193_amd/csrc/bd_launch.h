@@ -93,11 +93,14 @@ struct WideArgs {
     const uint32_t* signs[kWideMaxTiles];       // tiled: the tile's tenant's delta
     int32_t tenant[kWideMaxTiles];
     uint16_t col_token[kWideMaxTiles][16];
+    const float* wscale;                        // panels: w is the int8 base [out, in] and this its row scales
 };
 hipError_t launch_linear_wide(const WideArgs& args, int row_blocks_per_group, bool rowmajor, hipStream_t st);
-// the same products on the row-major tensors, panels of four row blocks (linear_panel.hip)
-constexpr int kPanelRowBlocks = 4, kPanelMaxChunk = 5;
-hipError_t launch_linear_panel(const WideArgs& args, hipStream_t st);
+// the same products on the row-major tensors, panels of four row blocks (linear_panel.hip): planes > 1: tables indexed by tenant * planes + plane;
+// args.wscale: the 8-bit base.  in % 64 == 0, args.units counts a half unit as one.
+constexpr int kPanelRowBlocks = 4, kPanelMaxPlanes = 4;
+constexpr int panel_max_chunk(int planes) { return planes == 1 ? 5 : planes == 2 ? 4 : planes == 3 ? 3 : 2; }   // column tiles of a workgroup
+hipError_t launch_linear_panel(const WideArgs& args, int planes, hipStream_t st);
 
 // 8-bit round-to-nearest base: q [out, in] int8 and one binary32 scale per row; the compressor against scale * q
 hipError_t launch_quantize_rtn8(const uint16_t* w, int64_t out, int64_t in, int8_t* q, float* scale, hipStream_t st);

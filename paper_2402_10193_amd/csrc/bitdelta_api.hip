@@ -284,14 +284,45 @@ double wide_units(int64_t in, bool rowmajor) {
     return steps_of_waves(u);
 }
 
-// How a launch of n column tiles is cut: row blocks per workgroup (1 or 2; kPanelRowBlocks: the panel kernel), column tiles per workgroup, and its
-// estimated time: workgroups take turns on the compute units of their XCD (LDS allows one at a time, the row blocks are dealt to the XCDs), some 4 us
-// around the loop of each, and every chunk fetches the base again.  Fitted to 3480 times: the batches described at BatchShape, every
-// split.  10 % at the 10 % and 90 % quantiles; the split it picks is the quickest or within 7 % of it in 95 % of the batches.
 struct WidePlan {
     int R, per_chunk;
     double us;
 };
+
+// The panel kernel on n column tiles (row-major): one workgroup per compute unit at a time, some 4 us around its loop, and per iteration and column
+// tile 0.31 us (8-bit base 0.29, k planes 0.03 + 0.18 k).  Fitted to 90 batches of 33 to 700 tokens on 300 .. 12000 x 512 .. 11520 (fp16, one plane) and
+// to 100 of 24 to 4096 tokens on 500 .. 11008 x 512 .. 11008 (50 over the 8-bit base, 50 with 2 to 4 planes) with every chunk size: 8 % at the 10 % and
+// 90 % quantiles; the chunk it picks is the quickest in all but a few.
+WidePlan panel_plan(int n, int64_t out, int64_t in, int cus, int planes, bool q8) {
+    WidePlan best{0, 0, 1e30};
+    const int64_t groups = (bd::tiled_row_blocks(out) + bd::kPanelRowBlocks - 1) / bd::kPanelRowBlocks, iterations = ((in + 127) / 128 + 1) / 2;
+    const int64_t per_xcd = std::max(1, cus / 8);
+    const double fixed = q8 ? 4.1 : planes == 1 ? 3.4 : 3.8, tile = q8 ? 0.29 : planes == 1 ? 0.306 : 0.03 + 0.183 * planes;
+    for (int run = 2; run <= bd::panel_max_chunk(planes); ++run) {
+        const int chunks = (n + run - 1) / run;
+        const int64_t rounds = ((groups + 7) / 8 * chunks + per_xcd - 1) / per_xcd;
+        const double us = (double)rounds * (fixed + tile * (double)(iterations * run)) + (double)chunks * (double)out * (double)in * (q8 ? 0.065e-6 : 0.075e-6);
+        if (us < best.us) best = WidePlan{bd::kPanelRowBlocks, std::min(run, n), us};
+    }
+    return best;
+}
+double panel_us(int n_all, int64_t out, int64_t in, int cus, int planes, bool q8) {
+    double us = 3.5;
+    const int launches = (n_all + bd::kWideMaxTiles - 1) / bd::kWideMaxTiles;
+    for (int l = 0; l < launches; ++l)
+        us += panel_plan((int)((int64_t)n_all * (l + 1) / launches - (int64_t)n_all * l / launches), out, in, cus, planes, q8).us;
+    return us;
+}
+// What panels of any kind take: whole units or one half unit at the end of a row, 32-bit offsets, token ids below the mark of an empty column
+bool panel_fits(int64_t T, int64_t out, int64_t in, int planes, bool q8) {
+    return planes >= 1 && planes <= bd::kPanelMaxPlanes && in >= 128 && in % 64 == 0 && out >= 1 && T < 65535 &&
+           (uint64_t)T * (uint64_t)in * 2 < ((uint64_t)1 << 32) && (uint64_t)out * (uint64_t)in * (q8 ? 1 : 2) < ((uint64_t)1 << 32);
+}
+
+// How a launch of n column tiles is cut: row blocks per workgroup (1 or 2; kPanelRowBlocks: the panel kernel), column tiles per workgroup, and its
+// estimated time: workgroups take turns on the compute units of their XCD (LDS allows one at a time, the row blocks are dealt to the XCDs), some 4 us
+// around the loop of each, and every chunk fetches the base again.  Fitted to 3480 times: the batches described at BatchShape, every
+// split.  10 % at the 10 % and 90 % quantiles; the split it picks is the quickest or within 7 % of it in 95 % of the batches.
 WidePlan wide_plan(int n, int64_t out, int64_t in, int cus, bool rowmajor) {
     WidePlan best{0, 0, 1e30};
     const int64_t rb = bd::tiled_row_blocks(out), per_xcd = std::max(1, cus / 8);
@@ -306,19 +337,12 @@ WidePlan wide_plan(int n, int64_t out, int64_t in, int cus, bool rowmajor) {
             if (us < best.us) best = WidePlan{R, std::min(run, n), us};
         }
     }
-    // The panel kernel (row-major): one workgroup per compute unit too, some 3 us around its loop, 0.31 us per iteration and column tile.
-    // Fitted to 90 batches of 33 to 700 tokens on 300 .. 12000 x 512 .. 11520 with every chunk size: 7.5 % at the 10 % and 90 % quantiles, its
-    // pick within 5 % of the quickest in all of them.  Where it lies against the others (us, the other ways' best / panel): 4096 x 4096 200 tokens of
+    // The panel kernel, row-major.  Where it lies against the others (us, the other ways' best / panel): 4096 x 4096 200 tokens of
     // 16 tenants 55 / 34, 11008 x 4096 500 of 32 285 / 220, 1280 x 3278 604 of 64 90 / 54; with few rows or one token per tenant the others win:
     // 996 x 7680 154 of 7 21 / 28, 330 x 2816 87 of 4 10 / 14, 6828 x 8320 58 of 51 241 / 324.
     if (rowmajor) {
-        const int64_t groups = (rb + bd::kPanelRowBlocks - 1) / bd::kPanelRowBlocks, iterations = (in / 128 + 1) / 2;
-        for (int run = 2; run <= bd::kPanelMaxChunk; ++run) {
-            const int chunks = (n + run - 1) / run;
-            const int64_t rounds = ((groups + 7) / 8 * chunks + per_xcd - 1) / per_xcd;
-            const double us = (double)rounds * (3.4 + 0.306 * (double)(iterations * run)) + (double)chunks * (double)out * (double)in * 0.074e-6;
-            if (us < best.us) best = WidePlan{bd::kPanelRowBlocks, std::min(run, n), us};
-        }
+        const WidePlan panel = panel_plan(n, out, in, cus, 1, false);
+        if (panel.us < best.us) best = panel;
     }
     return best;
 }
@@ -343,10 +367,11 @@ bool wide_fits(int64_t T, int64_t out, int64_t in) {
            (uint64_t)(bd::tiled_row_blocks(out) * bd::tiled_k_tiles(in)) * bd::kTileBaseBytes < ((uint64_t)1 << 32);
 }
 
-// packed_dev: the row-major tensors (device pointer table); otherwise w is the tiled base and tiled_host the tenants' tiled deltas
+// packed_dev: the row-major tensors (device pointer table); otherwise w is the tiled base and tiled_host the tenants' tiled deltas.
+// panel_planes > 0: panels, with that many planes per tenant (tables indexed by tenant * planes + plane) or, wscale given, the int8 base
 hipError_t run_wide(const WideTiles& t, const uint16_t* x, const uint16_t* w, const uint32_t* const* packed_dev,
                     const uint32_t* const* tiled_host, const float* alpha, uint16_t* y, int64_t out, int64_t in, hipStream_t st,
-                    int split = 0) {
+                    int split = 0, int panel_planes = 0, const float* wscale = nullptr) {
     const int cus = cus_or_256(), n_all = (int)t.tenant.size(), launches = (n_all + bd::kWideMaxTiles - 1) / bd::kWideMaxTiles;
     for (int l = 0; l < launches; ++l) {
         const int first = (int)((int64_t)n_all * l / launches), n = (int)((int64_t)n_all * (l + 1) / launches) - first;
@@ -360,17 +385,18 @@ hipError_t run_wide(const WideTiles& t, const uint16_t* x, const uint16_t* w, co
         a.out = (int32_t)out;
         a.in = (int32_t)in;
         a.KT = (int32_t)bd::tiled_k_tiles(in);
-        a.units = (int32_t)(in / 128);
+        a.units = (int32_t)((in + 127) / 128);   // (in % 128 == 0 but for panels)
+        a.wscale = wscale;
         a.row_blocks = (int32_t)bd::tiled_row_blocks(out);
         a.n_tiles = n;
-        const WidePlan p = split ? WidePlan{split >> 4, std::min(split & 15, n), 0.0} : wide_plan(n, out, in, cus, packed_dev != nullptr);
+        const WidePlan p = panel_planes ? panel_plan(n, out, in, cus, panel_planes, wscale != nullptr) : split ? WidePlan{split >> 4, std::min(split & 15, n), 0.0} : wide_plan(n, out, in, cus, packed_dev != nullptr);
         a.tiles_per_chunk = p.per_chunk;
         for (int i = 0; i < n; ++i) {
             a.tenant[i] = t.tenant[(size_t)(first + i)];
             if (tiled_host) a.signs[i] = tiled_host[a.tenant[i]];
             std::memcpy(a.col_token[i], &t.token[(size_t)(first + i) * 16], 32);
         }
-        const hipError_t e = p.R == bd::kPanelRowBlocks ? bd::launch_linear_panel(a, st) : bd::launch_linear_wide(a, p.R, packed_dev != nullptr, st);
+        const hipError_t e = p.R == bd::kPanelRowBlocks ? bd::launch_linear_panel(a, std::max(panel_planes, 1), st) : bd::launch_linear_wide(a, p.R, packed_dev != nullptr, st);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -456,6 +482,24 @@ double gemm_us(const BatchShape& s, int64_t out, int64_t in, bool big, int cus) 
     const double full = 2.7 + steps * (s.tiles32 * 0.75 + s.tiles64 * 1.3 + s.tiles128 * 1.77) / (double)mtiles;
     const double rounds = (double)(tiles / cus) * full + (last == 0 ? 0.0 : 2 * last <= cus ? 2.7 + 0.68 * steps : full);
     return tables + std::max(rounds, (double)out * (double)in * (2.0 + (double)s.active / 8.0) / 2.9e6);
+}
+// The GEMM over the 8-bit base (its tiles as above, 0.62, 1.37 and 1.76 us per step and 7.7 around them) and with k planes (128 x 128 tiles, two workgroups per compute
+// unit: 1.2 + 0.4 k us per step while there is one of them per unit, 1.23 + 0.83 k where there are two; a few units with two take 60 % of that way,
+// half of them all of it: three planes, 272 workgroups on 256 units 189 us, 222 in panels).  Fitted to 100 prompts of 24 to 4096 tokens of 1 to 16 tenants on
+// 500 .. 11008 x 512 .. 11008: 14 % and 9 % at the 10 % and 90 % quantiles.
+double gemm_extended_us(const BatchShape& s, int64_t out, int64_t in, bool big, int planes, bool q8, int cus) {
+    if (q8 && !big) return gemm_us(s, out, in, false, cus);
+    const double steps = (double)in / 64.0;
+    const int64_t mtiles = s.tiles32 + s.tiles64 + s.tiles128, runs = s.runs + 3 * mtiles;
+    const int64_t by_value = (mtiles * (bd::kPrefillTile + 1) + 959) / 960, by_run = (runs + 319) / 320;
+    const double tables = 2.0 + (by_run < by_value ? 0.1 * (double)runs : 2.2 * (double)by_value);
+    if (!q8) {
+        const double per_unit = (double)(mtiles * ((out + 127) / 128)) / cus, one = 1.2 + 0.4 * planes, two = 1.23 + 0.83 * planes;
+        return tables + 3.3 + steps * (per_unit <= 1.0 ? one : per_unit < 1.5 ? one + (two - one) * (0.6 + 0.8 * (per_unit - 1.0)) : std::max(1.0, per_unit / 2.0) * two);
+    }
+    const int64_t tiles = mtiles * ((out + 255) / 256), last = tiles % cus;
+    const double step = (s.tiles32 * 0.62 + s.tiles64 * 1.37 + s.tiles128 * 1.76) / (double)mtiles;
+    return tables + (double)(tiles / cus) * (7.7 + steps * step) + (last == 0 ? 0.0 : 7.7 + steps * (2 * last <= cus ? std::min(0.8, step) : step));
 }
 // k tiles of the wavefronts of a decode launch
 double decode_k_tiles(int64_t in, bool rowmajor) {
@@ -1081,7 +1125,23 @@ static bd_status gemm_entry(const uint16_t* x_f16, const void* w, size_t w_bytes
     // The 8-bit base: 128 x 256 tiles where whole 64-wide steps and a full tile's width of output rows are there, as for fp16.
     // (k planes stay on the 128 x 128 tiles: their sums are formed in fp16 in LDS, which the large tile has no room for.)
     const bool big = wscale && k_planes == 0 && out >= 256 && bd::prefill_big_fits(T, out, in);
-    return run_prefill(x_f16, w, packed_by_tenant, alpha_by_tenant, tenant_of_token, order_by_tenant(tenant_of_token, T, n_tenants), y_f16, T, out, in, workspace,
+    const std::vector<int32_t> order = order_by_tenant(tenant_of_token, T, n_tenants);
+    // Few tokens per tenant, few rows: the GEMM's tiles are mostly padding and too few to fill the chip, each a serial chain of `in` / 64 steps.  The
+    // panel kernel splits `in` between its wavefronts and pads to 16 tokens (us, GEMM / panels; two planes: 29 tokens of 11 tenants on 724 x 2880
+    // 95 / 18, 731 of 4 on 2846 x 8960 290 / 175, 1588 of 14 on 5149 x 8960 678 / 663, 1270 of 5 on 5318 x 704 45 / 86; 8-bit base: 46 of 6 on 2884 x 7424
+    // 84 / 31, 648 of 14 on 1875 x 3456 59 / 45, 717 of 5 on 4705 x 4608 106 / 117).  It is taken where its estimate is clearly the lower one.
+    const int planes = std::max(k_planes, 1);
+    if (panel_fits(T, out, in, planes, wscale != nullptr)) {
+        const BatchShape shape = batch_shape(tenant_of_token, order);
+        const int cus = cus_or_256();
+        // 0.87: the two estimates miss by about a tenth each way; at 0.9 two of 150 prompts took panels 5 and 15 % above the GEMM, at 0.87 none of 250
+        if (panel_us(shape.tiles16, out, in, cus, planes, wscale != nullptr) < 0.87 * gemm_extended_us(shape, out, in, big, planes, wscale != nullptr, cus))
+            return run_wide(wide_tiles(tenant_of_token, order), x_f16, (const uint16_t*)w, packed_by_tenant, nullptr, alpha_by_tenant, y_f16, out, in,
+                            (hipStream_t)stream, 0, planes, wscale) == hipSuccess
+                       ? BD_OK
+                       : BD_ERR_DEVICE;
+    }
+    return run_prefill(x_f16, w, packed_by_tenant, alpha_by_tenant, tenant_of_token, order, y_f16, T, out, in, workspace,
                        (hipStream_t)stream, big ? 4 : 0, big, k_planes, wscale) == hipSuccess
                ? BD_OK
                : BD_ERR_DEVICE;

@@ -70,6 +70,45 @@ def test_gemm_q8_tiles(out, inn, counts):
     t.check(y, q.double() * scale.double()[:, None], f"q8 {out}x{inn} {counts}")
 
 
+# The same entry points with a few tokens per tenant, which panels of 64 output rows take: `in` of whole and half units of 128, one to
+# many per half of the row, the half unit in either half; `out` that ends inside a row block, a panel, not at a multiple of four;
+# every number of column tiles per workgroup (by the number of them on some 4096 rows) and several launches' worth.
+PANELS = [(16, 128, [17]), (41, 1152, [20, 1, 33, 16, 0, 15, 40]), (373, 2240, [9, 31, 2, 5]), (24, 192, [40, 7]), (64, 704, [9] * 40 + [16] * 30),
+          (35, 4480, [12, 18, 30]), (203, 448, [5, 40]), (1, 320, [3]),
+          (4090, 192, [3] * 8), (4033, 576, [16] * 11 + [1]), (4096, 320, [5] * 16), (4096, 192, [2] * 20)]
+
+
+@pytest.mark.parametrize("k", [0, 1, 2, 3, 4])   # 0: the 8-bit base
+@pytest.mark.parametrize("case", range(len(PANELS)))
+def test_gemm_forms_in_panels(case, k):
+    out, inn, counts = PANELS[case]
+    t = Tensors(out, inn, tokens_of(counts, "shuffled"), len(counts), seed=case)
+    what = f"{out}x{inn} {counts} k {k}"
+    y = torch.full((len(t.tok), out), float("nan"), dtype=torch.float16, device=DEV)
+    if k == 0:
+        q, scale = bd.quantize_base_q8(t.w)
+        bd.linear_multitenant_gemm_q8(t.x, q, scale, bd.TenantTable(t.packed, t.alpha), t.tok, y=y)
+        return t.check(y, q.double() * scale.double()[:, None], what)
+    g = torch.Generator(device=DEV).manual_seed(case)
+    planes = [[p] + [torch.randint(-2**31, 2**31, p.shape, dtype=torch.int64, device=DEV, generator=g).to(torch.int32) for _ in range(k - 1)]
+              for p in t.packed]
+    alpha = (t.alpha[:, None] * 0.55 ** torch.arange(k, device=DEV)).half().float()
+    table = bd.PlaneTable([torch.stack(p) for p in planes], alpha.reshape(-1))
+    bd.linear_multitenant_gemm_kbit(t.x, t.w, table, t.tok, y=y)
+    x, w64 = t.x.double(), t.w.double()
+    exact, mag, delta = x @ w64.t(), x.abs() @ w64.abs().t(), torch.zeros((len(t.tok), 1), dtype=torch.float64, device=DEV)
+    for e in set(t.tok):
+        rows = torch.tensor([i for i, f in enumerate(t.tok) if f == e], device=DEV)
+        for j in range(k):
+            exact[rows] += alpha[e, j].double() * (x[rows] @ expand(planes[e][j], inn).t())
+            delta[rows] += alpha[e, j].double() * x[rows].abs().sum(dim=1, keepdim=True)
+    # the bound of `check`, and 2^-11 of the planes' sum per weight and plane where the GEMM's tiles form it in fp16
+    bound = 2.0**-11 * exact.abs() + 2.0**-25 + inn**0.5 * 2.0**-23 * (mag + delta) + k * 2.0**-11 * delta / inn**0.5
+    worst = ((y.double() - exact).abs() / bound).max().item()
+    assert worst <= 1.0, (what, worst)
+    assert torch.equal(bd.linear_multitenant_gemm_kbit(t.x, t.w, table, t.tok), y), what
+
+
 # More than 32 tokens with a few per tenant, as the library chooses to run them (which kernel that is, an estimate says),
 # against float64; the kernel of 16-column tiles by its number: test_wide_every_split.
 # Rows of `out` around one and two row blocks, one unit of `in` and counts that are no multiple of the eight wavefronts,
