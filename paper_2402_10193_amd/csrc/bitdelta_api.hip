@@ -338,7 +338,7 @@ WidePlan wide_plan(int n, int64_t out, int64_t in, int cus, bool rowmajor) {
         }
     }
     // The panel kernel, row-major.  Where it lies against the others (us, the other ways' best / panel): 4096 x 4096 200 tokens of
-    // 16 tenants 55 / 34, 11008 x 4096 500 of 32 285 / 220, 1280 x 3278 604 of 64 90 / 54; with few rows or one token per tenant the others win:
+    // 16 tenants 55 / 34, 11008 x 4096 500 of 32 285 / 220, 3278 x 1280 604 of 64 90 / 54; with few rows or one token per tenant the others win:
     // 996 x 7680 154 of 7 21 / 28, 330 x 2816 87 of 4 10 / 14, 6828 x 8320 58 of 51 241 / 324.
     if (rowmajor) {
         const WidePlan panel = panel_plan(n, out, in, cus, 1, false);
@@ -521,6 +521,32 @@ double decode_us(const BatchShape& s, int64_t row_blocks, double elems, int64_t 
         else us += 6.1 + std::max(tasks * ct * (1.65 + 0.21 * slots), bytes / 2.9e6);
     }
     return us;
+}
+// Row-major batches that fit one decode launch.  That launch takes every job slot through every fetch and waits for memory once per task; the
+// wide and panel kernels pad each tenant to 16 columns but share what they fetch between them (us, decode / the other): 4501 x 512 31 tokens of 2
+// tenants 14.6 / 7.3, 994 x 640 29 of 17 15.6 / 7.2, 953 x 4736 24 of 6 19.3 / 13.5, 11578 x 9216 21 of 2 73 / 54; 11708 x 4224 9 of 9 49 / 77,
+// 5827 x 2304 9 of 8 18 / 22, 3173 x 10624 2 of 2 22 / 28.  Both estimates are fitted to 500 batches of 1 to 32 tokens on 300 .. 12000 x 512 .. 11520
+// (decode 15 %, the others 8 % at the 10 % and 90 % quantiles) apart from those above, which are for several launches or many column tiles.
+bool few_tokens_wide(const BatchShape& s, int64_t out, int64_t in, int cus) {
+    const double elems = (double)out * (double)in, bytes = elems * (2.0 + (double)s.active / 8.0), units = wide_units(in, true);
+    const auto& l = s.launches[0];
+    const double tasks = (double)((bd::tiled_row_blocks(out) + cus - 1) / cus) * decode_k_tiles(in, true) * (l.tokens > 16 ? 2.0 : 1.0);
+    const double by_decode = 5.35 + std::max(tasks * (1.73 + 0.273 * (double)((l.jobs + 1) / 2 * 2)), bytes / 4.0e6);
+    const double limit = 0.86 * by_decode;   // at 0.88 none of 1000 is slower by more than 2.6 %, at 1.0 19 of 500 are by 3 to 15 %
+    const double least = 5.7 + bytes / 3.96e6;
+    if (limit <= std::max(least, 4.8 + 1.31 * units)) return false;   // no plan is quicker: the smallest calls need no search
+    const int n = s.tiles16;
+    const WidePlan p = wide_plan(n, out, in, cus, true);
+    const int64_t groups = (bd::tiled_row_blocks(out) + p.R - 1) / p.R, chunks = (n + p.per_chunk - 1) / p.per_chunk, per_xcd = std::max(1, cus / 8);
+    const double rounds = (double)(((groups + 7) / 8 * chunks + per_xcd - 1) / per_xcd);
+    double us = 1.5;
+    if (p.R == bd::kPanelRowBlocks)
+        us += rounds * (4.0 + 0.367 * (double)(((in + 127) / 128 + 1) / 2 * std::max(2, p.per_chunk))) + (double)chunks * elems * 0.064e-6;
+    else if (p.R == 2)
+        us += rounds * (4.2 + 0.783 * units * (double)((p.per_chunk + 1) / 2 * 2)) + (double)chunks * elems * 0.15e-6;
+    else
+        us += rounds * (3.3 + 1.31 * units) + (double)chunks * elems * 0.166e-6;
+    return std::max(us, least) < limit;
 }
 
 }  // namespace
@@ -707,6 +733,10 @@ bd_status bd_linear_multitenant_variant(const uint16_t* x_f16, const uint16_t* w
     const bool mfma_ok = (in % 128 == 0) && in > 0 && (uint64_t)out * (uint64_t)in * 2 < ((uint64_t)1 << 32) &&
                          (uint64_t)T * (uint64_t)in * 2 < ((uint64_t)1 << 32);
     if (variant >= 2 && !prefill_variant && !mfma_ok) return BD_ERR_UNSUPPORTED;
+    if (variant == 0 && T <= kMaxDecodeTokens && mfma_ok && wide_fits(T, out, in)) {
+        order = order_by_tenant(tenant_of_token, T, n_tenants);
+        if (few_tokens_wide(batch_shape(tenant_of_token, order), out, in, cus_or_256())) return wide(0);
+    }
     int use = variant;
     if (use == 0) use = mfma_ok ? kVariantRowMajorMfma : kVariantRowWave;
 

@@ -186,6 +186,31 @@ def test_wide_every_split(out, inn, counts, variant):
     assert torch.equal(*(bd.linear_multitenant_tiled(t.x, wt, out, large, t.tok, variant=v) for v in (variant, 2))), what
 
 
+# Row-major batches that one decode launch could take: one and two row blocks and panels per workgroup, and those that stay a decode
+# launch; one token, full and part-filled column tiles, a token per tenant, idle tenants, `out` that ends inside a row block.
+@pytest.mark.parametrize("out,inn,counts", [
+    (330, 768, [1, 0, 9, 14]), (994, 640, [2] * 15), (467, 2432, [1] * 15), (4501, 512, [16, 0, 15]), (2727, 640, [17, 15]),
+    (953, 4736, [4] * 6), (9217, 640, [5, 6, 5, 16]), (1533, 6912, [2] * 16), (11577, 1152, [21, 1]), (16, 128, [32]),
+    (2049, 4096, [1]), (4224, 512, [1] * 32),
+])
+@pytest.mark.parametrize("order", ["grouped", "shuffled"])
+def test_few_tokens_rowmajor(out, inn, counts, order):
+    t = Tensors(out, inn, tokens_of(counts, order), len(counts), seed=3)
+    table = bd.TenantTable(t.packed, t.alpha)
+    y = torch.full((len(t.tok), out), float("nan"), dtype=torch.float16, device=DEV)
+    t.check(bd.linear_multitenant(t.x, t.w, table, t.tok, y=y), what=f"{out}x{inn} {counts} {order}")
+    forms = [bd.linear_multitenant(t.x, t.w, table, t.tok, variant=v) for v in (2, 10)]
+    assert any(torch.equal(y, f) for f in forms)
+    g = torch.cuda.CUDAGraph()
+    captured = torch.empty_like(y)
+    with torch.cuda.graph(g):
+        bd.linear_multitenant(t.x, t.w, table, t.tok, y=captured)
+    for _ in range(2):
+        captured.fill_(float("nan"))
+        g.replay()
+        assert torch.equal(captured, y)
+
+
 # Panels of four row blocks (row-major, variant 10 where the plan prefers them): chunks of 2 to 5 column tiles, the last one partly
 # filled; one, two, an odd number and more than four units per half of `in`, the second half a unit shorter or empty; `out` that
 # ends inside a row block, a panel, and not at a multiple of four.
