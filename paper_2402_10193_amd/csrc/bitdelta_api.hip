@@ -548,6 +548,26 @@ bool few_tokens_wide(const BatchShape& s, int64_t out, int64_t in, int cus) {
         us += rounds * (3.3 + 1.31 * units) + (double)chunks * elems * 0.166e-6;
     return std::max(us, least) < limit;
 }
+// The same question on the serving layout, for one matrix and one plane (the same bits either way); a decode launch streams it better, so the line
+// lies further out: 414 x 5376 31 tokens of 14 tenants 23.8 / 12.4, 14008 x 512 28 of 2 22.3 / 11.4, 15357 x 1280 31 of 1 27.5 / 16.7, 1081 x 3584 32 of 4
+// 16.1 / 10.8; 8681 x 768 7 of 7 15.0 / 18.7, 4430 x 4608 19 of 4 24.0 / 25.9, 452 x 3072 1 token 7.2 / 8.4.  Fitted to 400 batches (decode 15 %, wide 9 %).
+bool few_tokens_wide_tiled(const BatchShape& s, int64_t out, int64_t in, int cus) {
+    const double elems = (double)out * (double)in, bytes = elems * (2.0 + (double)s.active / 8.0), units = wide_units(in, false);
+    const auto& l = s.launches[0];
+    const double tasks = (double)((bd::tiled_row_blocks(out) + cus - 1) / cus) * decode_k_tiles(in, false) * (l.tokens > 16 ? 2.0 : 1.0);
+    const double by_decode = 4.69 + std::max(tasks * (1.714 + 0.191 * (double)((l.jobs + 1) / 2 * 2)), bytes / 5.39e6);
+    const double limit = 0.82 * by_decode;   // of the 400 none is then slower; at 0.9 3 are by 3 to 14 %, at 1.0 13
+    const double least = 6.0 + bytes / 3.6e6;
+    if (limit <= std::max(least, 4.55 + 1.12 * units)) return false;   // no plan is quicker: the smallest calls need no search
+    const int n = s.tiles16, KT = (int)bd::tiled_k_tiles(in);
+    const WidePlan p = wide_plan(n, out, in, cus, false);
+    const int64_t per_group = p.R * (8 / bd::wide_k_waves(KT)), groups = (bd::tiled_row_blocks(out) + per_group - 1) / per_group;
+    const int64_t chunks = (n + p.per_chunk - 1) / p.per_chunk, per_xcd = std::max(1, cus / 8);
+    const double rounds = (double)(((groups + 7) / 8 * chunks + per_xcd - 1) / per_xcd), run = (double)((p.per_chunk + 1) / 2 * 2);
+    const double us = p.R == 2 ? rounds * (5.03 + 0.701 * units * run) + (double)chunks * elems * 0.047e-6
+                               : rounds * (2.25 + 0.56 * units * run) + (double)chunks * elems * 0.136e-6;
+    return std::max(2.3 + us, least) < limit;
+}
 
 }  // namespace
 
@@ -894,10 +914,11 @@ bd_status tiled_linear_impl(int32_t n_mats, const uint16_t* x_f16, const uint16_
             }
     }
     const std::vector<int32_t> order = order_by_tenant(tenant_of_token, T, n_tenants);
-    // Serving layout, one plane, more tokens than a launch takes: the wide kernel, a launch per matrix, where its estimate is
-    // below that of the decode launches, which take the matrices of a group together.
+    // Serving layout, one plane: the wide kernel, a launch per matrix, where its estimate is below that of the decode launches, which take
+    // the matrices of a group together (so a group of a single launch's tokens stays with them).
     const int wide_split = wide_split_of_variant(variant, in, false);
-    if (wide_split >= 0 || (!rm && !q8 && k == 1 && variant == 0 && T > bd::kMaxDecodeTokens)) {
+    const bool few = T <= bd::kMaxDecodeTokens;
+    if (wide_split >= 0 || (!rm && !q8 && k == 1 && variant == 0 && (!few || n_mats == 1))) {
         bool fits = true;
         for (int m = 0; m < n_mats; ++m) fits = fits && (out[m] == 0 || wide_fits(T, out[m], in));
         if (wide_split >= 0 && !fits) return BD_ERR_UNSUPPORTED;
@@ -906,12 +927,12 @@ bd_status tiled_linear_impl(int32_t n_mats, const uint16_t* x_f16, const uint16_
             const BatchShape shape = batch_shape(tenant_of_token, order);
             const int cus = cus_or_256();
             double us = 0.0, elems = 0.0;
-            for (int m = 0; m < n_mats; ++m) {
+            for (int m = 0; m < n_mats && !few; ++m) {
                 if (out[m] == 0) continue;
                 us += wide_us(shape.tiles16, shape.active, out[m], in, cus, false);
                 elems += (double)out[m] * (double)in;
             }
-            wide = us < decode_us(shape, row_blocks, elems, in, cus, true, true);
+            wide = few ? few_tokens_wide_tiled(shape, out[0], in, cus) : us < decode_us(shape, row_blocks, elems, in, cus, true, true);
         }
         if (wide) {
             const WideTiles tiles = wide_tiles(tenant_of_token, order);

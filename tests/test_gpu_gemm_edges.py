@@ -211,6 +211,23 @@ def test_few_tokens_rowmajor(out, inn, counts, order):
         assert torch.equal(captured, y)
 
 
+# The same on the serving layout, where the wide kernel gives the bits of a decode launch: `in` of less than a k tile and not a
+# multiple of one as well.
+@pytest.mark.parametrize("out,inn,counts", [
+    (414, 5376, [2] * 14 + [3, 0]), (14008, 512, [11, 17]), (368, 4352, [15, 16]), (1081, 3584, [8] * 4), (15357, 1280, [31]),
+    (1150, 512, [1] * 17), (1001, 128, [32]), (742, 2432, [3] * 10), (452, 3072, [1]), (300, 2304, [1, 0, 7]),
+])
+@pytest.mark.parametrize("order", ["grouped", "shuffled"])
+def test_few_tokens_tiled(out, inn, counts, order):
+    t = Tensors(out, inn, tokens_of(counts, order), len(counts), seed=4)
+    wt = bd.tile_base(t.w)
+    table = bd.TiledTenantTable([bd.tile_signs(p, out, inn) for p in t.packed], t.alpha)
+    y = torch.full((len(t.tok), out), float("nan"), dtype=torch.float16, device=DEV)
+    t.check(bd.linear_multitenant_tiled(t.x, wt, out, table, t.tok, y=y), what=f"{out}x{inn} {counts} {order}")
+    for variant in (2, 10):
+        assert torch.equal(y, bd.linear_multitenant_tiled(t.x, wt, out, table, t.tok, variant=variant)), variant
+
+
 # Panels of four row blocks (row-major, variant 10 where the plan prefers them): chunks of 2 to 5 column tiles, the last one partly
 # filled; one, two, an odd number and more than four units per half of `in`, the second half a unit shorter or empty; `out` that
 # ends inside a row block, a panel, and not at a multiple of four.
