@@ -426,13 +426,20 @@ __global__ __launch_bounds__(kMaxWavesTiled * kWave) void linear_decode_tiled_ke
     // first multiplications back by microseconds.
     // Consecutive lanes write consecutive 16-byte copies (16 per entry), a wavefront 1 KiB at a stretch: with a
     // lane per entry the writes of a wavefront were 128 bytes apart, eight of them on every bank.
-    for (int q = threadIdx.x; q < 256 * 16; q += blockDim.x) {
-        const uint32_t b = (uint32_t)q >> 4;
-        u32x4 e;
+    // Entry b = 32 i + 4 j + lane / 16: eight writes (j) per turn of the loop, whose words are constants but for bits 0 and 1 (the lane's) and
+    // 5 to 7 (the turn's).  With its words formed for every write on its own, the loop was 27 instructions per KiB, turned 64 times by a single wavefront and
+    // 32 times by two, and the time of a short launch hung on where the compiler had placed it: 2048 x 512, two wavefronts, 1 tenant 6.4 us,
+    // but 7.3 where it began 28 bytes behind a multiple of 32 (in kernels of 2, 4 and 8 job slots); now 4.9, 2048 x 256 8.9 -> 5.6, 2048 x 1024 5.7 -> 5.3.
+    {
+        const uint32_t e0 = 0xBC00BC00u ^ ((uint32_t)(g & 1) << 15) ^ ((uint32_t)(g >> 1) << 31);
+        for (int i = wave; i < 8; i += nw) {
+            unsigned char* const at = smem + i * 8192 + lane * 16;
+            const uint32_t e3 = 0xBC00BC00u ^ (((uint32_t)i >> 1 & 1u) << 15) ^ (((uint32_t)i >> 2) << 31);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            e[i] = 0xBC00BC00u ^ (((b >> (2 * i)) & 1u) << 15) ^ (((b >> (2 * i + 1)) & 1u) << 31);
-        *(u32x4*)(smem + q * 16) = e;
+            for (uint32_t j = 0; j < 8; ++j)
+                *(u32x4*)(at + j * 1024) = u32x4{e0, 0xBC00BC00u ^ ((j & 1u) << 15) ^ ((j >> 1 & 1u) << 31),
+                                                 0xBC00BC00u ^ ((j >> 2) << 15) ^ (((uint32_t)i & 1u) << 31), e3};
+        }
     }
     // What the write of y needs per column, read from the kernel arguments with a lane's own index (a load from memory)
     // here, where it waits with everything else, and from LDS when a row block is finished: at the end of a launch a trip
