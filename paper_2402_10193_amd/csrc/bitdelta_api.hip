@@ -249,9 +249,11 @@ hipError_t run_prefill(const uint16_t* x, const void* w, const uint32_t* const* 
 struct WideTiles {
     std::vector<int32_t> tenant;               // per tile
     std::vector<uint16_t> token;               // 16 per tile, kWideNoToken where empty
+    int64_t tokens = 0;
 };
 WideTiles wide_tiles(const int32_t* tenant_of_token, const std::vector<int32_t>& order) {
     WideTiles t;
+    t.tokens = (int64_t)order.size();
     int in_tile = 16;
     for (size_t i = 0; i < order.size(); ++i) {
         const int32_t tenant = tenant_of_token[order[i]];
@@ -323,7 +325,7 @@ bool panel_fits(int64_t T, int64_t out, int64_t in, int planes, bool q8) {
 // estimated time: workgroups take turns on the compute units of their XCD (LDS allows one at a time, the row blocks are dealt to the XCDs), some 4 us
 // around the loop of each, and every chunk fetches the base again.  Fitted to 3480 times: the batches described at BatchShape, every
 // split.  10 % at the 10 % and 90 % quantiles; the split it picks is the quickest or within 7 % of it in 95 % of the batches.
-WidePlan wide_plan(int n, int64_t out, int64_t in, int cus, bool rowmajor) {
+WidePlan wide_plan(int n, int64_t tokens, int64_t out, int64_t in, int cus, bool rowmajor) {
     WidePlan best{0, 0, 1e30};
     const int64_t rb = bd::tiled_row_blocks(out), per_xcd = std::max(1, cus / 8);
     const double units = wide_units(in, rowmajor);
@@ -340,17 +342,20 @@ WidePlan wide_plan(int n, int64_t out, int64_t in, int cus, bool rowmajor) {
     // The panel kernel, row-major.  Where it lies against the others (us, the other ways' best / panel): 4096 x 4096 200 tokens of
     // 16 tenants 55 / 34, 11008 x 4096 500 of 32 285 / 220, 3278 x 1280 604 of 64 90 / 54; with few rows or one token per tenant the others win:
     // 996 x 7680 154 of 7 21 / 28, 330 x 2816 87 of 4 10 / 14, 6828 x 8320 58 of 51 241 / 324.
+    // One group of panels per XCD, long rows, tiles of hardly more than one token: every wavefront's own fetch of x, what panels save, is then
+    // mostly one line again and again.  460 x 9472 61 tokens of 53 34.5 / 35.7, 419 x 9344 57 of 52 34.5 / 35.7, 311 x 7552 44 of 43 26.4 / 27.1
+    // (14 of 18 such batches); but 479 x 7680 195 of 34 31.2 / 29.9, 440 x 5632 36 of 34 21.3 / 20.9, 837 x 10112 58 of 45 49.9 / 50.3.
     if (rowmajor) {
         const WidePlan panel = panel_plan(n, out, in, cus, 1, false);
-        if (panel.us < best.us) best = panel;
+        if (panel.us < (out <= 512 && in > 7296 && tokens < 2 * (int64_t)n ? 0.95 : 1.0) * best.us) best = panel;
     }
     return best;
 }
-double wide_us(int n_all, int active, int64_t out, int64_t in, int cus, bool rowmajor) {
+double wide_us(int n_all, int64_t tokens, int active, int64_t out, int64_t in, int cus, bool rowmajor) {
     double us = 3.0;
     const int launches = (n_all + bd::kWideMaxTiles - 1) / bd::kWideMaxTiles;
     for (int l = 0; l < launches; ++l)
-        us += wide_plan((int)((int64_t)n_all * (l + 1) / launches - (int64_t)n_all * l / launches), out, in, cus, rowmajor).us;
+        us += wide_plan((int)((int64_t)n_all * (l + 1) / launches - (int64_t)n_all * l / launches), tokens / launches, out, in, cus, rowmajor).us;
     const double elems = (double)out * (double)in;   // the stream: the base once, every active tenant's signs once
     return std::max(us, 6.0 + elems * (2.0 + (double)active / 8.0) / 4.5e6);
 }
@@ -389,7 +394,7 @@ hipError_t run_wide(const WideTiles& t, const uint16_t* x, const uint16_t* w, co
         a.wscale = wscale;
         a.row_blocks = (int32_t)bd::tiled_row_blocks(out);
         a.n_tiles = n;
-        const WidePlan p = panel_planes ? panel_plan(n, out, in, cus, panel_planes, wscale != nullptr) : split ? WidePlan{split >> 4, std::min(split & 15, n), 0.0} : wide_plan(n, out, in, cus, packed_dev != nullptr);
+        const WidePlan p = panel_planes ? panel_plan(n, out, in, cus, panel_planes, wscale != nullptr) : split ? WidePlan{split >> 4, std::min(split & 15, n), 0.0} : wide_plan(n, t.tokens / launches, out, in, cus, packed_dev != nullptr);
         a.tiles_per_chunk = p.per_chunk;
         for (int i = 0; i < n; ++i) {
             a.tenant[i] = t.tenant[(size_t)(first + i)];
@@ -536,7 +541,7 @@ bool few_tokens_wide(const BatchShape& s, int64_t out, int64_t in, int cus) {
     const double least = 5.7 + bytes / 3.96e6;
     if (limit <= std::max(least, 4.8 + 1.31 * units)) return false;   // no plan is quicker: the smallest calls need no search
     const int n = s.tiles16;
-    const WidePlan p = wide_plan(n, out, in, cus, true);
+    const WidePlan p = wide_plan(n, l.tokens, out, in, cus, true);
     const int64_t groups = (bd::tiled_row_blocks(out) + p.R - 1) / p.R, chunks = (n + p.per_chunk - 1) / p.per_chunk, per_xcd = std::max(1, cus / 8);
     const double rounds = (double)(((groups + 7) / 8 * chunks + per_xcd - 1) / per_xcd);
     double us = 1.5;
@@ -560,7 +565,7 @@ bool few_tokens_wide_tiled(const BatchShape& s, int64_t out, int64_t in, int cus
     const double least = 6.0 + bytes / 3.6e6;
     if (limit <= std::max(least, 4.55 + 1.12 * units)) return false;   // no plan is quicker: the smallest calls need no search
     const int n = s.tiles16, KT = (int)bd::tiled_k_tiles(in);
-    const WidePlan p = wide_plan(n, out, in, cus, false);
+    const WidePlan p = wide_plan(n, l.tokens, out, in, cus, false);
     const int64_t per_group = p.R * (8 / bd::wide_k_waves(KT)), groups = (bd::tiled_row_blocks(out) + per_group - 1) / per_group;
     const int64_t chunks = (n + p.per_chunk - 1) / p.per_chunk, per_xcd = std::max(1, cus / 8);
     const double rounds = (double)(((groups + 7) / 8 * chunks + per_xcd - 1) / per_xcd), run = (double)((p.per_chunk + 1) / 2 * 2);
@@ -774,7 +779,12 @@ bd_status bd_linear_multitenant_variant(const uint16_t* x_f16, const uint16_t* w
         const int cus = cus_or_256();
         const double by_decode = decode_us(shape, bd::tiled_row_blocks(out), (double)out * (double)in, in, cus, false, mfma_ok);
         const double by_gemm = can_prefill ? gemm_us(shape, out, in, big_default, cus) : 1e30;
-        if (mfma_ok && wide_fits(T, out, in) && wide_us(shape.tiles16, shape.active, out, in, cus, true) < std::min(by_decode, by_gemm))
+        // Halves of five units: a panel fetches and turns the signs of four units at a time, here three for nothing, and its estimate is a tenth short.
+        // Decode launches / panels: 5250 x 1280 64 tokens of 58 tenants 60 / 71, 10080 x 1152 58 of 44 73 / 80, 5131 x 1152 73 of 66 76 / 82 (11 of 22
+        // such batches between 3 and 15 %); beyond that line 5870 x 1152 41 of 36 45.5 / 42.7, 3051 x 1152 46 of 41 30.9 / 29.0.
+        const double against_decode = (in / 128 + 1) / 2 == 5 ? 0.9 : 1.0;
+        if (mfma_ok && wide_fits(T, out, in) &&
+            wide_us(shape.tiles16, T, shape.active, out, in, cus, true) < std::min(against_decode * by_decode, by_gemm))
             return wide(0);
         gemm_pays = by_gemm < by_decode;
     }
@@ -929,7 +939,7 @@ bd_status tiled_linear_impl(int32_t n_mats, const uint16_t* x_f16, const uint16_
             double us = 0.0, elems = 0.0;
             for (int m = 0; m < n_mats && !few; ++m) {
                 if (out[m] == 0) continue;
-                us += wide_us(shape.tiles16, shape.active, out[m], in, cus, false);
+                us += wide_us(shape.tiles16, T, shape.active, out[m], in, cus, false);
                 elems += (double)out[m] * (double)in;
             }
             wide = few ? few_tokens_wide_tiled(shape, out[0], in, cus) : us < decode_us(shape, row_blocks, elems, in, cus, true, true);

@@ -186,6 +186,17 @@ def test_wide_every_split(out, inn, counts, variant):
     assert torch.equal(*(bd.linear_multitenant_tiled(t.x, wt, out, large, t.tok, variant=v) for v in (variant, 2))), what
 
 
+# Hardly more than one token per tenant, where panels were taken although the kernel of 16-column tiles (36: two row blocks, four tiles) or
+# decode launches (2) are the quicker ones: the library's choice gives those kernels' bits.
+@pytest.mark.parametrize("out,inn,counts,variant", [(460, 9472, [2] * 8 + [1] * 45, 36), (5250, 1280, [2] * 6 + [1] * 52, 2)])
+def test_one_token_per_tenant_keeps_its_kernel(out, inn, counts, variant):
+    t = Tensors(out, inn, tokens_of(counts, "shuffled"), len(counts), seed=6)
+    table = bd.TenantTable(t.packed, t.alpha)
+    y = bd.linear_multitenant(t.x, t.w, table, t.tok)
+    t.check(y, what=f"{out}x{inn}")
+    assert torch.equal(y, bd.linear_multitenant(t.x, t.w, table, t.tok, variant=variant))
+
+
 # Row-major batches that one decode launch could take: one and two row blocks and panels per workgroup, and those that stay a decode
 # launch; one token, full and part-filled column tiles, a token per tenant, idle tenants, `out` that ends inside a row block.
 @pytest.mark.parametrize("out,inn,counts", [
