@@ -168,9 +168,10 @@ bd_status bd_linear_multitenant(const uint16_t* x_f16, const uint16_t* w_base_f1
  *              tiles.  Half the matrix-core work of variants 4 to 7; the result differs from theirs by that
  *              rounding of the weights (about 2e-4 of the largest output at in = 4096) and equals, up to
  *              summation order, bd_linear_naive on bd_materialize'd weights.  Same conditions as 5.
- *   variant 10 the kernel for tens to a few hundred tokens with a few per tenant, for any T (in % 128 == 0, x and base
- *              below 4 GiB, else BD_ERR_UNSUPPORTED; no workspace); 16 R + n: with R = 1 or 2 row blocks and up to n column
- *              tiles per workgroup instead of the library's split (n = 1 .. 10 with R = 1, 1 .. 6 with R = 2) */
+ *   variant 10 the kernels for tens to a few hundred tokens with a few per tenant, for any T (in % 128 == 0, x and base
+ *              below 4 GiB, else BD_ERR_UNSUPPORTED; no workspace), one or two row blocks of 16 output features per workgroup or panels
+ *              of four, as the library splits them; 16 R + n: with R = 1 or 2 row blocks and up to n column tiles per workgroup
+ *              (n = 1 .. 10 with R = 1, 1 .. 6 with R = 2); 128 + n: panels (n = 1 .. 5, 0 for the library's split) */
 bd_status bd_linear_multitenant_variant(const uint16_t* x_f16, const uint16_t* w_base_f16,
                                         const uint32_t* const* packed_by_tenant,
                                         const float* alpha_by_tenant,
@@ -340,6 +341,21 @@ bd_status bd_linear_multitenant_gemm_q8(const uint16_t* x_f16, const int8_t* q, 
                                         const int32_t* tenant_of_token, uint16_t* y_f16,
                                         int64_t T, int64_t out, int64_t in, int32_t n_tenants,
                                         void* workspace, size_t workspace_bytes, void* stream);
+
+/* The same with the kernel chosen by the caller instead of by the library: 0 = the library's choice, 4 = the GEMM on 128 x 128 tiles,
+ * 5 = on 128 x 256 tiles (8-bit base, out >= 256, in % 64 == 0), 128 + n = panels with up to n column tiles per workgroup (in % 64 == 0, in >= 128,
+ * x and base below 4 GiB; n = 0 for the library's split, else 1 .. 5, 4, 3, 2 with k = 1, 2, 3, 4 and 1 .. 5 over the 8-bit base).  Anything else
+ * gives BD_ERR_UNSUPPORTED. */
+bd_status bd_linear_multitenant_gemm_kbit_variant(const uint16_t* x_f16, const uint16_t* w_base_f16,
+                                                  const uint32_t* const* planes_by_tenant, const float* alpha_by_tenant,
+                                                  const int32_t* tenant_of_token, uint16_t* y_f16,
+                                                  int64_t T, int64_t out, int64_t in, int32_t n_tenants, int32_t k,
+                                                  void* workspace, size_t workspace_bytes, void* stream, int32_t variant);
+bd_status bd_linear_multitenant_gemm_q8_variant(const uint16_t* x_f16, const int8_t* q, const float* wscale,
+                                                const uint32_t* const* packed_by_tenant, const float* alpha_by_tenant,
+                                                const int32_t* tenant_of_token, uint16_t* y_f16,
+                                                int64_t T, int64_t out, int64_t in, int32_t n_tenants,
+                                                void* workspace, size_t workspace_bytes, void* stream, int32_t variant);
 
 /* Eq. 6 with k planes per tenant over the serving layout:
  *   y[t] = x[t] W_base^T + sum_{j<k} alpha[e*k+j] * (x[t] S_{e,j}^T),   e = tenant_of_token[t]

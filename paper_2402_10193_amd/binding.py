@@ -33,7 +33,8 @@ EXPORTS = ["bd_status_string", "bd_version", "bd_workspace_bytes", "bd_pack_sign
            "bd_delta_file_bytes", "bd_delta_file_read", "bd_delta_upload", "bd_delta_install", "bd_quantize_base_q8",
            "bd_compress_q8", "bd_tiled_base_q8_bytes", "bd_tile_base_q8", "bd_linear_multitenant_tiled_q8",
            "bd_linear_multitenant_tiled_group_q8", "bd_linear_multitenant_kbit", "bd_linear_multitenant_gemm_kbit",
-           "bd_linear_multitenant_gemm_q8", "bd_linear_multitenant_q8"]
+           "bd_linear_multitenant_gemm_q8", "bd_linear_multitenant_q8", "bd_linear_multitenant_gemm_kbit_variant",
+           "bd_linear_multitenant_gemm_q8_variant"]
 
 
 class BitDeltaError(RuntimeError):
@@ -108,6 +109,8 @@ def lib() -> ctypes.CDLL:
         L.bd_linear_multitenant_kbit.argtypes = [vp, vp, vp, vp, pi, vp, i64, i64, i64, i32, i32, vp]
         L.bd_linear_multitenant_gemm_kbit.argtypes = [vp, vp, vp, vp, pi, vp, i64, i64, i64, i32, i32, vp, sz, vp]
         L.bd_linear_multitenant_gemm_q8.argtypes = [vp, vp, vp, vp, vp, pi, vp, i64, i64, i64, i32, vp, sz, vp]
+        L.bd_linear_multitenant_gemm_kbit_variant.argtypes = L.bd_linear_multitenant_gemm_kbit.argtypes + [i32]
+        L.bd_linear_multitenant_gemm_q8_variant.argtypes = L.bd_linear_multitenant_gemm_q8.argtypes + [i32]
         L.bd_linear_multitenant_q8.argtypes = [vp, vp, vp, vp, vp, pi, vp, i64, i64, i64, i32, vp]
         L.bd_compress_batch.argtypes = [i32, pvp, pvp, pi64, pi64, pvp, vp, vp, sz, vp]
         L.bd_compress_batch.restype = ctypes.c_int
@@ -524,8 +527,8 @@ def linear_multitenant_kbit(x: torch.Tensor, w_base: torch.Tensor, tenants: Plan
 
 def linear_multitenant_gemm_kbit(x: torch.Tensor, w_base: torch.Tensor, tenants: PlaneTable, tenant_of_token: Sequence[int],
                                  y: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None, stream=None,
-                                 tok_array=None) -> torch.Tensor:
-    """bd_linear_multitenant_gemm_kbit: the GEMM form (any T >= 1) with k row-major planes per tenant."""
+                                 tok_array=None, variant: int = 0) -> torch.Tensor:
+    """bd_linear_multitenant_gemm_kbit (variant 0) or _gemm_kbit_variant: the GEMM form (any T >= 1) with k row-major planes per tenant."""
     _dev(x, torch.float16, "x")
     _dev(w_base, torch.float16, "w_base")
     T, inn = x.shape
@@ -535,9 +538,11 @@ def linear_multitenant_gemm_kbit(x: torch.Tensor, w_base: torch.Tensor, tenants:
     if workspace is None:
         workspace = new_workspace(workspace_bytes(OP_LINEAR_GEMM, T, out, inn, tenants.n_tenants), x.device)
     tok = tok_array if tok_array is not None else _tok_array(tenant_of_token)
-    _check(lib().bd_linear_multitenant_gemm_kbit(_ptr(x), _ptr(w_base), _ptr(tenants.ptrs), _ptr(tenants.alpha), tok, _ptr(y), T,
-                                                 out, inn, tenants.n_tenants, tenants.k, _ptr(workspace), workspace.numel(),
-                                                 _stream(stream)), "bd_linear_multitenant_gemm_kbit")
+    args = (_ptr(x), _ptr(w_base), _ptr(tenants.ptrs), _ptr(tenants.alpha), tok, _ptr(y), T, out, inn, tenants.n_tenants, tenants.k,
+            _ptr(workspace), workspace.numel(), _stream(stream))
+    L = lib()
+    _check(L.bd_linear_multitenant_gemm_kbit(*args) if variant == 0 else L.bd_linear_multitenant_gemm_kbit_variant(*args, int(variant)),
+           "bd_linear_multitenant_gemm_kbit")
     return y
 
 
@@ -560,8 +565,10 @@ def linear_multitenant_q8(x: torch.Tensor, q: torch.Tensor, scale: torch.Tensor,
 
 def linear_multitenant_gemm_q8(x: torch.Tensor, q: torch.Tensor, scale: torch.Tensor, tenants: "TenantTable",
                                tenant_of_token: Sequence[int], y: Optional[torch.Tensor] = None,
-                               workspace: Optional[torch.Tensor] = None, stream=None, tok_array=None) -> torch.Tensor:
-    """bd_linear_multitenant_gemm_q8: the GEMM form (any T >= 1) on the row-major 8-bit base (q int8 [out, in], scale [out])."""
+                               workspace: Optional[torch.Tensor] = None, stream=None, tok_array=None,
+                               variant: int = 0) -> torch.Tensor:
+    """bd_linear_multitenant_gemm_q8 (variant 0) or _gemm_q8_variant: the GEMM form (any T >= 1) on the row-major 8-bit base (q int8 [out, in],
+    scale [out])."""
     _dev(x, torch.float16, "x")
     _dev(q, torch.int8, "q")
     _dev(scale, torch.float32, "scale")
@@ -572,9 +579,11 @@ def linear_multitenant_gemm_q8(x: torch.Tensor, q: torch.Tensor, scale: torch.Te
     if workspace is None:
         workspace = new_workspace(workspace_bytes(OP_LINEAR_GEMM, T, out, inn, tenants.n_tenants), x.device)
     tok = tok_array if tok_array is not None else _tok_array(tenant_of_token)
-    _check(lib().bd_linear_multitenant_gemm_q8(_ptr(x), _ptr(q), _ptr(scale), _ptr(tenants.ptrs), _ptr(tenants.alpha), tok, _ptr(y),
-                                               T, out, inn, tenants.n_tenants, _ptr(workspace), workspace.numel(),
-                                               _stream(stream)), "bd_linear_multitenant_gemm_q8")
+    args = (_ptr(x), _ptr(q), _ptr(scale), _ptr(tenants.ptrs), _ptr(tenants.alpha), tok, _ptr(y), T, out, inn, tenants.n_tenants,
+            _ptr(workspace), workspace.numel(), _stream(stream))
+    L = lib()
+    _check(L.bd_linear_multitenant_gemm_q8(*args) if variant == 0 else L.bd_linear_multitenant_gemm_q8_variant(*args, int(variant)),
+           "bd_linear_multitenant_gemm_q8")
     return y
 
 

@@ -24,6 +24,7 @@ constexpr int kVariantPrefillBig8 = 6;    // ... the same tile with two wavefron
 constexpr int kVariantPrefillBigWhole = 7;   // ... as 5, but never cutting the tiles of the last round in two
 constexpr int kVariantPrefillMerged = 8;     // ... one product on W + alpha S, formed in fp16 on the way to the matrix cores (256 x 256 tiles)
 constexpr int kVariantWide = 10;             // the kernel for tens to a few hundred tokens; 16 R + n: R row blocks and up to n column tiles per workgroup
+constexpr int kVariantPanels = 128;          // panels, row-major; + n: up to n column tiles per workgroup
 
 inline bool misaligned(const void* p, size_t a) { return ((uintptr_t)p & (a - 1)) != 0; }
 
@@ -360,9 +361,13 @@ double wide_us(int n_all, int64_t tokens, int active, int64_t out, int64_t in, i
     return std::max(us, 6.0 + elems * (2.0 + (double)active / 8.0) / 4.5e6);
 }
 
-// The split that a variant number asks for: 0 = the plan's, -1 = none of the kernel's.
+// The split that a variant number asks for: 0 = the plan's, kVariantPanels = the plan's of panels, -1 = none.
+int panel_split_of_variant(int32_t variant, int planes) {
+    return variant >= kVariantPanels && variant <= kVariantPanels + bd::panel_max_chunk(planes) ? variant : -1;
+}
 int wide_split_of_variant(int32_t variant, int64_t in, bool rowmajor) {
     if (variant == kVariantWide) return 0;
+    if (rowmajor && variant >= kVariantPanels) return panel_split_of_variant(variant, 1);
     const int R = variant >> 4, n = variant & 15;
     return (R == 1 || R == 2) && n >= 1 && n <= bd::wide_max_chunk(R, (int)bd::tiled_k_tiles(in), rowmajor) ? variant : -1;
 }
@@ -394,7 +399,9 @@ hipError_t run_wide(const WideTiles& t, const uint16_t* x, const uint16_t* w, co
         a.wscale = wscale;
         a.row_blocks = (int32_t)bd::tiled_row_blocks(out);
         a.n_tiles = n;
-        const WidePlan p = panel_planes ? panel_plan(n, out, in, cus, panel_planes, wscale != nullptr) : split ? WidePlan{split >> 4, std::min(split & 15, n), 0.0} : wide_plan(n, t.tokens / launches, out, in, cus, packed_dev != nullptr);
+        const WidePlan p = split & 15     ? WidePlan{split >= kVariantPanels ? bd::kPanelRowBlocks : split >> 4, std::min(split & 15, n), 0.0}
+                           : panel_planes ? panel_plan(n, out, in, cus, panel_planes, wscale != nullptr)
+                                          : wide_plan(n, t.tokens / launches, out, in, cus, packed_dev != nullptr);
         a.tiles_per_chunk = p.per_chunk;
         for (int i = 0; i < n; ++i) {
             a.tenant[i] = t.tenant[(size_t)(first + i)];
@@ -747,7 +754,7 @@ bd_status bd_linear_multitenant_variant(const uint16_t* x_f16, const uint16_t* w
     std::vector<int32_t> order;
     auto wide = [&](const int split) {
         return run_wide(wide_tiles(tenant_of_token, order), x_f16, w_base_f16, packed_by_tenant, nullptr, alpha_by_tenant, y_f16, out, in,
-                        (hipStream_t)stream, split) == hipSuccess
+                        (hipStream_t)stream, split, split >= kVariantPanels ? 1 : 0) == hipSuccess
                    ? BD_OK
                    : BD_ERR_DEVICE;
     };
@@ -1175,30 +1182,36 @@ bd_status bd_linear_multitenant_kbit(const uint16_t* x_f16, const uint16_t* w_ba
 static bd_status gemm_entry(const uint16_t* x_f16, const void* w, size_t w_bytes_per_el, const uint32_t* const* packed_by_tenant,
                             const float* alpha_by_tenant, const float* wscale, const int32_t* tenant_of_token, uint16_t* y_f16,
                             int64_t T, int64_t out, int64_t in, int32_t n_tenants, int k_planes, void* workspace,
-                            size_t workspace_bytes, void* stream) {
+                            size_t workspace_bytes, void* stream, int32_t variant = 0) {
     const bd_status st = check_linear_args(x_f16, w, packed_by_tenant, alpha_by_tenant, tenant_of_token, y_f16, T, out, in,
                                            n_tenants, w_bytes_per_el);
     if (st != BD_OK) return st;
+    const int planes = std::max(k_planes, 1);
+    const int panel_split = panel_split_of_variant(variant, planes);
+    if (variant != 0 && variant != kVariantPrefillSmall && variant != kVariantPrefillBig && panel_split < 0) return BD_ERR_UNSUPPORTED;
     if (T == 0 || out == 0) return BD_OK;
     if (in == 0) return BD_ERR_UNSUPPORTED;   // the empty reduction (y = 0) is bd_linear_multitenant's
     const size_t need = prefill_table_bytes(T, n_tenants);
     if (!workspace || workspace_bytes < need || misaligned(workspace, 256)) return BD_ERR_WORKSPACE;
     // The 8-bit base: 128 x 256 tiles where whole 64-wide steps and a full tile's width of output rows are there, as for fp16.
     // (k planes stay on the 128 x 128 tiles: their sums are formed in fp16 in LDS, which the large tile has no room for.)
-    const bool big = wscale && k_planes == 0 && out >= 256 && bd::prefill_big_fits(T, out, in);
+    const bool big = wscale && k_planes == 0 && out >= 256 && bd::prefill_big_fits(T, out, in) && variant != kVariantPrefillSmall;
+    if (variant == kVariantPrefillBig && !big) return BD_ERR_UNSUPPORTED;
+    const bool panels = panel_fits(T, out, in, planes, wscale != nullptr);
+    if (panel_split >= 0 && !panels) return BD_ERR_UNSUPPORTED;
     const std::vector<int32_t> order = order_by_tenant(tenant_of_token, T, n_tenants);
     // Few tokens per tenant, few rows: the GEMM's tiles are mostly padding and too few to fill the chip, each a serial chain of `in` / 64 steps.  The
     // panel kernel splits `in` between its wavefronts and pads to 16 tokens (us, GEMM / panels; two planes: 29 tokens of 11 tenants on 724 x 2880
     // 95 / 18, 731 of 4 on 2846 x 8960 290 / 175, 1588 of 14 on 5149 x 8960 678 / 663, 1270 of 5 on 5318 x 704 45 / 86; 8-bit base: 46 of 6 on 2884 x 7424
     // 84 / 31, 648 of 14 on 1875 x 3456 59 / 45, 717 of 5 on 4705 x 4608 106 / 117).  It is taken where its estimate is clearly the lower one.
-    const int planes = std::max(k_planes, 1);
-    if (panel_fits(T, out, in, planes, wscale != nullptr)) {
+    if (panels && (variant == 0 || panel_split >= 0)) {
         const BatchShape shape = batch_shape(tenant_of_token, order);
         const int cus = cus_or_256();
         // 0.87: the two estimates miss by about a tenth each way; at 0.9 two of 150 prompts took panels 5 and 15 % above the GEMM, at 0.87 none of 250
-        if (panel_us(shape.tiles16, out, in, cus, planes, wscale != nullptr) < 0.87 * gemm_extended_us(shape, out, in, big, planes, wscale != nullptr, cus))
+        if (panel_split >= 0 ||
+            panel_us(shape.tiles16, out, in, cus, planes, wscale != nullptr) < 0.87 * gemm_extended_us(shape, out, in, big, planes, wscale != nullptr, cus))
             return run_wide(wide_tiles(tenant_of_token, order), x_f16, (const uint16_t*)w, packed_by_tenant, nullptr, alpha_by_tenant, y_f16, out, in,
-                            (hipStream_t)stream, 0, planes, wscale) == hipSuccess
+                            (hipStream_t)stream, std::max(panel_split, 0), planes, wscale) == hipSuccess
                        ? BD_OK
                        : BD_ERR_DEVICE;
     }
@@ -1208,23 +1221,41 @@ static bd_status gemm_entry(const uint16_t* x_f16, const void* w, size_t w_bytes
                : BD_ERR_DEVICE;
 }
 
+bd_status bd_linear_multitenant_gemm_kbit_variant(const uint16_t* x_f16, const uint16_t* w_base_f16,
+                                                  const uint32_t* const* planes_by_tenant, const float* alpha_by_tenant,
+                                                  const int32_t* tenant_of_token, uint16_t* y_f16, int64_t T, int64_t out, int64_t in,
+                                                  int32_t n_tenants, int32_t k, void* workspace, size_t workspace_bytes, void* stream,
+                                                  int32_t variant) {
+    if (k < 1 || k > bd::kTiledMaxPlanes) return BD_ERR_SHAPE;
+    return gemm_entry(x_f16, w_base_f16, 2, planes_by_tenant, alpha_by_tenant, nullptr, tenant_of_token, y_f16, T, out, in,
+                      n_tenants, k, workspace, workspace_bytes, stream, variant);
+}
+
 bd_status bd_linear_multitenant_gemm_kbit(const uint16_t* x_f16, const uint16_t* w_base_f16,
                                           const uint32_t* const* planes_by_tenant, const float* alpha_by_tenant,
                                           const int32_t* tenant_of_token, uint16_t* y_f16, int64_t T, int64_t out, int64_t in,
                                           int32_t n_tenants, int32_t k, void* workspace, size_t workspace_bytes, void* stream) {
-    if (k < 1 || k > bd::kTiledMaxPlanes) return BD_ERR_SHAPE;
-    return gemm_entry(x_f16, w_base_f16, 2, planes_by_tenant, alpha_by_tenant, nullptr, tenant_of_token, y_f16, T, out, in,
-                      n_tenants, k, workspace, workspace_bytes, stream);
+    return bd_linear_multitenant_gemm_kbit_variant(x_f16, w_base_f16, planes_by_tenant, alpha_by_tenant, tenant_of_token, y_f16, T, out,
+                                                   in, n_tenants, k, workspace, workspace_bytes, stream, 0);
+}
+
+bd_status bd_linear_multitenant_gemm_q8_variant(const uint16_t* x_f16, const int8_t* q, const float* wscale,
+                                                const uint32_t* const* packed_by_tenant, const float* alpha_by_tenant,
+                                                const int32_t* tenant_of_token, uint16_t* y_f16, int64_t T, int64_t out, int64_t in,
+                                                int32_t n_tenants, void* workspace, size_t workspace_bytes, void* stream,
+                                                int32_t variant) {
+    if (T > 0 && out > 0 && !wscale) return BD_ERR_NULL;
+    if (misaligned(wscale, 4)) return BD_ERR_ALIGN;
+    return gemm_entry(x_f16, q, 1, packed_by_tenant, alpha_by_tenant, wscale, tenant_of_token, y_f16, T, out, in, n_tenants, 0,
+                      workspace, workspace_bytes, stream, variant);
 }
 
 bd_status bd_linear_multitenant_gemm_q8(const uint16_t* x_f16, const int8_t* q, const float* wscale,
                                         const uint32_t* const* packed_by_tenant, const float* alpha_by_tenant,
                                         const int32_t* tenant_of_token, uint16_t* y_f16, int64_t T, int64_t out, int64_t in,
                                         int32_t n_tenants, void* workspace, size_t workspace_bytes, void* stream) {
-    if (T > 0 && out > 0 && !wscale) return BD_ERR_NULL;
-    if (misaligned(wscale, 4)) return BD_ERR_ALIGN;
-    return gemm_entry(x_f16, q, 1, packed_by_tenant, alpha_by_tenant, wscale, tenant_of_token, y_f16, T, out, in, n_tenants, 0,
-                      workspace, workspace_bytes, stream);
+    return bd_linear_multitenant_gemm_q8_variant(x_f16, q, wscale, packed_by_tenant, alpha_by_tenant, tenant_of_token, y_f16, T, out, in,
+                                                 n_tenants, workspace, workspace_bytes, stream, 0);
 }
 
 bd_status bd_linear_multitenant_q8(const uint16_t* x_f16, const int8_t* q, const float* wscale,

@@ -65,9 +65,14 @@ def tokens_of(counts, order="grouped"):
 def test_gemm_q8_tiles(out, inn, counts):
     t = Tensors(out, inn, tokens_of(counts, "shuffled"), len(counts))
     q, scale = bd.quantize_base_q8(t.w)
-    y = torch.full((len(t.tok), out), float("nan"), dtype=torch.float16, device=DEV)
-    bd.linear_multitenant_gemm_q8(t.x, q, scale, bd.TenantTable(t.packed, t.alpha), t.tok, y=y)
-    t.check(y, q.double() * scale.double()[:, None], f"q8 {out}x{inn} {counts}")
+    big = out >= 256 and inn % 64 == 0
+    for variant in (0, 4) + (5,) * big:      # the library's choice; the GEMM on 128 x 128 tiles; on 128 x 256 tiles
+        y = torch.full((len(t.tok), out), float("nan"), dtype=torch.float16, device=DEV)
+        bd.linear_multitenant_gemm_q8(t.x, q, scale, bd.TenantTable(t.packed, t.alpha), t.tok, y=y, variant=variant)
+        t.check(y, q.double() * scale.double()[:, None], f"q8 {out}x{inn} {counts} variant {variant}")
+    if not big:
+        with pytest.raises(bd.BitDeltaError):
+            bd.linear_multitenant_gemm_q8(t.x, q, scale, bd.TenantTable(t.packed, t.alpha), t.tok, variant=5)
 
 
 # The same entry points with a few tokens per tenant, which panels of 64 output rows take: `in` of whole and half units of 128, one to
@@ -81,32 +86,47 @@ PANELS = [(16, 128, [17]), (41, 1152, [20, 1, 33, 16, 0, 15, 40]), (373, 2240, [
 @pytest.mark.parametrize("k", [0, 1, 2, 3, 4])   # 0: the 8-bit base
 @pytest.mark.parametrize("case", range(len(PANELS)))
 def test_gemm_forms_in_panels(case, k):
+    """Panels by their number, in every split, which all give the same bits; the GEMM's tiles by theirs; the library's choice."""
     out, inn, counts = PANELS[case]
     t = Tensors(out, inn, tokens_of(counts, "shuffled"), len(counts), seed=case)
     what = f"{out}x{inn} {counts} k {k}"
-    y = torch.full((len(t.tok), out), float("nan"), dtype=torch.float16, device=DEV)
+    nan = lambda: torch.full((len(t.tok), out), float("nan"), dtype=torch.float16, device=DEV)
+    splits = [128 + n for n in range(1, {0: 5, 1: 5, 2: 4, 3: 3, 4: 2}[k] + 1)]
     if k == 0:
         q, scale = bd.quantize_base_q8(t.w)
-        bd.linear_multitenant_gemm_q8(t.x, q, scale, bd.TenantTable(t.packed, t.alpha), t.tok, y=y)
-        return t.check(y, q.double() * scale.double()[:, None], what)
-    g = torch.Generator(device=DEV).manual_seed(case)
-    planes = [[p] + [torch.randint(-2**31, 2**31, p.shape, dtype=torch.int64, device=DEV, generator=g).to(torch.int32) for _ in range(k - 1)]
-              for p in t.packed]
-    alpha = (t.alpha[:, None] * 0.55 ** torch.arange(k, device=DEV)).half().float()
-    table = bd.PlaneTable([torch.stack(p) for p in planes], alpha.reshape(-1))
-    bd.linear_multitenant_gemm_kbit(t.x, t.w, table, t.tok, y=y)
-    x, w64 = t.x.double(), t.w.double()
-    exact, mag, delta = x @ w64.t(), x.abs() @ w64.abs().t(), torch.zeros((len(t.tok), 1), dtype=torch.float64, device=DEV)
-    for e in set(t.tok):
-        rows = torch.tensor([i for i, f in enumerate(t.tok) if f == e], device=DEV)
-        for j in range(k):
-            exact[rows] += alpha[e, j].double() * (x[rows] @ expand(planes[e][j], inn).t())
-            delta[rows] += alpha[e, j].double() * x[rows].abs().sum(dim=1, keepdim=True)
-    # the bound of `check`, and 2^-11 of the planes' sum per weight and plane where the GEMM's tiles form it in fp16
-    bound = 2.0**-11 * exact.abs() + 2.0**-25 + inn**0.5 * 2.0**-23 * (mag + delta) + k * 2.0**-11 * delta / inn**0.5
-    worst = ((y.double() - exact).abs() / bound).max().item()
-    assert worst <= 1.0, (what, worst)
-    assert torch.equal(bd.linear_multitenant_gemm_kbit(t.x, t.w, table, t.tok), y), what
+        table, w8 = bd.TenantTable(t.packed, t.alpha), q.double() * scale.double()[:, None]
+        run = lambda variant=0: bd.linear_multitenant_gemm_q8(t.x, q, scale, table, t.tok, y=nan(), variant=variant)
+        panels = run(128)
+        for y in (panels, run(4), run()):
+            t.check(y, w8, what)
+    else:
+        g = torch.Generator(device=DEV).manual_seed(case)
+        planes = [[p] + [torch.randint(-2**31, 2**31, p.shape, dtype=torch.int64, device=DEV, generator=g).to(torch.int32) for _ in range(k - 1)]
+                  for p in t.packed]
+        alpha = (t.alpha[:, None] * 0.55 ** torch.arange(k, device=DEV)).half().float()
+        table = bd.PlaneTable([torch.stack(p) for p in planes], alpha.reshape(-1))
+        run = lambda variant=0: bd.linear_multitenant_gemm_kbit(t.x, t.w, table, t.tok, y=nan(), variant=variant)
+        panels = run(128)
+        x, w64 = t.x.double(), t.w.double()
+        exact, mag, delta = x @ w64.t(), x.abs() @ w64.abs().t(), torch.zeros((len(t.tok), 1), dtype=torch.float64, device=DEV)
+        for e in set(t.tok):
+            rows = torch.tensor([i for i, f in enumerate(t.tok) if f == e], device=DEV)
+            for j in range(k):
+                exact[rows] += alpha[e, j].double() * (x[rows] @ expand(planes[e][j], inn).t())
+                delta[rows] += alpha[e, j].double() * x[rows].abs().sum(dim=1, keepdim=True)
+        bound = 2.0**-11 * exact.abs() + 2.0**-25 + inn**0.5 * 2.0**-23 * (mag + delta)      # as in `check`
+        # the GEMM's tiles form the planes' sum in fp16: k - 1 additions, each rounded by at most 2^-11 of the scales' sum; over a row these
+        # errors meet x of random signs, so their sum is below 6 standard deviations in all of some 10^6 elements
+        of_row = alpha.double().sum(dim=1)[torch.tensor(t.tok, device=DEV)][:, None]
+        in_fp16 = 6 * (k - 1) * 2.0**-11 * of_row * x.norm(dim=1, keepdim=True)
+        for y, b in ((panels, bound), (run(4), bound + in_fp16), (run(), bound + in_fp16)):
+            worst = ((y.double() - exact).abs() / b).max().item()
+            assert worst <= 1.0, (what, worst)
+    for variant in splits:
+        assert torch.equal(run(variant), panels), (what, variant)
+    assert torch.equal(run(), run()), what
+    with pytest.raises(bd.BitDeltaError):
+        run(splits[-1] + 1)
 
 
 # More than 32 tokens with a few per tenant, as the library chooses to run them (which kernel that is, an estimate says),
@@ -210,7 +230,9 @@ def test_few_tokens_rowmajor(out, inn, counts, order):
     table = bd.TenantTable(t.packed, t.alpha)
     y = torch.full((len(t.tok), out), float("nan"), dtype=torch.float16, device=DEV)
     t.check(bd.linear_multitenant(t.x, t.w, table, t.tok, y=y), what=f"{out}x{inn} {counts} {order}")
-    forms = [bd.linear_multitenant(t.x, t.w, table, t.tok, variant=v) for v in (2, 10)]
+    forms = [bd.linear_multitenant(t.x, t.w, table, t.tok, variant=v) for v in (2, 18, 34, 128)]   # decode launch, one, two row blocks, panels
+    for f in forms:
+        t.check(f, what=f"{out}x{inn} {counts} {order}")
     assert any(torch.equal(y, f) for f in forms)
     g = torch.cuda.CUDAGraph()
     captured = torch.empty_like(y)
@@ -239,7 +261,7 @@ def test_few_tokens_tiled(out, inn, counts, order):
         assert torch.equal(y, bd.linear_multitenant_tiled(t.x, wt, out, table, t.tok, variant=variant)), variant
 
 
-# Panels of four row blocks (row-major, variant 10 where the plan prefers them): chunks of 2 to 5 column tiles, the last one partly
+# Panels of four row blocks (row-major, variants 128 and 128 + n): chunks of 1 to 5 column tiles, the last one partly
 # filled; one, two, an odd number and more than four units per half of `in`, the second half a unit shorter or empty; `out` that
 # ends inside a row block, a panel, and not at a multiple of four.
 @pytest.mark.parametrize("tiles", [8, 11, 16, 19, 20, 66])
@@ -250,13 +272,16 @@ def test_wide_panels(out, inn, tiles):
     table = bd.TenantTable(t.packed, t.alpha)
     what = f"panels {out}x{inn} {tiles} tiles"
     y = torch.full((len(t.tok), out), float("nan"), dtype=torch.float16, device=DEV)
-    t.check(bd.linear_multitenant(t.x, t.w, table, t.tok, y=y, variant=10), what=what)
-    assert torch.equal(bd.linear_multitenant(t.x, t.w, table, t.tok, variant=10), y), what       # bitwise reproducible
+    t.check(bd.linear_multitenant(t.x, t.w, table, t.tok, y=y, variant=128), what=what)
+    for variant in range(128, 134):                   # bitwise reproducible, and in every split
+        y2 = torch.full_like(y, float("nan"))
+        assert torch.equal(bd.linear_multitenant(t.x, t.w, table, t.tok, y=y2, variant=variant), y), (what, variant)
+    t.check(bd.linear_multitenant(t.x, t.w, table, t.tok, variant=10), what=what + " the library's split")
     # infinities and NaN stay in their token and their row; an infinite scale gives the sign of the +-1 sum
     t.x[5, inn - 1], t.x[9, 0], t.w[out - 1, 3] = float("inf"), float("nan"), float("nan")
     alpha = t.alpha.clone()
     alpha[t.tok[0]] = float("inf")
-    bad = bd.linear_multitenant(t.x, t.w, bd.TenantTable(t.packed, alpha), t.tok, variant=10)
+    bad = bd.linear_multitenant(t.x, t.w, bd.TenantTable(t.packed, alpha), t.tok, variant=128)
     keep = [i for i, e in enumerate(t.tok) if i not in (5, 9) and e != t.tok[0]]
     assert torch.equal(bad[keep][:, :-1], y[keep][:, :-1]) and torch.isnan(bad[9]).all() and torch.isnan(bad[:, -1]).all()
     assert not torch.isfinite(bad[5]).any()
@@ -381,8 +406,9 @@ def test_gemm_more_tiles_than_compute_units():
     t.check(bd.linear_multitenant_tiled_gemm(t.x, wt, out, tiled, t.tok, y=nan()), what="two products")
     t.check(bd.linear_multitenant(t.x, t.w, bd.TenantTable(t.packed, t.alpha), t.tok, y=nan(), variant=5), what="row-major")
     q, scale = bd.quantize_base_q8(t.w)
-    y = bd.linear_multitenant_gemm_q8(t.x, q, scale, bd.TenantTable(t.packed, t.alpha), t.tok, y=nan())
-    t.check(y, q.double() * scale.double()[:, None], "8-bit base")
+    for variant in (4, 5):
+        y = bd.linear_multitenant_gemm_q8(t.x, q, scale, bd.TenantTable(t.packed, t.alpha), t.tok, y=nan(), variant=variant)
+        t.check(y, q.double() * scale.double()[:, None], f"8-bit base, variant {variant}")
     y = bd.linear_multitenant_tiled_gemm(t.x, wt, out, tiled, t.tok, one_product=True, y=nan())
     for e in set(t.tok):   # one product: the fine-tuned weight rounded to binary16
         rows = torch.tensor([i for i, k in enumerate(t.tok) if k == e], device=DEV)

@@ -59,6 +59,9 @@ def test_gemm_kbit_matches_oracle(ref, case):
     _, y32 = ref.linear_multitenant_kbit(to_np(x), prob.w_base_np, prob.planes_np, prob.alpha_np, tok)
     check_close(y, y32, f"gemm kbit case {case}")
     assert torch.equal(y, bd.linear_multitenant_gemm_kbit(x, prob.w_base, table, tok))   # reproducible
+    y4 = bd.linear_multitenant_gemm_kbit(x, prob.w_base, table, tok, variant=4)          # the GEMM, whatever the library chose above
+    check_close(y4, y32, f"gemm kbit case {case}, 128 x 128 tiles")
+    assert torch.equal(y4, bd.linear_multitenant_gemm_kbit(x, prob.w_base, table, tok, variant=4))
     if inn % 128 == 0:   # the decode launches of the same call family agree within the same tolerance
         check_close(bd.linear_multitenant_kbit(x, prob.w_base, table, tok), y32, f"decode kbit case {case}")
 
@@ -95,6 +98,8 @@ def test_gemm_q8_matches_oracle(ref, case):
     y64 = ref.linear_multitenant_q8_f64(to_np(x), prob.q_np, prob.s_np, prob.packed_np, prob.alpha_np, tok)
     check_close(y, y64, f"gemm q8 case {case} vs f64")
     assert torch.equal(y, bd.linear_multitenant_gemm_q8(x, q, s, table, tok))
+    for variant in (4,) + (5,) * (out >= 256 and inn % 64 == 0):   # the GEMM on 128 x 128 and on 128 x 256 tiles
+        check_close(bd.linear_multitenant_gemm_q8(x, q, s, table, tok, variant=variant), y64, f"gemm q8 case {case} variant {variant}")
     # same tenants through the decode kernel on the tiled 8-bit base: within the tolerance of each other as well
     if len(tok) <= 32:
         check_close(bd.linear_multitenant_tiled_q8(x, prob.wq, out, prob.table, tok), y32, "tiled q8")
@@ -131,6 +136,8 @@ def test_gemm_kbit_and_q8_llama2_7b_gate(ref):
     torch.cuda.synchronize()
     _, y32 = ref.linear_multitenant_kbit(to_np(x), prob.w_base_np, prob.planes_np, prob.alpha_np, tok)
     check_close(y, y32, "7B gate gemm kbit")
+    for variant in (4, 128):
+        check_close(bd.linear_multitenant_gemm_kbit(x, prob.w_base, table, tok, variant=variant), y32, f"7B gate gemm kbit variant {variant}")
     del prob, planes, table
     qp = Q8Problem(ref, out, inn, nt, ("gq7b",))
     q, s, qtable = q8_device(qp)

@@ -187,6 +187,16 @@ def test_gemm_variants_argument_errors(bd):
     assert g(A, 2 * A, 6 * A, 3 * A, 4 * A, _tok(2), 5 * A, 1, 16, 128, 2, W, 4096, 0) == 4
     assert g(A, 2 * A, 6 * A, 3 * A, 4 * A, _tok(0), 5 * A, 1, 16, 128, 1, 0, 0, 0) == 5
     assert g(A, A, 6 * A, 3 * A, 4 * A, _tok(0), A, 1, 16, 128, 1, W, 4096, 0) == 8          # y on top of x
+    fv, gv = L.bd_linear_multitenant_gemm_kbit_variant, L.bd_linear_multitenant_gemm_q8_variant
+    for inn, k, variant in ((128, 2, 1), (128, 2, 5), (128, 2, 133), (128, 5, 128), (96, 2, 128), (64, 2, 128), (128, 1, 134), (128, 1, 64)):
+        assert fv(A, 2 * A, 3 * A, 4 * A, _tok(0), 5 * A, 1, 16, inn, 1, k, W, 4096, 0, variant) == 7, (inn, k, variant)
+    for out, inn, variant in ((255, 128, 5), (256, 96, 5), (256, 128, 134), (256, 96, 128), (256, 128, 2)):
+        assert gv(A, 2 * A, 6 * A, 3 * A, 4 * A, _tok(0), 5 * A, 1, out, inn, 1, W, 4096, 0, variant) == 7, (out, inn, variant)
+    assert fv(A, 2 * A, 3 * A, 4 * A, _tok(0), 5 * A, 1, 16, 128, 1, 2, 0, 0, 0, 128) == 5     # the workspace is asked for all the same
+    assert fv(A, 2 * A, 3 * A, 4 * A, _tok(0), 5 * A, 0, 16, 128, 1, 2, 0, 0, 0, 128) == 0
+    m = L.bd_linear_multitenant_variant
+    for inn, variant in ((192, 128), (128, 134), (128, 64), (128, 144)):
+        assert m(A, 2 * A, 3 * A, 4 * A, _tok(0), 5 * A, 1, 16, inn, 1, 0, 0, 0, variant) == 7, (inn, variant)
     d = L.bd_linear_multitenant_q8                                                          # the decode form
     assert d(A, 2 * A, 0, 3 * A, 4 * A, _tok(0), 5 * A, 1, 16, 128, 1, 0) == 1
     assert d(A, 2 * A, 6 * A, 3 * A, 4 * A, _tok(1), 5 * A, 1, 16, 128, 1, 0) == 4
