@@ -25,10 +25,15 @@ def test_decode_launches(mix):
     table = bd.TenantTable(t.packed, t.alpha)
     q, scale = bd.quantize_base_q8(t.w)
     w8 = q.double() * scale.double()[:, None]
-    t.check(bd.linear_multitenant_tiled(t.x, bd.tile_base(t.w), out, tiled, t.tok), what=what + " tiled")
-    t.check(bd.linear_multitenant(t.x, t.w, table, t.tok), what=what + " row-major")
+    wt = bd.tile_base(t.w)
+    # by number: left to itself the library runs many of these small batches in the kernels of 16-column tiles
+    y = bd.linear_multitenant_tiled(t.x, wt, out, tiled, t.tok, variant=2)
+    t.check(y, what=what + " tiled")
+    assert torch.equal(y, bd.linear_multitenant_tiled(t.x, wt, out, tiled, t.tok)), what
+    t.check(bd.linear_multitenant(t.x, t.w, table, t.tok, variant=2), what=what + " row-major")
+    t.check(bd.linear_multitenant(t.x, t.w, table, t.tok), what=what + " row-major, the library's choice")
     # the 8-bit base: the sum runs over x (1152 + q) and 1152 sum x is taken off again, 2 * 1152 / 127 of the magnitude more per term
-    for y in (bd.linear_multitenant_tiled_q8(t.x, bd.tile_base_q8(q, scale), out, tiled, t.tok),
+    for y in (bd.linear_multitenant_tiled_q8(t.x, bd.tile_base_q8(q, scale), out, tiled, t.tok),   # (always decode launches)
               bd.linear_multitenant_q8(t.x, q, scale, table, t.tok)):
         t.check(y, w8, what + " 8-bit base", extra=(2304.0 * scale.double())[None, :] * t.x.double().abs().sum(dim=1, keepdim=True))
 
@@ -42,7 +47,7 @@ def test_row_major_rows_of_every_kind(out, inn, n):
     t = Tensors(out, inn, tokens_of([1] * n, "shuffled"), n, seed=n)
     table = bd.TenantTable(t.packed, t.alpha)
     q, scale = bd.quantize_base_q8(t.w)
-    t.check(bd.linear_multitenant(t.x, t.w, table, t.tok), what=f"{out}x{inn} {n}")
+    t.check(bd.linear_multitenant(t.x, t.w, table, t.tok, variant=2), what=f"{out}x{inn} {n}")
     t.check(bd.linear_multitenant_q8(t.x, q, scale, table, t.tok), q.double() * scale.double()[:, None], f"{out}x{inn} {n} 8-bit base",
             extra=(2304.0 * scale.double())[None, :] * t.x.double().abs().sum(dim=1, keepdim=True))
 
