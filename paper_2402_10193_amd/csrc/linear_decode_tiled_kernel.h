@@ -874,7 +874,7 @@ static hipError_t launch_inst(const TiledArgs& args, int n_waves, unsigned grid,
 }
 
 template <bool Q8, bool RM, int NJ>
-static hipError_t launch_nj(const TiledArgs& args, int n_waves, int xsteps, unsigned grid, hipStream_t st) {
+static hipError_t launch_nj(const TiledArgs& args, int n_waves, int xsteps, unsigned grid, int rounds, int cus, hipStream_t st) {
     // Row-major: the signs slot by slot (see S4) where that is the better one, both measured with the tensors coming from HBM (180
     // + 260 + 290 launches of 2 to 32 tenants).  Four slots at a time issue half the loads, but ask L2 twice for a row's 32 bytes, and the second
     // time the line may be gone: with long rows, with several row blocks per workgroup, and where rows of signs do not start on 128-byte
@@ -885,12 +885,19 @@ static hipError_t launch_nj(const TiledArgs& args, int n_waves, int xsteps, unsi
     const bool several = args.rb_end[args.n_mats - 1] > (int)grid;
     const int KT = args.KT;
     // Streamed x: two row blocks at a time (RG) where workgroups have several, rows are long and x is a large part of what a task asks for.  One
-    // at a time / two, us, 12000 rows where nothing else is said:
-    //   one column tile: 3008 12 slots 28.4 / 28.0, 7104 12 slots 55.6 / 54.3, row-major 4992 10 slots 50.6 / 49.7, a 70B layer with 16 slots 616 / 588, 4
-    //     slots 341 / 338, 8-bit base 12 tokens 394 / 371; but 2496 10 and 12 slots 1.00, 704 to 1728 0.97 to 0.99 x, 6 slots up to 7104 0.97 to 0.99 x
-    //   two: 5 tenants, 20 tokens: 3008 31.4 / 30.2, 7104 59.1 / 55.7, a 70B layer 527 / 463, but 2496 29.4 / 29.7, 1216 21.6 / 22.8;
-    //     30 tenants: 1216 41.9 / 40.7, 2496 57.7 / 56.6, 7104 118.5 / 115.4, a 70B layer of 32 1088 / 1029, 8-bit base 5056 86.6 / 84.2, but 640 row-major 42.8 / 43.8
-    const bool two = several && (args.n_ct == 2 ? KT >= (NJ >= 12 ? 5 : 12) : KT >= (NJ >= 8 ? 12 : 30));
+    // at a time / two, us, weights from HBM:
+    //   one column tile, 12 and 16 slots, a 70B layer's 28672 x 8192: 141 / 135 and 171 / 160, 8-bit base 123 / 115 and 155 / 145, row-major 189 / 178 and
+    //     229 / 218; 8 slots, 5120 x 5120 21.2 / 20.0, 8-bit base 8192 x 3328 1.06 x, 12288 x 3328 0.98 to 0.99 x; 12000 rows of 2496 and fewer 0.97 to 1.00 x
+    //   4 and 6 slots, 28672 x 8192: 8-bit base 65.3 / 63.5 and 80.0 / 76.0, row-major 120.8 / 117.5 and 136 / 131, row-major over the 8-bit base 95.9 / 88.7 and
+    //     115 / 107; 12000 rows of 704 to 7104 0.97 to 0.99 x
+    //   two: 5 tenants, 20 tokens: 28672 x 8192 147 / 128, 8192 x 3584 25.1 / 23.4, 12000 x 2496 29.4 / 29.7, 12000 x 1216 21.6 / 22.8; 24 and 32 tenants:
+    //     28672 x 8192 239 / 224, 12000 x 1280 34.9 / 33.6 and 41.1 / 40.4, row-major 5120 x 2304 43.4 / 41.3, but 12000 x 640 42.8 / 43.8
+    // Few slots over the fp16 base ask for little but weights, and where nearly all units have a workgroup the memory sets the time: 8192 x 8192
+    // and 28672 x 8192 with 4 slots 31.9 / 32.8 and 96.0 / 97.8, row-major 8192 x 8192 43.8 / 44.8; with 8 slots 12288 x 4608 (a row block is left over) 0.98 x.
+    // Where a fifth of the units is idle the others' requests are the limit: 5120 x 8192 4, 6 and 8 slots 1.06, 1.08 and 1.10 x.
+    const bool full = 5 * (int)grid > 4 * cus;
+    const bool pays = Q8 || !full || (RM ? NJ > 4 || rounds > 2 : NJ > 8 || (NJ == 8 && rounds != 3));
+    const bool two = several && (args.n_ct == 2 ? KT >= (NJ >= 12 ? 5 : 12) : pays && KT >= (NJ >= 8 ? 12 : 30));
     auto streamed = [&](auto nct_tag, auto s4_tag) {
         constexpr int NCT = decltype(nct_tag)::value;
         constexpr bool S4 = decltype(s4_tag)::value;
@@ -948,7 +955,7 @@ static hipError_t launch_tiled_t(const TiledArgs& args, int n_jobs, hipStream_t 
     int xsteps = 0;
     if (args.KT > 0 && args.KT % n_waves == 0 && args.KT / n_waves <= 2) xsteps = args.KT / n_waves;
     auto go = [&](auto nj) {
-        return launch_nj<Q8, RM, decltype(nj)::value>(args, n_waves, args.n_ct == 2 ? 0 : xsteps, grid, st);
+        return launch_nj<Q8, RM, decltype(nj)::value>(args, n_waves, args.n_ct == 2 ? 0 : xsteps, grid, rounds, cus, st);
     };
     // A slot without a job costs as much as one with: its signs are requested (slot 0's again) and looked up.  With slots for 4, 8
     // or 16 only, a 7B layer took 142 us with 9 tenants and 149 with 12 (134 and 139 over the 8-bit base); in steps of two it
