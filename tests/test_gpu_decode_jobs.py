@@ -52,18 +52,25 @@ def test_row_major_rows_of_every_kind(out, inn, n):
             extra=(2304.0 * scale.double())[None, :] * t.x.double().abs().sum(dim=1, keepdim=True))
 
 
-# Streamed x: a workgroup's row blocks are multiplied two at a time where two of one matrix are left.  More row blocks than compute
-# units, so that workgroups have 2, 3 and 4 of them, odd numbers at the end of a matrix and of the launch; `in` whole k tiles, half
-# and ragged ones, one and several per wavefront.
-@pytest.mark.parametrize("counts", [[1, 2], [1] * 11, [16], [3] * 10, [30, 2]])
-@pytest.mark.parametrize("out,inn", [(4160, 640), (8208, 2176), (12300, 2336), (16400, 2304)])
+# Streamed x.  More row blocks than compute units, so that workgroups have 2, 3, 4 and 5 of them, odd numbers at the end of a matrix and of the
+# launch; `in` whole k tiles, half and ragged ones, one and several per wavefront.
+ROW_BLOCKS = [(out, inn, counts) for out, inn in [(4160, 640), (8208, 2176), (12300, 2336), (16400, 2304)]
+              for counts in ([1, 2], [1] * 11, [16], [3] * 10, [30, 2])]
+# Two row blocks of a matrix at a time where two are left: one column tile of at least 12 k tiles (4 and 6 slots: 30), ...
+ROW_BLOCKS += [(4160, 3104, [1] * 11), (4160, 3328, [2] * 7), (8208, 3328, [1] * 11), (12300, 3200, [1] * 16), (16400, 3104, [1] * 9), (4160, 7808, [1] * 3),
+               (8208, 7744, [2] * 5)]
+# ... two of 12 k tiles, or of 5 with at least 12 slots
+ROW_BLOCKS += [(4160, 3328, [5] * 5), (8208, 3104, [9, 9]), (4160, 1280, [1] * 24), (8208, 1184, [1] * 27), (12300, 1408, [1] * 32), (16400, 1280, [1] * 24)]
+
+
+@pytest.mark.parametrize("out,inn,counts", ROW_BLOCKS)
 def test_row_blocks_in_pairs(out, inn, counts):
     t = Tensors(out, inn, tokens_of(counts, "shuffled"), len(counts), seed=len(counts))
     what = f"{out}x{inn} {counts}"
     nan = lambda n=out: torch.full((len(t.tok), n), float("nan"), dtype=torch.float16, device=DEV)
     signs = [bd.tile_signs(p, out, inn) for p in t.packed]
     tiled, wt = bd.TiledTenantTable(signs, t.alpha), bd.tile_base(t.w)
-    y = bd.linear_multitenant_tiled(t.x, wt, out, tiled, t.tok, y=nan())
+    y = bd.linear_multitenant_tiled(t.x, wt, out, tiled, t.tok, y=nan(), variant=2)
     t.check(y, what=what + " tiled")
     # matrices that end inside a workgroup's row blocks: each gives the bits of its own call
     group = bd.TiledGroup([wt, wt, wt], [out, 48, 2000], [tiled] * 3)
@@ -74,8 +81,14 @@ def test_row_blocks_in_pairs(out, inn, counts):
     q, scale = bd.quantize_base_q8(t.w)
     w8 = q.double() * scale.double()[:, None]
     extra = t.x.double().abs() @ torch.full_like(w8, 2 * 1152.0 / 127).mul_(w8.abs().amax(dim=1, keepdim=True)).t()
-    t.check(bd.linear_multitenant_tiled_q8(t.x, bd.tile_base_q8(q, scale), out, tiled, t.tok, y=nan()), w8, what + " 8-bit base", extra)
+    wq = bd.tile_base_q8(q, scale)
+    y = bd.linear_multitenant_tiled_q8(t.x, wq, out, tiled, t.tok, y=nan())
+    t.check(y, w8, what + " 8-bit base", extra)
+    w48 = bd.tile_base_q8(q[:48].contiguous(), scale[:48].contiguous())       # (the scales are behind a matrix's own tiles)
+    group = bd.TiledGroup([wq, w48, wq], [out, 48, out], [tiled] * 3)
+    for part, n in zip(bd.linear_multitenant_tiled_group_q8(t.x, group, t.tok, ys=[nan(), nan(48), nan()]), (out, 48, out)):
+        assert torch.equal(part, y[:, :n]), what + f" 8-bit group, {n} rows"
     if inn % 128 == 0:
         table = bd.TenantTable(t.packed, t.alpha)
-        t.check(bd.linear_multitenant(t.x, t.w, table, t.tok, y=nan()), what=what + " row-major")
+        t.check(bd.linear_multitenant(t.x, t.w, table, t.tok, y=nan(), variant=2), what=what + " row-major")
         t.check(bd.linear_multitenant_q8(t.x, q, scale, table, t.tok, y=nan()), w8, what + " row-major, 8-bit base", extra)
