@@ -203,7 +203,8 @@ bd_status bd_tile_signs(const uint32_t* packed, int64_t out, int64_t in, uint32_
 
 /* The multi-tenant linear of Eq. 6 over the serving layout; the arithmetic and rounding of
  * bd_linear_multitenant's decode launches.  A token's result does not depend on the other tokens of the call, however many
- * there are (finite scales; an infinite one multiplies the whole row's +-1 sum in the kernel for tens to a few hundred tokens).
+ * there are (finite scales; an infinite one multiplies the whole row's +-1 sum where the kernel for tens to a few hundred tokens
+ * takes more than 32).
  *   w_tiled          tiled base (bd_tile_base)
  *   tiled_by_tenant  HOST array of n_tenants DEVICE pointers to tiled deltas (bd_tile_signs); the
  *                    pointers travel in the kernel arguments, so no device-side pointer table is read.
@@ -262,7 +263,7 @@ bd_status bd_linear_multitenant_tiled_gemm(const uint16_t* x_f16, const uint16_t
  *   alpha_by_mat        HOST [n_mats] of device arrays [n_tenants]
  *   y_f16               HOST [n_mats] of device pointers, y_m is [T, out[m]]
  *   out                 HOST [n_mats]; `in`, x, T and tenant_of_token are shared.
- * The bits of n_mats separate calls. */
+ * The bits of n_mats separate calls (more than 32 tokens: for finite scales). */
 bd_status bd_linear_multitenant_tiled_group(int32_t n_mats, const uint16_t* x_f16,
                                             const uint16_t* const* w_tiled,
                                             const uint32_t* const* tiled_by_mat_tenant,

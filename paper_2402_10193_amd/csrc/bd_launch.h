@@ -94,6 +94,7 @@ struct WideArgs {
     int32_t tenant[kWideMaxTiles];
     uint16_t col_token[kWideMaxTiles][16];
     const float* wscale;                        // panels: w is the int8 base [out, in] and this its row scales
+    int32_t inf_in_parts;                       // tiled: an infinite scale multiplies the wavefronts' parts, as in a decode launch
 };
 hipError_t launch_linear_wide(const WideArgs& args, int row_blocks_per_group, bool rowmajor, hipStream_t st);
 // the same products on the row-major tensors, panels of four row blocks (linear_panel.hip): planes > 1: tables indexed by tenant * planes + plane;

@@ -381,7 +381,7 @@ bool wide_fits(int64_t T, int64_t out, int64_t in) {
 // panel_planes > 0: panels, with that many planes per tenant (tables indexed by tenant * planes + plane) or, wscale given, the int8 base
 hipError_t run_wide(const WideTiles& t, const uint16_t* x, const uint16_t* w, const uint32_t* const* packed_dev,
                     const uint32_t* const* tiled_host, const float* alpha, uint16_t* y, int64_t out, int64_t in, hipStream_t st,
-                    int split = 0, int panel_planes = 0, const float* wscale = nullptr) {
+                    int split = 0, int panel_planes = 0, const float* wscale = nullptr, bool inf_in_parts = false) {
     const int cus = cus_or_256(), n_all = (int)t.tenant.size(), launches = (n_all + bd::kWideMaxTiles - 1) / bd::kWideMaxTiles;
     for (int l = 0; l < launches; ++l) {
         const int first = (int)((int64_t)n_all * l / launches), n = (int)((int64_t)n_all * (l + 1) / launches) - first;
@@ -397,6 +397,7 @@ hipError_t run_wide(const WideTiles& t, const uint16_t* x, const uint16_t* w, co
         a.KT = (int32_t)bd::tiled_k_tiles(in);
         a.units = (int32_t)((in + 127) / 128);   // (in % 128 == 0 but for panels)
         a.wscale = wscale;
+        a.inf_in_parts = inf_in_parts ? 1 : 0;
         a.row_blocks = (int32_t)bd::tiled_row_blocks(out);
         a.n_tiles = n;
         const WidePlan p = split & 15     ? WidePlan{split >= kVariantPanels ? bd::kPanelRowBlocks : split >> 4, std::min(split & 15, n), 0.0}
@@ -955,7 +956,8 @@ bd_status tiled_linear_impl(int32_t n_mats, const uint16_t* x_f16, const uint16_
             const WideTiles tiles = wide_tiles(tenant_of_token, order);
             for (int m = 0; m < n_mats; ++m)
                 if (out[m] > 0 && run_wide(tiles, x_f16, w_tiled[m], nullptr, tiled_by_mat_tenant + (size_t)m * n_tenants, alpha_by_mat[m],
-                                           y_f16[m], out[m], in, (hipStream_t)stream, std::max(wide_split, 0)) != hipSuccess)
+                                           y_f16[m], out[m], in, (hipStream_t)stream, std::max(wide_split, 0), 0, nullptr,
+                                           few && wide_split < 0) != hipSuccess)   // (a group of that size is a decode launch)
                     return BD_ERR_DEVICE;
             return BD_OK;
         }

@@ -384,18 +384,19 @@ __global__ __launch_bounds__(kWideWaves * kWave) void linear_wide_kernel(const W
         write_y(0, 1, true);
     } else {
         // as the decode kernel: every wavefront scales its own part, and the parts are added in order
+        bool any_inf = false;
+#pragma unroll
+        for (int ct = 0; ct < MT; ++ct) any_inf = any_inf || __builtin_isinf(scale_of(ct));
+        any_inf = any_inf && !a.inf_in_parts;
         auto scaled = [&](int r, int ct) {
             const float al = scale_of(ct);
             float4v p = acc[r][ct];
-            if (!__builtin_isinf(al)) {
+            if (!any_inf || !__builtin_isinf(al)) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) p[e] = acc[r][ct][e] + al * dsum[r][ct][e];
             }
             return p;
         };
-        bool any_inf = false;
-#pragma unroll
-        for (int ct = 0; ct < MT; ++ct) any_inf = any_inf || __builtin_isinf(scale_of(ct));
         if (!any_inf) {
             put(wave * kSet, scaled);
             __syncthreads();

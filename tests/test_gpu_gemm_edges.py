@@ -259,6 +259,15 @@ def test_few_tokens_tiled(out, inn, counts, order):
     t.check(bd.linear_multitenant_tiled(t.x, wt, out, table, t.tok, y=y), what=f"{out}x{inn} {counts} {order}")
     for variant in (2, 10):
         assert torch.equal(y, bd.linear_multitenant_tiled(t.x, wt, out, table, t.tok, variant=variant)), variant
+    # an infinite scale, also where the +-1 sums of whole parts of the row are zero: what a decode launch and a group of matrices give
+    t.x[:, inn // 3:] = 0
+    alpha = t.alpha.clone()
+    alpha[0], alpha[-1] = float("inf"), float("-inf")
+    table = bd.TiledTenantTable(table.tiled, alpha)
+    y = bd.linear_multitenant_tiled(t.x, wt, out, table, t.tok).view(torch.int16)
+    assert torch.equal(y, bd.linear_multitenant_tiled(t.x, wt, out, table, t.tok, variant=2).view(torch.int16))
+    for part in bd.linear_multitenant_tiled_group(t.x, bd.TiledGroup([wt, wt], [out, out], [table, table]), t.tok):
+        assert torch.equal(y, part.view(torch.int16))
 
 
 # Panels of four row blocks (row-major, variants 128 and 128 + n): chunks of 1 to 5 column tiles, the last one partly
