@@ -131,14 +131,17 @@ bd_status bd_compress_batch(int32_t n, const uint16_t* const* w_base_f16, const 
  * the result is rounded once to fp16 (nearest even).  (In decode launches the sum of each wavefront's share of `in`, at most
  * eight of them, which are then added: an infinite alpha gives NaN where one of those is zero.)
  * T == 0 or out == 0 is a no-op returning BD_OK.  T up to 65535.
- * Up to 32 tokens run as one decode launch and need no workspace.  More tokens (the prefill regime
+ * Up to 32 tokens fit one decode launch and need no workspace.  More tokens (the prefill regime
  * of Sec. 4.3: many tokens per tenant) can run as ONE matrix-core GEMM launch over all tokens if
  * `workspace` holds bd_workspace_bytes(BD_OP_LINEAR_MULTITENANT, T, out, in, n_tenants) bytes
  * (256-byte aligned; it receives the token permutation).  Without one the same result (up to the order of
- * additions) is produced by ceil(T / 32) decode launches, each re-reading the base, or, for in % 128 == 0, by a
- * kernel for tens to a few hundred tokens with a few per tenant, which reads the base once per up to 160 columns (a
- * tenant's tokens padded to 16); the library takes whichever a cost estimate on the host says is quickest for the
- * whole batch, so the order of additions of a token may change with the other tokens of its call.
+ * additions) is produced by ceil(T / 32) decode launches, each re-reading the base.  For in % 128 == 0 there are also two
+ * kernels that pad a tenant's tokens to column tiles of 16: one reads the base once per up to 160 columns, the other, panels of 64
+ * output rows, once per up to 80.  They are meant for tens to a few hundred tokens with a few per tenant, but also take batches of up to 32
+ * tokens for which a decode launch would mostly wait (few output rows, short rows, several tokens per tenant).  The library takes
+ * whichever a cost estimate on the host says is quickest for the whole batch, so the order of additions of a token, and with it the last
+ * bits of its result, may change with the other tokens of its call, whatever their number (variant 2 of
+ * bd_linear_multitenant_variant and the serving layout keep them).
  * Speed: this call reads the tensors in the canonical row-major layout, which costs a decode launch four times the
  * cache accesses per byte of the serving layout; a decode step through it runs at about two thirds of the rate of
  * bd_linear_multitenant_tiled on the same matrices (and the grouped tiled call saves three launches per layer on top).
@@ -157,7 +160,7 @@ bd_status bd_linear_multitenant(const uint16_t* x_f16, const uint16_t* w_base_f1
  *   variant 0  library's choice (identical to bd_linear_multitenant)
  *   variant 1  plain vector-ALU kernel: one wavefront per output row, DPP reductions
  *   variant 2  the matrix-core decode kernel of the serving path reading the row-major tensors as they are
- *              (in % 128 == 0 and a base below 4 GiB, else BD_ERR_UNSUPPORTED); the library's choice for such sizes
+ *              (in % 128 == 0 and a base below 4 GiB, else BD_ERR_UNSUPPORTED), 32 tokens per launch
  *   variant 4, 5, 6  the prefill GEMM with 128 x 128 tiles / 128 x 256 tiles and 4 wavefronts / 128 x 256
  *              tiles and 8 wavefronts (T > 32 and a workspace as for variant 0, else BD_ERR_UNSUPPORTED /
  *              BD_ERR_WORKSPACE; 5, 6 and 7 need in % 64 == 0)
@@ -168,7 +171,7 @@ bd_status bd_linear_multitenant(const uint16_t* x_f16, const uint16_t* w_base_f1
  *              tiles.  Half the matrix-core work of variants 4 to 7; the result differs from theirs by that
  *              rounding of the weights (about 2e-4 of the largest output at in = 4096) and equals, up to
  *              summation order, bd_linear_naive on bd_materialize'd weights.  Same conditions as 5.
- *   variant 10 the kernels for tens to a few hundred tokens with a few per tenant, for any T (in % 128 == 0, x and base
+ *   variant 10 the kernels of 16-column tiles (see bd_linear_multitenant), for any T (in % 128 == 0, x and base
  *              below 4 GiB, else BD_ERR_UNSUPPORTED; no workspace), one or two row blocks of 16 output features per workgroup or panels
  *              of four, as the library splits them; 16 R + n: with R = 1 or 2 row blocks and up to n column tiles per workgroup
  *              (n = 1 .. 10 with R = 1, 1 .. 6 with R = 2); 128 + n: panels (n = 1 .. 5, 0 for the library's split) */
@@ -211,11 +214,11 @@ bd_status bd_tile_signs(const uint32_t* packed, int64_t out, int64_t in, uint32_
  *                    Entries of tenants without a token in this call may be NULL.
  *   alpha_by_tenant  device array of n_tenants floats
  *   tenant_of_token  HOST [T]; x_f16 [T, in]; y_f16 [T, out], must not overlap x or w_tiled.
- * Tokens are grouped by tenant inside the call, over the whole batch; up to 32 tokens are one launch
+ * Tokens are grouped by tenant inside the call, over the whole batch; up to 32 tokens fit one decode launch
  * (two 16-column tiles that share the base registers), more run as several launches of 32 consecutive
  * tokens of the grouped order (the base is then streamed once per launch, a delta once per launch that
- * holds one of its tenant's tokens) or, where an estimate says it is quicker, through the kernel for tens to a few
- * hundred tokens (see bd_linear_multitenant; in % 128 == 0).  Needs no workspace. */
+ * holds one of its tenant's tokens).  Where an estimate says it is quicker, for any number of tokens, the kernel of 16-column
+ * tiles runs instead (in % 128 == 0; see bd_linear_multitenant): another launch, the same bits.  Needs no workspace. */
 bd_status bd_linear_multitenant_tiled(const uint16_t* x_f16, const uint16_t* w_tiled,
                                       const uint32_t* const* tiled_by_tenant,
                                       const float* alpha_by_tenant,
@@ -225,7 +228,7 @@ bd_status bd_linear_multitenant_tiled(const uint16_t* x_f16, const uint16_t* w_t
                                       void* stream);
 
 /* bd_linear_multitenant_tiled with the kernel chosen by the caller: 0 = the library's choice, 2 = decode launches,
- * 10 or 16 R + n = the kernel for tens to a few hundred tokens (see bd_linear_multitenant_variant; R = 2 with n = 5 or 6
+ * 10 or 16 R + n = the kernel of 16-column tiles (see bd_linear_multitenant_variant; R = 2 with n = 5 or 6
  * only where `in` makes 1, 2, 4 or 8 k tiles of 256).  All of them give the same bits for finite scales. */
 bd_status bd_linear_multitenant_tiled_variant(const uint16_t* x_f16, const uint16_t* w_tiled,
                                               const uint32_t* const* tiled_by_tenant,

@@ -312,7 +312,7 @@ def linear_multitenant(x: torch.Tensor, w_base: torch.Tensor, tenants: TenantTab
                        tok_array=None, workspace="auto") -> torch.Tensor:
     """bd_linear_multitenant (variant 0) or bd_linear_multitenant_variant: y fp16 [T, out].
     workspace: "auto" allocates what bd_workspace_bytes asks for (more than 32 tokens: the prefill GEMM),
-    None passes no workspace (the call then runs as decode launches), or a caller-owned uint8 tensor."""
+    None passes no workspace (the call then runs without that GEMM), or a caller-owned uint8 tensor."""
     _dev(x, torch.float16, "x")
     _dev(w_base, torch.float16, "w_base")
     T, inn = x.shape

@@ -437,12 +437,14 @@ int split_of_launch(const int32_t* tenant_of_token, const int32_t* order, int n,
     return best;
 }
 
-// What a batch of T > 32 tokens looks like to the three ways of running it: decode launches of 32 tokens of the sorted
-// order, which re-read the base per launch but spend nothing on empty rows; the wide kernel, 16-column tiles of one tenant;
+// What a batch looks like to the ways of running it: decode launches of 32 tokens of the sorted
+// order, which re-read the base per launch but spend nothing on empty rows; the wide kernel and panels, 16-column tiles of one tenant;
 // the GEMM, tiles of 32, 64 or 128 rows of one tenant.  A wrong guess costs time, never correctness.
-// The estimates were fitted to batches of 33 to 600 tokens of 1 to 64 tenants on 300 .. 12000 x 512 .. 11520, weights from HBM, replayed from
+// The estimates for T > 32 were fitted to batches of 33 to 600 tokens of 1 to 64 tenants on 300 .. 12000 x 512 .. 11520 (28672 rows or as long ones are
+// extrapolated, here as in the other fits of this file), weights from HBM, replayed from
 // graphs (250 row-major, 200 on the serving layout): each is within 10 % at its 10 % and 90 % quantiles (the GEMM's 15 %).  Of 150 other
-// batches each, up to 4096 (row-major) or 1500 tokens, 5 % ran more than 8 % (5 %) longer than the quickest of the three ways, 1 % more than 17 % (8 %).
+// batches each, up to 4096 (row-major) or 1500 tokens, 5 % ran more than 8 % (5 %) longer than the quickest of the three ways, 1 % more than 17 % (8 %)
+// (before panels).  Up to 32 tokens: few_tokens_wide.
 struct BatchShape {
     struct Launch {
         int tokens, tenants, jobs;                       // jobs of its fuller column tile

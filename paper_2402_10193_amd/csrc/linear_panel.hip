@@ -1,5 +1,6 @@
 // The multi-tenant linear (Eq. 6 of the paper) on the row-major tensors for batches of tens to a few hundred tokens, a few of each tenant,
-// where `out` has enough rows to fill the chip (the kernel of linear_wide.hip takes the others), and its two extensions, k sign planes per
+// where `out` has enough rows to fill the chip (the kernel of linear_wide.hip takes the others), for batches of up to 32 tokens that a decode
+// launch would mostly wait on, and its two extensions, k sign planes per
 // tenant and the 8-bit base, for prompts that are too short or matrices too small for the GEMM's tiles.
 //     y[t, n] = sum_k x[t,k] W_base[n,k]  +  sum_j alpha_{e,j} * sum_k x[t,k] s_{e,j}[n,k],   e = tenant(t)
 //

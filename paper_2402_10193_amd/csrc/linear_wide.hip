@@ -1,6 +1,6 @@
 // The multi-tenant linear (Eq. 6 of the paper) for batches between a decode launch and a prefill GEMM: tens to a few
-// hundred tokens, a few of each tenant (drafted tokens to verify, short prompts among decode tokens).  Row-major batches with rows enough for
-// panels of 64 take the kernel of linear_panel.hip.
+// hundred tokens, a few of each tenant (drafted tokens to verify, short prompts among decode tokens), and for up to 32 tokens where rows are few or
+// short.  Row-major batches with rows enough for panels of 64 take the kernel of linear_panel.hip.
 //     y[t, n] = sum_k x[t,k] W_base[n,k]  +  alpha_e * sum_k x[t,k] s_e[n,k],   e = tenant(t)
 //
 // A decode launch takes 32 tokens and streams the base once per launch; a GEMM tile of 64 or 128 rows holds one tenant's
