@@ -309,6 +309,8 @@ WidePlan panel_plan(int n, int64_t out, int64_t in, int cus, int planes, bool q8
     }
     return best;
 }
+// (No bound by the stream, nor in gemm_extended_us, which this is compared with: few tokens on matrices of a gigabyte come out below what HBM gives, but
+// both ways then stream the same bytes.)
 double panel_us(int n_all, int64_t out, int64_t in, int cus, int planes, bool q8) {
     double us = 3.5;
     const int launches = (n_all + bd::kWideMaxTiles - 1) / bd::kWideMaxTiles;
